@@ -182,6 +182,108 @@ __device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, in
   }
 }
 
+// ---- rows of any length ("ragged": Sk % 8 != 0) --------------------------------------------
+// A row is still owned in 16-byte pieces counted from its own start, piece c of lane t =
+// c*LANES + t, read and written by 16-byte accesses at element-aligned addresses; the last piece
+// is moved back to end with the row, so that no access leaves the row and none is partial.  The
+// elements it shares with the piece before ("dup", at most V - 1) are computed and stored twice
+// with the same value and left out of the row sums.  Pieces do not line up with the generator's
+// groups of 8 elements, nor rows with mask words: the row's keep bytes, one per group, go through
+// LDS, from where a lane takes the 8-bit window that starts at its piece.  One generator call
+// per 8 elements, as on the aligned path.
+template <bool RAG, int V>
+__device__ __forceinline__ int piece_col(int pc, int pieces, int Sk) {
+  return (RAG && pc == pieces - 1) ? max(Sk - V, 0) : pc * V;
+}
+template <bool RAG, int V>
+__device__ __forceinline__ int piece_dup(int pc, int pieces, int Sk) {
+  return (RAG && pc == pieces - 1 && Sk >= V) ? pieces * V - Sk : 0;
+}
+// Rows shorter than a piece (SHORT: only the kernels with the fewest lanes per row take them) are
+// read and written element by element; `fill` stands for the rest of the piece.
+template <typename T, bool RAG, bool SHORT>
+__device__ __forceinline__ u32x4 load_row_piece(const T* p, int Sk, u32x4 fill) {
+  constexpr int V = Store<T>::kVec;
+  if constexpr (SHORT) {
+    if (Sk < V) {
+      float v[V];
+      Store<T>::unpack(fill, v);
+#pragma unroll
+      for (int k = 0; k < V; ++k)
+        if (k < Sk) v[k] = Store<T>::load1(p + k);
+      return Store<T>::pack(v);
+    }
+  }
+  return ldg_piece<RAG>(p);
+}
+template <typename T, bool RAG, bool SHORT>
+__device__ __forceinline__ void store_row_piece(T* p, int Sk, u32x4 w) {
+  constexpr int V = Store<T>::kVec;
+  if constexpr (SHORT) {
+    if (Sk < V) {
+      float v[V];
+      Store<T>::unpack(w, v);
+#pragma unroll
+      for (int k = 0; k < V; ++k)
+        if (k < Sk) Store<T>::store1(p + k, v[k]);
+      return;
+    }
+  }
+  stg_piece<RAG>(p, w);
+}
+constexpr bool takes_short_rows(bool ragged, int lanes, int vec) { return ragged && lanes * vec == 32; }
+// Keep bytes of a row of up to `elements` elements, whatever its alignment, and one more that a
+// window may touch.
+constexpr int keep_row_bytes(int elements) { return (elements + 7 + 7) / 8 + 2; }
+
+// Draws the keep bytes of the row that starts at element e0 into `row` (LDS) and, if keep_bits is
+// given, stores those of the groups that begin in this row: every byte of the mask has one
+// writer.  n: elements of the whole tensor; the last group's bits beyond it are 0, and so is the
+// rest of the last word.
+template <int LANES>
+__device__ __forceinline__ void draw_row_keep(uint8_t* row, int64_t e0, int Sk, int t,
+                                              const RngArgs& rng, uint32_t* keep_bits, int64_t n) {
+  const int64_t g0 = e0 >> 3;
+  const int h = static_cast<int>(e0 & 7);
+  const int groups = (h + Sk + 7) >> 3;
+  for (int b = t; b < groups; b += LANES) {
+    const uint32_t byte = keep_byte(static_cast<uint64_t>(g0 + b), rng);
+    row[b] = static_cast<uint8_t>(byte);
+    if (keep_bits && (b > 0 || h == 0)) {
+      uint8_t* kb = reinterpret_cast<uint8_t*>(keep_bits) + g0 + b;
+      const int64_t left = n - (g0 + b) * 8;
+      if (left > 8) {
+        *kb = static_cast<uint8_t>(byte);
+      } else {  // the last group of the tensor
+        *kb = static_cast<uint8_t>(byte & ((1u << left) - 1u));
+        for (int64_t i = g0 + b + 1; (i & 3) != 0; ++i) *++kb = 0;
+      }
+    }
+  }
+}
+// Keep bits of the piece that starts `r` elements after the first group of the row.
+template <int V>
+__device__ __forceinline__ uint32_t row_keep_window(const uint8_t* row, int r) {
+  const int b = r >> 3;
+  const uint32_t w = row[b] | (static_cast<uint32_t>(row[b + 1]) << 8);
+  return (w >> (r & 7)) & ((1u << V) - 1u);
+}
+// The same from the stored mask: bits e .. e + V - 1, by one two-byte load that stays inside the
+// mask's ceil(n / 32) words.
+template <int V>
+__device__ __forceinline__ uint32_t mask_window(const uint32_t* keep_bits, int64_t e, int64_t n) {
+  typedef uint16_t u16_any __attribute__((aligned(1)));
+  const int64_t last = ((n + 31) >> 5) * 4 - 2;
+  const int64_t b = min(e >> 3, last);
+  const uint32_t w =
+      *reinterpret_cast<const u16_any*>(reinterpret_cast<const uint8_t*>(keep_bits) + b);
+  return (w >> static_cast<int>(e - b * 8)) & ((1u << V) - 1u);
+}
+
+// How the keep bits of a row meet the mask: whole words (Sk % 32 == 0), whole bytes (Sk % 8 == 0),
+// or anyhow (ragged rows).
+enum MaskLayout { kWords, kBytes, kRagged };
+
 // Work unit = one "row set": kGroups*R consecutive query rows of one [Sq, Sk] slice, where
 // kGroups = kThreads/LANES lane groups each own R rows (rows base + r*kGroups + g) and CH
 // 16-byte pieces per row (piece c of lane t = c*LANES + t).  All R rows of a group are fetched
@@ -192,7 +294,7 @@ __device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, in
 // LANES = 128 or 256 spreads a long row over 2 or 4 waves: the pieces per lane, and with them
 // the registers per lane, stay small enough for many resident waves (a 3072-element bfloat16
 // row on one wave needs over 200 registers per lane, which leaves 2 waves per SIMD).
-template <typename T, int LANES, int CH, int R, bool WORDS, int THREADS>
+template <typename T, int LANES, int CH, int R, MaskLayout MASK, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
     const T* scores, const int32_t* __restrict__ key_len, int causal, T* probs,
     T* __restrict__ out, uint32_t* __restrict__ keep_bits, int slices, int A, int Sq, int Sk,
@@ -202,14 +304,21 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
   constexpr int V = Store<T>::kVec;
   const int g = threadIdx.x / LANES;
   const int t = threadIdx.x % LANES;
-  const int pieces = Sk / V;
+  constexpr bool RAG = MASK == kRagged;
+  constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
+  const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
   const int sets_per_slice = (Sq + kGroups * R - 1) / (kGroups * R);
   const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice;
   const int64_t total_pieces = static_cast<int64_t>(slices) * Sq * pieces;
   __shared__ float red[2][THREADS / kWave];
   static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
+  static_assert(!RAG || R == 1, "ragged rows: one row per group");
+  // two sets of rows: a wave may draw its next row while a slow one still reads this one's
+  constexpr int kKeepRow = keep_row_bytes(LANES * CH * V);
+  __shared__ uint8_t keep_lds[RAG ? 2 : 1][RAG ? kGroups : 1][RAG ? kKeepRow : 1];
+  int flip = 0;
 
-  for (int64_t rs = blockIdx.x; rs < total_sets; rs += gridDim.x) {
+  for (int64_t rs = blockIdx.x; rs < total_sets; rs += gridDim.x, flip ^= 1) {
     const int slice = static_cast<int>(rs / sets_per_slice);
     const int i0 = static_cast<int>(rs % sets_per_slice) * (kGroups * R) + g;
     const int key_limit = key_len ? min(max(key_len[slice / A], 0), Sk) : Sk;
@@ -223,10 +332,17 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
       const T* sr = scores + row_offset(static_cast<uint32_t>(slice) * Sq + i, Sk);
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const int col0 = (c * LANES + t) * V;
+        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
         if constexpr (CH == 1) raw[r][c].a = Store<T>::neg_inf_piece();  // see below
-        if (col0 < limit[r]) raw[r][c].load(sr + col0);
+        if (col0 < limit[r]) raw[r][c].a = load_row_piece<T, RAG, SHORT>(sr + col0, Sk, Store<T>::neg_inf_piece());
       }
+    }
+    uint8_t* const keep_row = keep_lds[RAG ? flip : 0][RAG ? g : 0];
+    if constexpr (RAG) {  // while the loads are under way
+      if (limit[0] >= 0)
+        draw_row_keep<LANES>(keep_row, row_offset(static_cast<uint32_t>(slice) * Sq + i0, Sk), Sk, t,
+                             rng, keep_bits, static_cast<int64_t>(slices) * Sq * Sk);
+      if constexpr (LANES <= kWave) wave_lds_fence();  // else the reductions' barriers order it
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -244,7 +360,7 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
       constexpr bool kSkip = CH > 1;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const int col0 = (c * LANES + t) * V;
+        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
         if (!kSkip || col0 < limit[r]) {
           raw[r][c].unpack(v[c]);
           if (col0 < limit[r] && col0 + V > limit[r]) {  // the piece the limit falls into
@@ -260,13 +376,14 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
       float sum = 0.0f;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const int col0 = (c * LANES + t) * V;
+        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
+        const int dup = piece_dup<RAG, V>(c * LANES + t, pieces, Sk);
         if (!kSkip || col0 < limit[r]) {
 #pragma unroll
           for (int k = 0; k < V; ++k) {
             const float e = __builtin_amdgcn_exp2f(fmaf(v[c][k], kLog2e, -shift));
             v[c][k] = e;
-            sum += e;
+            sum += (RAG && k < dup) ? 0.0f : e;
           }
         } else {  // masked, or padding beyond the row
 #pragma unroll
@@ -275,29 +392,33 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
       }
       sum = row_reduce<LANES, false>(sum, red[1]);
       const float rinv = (sum > 0.0f) ? __builtin_amdgcn_rcpf(sum) : 0.0f;
-      const int64_t piece0 = row0 / V;  // Sk is a multiple of the piece length here
+      const int64_t piece0 = row0 / V;  // aligned rows: Sk is a multiple of the piece length
       uint32_t bits[CH];
-      lane_keep_bits<T, LANES, CH>(piece0, t, rng, bits);
+      if constexpr (!RAG) lane_keep_bits<T, LANES, CH>(piece0, t, rng, bits);
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int pc = c * LANES + t;
         const bool valid = live && pc < pieces;
+        const int col0 = piece_col<RAG, V>(pc, pieces, Sk);
         if (valid) {
+          if constexpr (RAG)
+            bits[c] = row_keep_window<V>(keep_row, static_cast<int>(row0 & 7) + col0);
           float p8[V], o8[V];
 #pragma unroll
           for (int k = 0; k < V; ++k) p8[k] = v[c][k] * rinv;
           // round P once, into the words that are stored; Out is computed from the stored P
           const u32x4 pw = Store<T>::pack(p8);
           Store<T>::unpack(pw, p8);
-          stg_stream(probs + row0 + pc * V, pw);
+          store_row_piece<T, RAG, SHORT>(probs + row0 + col0, Sk, pw);
           if (out) {
 #pragma unroll
             for (int k = 0; k < V; ++k) o8[k] = p8[k] * scale;
-            stg_stream(out + row0 + pc * V, apply_keep<T>(Store<T>::pack(o8), bits[c]));
+            store_row_piece<T, RAG, SHORT>(out + row0 + col0, Sk, apply_keep<T>(Store<T>::pack(o8), bits[c]));
           }
         }
-        store_keep_bits<T, WORDS>(keep_bits, piece0 + pc, t, valid ? bits[c] : 0u, valid,
-                                  total_pieces);
+        if constexpr (!RAG)
+          store_keep_bits<T, MASK == kWords>(keep_bits, piece0 + pc, t, valid ? bits[c] : 0u, valid,
+                                             total_pieces);
       }
     }
   }
@@ -314,15 +435,26 @@ __device__ __forceinline__ uint32_t nonzero_bytes_to_bits(uint32_t w) {
   w &= 0x01010101u;
   return (w * 0x01020408u) >> 24;  // byte i -> bit i
 }
-template <typename T>
-__device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, int64_t element) {
+template <typename T, bool SHORT>
+__device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, int64_t element,
+                                                    int Sk) {
+  if constexpr (SHORT) {
+    if (Sk < Store<T>::kVec) {
+      uint32_t bits = 0;
+      for (int k = 0; k < Sk; ++k) bits |= (keep_bytes[element + k] != 0 ? 1u : 0u) << k;
+      return bits;
+    }
+  }
+  // at any byte address (ragged rows); aligned ones take the same instructions
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32_any __attribute__((aligned(1)));
+  typedef u32x2 u32x2_any __attribute__((aligned(1)));
   if constexpr (Store<T>::kVec == 4) {
     return nonzero_bytes_to_bits(
-        __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(keep_bytes + element)));
+        __builtin_nontemporal_load(reinterpret_cast<const u32_any*>(keep_bytes + element)));
   } else {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     const u32x2 w =
-        __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(keep_bytes + element));
+        __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(keep_bytes + element));
     return nonzero_bytes_to_bits(w.x) | (nonzero_bytes_to_bits(w.y) << 4);
   }
 }
@@ -333,7 +465,7 @@ __device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, i
 // bytes).
 enum MaskSource { kMaskWords, kMaskBytes, kMaskRegen, kMaskBools };
 
-template <typename T, int LANES, int CH, int R, MaskSource MASK, int THREADS>
+template <typename T, int LANES, int CH, int R, MaskSource MASK, bool RAG, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
     const T* dout, const T* __restrict__ probs, const uint32_t* __restrict__ keep_bits,
     T* dscores, T* __restrict__ out_re, uint32_t rows, int Sk, float scale, RngArgs rng) {
@@ -342,9 +474,14 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
   constexpr int V = Store<T>::kVec;
   const int g = threadIdx.x / LANES;
   const int t = threadIdx.x % LANES;
-  const int pieces = Sk / V;
+  constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
+  const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
   __shared__ float red[2][THREADS / kWave];
   static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
+  static_assert(!RAG || (R == 1 && MASK != kMaskWords), "ragged rows: one row per group, no whole words");
+  constexpr bool kDraw = RAG && MASK == kMaskRegen;  // the keep bytes of the rows, drawn into LDS
+  constexpr int kKeepRow = keep_row_bytes(LANES * CH * V);
+  __shared__ uint8_t keep_lds[kDraw ? 2 : 1][kDraw ? kGroups : 1][kDraw ? kKeepRow : 1];
   int flip = 0;  // one reduction per row set: consecutive sets alternate between the slot arrays
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * (kGroups * R); base < rows;
        base += static_cast<int64_t>(gridDim.x) * (kGroups * R), flip ^= 1) {
@@ -359,17 +496,33 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
         bits[r][c] = 0;
         if (row < rows && pc < pieces) {
           const int64_t row0 = row_offset(static_cast<uint32_t>(row), Sk);
-          rdo[r][c].load(dout + row0 + pc * V);
-          rp[r][c].load(probs + row0 + pc * V);
+          const int64_t e = row0 + piece_col<RAG, V>(pc, pieces, Sk);
+          rdo[r][c].a = load_row_piece<T, RAG, SHORT>(dout + e, Sk, u32x4{0u, 0u, 0u, 0u});
+          rp[r][c].a = load_row_piece<T, RAG, SHORT>(probs + e, Sk, u32x4{0u, 0u, 0u, 0u});
           if constexpr (MASK == kMaskBools)
-            bits[r][c] = load_keep_bools<T>(reinterpret_cast<const uint8_t*>(keep_bits),
-                                            row0 + pc * V);
+            bits[r][c] = load_keep_bools<T, SHORT>(reinterpret_cast<const uint8_t*>(keep_bits), e, Sk);
+          else if constexpr (RAG && MASK != kMaskRegen)
+            bits[r][c] = mask_window<V>(keep_bits, e, static_cast<int64_t>(rows) * Sk);
           else if constexpr (MASK != kMaskRegen)
             bits[r][c] = load_keep_bits<T, MASK == kMaskWords>(keep_bits, row0 / V + pc);
         }
       }
     }
-    if constexpr (MASK == kMaskRegen) {  // every lane takes part: lane pairs share draws
+    if constexpr (kDraw) {
+      uint8_t* const keep_row = keep_lds[flip][g];
+      const int64_t row0 = row_offset(static_cast<uint32_t>(base + g), Sk);
+      const bool live = base + g < rows;
+      if (live) draw_row_keep<LANES>(keep_row, row0, Sk, t, rng, nullptr, 0);
+      if constexpr (LANES <= kWave) wave_lds_fence();
+      else lds_barrier();
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const int pc = c * LANES + t;
+        if (live && pc < pieces)
+          bits[0][c] = row_keep_window<V>(
+              keep_row, static_cast<int>(row0 & 7) + piece_col<RAG, V>(pc, pieces, Sk));
+      }
+    } else if constexpr (MASK == kMaskRegen) {  // every lane takes part: lane pairs share draws
 #pragma unroll
       for (int r = 0; r < R; ++r)
         lane_keep_bits<T, LANES, CH>(
@@ -388,6 +541,7 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int pc = c * LANES + t;
+        const int dup = piece_dup<RAG, V>(pc, pieces, Sk);
         if (live && pc < pieces) {
           Store<T>::unpack(apply_keep<T>(rdo[r][c].a, bits[r][c]), dp[c]);  // dropped: dP = 0
           rp[r][c].unpack(pr[c]);
@@ -398,7 +552,7 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
 #pragma unroll
         for (int k = 0; k < V; ++k) {
           dp[c][k] *= scale;
-          dot = fmaf(dp[c][k], pr[c][k], dot);
+          if (!RAG || k >= dup) dot = fmaf(dp[c][k], pr[c][k], dot);
         }
       }
       dot = row_reduce<LANES, false>(dot, red[flip]);
@@ -406,16 +560,17 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
       for (int c = 0; c < CH; ++c) {
         const int pc = c * LANES + t;
         if (live && pc < pieces) {
+          const int64_t e = row0 + piece_col<RAG, V>(pc, pieces, Sk);
           float ds[V];
 #pragma unroll
           for (int k = 0; k < V; ++k) ds[k] = pr[c][k] * (dp[c][k] - dot);
-          store_piece<T>(dscores + row0 + pc * V, ds);
+          store_row_piece<T, RAG, SHORT>(dscores + e, Sk, Store<T>::pack(ds));
           if (out_re) {
             float o8[V];
 #pragma unroll
             for (int k = 0; k < V; ++k) o8[k] = pr[c][k] * scale;
-            stg_stream(out_re + row0 + pc * V,
-                       apply_keep<T>(Store<T>::pack(o8), bits[r][c]));
+            store_row_piece<T, RAG, SHORT>(out_re + e, Sk,
+                                           apply_keep<T>(Store<T>::pack(o8), bits[r][c]));
           }
         }
       }
@@ -549,191 +704,15 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_generic_kernel(
   }
 }
 
-// ---- any Sk up to 64 * KMAX: one wave per row, scalar accesses, the row held in registers ---
-// Element j of a row belongs to lane j % 64 (chunk k = j / 64), so every access of a wave is one
-// contiguous run whatever the row's alignment, and the row is read once.  Same arithmetic, in the
-// same order per lane, as the any-length kernels above.
+constexpr int kMaxPieces = 1024;  // 4 per lane of 4 waves
 
-// Keep bits of the chunks of such a row.  One generator call yields the bits of 8 consecutive
-// elements, so instead of one call per element each lane draws one group of a block of 7 chunks
-// (448 elements: at most 57 groups, whatever the block's alignment) and the lanes fetch the byte
-// of their element's group from the lane that drew it.
-constexpr int kChunksPerDraw = 7;
-template <int KMAX>
-struct RowKeep {
-  static constexpr int kBlocks = (KMAX + kChunksPerDraw - 1) / kChunksPerDraw;
-  uint32_t bytes[kBlocks];
-  int64_t e_row;
-  __device__ __forceinline__ void draw(int64_t row_start, int Sk, int lane, const RngArgs& rng) {
-    e_row = row_start;
-#pragma unroll
-    for (int b = 0; b < kBlocks; ++b) {
-      bytes[b] = 0;
-      if (b * kChunksPerDraw * kWave < Sk)  // uniform over the wave
-        bytes[b] = keep_byte(
-            static_cast<uint64_t>((e_row + b * kChunksPerDraw * kWave) >> 3) + lane, rng);
-    }
-  }
-  // Every lane of the wave has to make the call (cross-lane fetch), also lanes beyond the row.
-  __device__ __forceinline__ bool kept(int k, int lane) const {
-    const int b = k / kChunksPerDraw;
-    const int64_t e = e_row + k * kWave + lane;
-    const int src = static_cast<int>((e >> 3) - ((e_row + b * kChunksPerDraw * kWave) >> 3));
-    return (__shfl(bytes[b], src, kWave) >> (e & 7)) & 1u;
-  }
-};
-
-// The stored keep bits of such a row: the row's words (at most 2 per lane: 64 * KMAX elements
-// span up to 2 * KMAX + 1 words) are loaded once, one per lane, and fetched across lanes, instead
-// of one load per element.
-template <int KMAX>
-struct RowMaskWords {
-  static constexpr int kRegs = (2 * KMAX + 1 + kWave - 1) / kWave;
-  uint32_t w[kRegs];
-  int64_t e_row;
-  __device__ __forceinline__ void load(const uint32_t* keep_bits, int64_t row_start,
-                                       int64_t total_words, int lane) {
-    e_row = row_start;
-#pragma unroll
-    for (int r = 0; r < kRegs; ++r) {
-      const int64_t i = (e_row >> 5) + r * kWave + lane;
-      w[r] = (i < total_words) ? keep_bits[i] : 0u;
-    }
-  }
-  // Every lane of the wave has to make the call, also lanes beyond the row.
-  __device__ __forceinline__ bool kept(int k, int lane) const {
-    const int64_t e = e_row + k * kWave + lane;
-    const int wi = static_cast<int>((e >> 5) - (e_row >> 5));
-    uint32_t word = __shfl(w[0], wi & (kWave - 1), kWave);
-    if constexpr (kRegs > 1) {
-      const uint32_t hi = __shfl(w[1], wi & (kWave - 1), kWave);
-      word = wi < kWave ? word : hi;
-    }
-    return (word >> (e & 31)) & 1u;
-  }
-};
-
-template <typename T, int KMAX>
-__global__ __launch_bounds__(kThreads) void attn_fwd_rows_kernel(
-    const T* scores, const int32_t* __restrict__ key_len, int causal, T* probs,
-    T* __restrict__ out, int64_t rows, int64_t rows_per_batch, int Sq, int Sk, float scale,
-    RngArgs rng) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: row math stays scalar
-  constexpr int kWaves = kThreads / kWave;
-  for (int64_t row = static_cast<int64_t>(blockIdx.x) * kWaves + wave; row < rows;
-       row += static_cast<int64_t>(gridDim.x) * kWaves) {
-    const int key_limit = key_len ? min(max(key_len[row / rows_per_batch], 0), Sk) : Sk;
-    const int limit = row_limit(static_cast<int>(row % Sq), key_limit, causal, Sq, Sk);
-    const T* sr = scores + row * Sk;
-    T* pr = probs + row * Sk;
-    T* orow = out ? out + row * Sk : nullptr;
-    float v[KMAX];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      const int j = k * kWave + lane;
-      v[k] = -INFINITY;
-      if (k * kWave < limit) {  // uniform over the wave
-        if (j < limit) v[k] = Store<T>::load1(sr + j);
-        mx = fmaxf(mx, v[k]);
-      }
-    }
-    mx = group_max<kWave>(mx);
-    const float shift = (mx == -INFINITY) ? 0.0f : mx * kLog2e;
-    float sum = 0.0f;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      const int j = k * kWave + lane;
-      float e = 0.0f;
-      if (k * kWave < limit && j < limit) {
-        e = __builtin_amdgcn_exp2f(fmaf(v[k], kLog2e, -shift));
-        sum += e;
-      }
-      v[k] = e;
-    }
-    sum = group_sum<kWave>(sum);
-    const float rinv = (sum > 0.0f) ? 1.0f / sum : 0.0f;
-    RowKeep<KMAX> keep;
-    if (out) keep.draw(row * Sk, Sk, lane, rng);
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      if (k * kWave < Sk) {  // uniform over the wave
-        const int j = k * kWave + lane;
-        const float p = (j < limit) ? Store<T>::round(v[k] * rinv) : 0.0f;
-        const bool kb = out ? keep.kept(k, lane) : false;
-        if (j < Sk) {
-          Store<T>::store1(pr + j, p);
-          if (out) Store<T>::store1(orow + j, kb ? p * scale : 0.0f);
-        }
-      }
-    }
-  }
+// Shapes of the ragged rows: those that at most kRaggedMaxPieces pieces per lane lead to, whatever
+// the knobs say, in workgroups of two waves (of the row's four where it takes four).
+constexpr int kRaggedMaxPieces = 4;
+constexpr bool is_ragged_shape(int lanes, int ch) {
+  return ch <= kRaggedMaxPieces && (lanes <= kWave || ch > 2);
 }
-
-template <typename T, MaskSource MASK, int KMAX>
-__global__ __launch_bounds__(kThreads) void attn_bwd_rows_kernel(
-    const T* dout, const T* __restrict__ probs, const uint32_t* __restrict__ keep_bits,
-    T* dscores, T* __restrict__ out_re, int64_t rows, int Sk, float scale, RngArgs rng) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: row math stays scalar
-  constexpr int kWaves = kThreads / kWave;
-  for (int64_t row = static_cast<int64_t>(blockIdx.x) * kWaves + wave; row < rows;
-       row += static_cast<int64_t>(gridDim.x) * kWaves) {
-    const int64_t e_row = row * Sk;
-    RowKeep<KMAX> keep;
-    RowMaskWords<KMAX> stored;
-    if constexpr (MASK == kMaskRegen) keep.draw(e_row, Sk, lane, rng);
-    if constexpr (MASK == kMaskWords) stored.load(keep_bits, e_row, (rows * Sk + 31) >> 5, lane);
-    const T* do_row = dout + e_row;
-    const T* p_row = probs + e_row;
-    T* ds_row = dscores + e_row;
-    T* or_row = out_re ? out_re + e_row : nullptr;
-    float dp[KMAX], pr[KMAX];
-    uint32_t kept_bits = 0;  // bit k: element k * 64 + lane is kept
-    float dot = 0.0f;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      dp[k] = pr[k] = 0.0f;
-      if (k * kWave < Sk) {  // uniform over the wave
-        const int j = k * kWave + lane;
-        const int64_t e = e_row + j;
-        bool kb = false;
-        if constexpr (MASK == kMaskRegen) {
-          kb = keep.kept(k, lane);
-        } else if constexpr (MASK == kMaskWords) {
-          kb = stored.kept(k, lane);
-        } else if (j < Sk) {
-          kb = reinterpret_cast<const uint8_t*>(keep_bits)[e] != 0;
-        }
-        if (j < Sk) {
-          pr[k] = Store<T>::load1(p_row + j);
-          dp[k] = kb ? Store<T>::load1(do_row + j) * scale : 0.0f;
-          dot = fmaf(dp[k], pr[k], dot);
-          kept_bits |= (kb ? 1u : 0u) << k;
-        }
-      }
-    }
-    dot = group_sum<kWave>(dot);
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      const int j = k * kWave + lane;
-      if (k * kWave < Sk && j < Sk) {
-        Store<T>::store1(ds_row + j, pr[k] * (dp[k] - dot));
-        if (out_re) Store<T>::store1(or_row + j, ((kept_bits >> k) & 1u) ? pr[k] * scale : 0.0f);
-      }
-    }
-  }
-}
-
-// Chunks of 64 elements a row of Sk elements needs in registers: 4, 16 or 32; 0: too long.
-int row_chunks(int64_t Sk) { return Sk <= 256 ? 4 : (Sk <= 1024 ? 16 : (Sk <= 2048 ? 32 : 0)); }
-template <typename F>
-void with_row_chunks(int kmax, F&& f) {
-  if (kmax == 4) f(std::integral_constant<int, 4>{});
-  else if (kmax == 16) f(std::integral_constant<int, 16>{});
-  else f(std::integral_constant<int, 32>{});
-}
+constexpr int ragged_threads(int lanes) { return lanes > 2 * kWave ? lanes : 2 * kWave; }
 
 struct Shape {
   int lanes;
@@ -767,6 +746,14 @@ Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
     }
   }
   return one;
+}
+
+// Shape for rows of Sk elements; ch == 0: too long for the register-resident kernels.
+Shape row_shape(int64_t Sk, int vec, int max_ch) {
+  const bool ragged = Sk % 8 != 0;
+  const int64_t pieces = (Sk + vec - 1) / vec;
+  if (pieces > kMaxPieces) return {0, 0};
+  return pick_wide_shape(static_cast<int>(pieces), 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
 }
 
 // Rows a lane group of the forward kernel fetches at once: 2 (if the knob allows) when a
@@ -831,26 +818,31 @@ int row_grid(int64_t rows, int lanes, int blocks_per_cu, int rows_per_group = 1,
     default: return TEMPO_ERR_UNSUPPORTED;                                                 \
   }
 
-// Calls f with the workgroup size as a compile-time constant (64, 128 or 256, at least L).
-template <int L, typename F>
+// Calls f with the workgroup size as a compile-time constant: 64, 128 or 256, at least L; with
+// FIXED the default size only.
+template <int L, bool FIXED, typename F>
 static void with_threads(int threads, F&& f) {
   using std::integral_constant;
-  if constexpr (L <= 64) {
-    if (threads == 64) return f(integral_constant<int, 64>{});
+  if constexpr (FIXED) {
+    return f(integral_constant<int, ragged_threads(L)>{});
+  } else {
+    if constexpr (L <= 64) {
+      if (threads == 64) return f(integral_constant<int, 64>{});
+    }
+    if constexpr (L <= 128) {
+      if (threads == 128) return f(integral_constant<int, 128>{});
+    }
+    f(integral_constant<int, 256>{});
   }
-  if constexpr (L <= 128) {
-    if (threads == 128) return f(integral_constant<int, 128>{});
-  }
-  f(integral_constant<int, 256>{});
 }
 
 template <typename T, int L, int C>
-static void attn_fwd_go(int rr, bool words, int threads, dim3 grid, hipStream_t st,
+static void attn_fwd_go(int rr, MaskLayout layout, int threads, dim3 grid, hipStream_t st,
                         const void* scores, const int32_t* key_len, int causal, void* probs,
                         void* out, uint32_t* keep_bits, int slices, int64_t A, int64_t Sq,
                         int64_t Sk, float scale, const RngArgs& rng) {
   auto go = [&](auto rows, auto w) {
-    with_threads<L>(threads, [&](auto th) {
+    with_threads<L, decltype(w)::value == kRagged>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL(
           (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), grid, dim3(TH),
@@ -860,34 +852,49 @@ static void attn_fwd_go(int rr, bool words, int threads, dim3 grid, hipStream_t 
     });
   };
   using std::integral_constant;
+  const integral_constant<MaskLayout, kWords> words{};
+  const integral_constant<MaskLayout, kBytes> bytes{};
   if constexpr (C <= 2 && L <= kWave) {
     if (rr == 2) {
-      if (words) return go(integral_constant<int, 2>{}, std::true_type{});
-      return go(integral_constant<int, 2>{}, std::false_type{});
+      if (layout == kWords) return go(integral_constant<int, 2>{}, words);
+      return go(integral_constant<int, 2>{}, bytes);
     }
   }
-  if (words) return go(integral_constant<int, 1>{}, std::true_type{});
-  go(integral_constant<int, 1>{}, std::false_type{});
+  if constexpr (is_ragged_shape(L, C)) {
+    if (layout == kRagged) return go(integral_constant<int, 1>{}, integral_constant<MaskLayout, kRagged>{});
+  }
+  if (layout == kWords) return go(integral_constant<int, 1>{}, words);
+  go(integral_constant<int, 1>{}, bytes);
 }
 
 template <typename T, int L, int C>
-static void attn_bwd_go(MaskSource mask, int threads, int grid, hipStream_t st, const void* dout,
+static void attn_bwd_go(MaskSource mask, bool ragged, int threads, int grid, hipStream_t st, const void* dout,
                         const void* probs, const uint32_t* keep_bits, void* dscores, void* out_re,
                         int64_t rows, int64_t Sk, float scale, const RngArgs& rng) {
-  auto go = [&](auto m) {
-    with_threads<L>(threads, [&](auto th) {
+  auto go = [&](auto m, auto rag) {
+    with_threads<L, decltype(rag)::value>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
-      hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, 1, decltype(m)::value, TH>), dim3(grid), dim3(TH),
+      hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, 1, decltype(m)::value, decltype(rag)::value, TH>), dim3(grid), dim3(TH),
                          0, st, static_cast<const T*>(dout), static_cast<const T*>(probs), keep_bits,
                          static_cast<T*>(dscores), static_cast<T*>(out_re),
                          static_cast<uint32_t>(rows), static_cast<int>(Sk), scale, rng);
     });
   };
   using std::integral_constant;
-  if (mask == kMaskWords) return go(integral_constant<MaskSource, kMaskWords>{});
-  if (mask == kMaskBytes) return go(integral_constant<MaskSource, kMaskBytes>{});
-  if (mask == kMaskBools) return go(integral_constant<MaskSource, kMaskBools>{});
-  go(integral_constant<MaskSource, kMaskRegen>{});
+  const integral_constant<MaskSource, kMaskBytes> bytes{};
+  const integral_constant<MaskSource, kMaskBools> bools{};
+  const integral_constant<MaskSource, kMaskRegen> regen{};
+  if constexpr (is_ragged_shape(L, C)) {
+    if (ragged) {
+      if (mask == kMaskBytes) return go(bytes, std::true_type{});
+      if (mask == kMaskBools) return go(bools, std::true_type{});
+      return go(regen, std::true_type{});
+    }
+  }
+  if (mask == kMaskWords) return go(integral_constant<MaskSource, kMaskWords>{}, std::false_type{});
+  if (mask == kMaskBytes) return go(bytes, std::false_type{});
+  if (mask == kMaskBools) return go(bools, std::false_type{});
+  go(regen, std::false_type{});
 }
 
 static RngArgs make_rng(float p, uint64_t seed, uint64_t offset) {
@@ -912,22 +919,23 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
   const RngArgs rng = make_rng(p, seed, offset);
   const int bpc = tune_get(kTuneAttnFwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
-  Shape sh = pick_wide_shape(static_cast<int>(Sk / vec), 32 / vec,
-                            tune_get(kTuneAttnFwdMaxPieces));
-  if (Sk % 8 == 0 && sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
+  const bool ragged = Sk % 8 != 0;
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnFwdMaxPieces));
+  if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int slices = static_cast<int>(B * A);
-    const int rr = sh.lanes > kWave ? 1 : attn_rows(sh.ch, sh.lanes, vec, tune_get(kTuneAttnFwdRows));
-    const int threads = group_threads(sh.lanes);
+    const int rr = sh.lanes > kWave || ragged
+                       ? 1 : attn_rows(sh.ch, sh.lanes, vec, tune_get(kTuneAttnFwdRows));
+    const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
     const int rows_per_set = (threads / sh.lanes) * rr;
     const int64_t total_sets =
         static_cast<int64_t>(slices) * ((Sq + rows_per_set - 1) / rows_per_set);
     const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
     const dim3 grid(static_cast<unsigned>(total_sets < cap ? total_sets : cap));
-    const bool words = (Sk % 32 == 0);
+    const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, words, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);   \
-    else attn_fwd_go<bf16_t, L, C>(rr, words, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);   \
+    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);                  \
   } while (0)
     if (sh.lanes > kWave) {
       TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
@@ -938,21 +946,7 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     return launch_status();
   }
   const int grid = row_grid(rows, kWave, bpc);
-  if (const int kmax = row_chunks(Sk)) {
-    with_row_chunks(kmax, [&](auto km) {
-      constexpr int KM = decltype(km)::value;
-      if (dt == TEMPO_F32)
-        hipLaunchKernelGGL((attn_fwd_rows_kernel<float, KM>), dim3(grid), dim3(kThreads), 0, st,
-                           static_cast<const float*>(scores), key_len, causal,
-                           static_cast<float*>(probs), static_cast<float*>(out), rows,
-                           rows_per_batch, static_cast<int>(Sq), static_cast<int>(Sk), scale, rng);
-      else
-        hipLaunchKernelGGL((attn_fwd_rows_kernel<bf16_t, KM>), dim3(grid), dim3(kThreads), 0, st,
-                           static_cast<const bf16_t*>(scores), key_len, causal,
-                           static_cast<bf16_t*>(probs), static_cast<bf16_t*>(out), rows,
-                           rows_per_batch, static_cast<int>(Sq), static_cast<int>(Sk), scale, rng);
-    });
-  } else if (dt == TEMPO_F32)
+  if (dt == TEMPO_F32)
     hipLaunchKernelGGL((attn_fwd_generic_kernel<float>), dim3(grid), dim3(kThreads), 0, st,
                        static_cast<const float*>(scores), key_len, causal,
                        static_cast<float*>(probs), static_cast<float*>(out), rows, rows_per_batch,
@@ -983,17 +977,17 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
   const bool regen = keep_bits == nullptr;
   const int bpc = tune_get(kTuneAttnBwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
-  Shape sh = pick_wide_shape(static_cast<int>(Sk / vec), 32 / vec,
-                            tune_get(kTuneAttnBwdMaxPieces));
-  if (Sk % 8 == 0 && sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
-    const int threads = group_threads(sh.lanes);
+  const bool ragged = Sk % 8 != 0;
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces));
+  if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
+    const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
     const int grid = row_grid(rows, sh.lanes, bpc, 1, threads);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
-    else attn_bwd_go<bf16_t, L, C>(mask, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
+    else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
   } while (0)
     if (sh.lanes > kWave) {
       TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
@@ -1004,18 +998,8 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
     return launch_status();
   }
   const int grid = row_grid(rows, kWave, bpc);
-  const int kmax = row_chunks(Sk);
   auto go = [&](auto tag, auto m) {
     using T = decltype(tag);
-    if (kmax) {
-      with_row_chunks(kmax, [&](auto km) {
-        hipLaunchKernelGGL((attn_bwd_rows_kernel<T, decltype(m)::value, decltype(km)::value>),
-                           dim3(grid), dim3(kThreads), 0, st, static_cast<const T*>(dout),
-                           static_cast<const T*>(probs), keep_bits, static_cast<T*>(dscores),
-                           static_cast<T*>(out_re), rows, static_cast<int>(Sk), scale, rng);
-      });
-      return;
-    }
     hipLaunchKernelGGL((attn_bwd_generic_kernel<T, decltype(m)::value>), dim3(grid),
                        dim3(kThreads), 0, st, static_cast<const T*>(dout),
                        static_cast<const T*>(probs), keep_bits, static_cast<T*>(dscores),

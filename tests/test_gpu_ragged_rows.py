@@ -1,0 +1,96 @@
+"""Rows whose length is no multiple of a 16-byte piece, against the oracle: both sides of every
+shape of the ragged kernels (shorter than a piece, one element more than a piece, the last lane of a
+group, one or several pieces per lane, one or several waves per row), every mask source, in place,
+and with guard words behind every output."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import TOL, rel_err
+from oracle import tempo_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+TDT = {"f32": torch.float32, "bf16": torch.bfloat16}
+GUARD = 64
+
+
+@pytest.fixture(scope="module")
+def B():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2210_10246_amd import binding
+    binding.load()
+    return binding
+
+
+def dev(a, dt):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(TDT[dt]).cuda()
+
+
+def host(t):
+    return t.detach().cpu().to(torch.float64).numpy()
+
+
+def stored(rng, shape, dt, scale=1.0):
+    return O.round_to_dtype(rng.standard_normal(shape) * scale, dt)
+
+
+def guarded(shape, dtype, init=None):
+    """A tensor of that shape with GUARD elements of 7 behind it."""
+    n = int(np.prod(shape))
+    buf = torch.full((n + GUARD,), 7, dtype=dtype, device="cuda")
+    if init is not None:
+        buf[:n] = init.reshape(-1)
+    return buf[:n].view(shape), buf[n:]
+
+
+# row length, rows: the last row ends inside a mask word, on one, or one element before one
+ATTN_ROWS = [(1, 33), (3, 21), (5, 13), (7, 9), (9, 7), (15, 3), (31, 5), (33, 9), (63, 3), (65, 2), (127, 3),
+             (129, 5), (253, 3), (255, 2), (257, 3), (333, 5), (505, 2), (511, 3), (513, 3), (769, 2),
+             (1023, 3), (1025, 2), (1535, 2), (2047, 2), (2049, 2), (3071, 1), (4093, 2), (4095, 1),
+             (8191, 1)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Sk,Sq", ATTN_ROWS)
+def test_attention_ragged_rows(B, Sk, Sq, dt):
+    rng = np.random.default_rng(Sk)
+    shape = (2, 1, Sq, Sk)
+    p, seed, offset = np.float32(0.2), 0x123456789ABC, 5
+    causal = Sk % 4 == 1
+    key_len = np.array([Sk, max(1, Sk * 2 // 3)], dtype=np.int32) if Sk % 4 == 3 else None
+    s = stored(rng, shape, dt, 0.5)
+    P_ref, out_ref, K_ref = O.attn_softmax_dropout_fwd(s, key_len, causal, p, seed, offset, dt)
+    sd = dev(s, dt)
+    kd = None if key_len is None else torch.from_numpy(key_len).cuda()
+    n = s.size
+    for in_place in (False, True):
+        Pd, g0 = guarded(shape, TDT[dt], sd if in_place else None)
+        od, g1 = guarded(shape, TDT[dt])
+        md, g2 = guarded((B.mask_words(n),), torch.int32)
+        B.tempo_attn_softmax_dropout_fwd(Pd if in_place else sd, kd, causal, Pd, od, md, float(p), seed, offset)
+        assert np.array_equal(md.cpu().numpy().view(np.uint32), O.pack_bits(K_ref))
+        assert rel_err(host(Pd), P_ref) <= TOL[dt]
+        assert rel_err(host(od), out_ref) <= TOL[dt]
+        for g in (g0, g1, g2):
+            assert (g == 7).all()
+    dout = stored(rng, shape, dt)
+    dS_ref, out_re_ref = O.attn_softmax_dropout_bwd(dout, P_ref, K_ref, p, dt)
+    dod, Pd2 = dev(dout, dt), dev(P_ref, dt)
+    keep = torch.from_numpy(np.ascontiguousarray(K_ref).reshape(-1).astype(np.uint8)).cuda()
+    results = []
+    for source in ("bits", "regen", "bytes"):
+        dsd, g0 = guarded(shape, TDT[dt], dod)
+        rd, g1 = guarded(shape, TDT[dt])
+        if source == "bits":       # in place: dscores is dout
+            B.tempo_attn_softmax_dropout_bwd(dsd, Pd2, md, dsd, rd, float(p))
+        elif source == "regen":
+            B.tempo_attn_softmax_dropout_bwd_regen(dod, Pd2, dsd, rd, float(p), seed, offset)
+        else:
+            B.tempo_attn_softmax_dropout_bwd_bytemask(dod, Pd2, keep, dsd, rd, float(p))
+        assert rel_err(host(dsd), dS_ref) <= TOL[dt], source
+        assert rel_err(host(rd), out_re_ref) <= TOL[dt], source
+        assert (g0 == 7).all() and (g1 == 7).all(), source
+        results.append((dsd, rd))
+    for dsd, rd in results[1:]:
+        assert torch.equal(dsd, results[0][0]) and torch.equal(rd, results[0][1])
