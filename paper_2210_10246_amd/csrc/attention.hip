@@ -183,22 +183,12 @@ __device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, in
 }
 
 // ---- rows of any length ("ragged": Sk % 8 != 0) --------------------------------------------
-// A row is still owned in 16-byte pieces counted from its own start, piece c of lane t =
-// c*LANES + t, read and written by 16-byte accesses at element-aligned addresses; the last piece
-// is moved back to end with the row, so that no access leaves the row and none is partial.  The
-// elements it shares with the piece before ("dup", at most V - 1) are computed and stored twice
-// with the same value and left out of the row sums.  Pieces do not line up with the generator's
-// groups of 8 elements, nor rows with mask words: the row's keep bytes, one per group, go through
-// LDS, from where a lane takes the 8-bit window that starts at its piece.  One generator call
-// per 8 elements, as on the aligned path.
-template <bool RAG, int V>
-__device__ __forceinline__ int piece_col(int pc, int pieces, int Sk) {
-  return (RAG && pc == pieces - 1) ? max(Sk - V, 0) : pc * V;
-}
-template <bool RAG, int V>
-__device__ __forceinline__ int piece_dup(int pc, int pieces, int Sk) {
-  return (RAG && pc == pieces - 1 && Sk >= V) ? pieces * V - Sk : 0;
-}
+// The pieces of a row (piece_col, piece_dup) do not line up with the generator's groups of 8
+// elements, nor rows with mask words: the row's keep bytes, one per group, go through LDS, from
+// where a lane takes the 8-bit window that starts at its piece.  One generator call per 8 elements,
+// as on the aligned path.
+// Measured, forward + backward: bfloat16 16x16x333x333 under a padding mask 198 us element by element,
+// 94 us this way (aligned rows of 336 elements: 81); 8x12x1001x1001 557 -> 254 us (regen).
 // Rows shorter than a piece (SHORT: only the kernels with the fewest lanes per row take them) are
 // read and written element by element; `fill` stands for the rest of the piece.
 template <typename T, bool RAG, bool SHORT>

@@ -32,13 +32,38 @@ constexpr int kMaxFastPiecesF32 = 2048;
 // workgroups of that size still fit a compute unit.
 constexpr size_t kOneStepLdsBytes = 64 * 1024;
 
+// The V parameters or column sums of a piece, at a 16-byte aligned address unless RAG.
+template <bool RAG, int V>
+__device__ __forceinline__ void load_cols(const float* p, float (&v)[V]) {
+  if constexpr (RAG) load_floats_any<V>(p, v);
+  else load_floats<V>(p, v);
+}
+// Column sums of piece ch of a row of M columns -> p[0 .. M).  The first `dup` sums of the last
+// piece of a ragged row belong to the piece before.  ALIGNED: p is 16-byte aligned.
+template <bool RAG, bool ALIGNED, int V>
+__device__ __forceinline__ void store_col_sums(float* p, int ch, int chunks, int M, const float (&v)[V]) {
+  if (RAG && ch == chunks - 1) {
+    const int col = piece_col<RAG, V>(ch, chunks, M), dup = piece_dup<RAG, V>(ch, chunks, M);
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (i >= dup) p[col + i] = v[i];
+  } else if constexpr (ALIGNED) {
+    store_floats<V>(p + ch * V, v);
+  } else {
+    store_floats_any<V>(p + ch * V, v);
+  }
+}
+// Length of a row of column sums in LDS: whole 16-byte pieces.
+__host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int64_t{3}; }
+
 // Forward.  A batch is kGroups*R consecutive rows; lane group g takes rows base + r*kGroups + g
 // and fetches all R of them (packed) before any arithmetic, so that short rows still keep
 // several 16-byte loads per lane in flight.  LOOP = false: one batch per workgroup (the grid
 // must cover every batch).  LOOP = true: workgroups walk the batches grid-stride, fetching the
 // next batch before they compute on the current one, and load gamma/beta once: for long rows
 // the parameters (8 bytes per column from L2) otherwise outweigh the row itself.
-template <typename T, int LANES, int CH, int R, bool LOOP>
+// RAG: rows of any length that is no multiple of the piece (see piece_col).
+template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
     const T* x, const float* __restrict__ gamma, const float* __restrict__ beta, T* y,
     float* __restrict__ rstd_out, float* __restrict__ mean_out, int64_t N, int M, float eps) {
@@ -46,7 +71,7 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
   constexpr int V = Store<T>::kVec;
   const int g = threadIdx.x / LANES;
   const int t = threadIdx.x % LANES;
-  const int chunks = M / V;
+  const int chunks = RAG ? (M + V - 1) / V : M / V;
   // mean and variance by a true division: a row of equal values c then has the mean c exactly
   // (its sum c*M is exact) and zero variance, whatever the rounding of 1/M would do
   const float m_f = static_cast<float>(M);
@@ -61,7 +86,7 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
           const int ch = c * LANES + t;
-          if (ch < chunks) f[r][c].load(x + row * M + ch * V);
+          if (ch < chunks) f[r][c].a = ldg_piece<RAG>(x + row * M + piece_col<RAG, V>(ch, chunks, M));
         }
       }
     }
@@ -77,8 +102,8 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
   for (int c = 0; c < CH; ++c) {
     const int ch = c * LANES + t;
     if (ch < chunks) {
-      load_floats<V>(gamma + ch * V, ga[c]);
-      load_floats<V>(beta + ch * V, be[c]);
+      load_cols<RAG, V>(gamma + piece_col<RAG, V>(ch, chunks, M), ga[c]);
+      load_cols<RAG, V>(beta + piece_col<RAG, V>(ch, chunks, M), be[c]);
     } else {
 #pragma unroll
       for (int i = 0; i < V; ++i) ga[c][i] = be[c][i] = 0.0f;
@@ -109,7 +134,8 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
           for (int i = 0; i < V; ++i) v[c][i] = 0.0f;
         }
 #pragma unroll
-        for (int i = 0; i < V; ++i) sum += v[c][i];
+        for (int i = 0; i < V; ++i)
+          sum += (RAG && i < piece_dup<RAG, V>(ch, chunks, M)) ? 0.0f : v[c][i];
       }
       const float mu = row_reduce<LANES, false>(sum, red[0]) / m_f;
       float sq = 0.0f;
@@ -120,7 +146,7 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
         for (int i = 0; i < V; ++i) {
           const float d = v[c][i] - mu;
           v[c][i] = d;
-          sq += (ch < chunks) ? d * d : 0.0f;
+          sq += (ch < chunks && i >= piece_dup<RAG, V>(ch, chunks, M)) ? d * d : 0.0f;
         }
       }
       const float var = row_reduce<LANES, false>(sq, red[1]) / m_f;
@@ -132,7 +158,7 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
           float o[V];
 #pragma unroll
           for (int i = 0; i < V; ++i) o[i] = fmaf(v[c][i] * rs, ga[c][i], be[c][i]);
-          store_piece<T>(y + row * M + ch * V, o);
+          stg_piece<RAG>(y + row * M + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(o));
         }
       }
       if (t == 0 && live) {
@@ -231,7 +257,8 @@ __global__ __launch_bounds__(256) void ln_fwd_generic_kernel(
 // LOOP = true: workgroups walk the batches grid-stride and fetch the next batch before they
 // compute on the current one; the column sums stay in registers across batches, so the LDS
 // tree and the partial store are paid once per workgroup however many rows it walks.
-template <typename T, int LANES, int CH, int R, bool LOOP>
+// RAG: rows of any length that is no multiple of the piece (see piece_col), parameters in registers.
+template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     const T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ rstd, T* dx,
@@ -243,7 +270,8 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   const int t = threadIdx.x % LANES;
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x & (kWave - 1);
-  const int chunks = M / V;
+  const int chunks = RAG ? (M + V - 1) / V : M / V;
+  const int Ml = RAG ? static_cast<int>(lds_row(M)) : M;  // a row of column sums in LDS
   const float inv_m = 1.0f / static_cast<float>(M);
   const int64_t batch_rows = kGroups * R;
   __shared__ float2 red[2][kBwdWaves];
@@ -255,6 +283,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   // vectors twice: at 8 waves per compute unit that is microseconds of LDS time per batch.
   // The column sums are always in registers.
   constexpr bool kRegParams = CH * V <= 24;
+  static_assert(!RAG || kRegParams, "ragged rows: parameters in registers");
   float* p_ga = lds;
   float* p_rg = lds + M;
   float* p_bg = lds + 2 * M;
@@ -281,8 +310,9 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
         for (int c = 0; c < CH; ++c) {
           const int ch = c * LANES + t;
           if (ch < chunks) {
-            fd[r][c].load(dy + row * M + ch * V);
-            fy[r][c].load(y + row * M + ch * V);
+            const int64_t e = row * M + piece_col<RAG, V>(ch, chunks, M);
+            fd[r][c].a = ldg_piece<RAG>(dy + e);
+            fy[r][c].a = ldg_piece<RAG>(y + e);
           }
         }
         fs[r] = rstd[row];
@@ -301,8 +331,8 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
       const int ch = c * LANES + t;
       float be[V];
       if (ch < chunks) {
-        load_floats<V>(gamma + ch * V, r_ga[c]);
-        load_floats<V>(beta + ch * V, be);
+        load_cols<RAG, V>(gamma + piece_col<RAG, V>(ch, chunks, M), r_ga[c]);
+        load_cols<RAG, V>(beta + piece_col<RAG, V>(ch, chunks, M), be);
       } else {
 #pragma unroll
         for (int i = 0; i < V; ++i) {
@@ -367,8 +397,10 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
           for (int i = 0; i < V; ++i) {
             const float h = fmaf(y8[i], rg[i], -bg[i]);  // xhat = (y - beta) / gamma
             const float q = d8[i] * ga[i];
-            c1[r] = fmaf(q, h, c1[r]);
-            c2[r] += q;
+            if (!RAG || i >= piece_dup<RAG, V>(ch, chunks, M)) {
+              c1[r] = fmaf(q, h, c1[r]);
+              c2[r] += q;
+            }
             acc_g[c][i] = fmaf(d8[i], h, acc_g[c][i]);
             acc_b[c][i] += d8[i];
             if constexpr (kKeep) {
@@ -422,7 +454,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
               o[i] = rs[r] * (d8[i] * ga[i] - fmaf(h, c1[r], c2[r]));
             }
           }
-          store_piece<T>(dx + row * M + ch * V, o);
+          stg_piece<RAG>(dx + row * M + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(o));
         }
       }
     }
@@ -469,24 +501,24 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   constexpr int kRowWaves = LANES > kWave ? LANES / kWave : 1;
   constexpr int S = kBwdWaves / kRowWaves;
   float* out = partial + static_cast<size_t>(blockIdx.x) * 2 * M;
-  if (static_cast<size_t>(S) * 2 * M * sizeof(float) <= kOneStepLdsBytes) {
+  if (static_cast<size_t>(S) * 2 * Ml * sizeof(float) <= kOneStepLdsBytes) {
     if constexpr (!kRegParams) lds_barrier();  // the parameters in LDS are no longer read
     if (owner) {
-      float* slot = lds + static_cast<size_t>(wave / kRowWaves) * 2 * M;
+      float* slot = lds + static_cast<size_t>(wave / kRowWaves) * 2 * Ml;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int ch = c * LANES + t;
         if (ch < chunks) {
-          store_floats<V>(slot + ch * V, acc_g[c]);
-          store_floats<V>(slot + M + ch * V, acc_b[c]);
+          store_col_sums<RAG, true, V>(slot, ch, chunks, M, acc_g[c]);
+          store_col_sums<RAG, true, V>(slot + Ml, ch, chunks, M, acc_b[c]);
         }
       }
     }
     lds_barrier();
-    for (int j = threadIdx.x * 4; j < 2 * M; j += kBwdThreads * 4) {
+    for (int j = threadIdx.x * 4; j < 2 * Ml; j += kBwdThreads * 4) {
       float v[S][4];
 #pragma unroll
-      for (int k = 0; k < S; ++k) load_floats<4>(lds + static_cast<size_t>(k) * 2 * M + j, v[k]);
+      for (int k = 0; k < S; ++k) load_floats<4>(lds + static_cast<size_t>(k) * 2 * Ml + j, v[k]);
 #pragma unroll
       for (int half = S / 2; half >= 1; half >>= 1) {
 #pragma unroll
@@ -495,7 +527,17 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
           for (int i = 0; i < 4; ++i) v[k][i] += v[k + half][i];
         }
       }
-      store_floats<4>(out + j, v[0]);
+      if constexpr (RAG) {  // from LDS rows of Ml to slot rows of M floats
+        const int col = j < Ml ? j : j - Ml;
+        float* o = out + (j < Ml ? 0 : M) + col;
+        if (col + 4 <= M) {
+          store_floats_any<4>(o, v[0]);
+        } else {
+          for (int i = 0; col + i < M; ++i) o[i] = v[0][i];
+        }
+      } else {
+        store_floats<4>(out + j, v[0]);
+      }
     }
     return;
   }
@@ -503,26 +545,26 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   for (int half = kBwdWaves / 2; half >= kRowWaves; half >>= 1) {
     lds_barrier();
     if (wave >= half && wave < 2 * half && owner) {
-      float* slot = lds + static_cast<size_t>((wave - half) / kRowWaves) * 2 * M;
+      float* slot = lds + static_cast<size_t>((wave - half) / kRowWaves) * 2 * Ml;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int ch = c * LANES + t;
         if (ch < chunks) {
-          store_floats<V>(slot + ch * V, acc_g[c]);
-          store_floats<V>(slot + M + ch * V, acc_b[c]);
+          store_col_sums<RAG, true, V>(slot, ch, chunks, M, acc_g[c]);
+          store_col_sums<RAG, true, V>(slot + Ml, ch, chunks, M, acc_b[c]);
         }
       }
     }
     lds_barrier();
     if (wave < half && owner) {
-      const float* slot = lds + static_cast<size_t>(wave / kRowWaves) * 2 * M;
+      const float* slot = lds + static_cast<size_t>(wave / kRowWaves) * 2 * Ml;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int ch = c * LANES + t;
         if (ch < chunks) {
           float a[V], b[V];
-          load_floats<V>(slot + ch * V, a);
-          load_floats<V>(slot + M + ch * V, b);
+          load_cols<RAG, V>(slot + piece_col<RAG, V>(ch, chunks, M), a);
+          load_cols<RAG, V>(slot + Ml + piece_col<RAG, V>(ch, chunks, M), b);
 #pragma unroll
           for (int i = 0; i < V; ++i) {
             acc_g[c][i] += a[i];
@@ -537,8 +579,8 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     for (int c = 0; c < CH; ++c) {
       const int ch = c * LANES + t;
       if (ch < chunks) {
-        store_floats<V>(out + ch * V, acc_g[c]);
-        store_floats<V>(out + M + ch * V, acc_b[c]);
+        store_col_sums<RAG, !RAG, V>(out, ch, chunks, M, acc_g[c]);
+        store_col_sums<RAG, !RAG, V>(out + M, ch, chunks, M, acc_b[c]);
       }
     }
   }
@@ -637,48 +679,16 @@ __global__ __launch_bounds__(256) void ln_bwd_generic_kernel(
   }
 }
 
-// dgamma[j] = sum_p partial[p][0][j], dbeta[j] = sum_p partial[p][1][j].  A workgroup of 1024
-// lanes owns 32 adjacent columns of the [2][M] row; its 32 slices each add every 32nd
-// partial (all loads of a lane are independent and issued together), then the slices are
-// combined through LDS in a fixed order.
+// dgamma[j] = sum_p partial[p][0][j], dbeta[j] = sum_p partial[p][1][j].  A workgroup of 4 waves
+// owns 32 adjacent columns of the [2][M] row, 8 lanes x 4 floats; its 32 slices each add every
+// 32nd partial (all loads of a lane are independent and issued together), then the slices are
+// combined through LDS in a fixed order.  ANY (M odd): slots start at any float's address and the
+// last 16-byte piece of a slot is half a piece.
 constexpr int kFinCols = 32;   // 128 contiguous bytes per partial row
 constexpr int kFinSlices = 32;
-__global__ __launch_bounds__(kFinCols* kFinSlices) void ln_bwd_finalize_kernel(
-    const float* __restrict__ partial, float* __restrict__ dgamma, float* __restrict__ dbeta,
-    int parts, int64_t M) {
-  __shared__ float lds[kFinSlices][kFinCols + 1];
-  const int col = threadIdx.x % kFinCols;
-  const int slice = threadIdx.x / kFinCols;
-  const int64_t j2 = static_cast<int64_t>(blockIdx.x) * kFinCols + col;  // index into [2][M]
-  float s = 0.0f;
-  if (j2 < 2 * M) {
-    const float* p0 = partial + j2;
-    int p = slice;
-    for (; p + 7 * kFinSlices < parts; p += 8 * kFinSlices) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p0[static_cast<size_t>(p + u * kFinSlices) * 2 * M];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; p < parts; p += kFinSlices) s += p0[static_cast<size_t>(p) * 2 * M];
-  }
-  lds[slice][col] = s;
-  lds_barrier();
-  if (slice == 0 && j2 < 2 * M) {
-    float tot = 0.0f;
-#pragma unroll
-    for (int k = 0; k < kFinSlices; ++k) tot += lds[k][col];
-    if (j2 < M) dgamma[j2] = tot;
-    else dbeta[j2 - M] = tot;
-  }
-}
-
-// The same sums in the same order with 16-byte loads: 8 lanes x 4 floats cover the 32 columns,
-// so a workgroup is 4 waves instead of 16 and a wave's load touches 8 slices.  Needs whole
-// 16-byte pieces in every [2][M] slot: M even.
 constexpr int kFinVecLanes = kFinCols / 4;
-__global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize4_kernel(
+template <bool ANY>
+__global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kernel(
     const float* __restrict__ partial, float* __restrict__ dgamma, float* __restrict__ dbeta,
     int parts, int64_t M) {
   __shared__ float lds[kFinSlices][kFinCols + 4];
@@ -686,14 +696,14 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize4_ker
   const int slice = threadIdx.x / kFinVecLanes;
   const int64_t j2 = static_cast<int64_t>(blockIdx.x) * kFinCols + q * 4;  // index into [2][M]
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (j2 < 2 * M) {
+  if (j2 + 4 <= 2 * M) {
     const float* p0 = partial + j2;
     int p = slice;
     for (; p + 7 * kFinSlices < parts; p += 8 * kFinSlices) {
       float v[8][4];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        load_floats<4>(p0 + static_cast<size_t>(p + u * kFinSlices) * 2 * M, v[u]);
+        load_cols<ANY, 4>(p0 + static_cast<size_t>(p + u * kFinSlices) * 2 * M, v[u]);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
 #pragma unroll
@@ -702,9 +712,14 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize4_ker
     }
     for (; p < parts; p += kFinSlices) {
       float v[4];
-      load_floats<4>(p0 + static_cast<size_t>(p) * 2 * M, v);
+      load_cols<ANY, 4>(p0 + static_cast<size_t>(p) * 2 * M, v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) s[i] += v[i];
+    }
+  } else if (ANY && j2 < 2 * M) {  // 2 * M - j2 is 2: the sums of two columns
+    for (int p = slice; p < parts; p += kFinSlices) {
+      s[0] += partial[static_cast<size_t>(p) * 2 * M + j2];
+      s[1] += partial[static_cast<size_t>(p) * 2 * M + j2 + 1];
     }
   }
   store_floats<4>(&lds[slice][q * 4], s);
@@ -810,17 +825,36 @@ constexpr int max_rows() {
   return L > 64 ? 1 : ((C <= 2 && L == 64) ? 4 : (C <= 4 ? 2 : 1));
 }
 
+// Shapes that ragged rows are dispatched to: those that the default knobs lead to.
+constexpr int kRaggedFwdMaxPieces = 4;
+constexpr int kRaggedBwdMaxPieces = 3;
+template <typename T>
+constexpr bool is_ragged_shape(bool backward, int lanes, int ch) {
+  constexpr bool f32 = std::is_same<T, float>::value;
+  const int most = backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces;
+  if (lanes <= kWave) return ch <= most;
+  if (lanes <= 256) return ch <= most || (f32 && (backward ? ch <= 6 : ch <= 8));
+  return backward;
+}
+
 template <typename T, int L, int C>
-static void ln_fwd_go(int rr, bool loop, int grid, hipStream_t st, const void* x, const float* gamma,
+static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, const void* x, const float* gamma,
                       const float* beta, void* y, float* rstd, float* mean, int64_t N, int64_t M,
                       float eps) {
   if constexpr ((std::is_same<T, bf16_t>::value && C > 4 && L > kWave) || L > kFwdThreads) {
     // shapes that exist for float32 only, or for the backward only (fast_shape never picks them here)
   } else {
-    auto go = [&](auto rows, auto lp) {
-      hipLaunchKernelGGL((ln_fwd_kernel<T, L, C, decltype(rows)::value, decltype(lp)::value>),
+    auto launch = [&](auto rows, auto lp, auto rag) {
+      hipLaunchKernelGGL((ln_fwd_kernel<T, L, C, decltype(rows)::value, decltype(lp)::value,
+                                        decltype(rag)::value>),
                          dim3(grid), dim3(kFwdThreads), 0, st, static_cast<const T*>(x), gamma, beta,
                          static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps);
+    };
+    auto go = [&](auto rows, auto lp) {
+      if constexpr (is_ragged_shape<T>(false, L, C)) {
+        if (ragged) return launch(rows, lp, std::true_type{});
+      }
+      launch(rows, lp, std::false_type{});
     };
     using std::integral_constant;
     if constexpr (C == 1 && L <= 64) {
@@ -840,12 +874,17 @@ static void ln_fwd_go(int rr, bool loop, int grid, hipStream_t st, const void* x
   }
 }
 
+static bool is_ragged(int64_t M, tempo_dtype dt) { return M % (dt == TEMPO_F32 ? 4 : 8) != 0; }
+
 static bool fast_shape(int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   const int vec = dt == TEMPO_F32 ? 4 : 8;
-  if (M % vec != 0 || M / vec > (dt == TEMPO_F32 ? kMaxFastPiecesF32 : kMaxFastPieces)) return false;
-  const int pieces = static_cast<int>(M / vec);
-  *sh = widen_shape(pick_shape(pieces, backward), pieces,
-                    tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces), 256);
+  if (M < vec || (M + vec - 1) / vec > (dt == TEMPO_F32 ? kMaxFastPiecesF32 : kMaxFastPieces))
+    return false;
+  const int pieces = static_cast<int>((M + vec - 1) / vec);
+  const bool ragged = is_ragged(M, dt);
+  const int max_ch = ragged ? (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces)
+                            : tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces);
+  *sh = widen_shape(pick_shape(pieces, backward), pieces, max_ch, 256);
   // Backward: four waves whose lanes would own more than 24 columns each (parameters in LDS,
   // read twice per element) give the row to all eight waves, which halves the columns per lane
   // and keeps the parameters in registers.
@@ -865,6 +904,9 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
     // Measured on 16384 x 512 and 65536 x 256 bf16: 9-10 % faster than 2 rows.
     const int tuned = tune_get(kTuneLnFwdRows);
     int rr = (sh.ch <= 2 && sh.lanes <= kWave && tuned >= 2) ? (sh.ch == 1 ? 4 : 2) : 1;
+    // few rows: fewer per lane group, so that every compute unit has a workgroup
+    while (rr > 1 && (N + (kFwdThreads / sh.lanes) * rr - 1) / ((kFwdThreads / sh.lanes) * rr) < compute_units())
+      rr >>= 1;
     if (rr == 4) cap += compute_units();
     int groups = (kFwdThreads / sh.lanes) * rr;
     int64_t want = (N + groups - 1) / groups;
@@ -881,8 +923,8 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
     const int grid = static_cast<int>(loop ? cap : want);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) ln_fwd_go<float, L, C>(rr, loop, grid, st, x, gamma, beta, y, rstd, mean, N, M, eps);   \
-    else ln_fwd_go<bf16_t, L, C>(rr, loop, grid, st, x, gamma, beta, y, rstd, mean, N, M, eps);    \
+    if (dt == TEMPO_F32) ln_fwd_go<float, L, C>(rr, loop, is_ragged(M, dt), grid, st, x, gamma, beta, y, rstd, mean, N, M, eps);   \
+    else ln_fwd_go<bf16_t, L, C>(rr, loop, is_ragged(M, dt), grid, st, x, gamma, beta, y, rstd, mean, N, M, eps);    \
   } while (0)
     TEMPO_LN_DISPATCH(TEMPO_LAUNCH)
 #undef TEMPO_LAUNCH
@@ -914,12 +956,15 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
 // are then held in registers: half the rows per batch for one-piece rows, one row otherwise) on
 // a grid of that many workgroups per compute unit.  A grid that does not loop has exactly one
 // workgroup per batch, however many that is.
+// Rows that are no multiple of a piece, and rows too long for the register-resident kernel, use at
+// most this many partial slots whatever the knobs say: a workspace of 8 KiB x M.
+constexpr int kMaxRaggedSlots = 1024;
 struct BwdPlan {
   int r;
   bool loop;
   int grid;
 };
-static BwdPlan bwd_plan(int64_t N, const Shape& sh) {
+static BwdPlan bwd_plan(int64_t N, const Shape& sh, bool ragged) {
   const int tuned = tune_get(kTuneLnBwdRowsPerGroup);
   const int regs_per_row = sh.ch * 8;  // dy and y, 4 registers per packed piece
   const int64_t groups = kBwdThreads / sh.lanes;
@@ -930,7 +975,8 @@ static BwdPlan bwd_plan(int64_t N, const Shape& sh) {
       sh.lanes > 64 ? 1 : ((sh.ch <= 2 && sh.lanes == 64) ? 4 : (sh.ch <= 4 ? 2 : 1));
   if (r > avail) r = avail;
   while (r > 1 && (r * regs_per_row > 64 || batches(r) < cus)) r >>= 1;
-  const int64_t most = static_cast<int64_t>(tune_get(kTuneLnBwdLoopBlocksPerCu)) * cus;
+  int64_t most = static_cast<int64_t>(tune_get(kTuneLnBwdLoopBlocksPerCu)) * cus;
+  if (ragged && most > kMaxRaggedSlots) most = kMaxRaggedSlots;
   BwdPlan p;
   if (batches(r) > most) {
     p.loop = true;
@@ -951,6 +997,7 @@ static BwdPlan bwd_plan(int64_t N, const Shape& sh) {
 static size_t bwd_lds_bytes(const Shape& sh, int64_t M, tempo_dtype dt) {
   const int row_waves = sh.lanes > kWave ? sh.lanes / kWave : 1;
   const int all = kBwdWaves / row_waves;
+  M = lds_row(M);
   const size_t one_step = static_cast<size_t>(all) * 2 * M * sizeof(float);
   const int slots = one_step <= kOneStepLdsBytes ? all : (all / 2 > 0 ? all / 2 : 1);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
@@ -964,7 +1011,7 @@ static size_t bwd_lds_bytes(const Shape& sh, int64_t M, tempo_dtype dt) {
 // number of partial slots written).  A looping launch is trimmed to the workgroups that are
 // resident at once, so that no second round of workgroups repeats the reduction epilogue.
 template <typename T, int L, int C>
-static int ln_bwd_go(const BwdPlan& plan, size_t lds_bytes, hipStream_t st, const void* dy,
+static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStream_t st, const void* dy,
                      const void* y, const float* gamma, const float* beta, const float* rstd,
                      void* dx, float* workspace, int64_t N, int64_t M) {
   int grid = plan.grid;
@@ -972,8 +1019,9 @@ static int ln_bwd_go(const BwdPlan& plan, size_t lds_bytes, hipStream_t st, cons
                 (L == kBwdThreads && C != (std::is_same<T, bf16_t>::value ? 2 : 4))) {
     return grid;  // shapes that exist for the other dtype only
   } else {
-    auto go = [&](auto rows, auto loop) {
-      auto kernel = ln_bwd_kernel<T, L, C, decltype(rows)::value, decltype(loop)::value>;
+    auto launch = [&](auto rows, auto loop, auto rag) {
+      auto kernel = ln_bwd_kernel<T, L, C, decltype(rows)::value, decltype(loop)::value,
+                                  decltype(rag)::value>;
       if (decltype(loop)::value) {
         static std::atomic<int> resident{0};  // workgroups per compute unit, per instantiation
         int per_cu = resident.load(std::memory_order_relaxed);
@@ -991,6 +1039,12 @@ static int ln_bwd_go(const BwdPlan& plan, size_t lds_bytes, hipStream_t st, cons
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBwdThreads), lds_bytes, st,
                          static_cast<const T*>(dy), static_cast<const T*>(y), gamma, beta, rstd,
                          static_cast<T*>(dx), workspace, N, static_cast<int>(M));
+    };
+    auto go = [&](auto rows, auto loop) {
+      if constexpr (is_ragged_shape<T>(true, L, C)) {
+        if (ragged) return launch(rows, loop, std::true_type{});
+      }
+      launch(rows, loop, std::false_type{});
     };
     using std::integral_constant;
     if (plan.loop) {
@@ -1031,14 +1085,14 @@ struct BwdLaunch {
 static BwdLaunch bwd_launch(int64_t N, int64_t M, tempo_dtype dt) {
   BwdLaunch b;
   b.fast = fast_shape(M, dt, true, &b.sh);
+  // rows that are no multiple of a piece: one slot per row up to kMaxRaggedSlots, for either kernel
+  const int per_row = static_cast<int>(N > kMaxRaggedSlots ? kMaxRaggedSlots : (N < 1 ? 1 : N));
   if (b.fast) {
-    b.plan = bwd_plan(N, b.sh);
-    b.slots = b.plan.grid;
+    b.plan = bwd_plan(N, b.sh, is_ragged(M, dt));
+    b.slots = is_ragged(M, dt) ? per_row : b.plan.grid;
   } else {
-    // one row per workgroup, strided; four 256-lane workgroups per compute unit, and a workspace
-    // of at most 1024 slots
-    b.plan = {1, true, static_cast<int>(N > 1024 ? 1024 : (N < 1 ? 1 : N))};
-    b.slots = b.plan.grid;
+    b.plan = {1, true, per_row};  // one row per workgroup, strided; four workgroups per compute unit
+    b.slots = per_row;
   }
   return b;
 }
@@ -1063,8 +1117,8 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
     const BwdPlan plan = b.plan;
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) grid = ln_bwd_go<float, L, C>(plan, lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);   \
-    else grid = ln_bwd_go<bf16_t, L, C>(plan, lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);                  \
+    if (dt == TEMPO_F32) grid = ln_bwd_go<float, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);   \
+    else grid = ln_bwd_go<bf16_t, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);                  \
   } while (0)
     TEMPO_LN_DISPATCH(TEMPO_LAUNCH)
 #undef TEMPO_LAUNCH
@@ -1085,12 +1139,9 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
   }
   if (hipGetLastError() != hipSuccess) return TEMPO_ERR_LAUNCH;
   const int fgrid = static_cast<int>((2 * M + kFinCols - 1) / kFinCols);
-  if (M % 2 == 0)
-    hipLaunchKernelGGL(ln_bwd_finalize4_kernel, dim3(fgrid), dim3(kFinVecLanes * kFinSlices), 0, st,
-                       workspace, dgamma, dbeta, grid, M);
-  else
-    hipLaunchKernelGGL(ln_bwd_finalize_kernel, dim3(fgrid), dim3(kFinCols * kFinSlices), 0, st,
-                       workspace, dgamma, dbeta, grid, M);
+  auto finalize = M % 2 == 0 ? ln_bwd_finalize_kernel<false> : ln_bwd_finalize_kernel<true>;
+  hipLaunchKernelGGL(finalize, dim3(fgrid), dim3(kFinVecLanes * kFinSlices), 0, st, workspace,
+                     dgamma, dbeta, grid, M);
   return launch_status();
 }
 

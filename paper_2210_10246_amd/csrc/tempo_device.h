@@ -135,11 +135,44 @@ __device__ __forceinline__ void load_floats(const float* p, float (&v)[V]) {
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
   }
 }
+// The same at any float's address (rows of parameters or column sums whose length is odd).
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+template <int V>
+__device__ __forceinline__ void load_floats_any(const float* p, float (&v)[V]) {
+  static_assert(V == 4 || V == 8, "piece length");
+#pragma unroll
+  for (int h = 0; h < V; h += 4) {
+    const f32x4 a = *reinterpret_cast<const f32x4_any*>(p + h);
+    v[h] = a.x; v[h + 1] = a.y; v[h + 2] = a.z; v[h + 3] = a.w;
+  }
+}
+template <int V>
+__device__ __forceinline__ void store_floats_any(float* p, const float (&v)[V]) {
+  static_assert(V == 4 || V == 8, "piece length");
+#pragma unroll
+  for (int h = 0; h < V; h += 4)
+    *reinterpret_cast<f32x4_any*>(p + h) = f32x4{v[h], v[h + 1], v[h + 2], v[h + 3]};
+}
 template <int V>
 __device__ __forceinline__ void store_floats(float* p, const float (&v)[V]) {
   static_assert(V == 4 || V == 8, "piece length");
   *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
   if constexpr (V == 8) *reinterpret_cast<f32x4*>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
+}
+
+// Rows of any length ("ragged": no multiple of the piece).  A row is owned in pieces counted from
+// its own start, at element-aligned addresses; the last piece is moved back to end with the row, so
+// that no access leaves the row and none is partial.  The elements it shares with the piece before
+// ("dup", at most V - 1, the first ones of the piece) are computed and stored twice with the same
+// value and left out of the row sums.  A row shorter than a piece has one piece at column 0 that
+// the kernel has to treat on its own.  pc: piece of the row, pieces: how many the row has.
+template <bool RAG, int V>
+__device__ __forceinline__ int piece_col(int pc, int pieces, int len) {
+  return (RAG && pc == pieces - 1) ? max(len - V, 0) : pc * V;
+}
+template <bool RAG, int V>
+__device__ __forceinline__ int piece_dup(int pc, int pieces, int len) {
+  return (RAG && pc == pieces - 1 && len >= V) ? pieces * V - len : 0;
 }
 
 // Raw (still packed) piece, so rows fetched ahead cost 4 registers per piece.

@@ -94,3 +94,46 @@ def test_attention_ragged_rows(B, Sk, Sq, dt):
         results.append((dsd, rd))
     for dsd, rd in results[1:]:
         assert torch.equal(dsd, results[0][0]) and torch.equal(rd, results[0][1])
+
+
+# columns, rows: rows enough for one batch, for several, or for workgroups that loop
+LN_ROWS = [(4, 5), (5, 40), (7, 9), (9, 3), (63, 70), (65, 130), (127, 9), (129, 4100), (255, 17), (258, 1030),
+           (385, 33), (511, 2100), (513, 41), (770, 700), (1001, 1300), (1023, 19), (1025, 600), (1535, 300),
+           (1537, 20), (2047, 300), (2049, 9), (3070, 7), (3073, 300), (4095, 5), (4097, 260), (4100, 270),
+           (6145, 3), (8191, 270)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N", LN_ROWS)
+def test_layernorm_ragged_rows(B, M, N, dt):
+    rng = np.random.default_rng(M)
+    x = O.round_to_dtype(2.0 * rng.standard_normal((N, M)) + 0.5, dt)
+    gamma = O.round_to_dtype(1 + 0.1 * rng.standard_normal(M), "f32")
+    beta = O.round_to_dtype(0.1 * rng.standard_normal(M), "f32")
+    dy = stored(rng, (N, M), dt)
+    y, rstd, mean = O.layernorm_fwd(x, gamma, beta, 1e-5, dt)
+    gd, bd = dev(gamma, "f32"), dev(beta, "f32")
+    yd, g0 = guarded((N, M), TDT[dt], dev(x, dt))            # in place
+    rd, g1 = guarded((N,), torch.float32)
+    md, g2 = guarded((N,), torch.float32)
+    B.tempo_layernorm_fwd(yd, gd, bd, yd, rd, md, 1e-5)
+    assert rel_err(host(yd), y) <= TOL[dt]
+    assert rel_err(host(rd), rstd) <= TOL["f32"]
+    assert rel_err(host(md), mean) <= TOL["f32"]
+    assert all((g == 7).all() for g in (g0, g1, g2))
+
+    dx_ref, dg_ref, db_ref = O.layernorm_bwd(dy, y, gamma, beta, rstd, dt)
+    size = B.tempo_layernorm_bwd_workspace_bytes(N, M)
+    runs = []
+    for _ in range(2):
+        dxd, g0 = guarded((N, M), TDT[dt], dev(dy, dt))      # in place
+        dgd, g1 = guarded((M,), torch.float32)
+        dbd, g2 = guarded((M,), torch.float32)
+        ws, g3 = guarded(((size + 15) // 16 * 16,), torch.uint8)
+        B.tempo_layernorm_bwd(dxd, dev(y, dt), gd, bd, dev(rstd, "f32"), dxd, dgd, dbd, ws)
+        assert rel_err(host(dxd), dx_ref) <= TOL[dt]
+        assert rel_err(host(dgd), dg_ref) <= TOL["f32"]
+        assert rel_err(host(dbd), db_ref) <= TOL["f32"]
+        assert all((g == 7).all() for g in (g0, g1, g2, g3))
+        runs.append((dxd, dgd, dbd))
+    assert all(torch.equal(a, b) for a, b in zip(*runs))     # fixed summation order
