@@ -892,6 +892,8 @@ static bool fast_shape(int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   return sh->ch != 0;
 }
 
+constexpr int kFwdFullBlocks = 3;
+
 tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float* beta, void* y,
                                   float* rstd, float* mean, int64_t N, int64_t M, float eps,
                                   tempo_dtype dt, hipStream_t st) {
@@ -904,8 +906,11 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
     // Measured on 16384 x 512 and 65536 x 256 bf16: 9-10 % faster than 2 rows.
     const int tuned = tune_get(kTuneLnFwdRows);
     int rr = (sh.ch <= 2 && sh.lanes <= kWave && tuned >= 2) ? (sh.ch == 1 ? 4 : 2) : 1;
-    // few rows: fewer per lane group, so that every compute unit has a workgroup
-    while (rr > 1 && (N + (kFwdThreads / sh.lanes) * rr - 1) / ((kFwdThreads / sh.lanes) * rr) < compute_units())
+    // Few rows: fewer per lane group as long as that leaves less than kFwdFullBlocks workgroups per
+    // compute unit.  Measured, us at 1, 3 and 4 per unit: 5000 x 512 bf16 5.1, 4.2, 4.2; 10000 x 256
+    // f32 5.8, 5.5, 5.5; 30000 x 128 bf16 5.0, 4.8, 5.9; 1024 x 256 f32 3.9 with four rows, 2.2 with one.
+    while (rr > 1 && (N + kFwdThreads / sh.lanes * rr - 1) / (kFwdThreads / sh.lanes * rr) <
+                         kFwdFullBlocks * compute_units())
       rr >>= 1;
     if (rr == 4) cap += compute_units();
     int groups = (kFwdThreads / sh.lanes) * rr;
