@@ -7,6 +7,7 @@
 // contiguous).  The keep bits come from Philox4x32-10, one call per 8 elements, so the mask is
 // a pure function of (seed, offset, element index) and does not depend on the launch shape;
 // backward can therefore also draw the bits again instead of reading a stored mask.
+#include <algorithm>
 #include <type_traits>
 
 #include "tempo_device.h"
@@ -32,6 +33,9 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 // the key advanced by the two Weyl constants between rounds.
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
+  // keeps the 18 round keys out of loops around the call: they would not fit the scalar registers,
+  // and adding is cheaper than fetching them back from the lanes of a spilled one
+  asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
@@ -48,21 +52,52 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   w[0] = c0; w[1] = c1; w[2] = c2; w[3] = c3;
 }
 
-// Keep bits of the 8 elements of group g (bit i = element 8g + i).  A 16-bit draw r is kept iff
-// r < t16, i.e. iff r - t16 is negative: v_alignbit shifts that sign bit into the byte, last
-// element first.
-__device__ __forceinline__ uint32_t keep_byte(uint64_t g, const RngArgs& a) {
-  if (a.t16 >= 65536u) return 0xFFu;
-  uint32_t w[4];
-  philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), a.off_lo, a.off_hi,
-                a.seed_lo, a.seed_hi, w);
+// Keep bits of the 8 elements whose draws are w (bit i = element i of the group).  A 16-bit draw r
+// is kept iff r < t16, i.e. iff r - t16 is negative: v_alignbit shifts that sign bit into the byte,
+// last element first.
+__device__ __forceinline__ uint32_t draws_to_byte(const uint32_t (&w)[4], uint32_t t16) {
   uint32_t byte = 0;
 #pragma unroll
   for (int i = 3; i >= 0; --i) {
-    byte = __builtin_amdgcn_alignbit(byte, (w[i] >> 16) - a.t16, 31);      // byte << 1 | sign
-    byte = __builtin_amdgcn_alignbit(byte, (w[i] & 0xFFFFu) - a.t16, 31);
+    byte = __builtin_amdgcn_alignbit(byte, (w[i] >> 16) - t16, 31);      // byte << 1 | sign
+    byte = __builtin_amdgcn_alignbit(byte, (w[i] & 0xFFFFu) - t16, 31);
   }
   return byte;
+}
+
+// Draws of group base + off.
+__device__ __forceinline__ void draw_group(uint64_t base, uint32_t off, const RngArgs& a,
+                                           uint32_t (&w)[4]) {
+  const uint64_t g = base + off;
+  philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), a.off_lo, a.off_hi,
+                a.seed_lo, a.seed_hi, w);
+}
+
+__device__ __forceinline__ uint32_t keep_byte(uint64_t base, uint32_t off, const RngArgs& a) {
+  if (a.t16 >= 65536u) return 0xFFu;
+  uint32_t w[4];
+  draw_group(base, off, a, w);
+  return draws_to_byte(w, a.t16);
+}
+
+// The keep decisions of a group in two forms a bfloat16 piece needs, without going through single
+// bits: flag words (0 or 1 in each half, one word per two elements) by a saturating subtraction and
+// a minimum, both packed 16-bit operations.  Spelled as instructions: from C++ the compiler makes
+// compares and selects, twice as many.
+__device__ __forceinline__ uint32_t keep_flags(uint32_t draws, uint32_t t16_pair) {
+  uint32_t f;
+  asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(f) : "s"(t16_pair), "v"(draws));  // 0 iff draw >= t16
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(f) : "v"(f), "s"(0x00010001u));
+  return f;
+}
+__device__ __forceinline__ uint32_t flags_to_mask(uint32_t f) {  // 0 or 0xFFFF in each half
+  uint32_t m;
+  asm("v_pk_sub_u16 %0, 0, %1" : "=v"(m) : "v"(f));
+  return m;
+}
+__device__ __forceinline__ uint32_t flags_to_byte(const uint32_t (&f)[4]) {
+  const uint32_t even = f[0] | (f[1] << 2) | (f[2] << 4) | (f[3] << 6);  // odd elements 16 higher
+  return (even | (even >> 15)) & 0xFFu;
 }
 
 // All ones if bit K of bits is set, else zero.  Written as the instruction itself: spelled in
@@ -95,6 +130,14 @@ __device__ __forceinline__ u32x4 apply_keep(u32x4 w, uint32_t bits) {
 }
 
 
+// Element `off` of p, p the same for the whole wave: a scalar address and a 32-bit offset.  (The
+// offsets stay inside one set of rows: at most 32 rows of 8192 elements.)
+template <typename T>
+__device__ __forceinline__ T* at_offset(T* p, uint32_t off) {
+  using Byte = std::conditional_t<std::is_const<T>::value, const char, char>;
+  return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + off * static_cast<uint32_t>(sizeof(T)));
+}
+
 // Element offset of the start of a row: rows are counted in 32 bits on the register-resident
 // paths (the host checks), so the product is one 32x32->64 multiply instead of a 64x64 one.
 __device__ __forceinline__ int64_t row_offset(uint32_t row, int Sk) {
@@ -108,24 +151,23 @@ __device__ __forceinline__ int row_limit(int i, int key_limit, int causal, int S
   return limit;
 }
 
-// Keep bits of the CH pieces a lane owns in one row.  Piece c of the lane is flat piece
-// piece0 + c*LANES + t.  bfloat16 pieces (8 elements) are whole Philox groups.  float32 pieces
+// Keep bits of the CH pieces a lane owns in one row.  Piece c of the lane is piece off + c*LANES + t
+// counted from group `base`.  bfloat16 pieces (8 elements) are whole Philox groups.  float32 pieces
 // (4 elements) are half groups: lanes 2k and 2k+1 hold the two halves of the same group for
 // every c, so the pair splits the generator calls (the even lane draws the groups of even c,
 // the odd lane those of odd c) and swaps the bytes with one DPP move.
 template <typename T, int LANES, int CH>
-__device__ __forceinline__ void lane_keep_bits(int64_t piece0, int t, const RngArgs& rng,
-                                               uint32_t (&bits)[CH]) {
+__device__ __forceinline__ void lane_keep_bits(uint64_t base, uint32_t off, int t,
+                                               const RngArgs& rng, uint32_t (&bits)[CH]) {
   if constexpr (Store<T>::kVec == 8) {
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-      bits[c] = keep_byte(static_cast<uint64_t>(piece0 + c * LANES + t), rng);
+    for (int c = 0; c < CH; ++c) bits[c] = keep_byte(base, off + c * LANES + t, rng);
   } else {
     const int odd = t & 1;
 #pragma unroll
     for (int c = 0; c < CH; c += 2) {
       const int mine = (c + 1 < CH) ? c + odd : c;  // a trailing single piece: both lanes draw
-      const uint32_t own = keep_byte(static_cast<uint64_t>(piece0 + mine * LANES + t) >> 1, rng);
+      const uint32_t own = keep_byte(base, (off + mine * LANES + t) >> 1, rng);
       const uint32_t other = dpp_u32<kDppXor1>(own);
       const uint32_t even_c = (c + 1 < CH) ? (odd ? other : own) : own;
       bits[c] = (even_c >> (4 * odd)) & 0xFu;
@@ -139,22 +181,22 @@ __device__ __forceinline__ void lane_keep_bits(int64_t piece0, int t, const RngA
 // lane (bf16) or by the even lane of each pair (f32).  All lanes of the sharing group must
 // call this together; `valid` says whether the lane's piece exists.
 template <typename T, bool WORDS>
-__device__ __forceinline__ void store_keep_bits(uint32_t* keep_bits, int64_t piece, int t,
+__device__ __forceinline__ void store_keep_bits(uint32_t* keep_bits, int64_t base, uint32_t off, int t,
                                                 uint32_t bits, bool valid, int64_t total_pieces) {
   constexpr int V = Store<T>::kVec;
   if constexpr (WORDS) {
     const uint32_t word = merge_mask_word<V>(bits, t);
     constexpr int kShare = 32 / V;
-    if ((t & (kShare - 1)) == 0 && valid) keep_bits[piece / kShare] = word;
+    if ((t & (kShare - 1)) == 0 && valid) *at_offset(keep_bits + base / kShare, off / kShare) = word;
   } else {
     uint8_t* kb = reinterpret_cast<uint8_t*>(keep_bits);
     uint32_t byte = bits;
-    int64_t bi = piece;  // byte index
+    int64_t bi = base + off;  // byte index
     bool writer = valid;
     if constexpr (V == 4) {
       byte = bits << (4 * (t & 1));
       byte |= dpp_u32<kDppXor1>(byte);
-      bi = piece >> 1;
+      bi >>= 1;
       writer = valid && (t & 1) == 0;
     }
     if (writer) {
@@ -167,18 +209,20 @@ __device__ __forceinline__ void store_keep_bits(uint32_t* keep_bits, int64_t pie
   }
 }
 
-// Mask bits of one piece as read by backward.
+// Mask bits of piece base + off (base the same for the whole wave) as read by backward.
 template <typename T, bool WORDS>
-__device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, int64_t piece) {
+__device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, int64_t base,
+                                                   uint32_t off) {
   constexpr int V = Store<T>::kVec;
-  if constexpr (WORDS) {
+  if constexpr (WORDS) {  // base is a multiple of the pieces per word
     constexpr int kShare = 32 / V;
-    return (keep_bits[piece / kShare] >> (V * static_cast<int>(piece & (kShare - 1)))) &
+    return (*at_offset(keep_bits + base / kShare, off / kShare) >>
+            (V * static_cast<int>(off & (kShare - 1)))) &
            ((1u << V) - 1u);
-  } else {
+  } else {  // base is a multiple of the pieces per byte
     const uint8_t* kb = reinterpret_cast<const uint8_t*>(keep_bits);
-    if constexpr (V == 8) return kb[piece];
-    return (kb[piece >> 1] >> (4 * static_cast<int>(piece & 1))) & 0xFu;
+    if constexpr (V == 8) return *at_offset(kb + base, off);
+    return (*at_offset(kb + (base >> 1), off >> 1) >> (4 * static_cast<int>(off & 1))) & 0xFu;
   }
 }
 
@@ -226,18 +270,22 @@ constexpr bool takes_short_rows(bool ragged, int lanes, int vec) { return ragged
 // window may touch.
 constexpr int keep_row_bytes(int elements) { return (elements + 7 + 7) / 8 + 2; }
 
-// Draws the keep bytes of the row that starts at element e0 into `row` (LDS) and, if keep_bits is
+// Draws the keep bytes of the row that starts at element base + off (base the same for the whole
+// wave) into `row` (LDS) and, if keep_bits is
 // given, stores those of the groups that begin in this row: every byte of the mask has one
 // writer.  n: elements of the whole tensor; the last group's bits beyond it are 0, and so is the
 // rest of the last word.
 template <int LANES>
-__device__ __forceinline__ void draw_row_keep(uint8_t* row, int64_t e0, int Sk, int t,
+__device__ __forceinline__ void draw_row_keep(uint8_t* row, int64_t base, uint32_t off, int Sk, int t,
                                               const RngArgs& rng, uint32_t* keep_bits, int64_t n) {
-  const int64_t g0 = e0 >> 3;
-  const int h = static_cast<int>(e0 & 7);
+  const int64_t b0 = base >> 3;                                    // the same for the whole wave
+  const uint32_t start = static_cast<uint32_t>(base & 7) + off;    // element of the row, from b0
+  const uint32_t goff = start >> 3;
+  const int64_t g0 = b0 + goff;
+  const int h = static_cast<int>(start & 7);
   const int groups = (h + Sk + 7) >> 3;
   for (int b = t; b < groups; b += LANES) {
-    const uint32_t byte = keep_byte(static_cast<uint64_t>(g0 + b), rng);
+    const uint32_t byte = keep_byte(static_cast<uint64_t>(b0), goff + b, rng);
     row[b] = static_cast<uint8_t>(byte);
     if (keep_bits && (b > 0 || h == 0)) {
       uint8_t* kb = reinterpret_cast<uint8_t*>(keep_bits) + g0 + b;
@@ -278,138 +326,159 @@ enum MaskLayout { kWords, kBytes, kRagged };
 // kGroups = kThreads/LANES lane groups each own R rows (rows base + r*kGroups + g) and CH
 // 16-byte pieces per row (piece c of lane t = c*LANES + t).  All R rows of a group are fetched
 // before any arithmetic: short rows would otherwise leave one 16-byte load per lane in
-// flight, too little to cover the memory latency at 32 waves per compute unit.  With the
-// default launch cap every row set has its own workgroup and the grid sweeps memory front to
-// back; under a smaller cap workgroups walk the row sets grid-stride.
+// flight, too little to cover the memory latency at 32 waves per compute unit.  Every row
+// set has its own workgroup and the grid sweeps memory front to back (the launch cap splits it into
+// several launches): a loop over row sets would keep lane addresses and round keys live across it,
+// more registers than there are, and cost a wave that owns a single row more than the row.
+// The forward is bound by the vector ALU while rows are short: bfloat16 16x16x336x336 runs at 1300
+// cycles per row and SIMD, of which Philox takes a third.  Hence the division by multiplication, scalar
+// base addresses with 32-bit lane offsets, packed 16-bit keep decisions and VALU lane swaps.
 // LANES = 128 or 256 spreads a long row over 2 or 4 waves: the pieces per lane, and with them
 // the registers per lane, stay small enough for many resident waves (a 3072-element bfloat16
 // row on one wave needs over 200 registers per lane, which leaves 2 waves per SIMD).
 template <typename T, int LANES, int CH, int R, MaskLayout MASK, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
     const T* scores, const int32_t* __restrict__ key_len, int causal, T* probs,
-    T* __restrict__ out, uint32_t* __restrict__ keep_bits, int slices, int A, int Sq, int Sk,
-    float scale, RngArgs rng) {
+    T* __restrict__ out, uint32_t* __restrict__ keep_bits, int slices, int Sq, int Sk, float scale,
+    RngArgs rng, FastDiv sets_per_slice, FastDiv heads, uint32_t first_set) {
   static_assert(THREADS % LANES == 0 && THREADS % kWave == 0, "whole lane groups, whole waves");
   constexpr int kGroups = THREADS / LANES;
   constexpr int V = Store<T>::kVec;
-  const int g = threadIdx.x / LANES;
+  int g = threadIdx.x / LANES;
+  if constexpr (LANES >= kWave) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
   const int t = threadIdx.x % LANES;
   constexpr bool RAG = MASK == kRagged;
   constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
   const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
-  const int sets_per_slice = (Sq + kGroups * R - 1) / (kGroups * R);
-  const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice;
   const int64_t total_pieces = static_cast<int64_t>(slices) * Sq * pieces;
   __shared__ float red[2][THREADS / kWave];
   static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
   static_assert(!RAG || R == 1, "ragged rows: one row per group");
-  // two sets of rows: a wave may draw its next row while a slow one still reads this one's
-  constexpr int kKeepRow = keep_row_bytes(LANES * CH * V);
-  __shared__ uint8_t keep_lds[RAG ? 2 : 1][RAG ? kGroups : 1][RAG ? kKeepRow : 1];
-  int flip = 0;
+  __shared__ uint8_t keep_lds[RAG ? kGroups : 1][RAG ? keep_row_bytes(LANES * CH * V) : 1];
 
-  for (int64_t rs = blockIdx.x; rs < total_sets; rs += gridDim.x, flip ^= 1) {
-    const int slice = static_cast<int>(rs / sets_per_slice);
-    const int i0 = static_cast<int>(rs % sets_per_slice) * (kGroups * R) + g;
-    const int key_limit = key_len ? min(max(key_len[slice / A], 0), Sk) : Sk;
-    // limit = number of leading columns of the row that take part in the softmax; -1: no row
-    int limit[R];
-    Raw<T> raw[R][CH];
+  const uint32_t set = first_set + blockIdx.x;
+  const uint32_t slice = sets_per_slice.divide(set);
+  const int set0 = static_cast<int>(set - slice * sets_per_slice.d) * (kGroups * R);
+  const int key_limit = key_len ? min(max(key_len[heads.divide(slice)], 0), Sk) : Sk;
+  // The set's first row is the workgroup's, what a lane adds to it fits 32 bits: addresses are a
+  // scalar base and a 32-bit offset.
+  const int64_t base = row_offset(slice * static_cast<uint32_t>(Sq) + set0, Sk);
+  const T* const s_base = scores + base;
+  // limit = number of leading columns of the row that take part in the softmax; -1: no row
+  int limit[R];
+  Raw<T> raw[R][CH];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + r * kGroups;
-      limit[r] = (i < Sq) ? row_limit(i, key_limit, causal, Sq, Sk) : -1;
-      const T* sr = scores + row_offset(static_cast<uint32_t>(slice) * Sq + i, Sk);
+  for (int r = 0; r < R; ++r) {
+    const int i = set0 + g + r * kGroups;
+    limit[r] = (i < Sq) ? row_limit(i, key_limit, causal, Sq, Sk) : -1;
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
-        if constexpr (CH == 1) raw[r][c].a = Store<T>::neg_inf_piece();  // see below
-        if (col0 < limit[r]) raw[r][c].a = load_row_piece<T, RAG, SHORT>(sr + col0, Sk, Store<T>::neg_inf_piece());
+    for (int c = 0; c < CH; ++c) {
+      const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
+      if constexpr (CH == 1) raw[r][c].a = Store<T>::neg_inf_piece();  // see below
+      if (col0 < limit[r])
+        raw[r][c].a = load_row_piece<T, RAG, SHORT>(
+            at_offset(s_base, (g + r * kGroups) * Sk + col0), Sk, Store<T>::neg_inf_piece());
+    }
+  }
+  uint8_t* const keep_row = keep_lds[RAG ? g : 0];
+  if constexpr (RAG) {  // while the loads are under way
+    if (limit[0] >= 0)
+      draw_row_keep<LANES>(keep_row, base, g * Sk, Sk, t, rng, keep_bits,
+                           static_cast<int64_t>(slices) * Sq * Sk);
+    if constexpr (LANES <= kWave) wave_lds_fence();  // else the reductions' barriers order it
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    // no row: uniform over the lane group; a group of several waves walks on (no loads, no
+    // stores) because the reductions below hold workgroup barriers
+    const bool live = limit[r] >= 0;
+    if (LANES <= kWave && !live) continue;
+    const uint32_t row_off = static_cast<uint32_t>(g + r * kGroups) * Sk;  // elements from base
+    float v[CH][V];
+    float mx = -INFINITY;
+    // One piece per lane: the lanes of a masked piece cannot save time by idling (their wave
+    // runs on for the others), so a piece that was not loaded holds -inf and goes through the
+    // same straight-line code, which gives 0 for it.  Several pieces per lane: a masked piece
+    // is skipped, which for a causal mask spares whole waves half of their work.
+    constexpr bool kSkip = CH > 1;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
+      if (!kSkip || col0 < limit[r]) {
+        raw[r][c].unpack(v[c]);
+        if (col0 < limit[r] && col0 + V > limit[r]) {  // the piece the limit falls into
+#pragma unroll
+          for (int k = 0; k < V; ++k) v[c][k] = (col0 + k < limit[r]) ? v[c][k] : -INFINITY;
+        }
+#pragma unroll
+        for (int k = 0; k < V; k += 2) mx = fmaxf(fmaxf(mx, v[c][k]), v[c][k + 1]);  // v_max3
       }
     }
-    uint8_t* const keep_row = keep_lds[RAG ? flip : 0][RAG ? g : 0];
-    if constexpr (RAG) {  // while the loads are under way
-      if (limit[0] >= 0)
-        draw_row_keep<LANES>(keep_row, row_offset(static_cast<uint32_t>(slice) * Sq + i0, Sk), Sk, t,
-                             rng, keep_bits, static_cast<int64_t>(slices) * Sq * Sk);
-      if constexpr (LANES <= kWave) wave_lds_fence();  // else the reductions' barriers order it
+    mx = row_reduce<LANES, true>(mx, red[0]);
+    const float shift = (mx == -INFINITY) ? 0.0f : mx * kLog2e;
+    float sum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
+      const int dup = piece_dup<RAG, V>(c * LANES + t, pieces, Sk);
+      if (!kSkip || col0 < limit[r]) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          const float e = __builtin_amdgcn_exp2f(fmaf(v[c][k], kLog2e, -shift));
+          v[c][k] = e;
+          sum += (RAG && k < dup) ? 0.0f : e;
+        }
+      } else {  // masked, or padding beyond the row
+#pragma unroll
+        for (int k = 0; k < V; ++k) v[c][k] = 0.0f;
+      }
     }
+    sum = row_reduce<LANES, false>(sum, red[1]);
+    const float rinv = (sum > 0.0f) ? __builtin_amdgcn_rcpf(sum) : 0.0f;
+    const uint64_t group0 = static_cast<uint64_t>(base) >> 3;  // aligned rows: whole groups
+    constexpr bool kFlags = !RAG && V == 8;  // keep decisions as flag words
+    uint32_t bits[CH];
+    if constexpr (!RAG && !kFlags)
+      lane_keep_bits<T, LANES, CH>(group0, row_off / V, t, rng, bits);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      // no row: uniform over the lane group; a group of several waves walks on (no loads, no
-      // stores) because the reductions below hold workgroup barriers
-      const bool live = limit[r] >= 0;
-      if (LANES <= kWave && !live) continue;
-      const int64_t row0 = row_offset(static_cast<uint32_t>(slice) * Sq + i0 + r * kGroups, Sk);
-      float v[CH][V];
-      float mx = -INFINITY;
-      // One piece per lane: the lanes of a masked piece cannot save time by idling (their wave
-      // runs on for the others), so a piece that was not loaded holds -inf and goes through the
-      // same straight-line code, which gives 0 for it.  Several pieces per lane: a masked piece
-      // is skipped, which for a causal mask spares whole waves half of their work.
-      constexpr bool kSkip = CH > 1;
+    for (int c = 0; c < CH; ++c) {
+      const int pc = c * LANES + t;
+      const bool valid = live && pc < pieces;
+      const int col0 = piece_col<RAG, V>(pc, pieces, Sk);
+      if constexpr (kFlags) bits[c] = 0xFFu;
+      if (valid) {
+        if constexpr (RAG)
+          bits[c] = row_keep_window<V>(
+              keep_row, static_cast<int>((static_cast<uint32_t>(base) + row_off) & 7) + col0);
+        float p8[V], o8[V];
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
-        if (!kSkip || col0 < limit[r]) {
-          raw[r][c].unpack(v[c]);
-          if (col0 < limit[r] && col0 + V > limit[r]) {  // the piece the limit falls into
+        for (int k = 0; k < V; ++k) p8[k] = v[c][k] * rinv;
+        // round P once, into the words that are stored; Out is computed from the stored P
+        const u32x4 pw = Store<T>::pack(p8);
+        Store<T>::unpack(pw, p8);
+        store_row_piece<T, RAG, SHORT>(at_offset(probs + base, row_off + col0), Sk, pw);
 #pragma unroll
-            for (int k = 0; k < V; ++k) v[c][k] = (col0 + k < limit[r]) ? v[c][k] : -INFINITY;
+        for (int k = 0; k < V; ++k) o8[k] = p8[k] * scale;
+        u32x4 ow = Store<T>::pack(o8);
+        if constexpr (kFlags) {
+          if (rng.t16 < 65536u) {  // else nothing is dropped
+            uint32_t w[4], flags[4];
+            draw_group(group0, row_off / V + pc, rng, w);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              flags[j] = keep_flags(w[j], rng.t16 * 0x00010001u);
+              ow[j] &= flags_to_mask(flags[j]);
+            }
+            bits[c] = flags_to_byte(flags);
           }
-#pragma unroll
-          for (int k = 0; k < V; ++k) mx = fmaxf(mx, v[c][k]);
+        } else {
+          ow = apply_keep<T>(ow, bits[c]);
         }
+        if (out) store_row_piece<T, RAG, SHORT>(at_offset(out + base, row_off + col0), Sk, ow);
       }
-      mx = row_reduce<LANES, true>(mx, red[0]);
-      const float shift = (mx == -INFINITY) ? 0.0f : mx * kLog2e;
-      float sum = 0.0f;
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int col0 = piece_col<RAG, V>(c * LANES + t, pieces, Sk);
-        const int dup = piece_dup<RAG, V>(c * LANES + t, pieces, Sk);
-        if (!kSkip || col0 < limit[r]) {
-#pragma unroll
-          for (int k = 0; k < V; ++k) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(v[c][k], kLog2e, -shift));
-            v[c][k] = e;
-            sum += (RAG && k < dup) ? 0.0f : e;
-          }
-        } else {  // masked, or padding beyond the row
-#pragma unroll
-          for (int k = 0; k < V; ++k) v[c][k] = 0.0f;
-        }
-      }
-      sum = row_reduce<LANES, false>(sum, red[1]);
-      const float rinv = (sum > 0.0f) ? __builtin_amdgcn_rcpf(sum) : 0.0f;
-      const int64_t piece0 = row0 / V;  // aligned rows: Sk is a multiple of the piece length
-      uint32_t bits[CH];
-      if constexpr (!RAG) lane_keep_bits<T, LANES, CH>(piece0, t, rng, bits);
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int pc = c * LANES + t;
-        const bool valid = live && pc < pieces;
-        const int col0 = piece_col<RAG, V>(pc, pieces, Sk);
-        if (valid) {
-          if constexpr (RAG)
-            bits[c] = row_keep_window<V>(keep_row, static_cast<int>(row0 & 7) + col0);
-          float p8[V], o8[V];
-#pragma unroll
-          for (int k = 0; k < V; ++k) p8[k] = v[c][k] * rinv;
-          // round P once, into the words that are stored; Out is computed from the stored P
-          const u32x4 pw = Store<T>::pack(p8);
-          Store<T>::unpack(pw, p8);
-          store_row_piece<T, RAG, SHORT>(probs + row0 + col0, Sk, pw);
-          if (out) {
-#pragma unroll
-            for (int k = 0; k < V; ++k) o8[k] = p8[k] * scale;
-            store_row_piece<T, RAG, SHORT>(out + row0 + col0, Sk, apply_keep<T>(Store<T>::pack(o8), bits[c]));
-          }
-        }
-        if constexpr (!RAG)
-          store_keep_bits<T, MASK == kWords>(keep_bits, piece0 + pc, t, valid ? bits[c] : 0u, valid,
-                                             total_pieces);
-      }
+      if constexpr (!RAG)
+        store_keep_bits<T, MASK == kWords>(keep_bits, base / V, row_off / V + pc, t,
+                                           valid ? bits[c] : 0u, valid, total_pieces);
     }
   }
 }
@@ -426,12 +495,11 @@ __device__ __forceinline__ uint32_t nonzero_bytes_to_bits(uint32_t w) {
   return (w * 0x01020408u) >> 24;  // byte i -> bit i
 }
 template <typename T, bool SHORT>
-__device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, int64_t element,
-                                                    int Sk) {
+__device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* p, int Sk) {
   if constexpr (SHORT) {
     if (Sk < Store<T>::kVec) {
       uint32_t bits = 0;
-      for (int k = 0; k < Sk; ++k) bits |= (keep_bytes[element + k] != 0 ? 1u : 0u) << k;
+      for (int k = 0; k < Sk; ++k) bits |= (p[k] != 0 ? 1u : 0u) << k;
       return bits;
     }
   }
@@ -441,10 +509,9 @@ __device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, i
   typedef u32x2 u32x2_any __attribute__((aligned(1)));
   if constexpr (Store<T>::kVec == 4) {
     return nonzero_bytes_to_bits(
-        __builtin_nontemporal_load(reinterpret_cast<const u32_any*>(keep_bytes + element)));
+        __builtin_nontemporal_load(reinterpret_cast<const u32_any*>(p)));
   } else {
-    const u32x2 w =
-        __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(keep_bytes + element));
+    const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p));
     return nonzero_bytes_to_bits(w.x) | (nonzero_bytes_to_bits(w.y) << 4);
   }
 }
@@ -455,114 +522,102 @@ __device__ __forceinline__ uint32_t load_keep_bools(const uint8_t* keep_bytes, i
 // bytes).
 enum MaskSource { kMaskWords, kMaskBytes, kMaskRegen, kMaskBools };
 
-template <typename T, int LANES, int CH, int R, MaskSource MASK, bool RAG, int THREADS>
+// Work unit = one row per lane group; like the forward, a scalar base address and 32-bit offsets.
+template <typename T, int LANES, int CH, MaskSource MASK, bool RAG, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
     const T* dout, const T* __restrict__ probs, const uint32_t* __restrict__ keep_bits,
-    T* dscores, T* __restrict__ out_re, uint32_t rows, int Sk, float scale, RngArgs rng) {
+    T* dscores, T* __restrict__ out_re, uint32_t rows, int Sk, float scale, RngArgs rng,
+    uint32_t first_set) {
   static_assert(THREADS % LANES == 0 && THREADS % kWave == 0, "whole lane groups, whole waves");
+  static_assert(!RAG || MASK != kMaskWords, "ragged rows: no whole words");
   constexpr int kGroups = THREADS / LANES;
   constexpr int V = Store<T>::kVec;
-  const int g = threadIdx.x / LANES;
+  int g = threadIdx.x / LANES;
+  if constexpr (LANES >= kWave) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
   const int t = threadIdx.x % LANES;
   constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
   const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
-  __shared__ float red[2][THREADS / kWave];
-  static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
-  static_assert(!RAG || (R == 1 && MASK != kMaskWords), "ragged rows: one row per group, no whole words");
+  __shared__ float red[THREADS / kWave];
   constexpr bool kDraw = RAG && MASK == kMaskRegen;  // the keep bytes of the rows, drawn into LDS
-  constexpr int kKeepRow = keep_row_bytes(LANES * CH * V);
-  __shared__ uint8_t keep_lds[kDraw ? 2 : 1][kDraw ? kGroups : 1][kDraw ? kKeepRow : 1];
-  int flip = 0;  // one reduction per row set: consecutive sets alternate between the slot arrays
-  for (int64_t base = static_cast<int64_t>(blockIdx.x) * (kGroups * R); base < rows;
-       base += static_cast<int64_t>(gridDim.x) * (kGroups * R), flip ^= 1) {
-    Raw<T> rdo[R][CH], rp[R][CH];
-    uint32_t bits[R][CH];
+  __shared__ uint8_t keep_lds[kDraw ? kGroups : 1][kDraw ? keep_row_bytes(LANES * CH * V) : 1];
+
+  const uint32_t row = (first_set + blockIdx.x) * kGroups;  // the workgroup's first
+  const int64_t base = row_offset(row, Sk);
+  const uint32_t row_off = static_cast<uint32_t>(g) * Sk;   // elements from base
+  // no row: uniform over the lane group; a group of several waves walks on (the reduction
+  // holds a workgroup barrier) with zeros and stores nothing
+  const bool live = static_cast<uint32_t>(g) < rows - row;
+  Raw<T> rdo[CH], rp[CH];
+  uint32_t bits[CH];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t row = base + r * kGroups + g;
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int pc = c * LANES + t;
-        bits[r][c] = 0;
-        if (row < rows && pc < pieces) {
-          const int64_t row0 = row_offset(static_cast<uint32_t>(row), Sk);
-          const int64_t e = row0 + piece_col<RAG, V>(pc, pieces, Sk);
-          rdo[r][c].a = load_row_piece<T, RAG, SHORT>(dout + e, Sk, u32x4{0u, 0u, 0u, 0u});
-          rp[r][c].a = load_row_piece<T, RAG, SHORT>(probs + e, Sk, u32x4{0u, 0u, 0u, 0u});
-          if constexpr (MASK == kMaskBools)
-            bits[r][c] = load_keep_bools<T, SHORT>(reinterpret_cast<const uint8_t*>(keep_bits), e, Sk);
-          else if constexpr (RAG && MASK != kMaskRegen)
-            bits[r][c] = mask_window<V>(keep_bits, e, static_cast<int64_t>(rows) * Sk);
-          else if constexpr (MASK != kMaskRegen)
-            bits[r][c] = load_keep_bits<T, MASK == kMaskWords>(keep_bits, row0 / V + pc);
-        }
-      }
+  for (int c = 0; c < CH; ++c) {
+    const int pc = c * LANES + t;
+    bits[c] = 0;
+    if (live && pc < pieces) {
+      const uint32_t off = row_off + piece_col<RAG, V>(pc, pieces, Sk);
+      rdo[c].a = load_row_piece<T, RAG, SHORT>(at_offset(dout + base, off), Sk, u32x4{0u, 0u, 0u, 0u});
+      rp[c].a = load_row_piece<T, RAG, SHORT>(at_offset(probs + base, off), Sk, u32x4{0u, 0u, 0u, 0u});
+      if constexpr (MASK == kMaskBools)
+        bits[c] = load_keep_bools<T, SHORT>(
+            at_offset(reinterpret_cast<const uint8_t*>(keep_bits) + base, off), Sk);
+      else if constexpr (RAG && MASK != kMaskRegen)
+        bits[c] = mask_window<V>(keep_bits, base + off, static_cast<int64_t>(rows) * Sk);
+      else if constexpr (MASK != kMaskRegen)
+        bits[c] = load_keep_bits<T, MASK == kMaskWords>(keep_bits, base / V, row_off / V + pc);
     }
-    if constexpr (kDraw) {
-      uint8_t* const keep_row = keep_lds[flip][g];
-      const int64_t row0 = row_offset(static_cast<uint32_t>(base + g), Sk);
-      const bool live = base + g < rows;
-      if (live) draw_row_keep<LANES>(keep_row, row0, Sk, t, rng, nullptr, 0);
-      if constexpr (LANES <= kWave) wave_lds_fence();
-      else lds_barrier();
+  }
+  if constexpr (kDraw) {
+    uint8_t* const keep_row = keep_lds[g];
+    if (live) draw_row_keep<LANES>(keep_row, base, row_off, Sk, t, rng, nullptr, 0);
+    if constexpr (LANES <= kWave) wave_lds_fence();
+    else lds_barrier();
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int pc = c * LANES + t;
-        if (live && pc < pieces)
-          bits[0][c] = row_keep_window<V>(
-              keep_row, static_cast<int>(row0 & 7) + piece_col<RAG, V>(pc, pieces, Sk));
-      }
-    } else if constexpr (MASK == kMaskRegen) {  // every lane takes part: lane pairs share draws
+    for (int c = 0; c < CH; ++c) {
+      const int pc = c * LANES + t;
+      if (live && pc < pieces)
+        bits[c] = row_keep_window<V>(
+            keep_row, static_cast<int>((static_cast<uint32_t>(base) + row_off) & 7) +
+                          piece_col<RAG, V>(pc, pieces, Sk));
+    }
+  } else if constexpr (MASK == kMaskRegen) {  // every lane takes part: lane pairs share draws
+    lane_keep_bits<T, LANES, CH>(static_cast<uint64_t>(base) >> 3, row_off / V, t, rng, bits);
+  }
+  if (LANES <= kWave && !live) return;
+  float dp[CH][V], pr[CH][V];
+  float dot = 0.0f;
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        lane_keep_bits<T, LANES, CH>(
-            row_offset(static_cast<uint32_t>(base + r * kGroups + g), Sk) / V, t, rng, bits[r]);
+  for (int c = 0; c < CH; ++c) {
+    const int pc = c * LANES + t;
+    const int dup = piece_dup<RAG, V>(pc, pieces, Sk);
+    if (live && pc < pieces) {
+      Store<T>::unpack(apply_keep<T>(rdo[c].a, bits[c]), dp[c]);  // dropped: dP = 0
+      rp[c].unpack(pr[c]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < V; ++k) dp[c][k] = pr[c][k] = 0.0f;
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t row = base + r * kGroups + g;
-      // no row: uniform over the lane group; a group of several waves walks on (the reduction
-      // holds a workgroup barrier) with zeros and stores nothing
-      const bool live = row < rows;
-      if (LANES <= kWave && !live) continue;
-      const int64_t row0 = row_offset(static_cast<uint32_t>(row), Sk);
-      float dp[CH][V], pr[CH][V];
-      float dot = 0.0f;
+    for (int k = 0; k < V; ++k) {
+      dp[c][k] *= scale;
+      if (!RAG || k >= dup) dot = fmaf(dp[c][k], pr[c][k], dot);
+    }
+  }
+  dot = row_reduce<LANES, false>(dot, red);
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int pc = c * LANES + t;
-        const int dup = piece_dup<RAG, V>(pc, pieces, Sk);
-        if (live && pc < pieces) {
-          Store<T>::unpack(apply_keep<T>(rdo[r][c].a, bits[r][c]), dp[c]);  // dropped: dP = 0
-          rp[r][c].unpack(pr[c]);
-        } else {
+  for (int c = 0; c < CH; ++c) {
+    const int pc = c * LANES + t;
+    if (live && pc < pieces) {
+      const uint32_t off = row_off + piece_col<RAG, V>(pc, pieces, Sk);
+      float ds[V];
 #pragma unroll
-          for (int k = 0; k < V; ++k) dp[c][k] = pr[c][k] = 0.0f;
-        }
+      for (int k = 0; k < V; ++k) ds[k] = pr[c][k] * (dp[c][k] - dot);
+      store_row_piece<T, RAG, SHORT>(at_offset(dscores + base, off), Sk, Store<T>::pack(ds));
+      if (out_re) {
+        float o8[V];
 #pragma unroll
-        for (int k = 0; k < V; ++k) {
-          dp[c][k] *= scale;
-          if (!RAG || k >= dup) dot = fmaf(dp[c][k], pr[c][k], dot);
-        }
-      }
-      dot = row_reduce<LANES, false>(dot, red[flip]);
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int pc = c * LANES + t;
-        if (live && pc < pieces) {
-          const int64_t e = row0 + piece_col<RAG, V>(pc, pieces, Sk);
-          float ds[V];
-#pragma unroll
-          for (int k = 0; k < V; ++k) ds[k] = pr[c][k] * (dp[c][k] - dot);
-          store_row_piece<T, RAG, SHORT>(dscores + e, Sk, Store<T>::pack(ds));
-          if (out_re) {
-            float o8[V];
-#pragma unroll
-            for (int k = 0; k < V; ++k) o8[k] = pr[c][k] * scale;
-            store_row_piece<T, RAG, SHORT>(out_re + e, Sk,
-                                           apply_keep<T>(Store<T>::pack(o8), bits[r][c]));
-          }
-        }
+        for (int k = 0; k < V; ++k) o8[k] = pr[c][k] * scale;
+        store_row_piece<T, RAG, SHORT>(at_offset(out_re + base, off), Sk,
+                                       apply_keep<T>(Store<T>::pack(o8), bits[c]));
       }
     }
   }
@@ -580,7 +635,7 @@ struct KeepBlock {
   int64_t group0;
   __device__ __forceinline__ void draw(int64_t e_block, int lane, const RngArgs& rng) {
     group0 = e_block >> 3;
-    byte = keep_byte(static_cast<uint64_t>(group0) + lane, rng);
+    byte = keep_byte(static_cast<uint64_t>(group0), lane, rng);
   }
   __device__ __forceinline__ bool kept(int64_t e) const {
     return (__shfl(byte, static_cast<int>((e >> 3) - group0), kWave) >> (e & 7)) & 1u;
@@ -637,7 +692,7 @@ __global__ __launch_bounds__(kThreads) void keep_words_kernel(uint32_t* __restri
        w += static_cast<int64_t>(gridDim.x) * kThreads) {
     uint32_t word = 0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) word |= keep_byte(static_cast<uint64_t>(w) * 4 + b, rng) << (8 * b);
+    for (int b = 0; b < 4; ++b) word |= keep_byte(static_cast<uint64_t>(w) * 4, b, rng) << (8 * b);
     const int64_t left = n - w * 32;
     if (left < 32) word &= (1u << left) - 1u;
     keep_bits[w] = word;
@@ -696,11 +751,11 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_generic_kernel(
 
 constexpr int kMaxPieces = 1024;  // 4 per lane of 4 waves
 
-// Shapes of the ragged rows: those that at most kRaggedMaxPieces pieces per lane lead to, whatever
-// the knobs say, in workgroups of two waves (of the row's four where it takes four).
+// Shapes of the ragged rows (row_shape never takes others, whatever the knobs say), in workgroups of
+// two waves (of the row's four where it takes four).
 constexpr int kRaggedMaxPieces = 4;
 constexpr bool is_ragged_shape(int lanes, int ch) {
-  return ch <= kRaggedMaxPieces && (lanes <= kWave || ch > 2);
+  return ch <= kRaggedMaxPieces && !(lanes == 2 * kWave && ch == 2);
 }
 constexpr int ragged_threads(int lanes) { return lanes > 2 * kWave ? lanes : 2 * kWave; }
 
@@ -739,11 +794,27 @@ Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
 }
 
 // Shape for rows of Sk elements; ch == 0: too long for the register-resident kernels.
-Shape row_shape(int64_t Sk, int vec, int max_ch) {
+// Rows longer than a wave take as many waves as give a lane a single piece, while that leaves few
+// lanes idle (an eighth of them at most forward, where the vector ALU counts, a quarter backward);
+// longer ones take four waves forward.  One wave with several pieces per lane against this, us:
+// 64x16x512x512 f32 547 -> 520 forward, 706 -> 695 backward; 8x12x1024x1024 bf16 causal backward
+// 134 -> 129; 1x16x2048 bf16 forward 72 -> 68; 2x12x3072 bf16 causal forward 206 -> 202; with more idle
+// lanes it loses (640 bf16 columns forward: 45 -> 53).  Ragged rows gain more (1001 f32: 363 -> 304
+// both ways), but two waves of bfloat16 lose 5 % (901 columns: 143 -> 151).  Several short rows per
+// wave with three pieces per lane lose a third wherever rows are not whole 128-byte lines.
+Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
   const bool ragged = Sk % 8 != 0;
   const int64_t pieces = (Sk + vec - 1) / vec;
   if (pieces > kMaxPieces) return {0, 0};
-  return pick_wide_shape(static_cast<int>(pieces), 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
+  const int p = static_cast<int>(pieces);
+  if (ragged || max_ch <= kRaggedMaxPieces) {
+    const int wide = p <= 2 * kWave ? 2 * kWave : kThreads;
+    const bool two_ragged_bf16 = ragged && vec == 8 && wide == 2 * kWave;
+    if (p > kWave && p <= kThreads && p * 8 >= wide * (backward ? 6 : 7) && !two_ragged_bf16)
+      return {wide, 1};
+    if (!backward && p > kThreads) return {kThreads, (p + kThreads - 1) / kThreads};
+  }
+  return pick_wide_shape(p, 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
 }
 
 // Rows a lane group of the forward kernel fetches at once: 2 (if the knob allows) when a
@@ -767,12 +838,11 @@ int group_threads(int lanes) {
   return want > least ? want : least;
 }
 
-int row_grid(int64_t rows, int lanes, int blocks_per_cu, int rows_per_group = 1, int threads = kThreads) {
-  const int groups = (threads / lanes) * rows_per_group;
-  const int64_t want = (rows + groups - 1) / groups;
+// Workgroups of the any-length kernels: one wave per row, rows beyond the cap in a loop.
+int row_grid(int64_t rows, int blocks_per_cu) {
+  const int64_t want = (rows + kThreads / kWave - 1) / (kThreads / kWave);
   const int64_t cap = static_cast<int64_t>(compute_units()) * blocks_per_cu;
-  const int64_t b = want < cap ? want : cap;
-  return static_cast<int>(b < 1 ? 1 : b);
+  return static_cast<int>(std::max<int64_t>(1, std::min(want, cap)));
 }
 
 }  // namespace
@@ -827,18 +897,19 @@ static void with_threads(int threads, F&& f) {
 }
 
 template <typename T, int L, int C>
-static void attn_fwd_go(int rr, MaskLayout layout, int threads, dim3 grid, hipStream_t st,
+static void attn_fwd_go(int rr, MaskLayout layout, int threads, uint32_t first_set, uint32_t sets, hipStream_t st,
                         const void* scores, const int32_t* key_len, int causal, void* probs,
-                        void* out, uint32_t* keep_bits, int slices, int64_t A, int64_t Sq,
-                        int64_t Sk, float scale, const RngArgs& rng) {
+                        void* out, uint32_t* keep_bits, int slices, const FastDiv& heads,
+                        const FastDiv& sets_per_slice, int64_t Sq, int64_t Sk, float scale,
+                        const RngArgs& rng) {
   auto go = [&](auto rows, auto w) {
     with_threads<L, decltype(w)::value == kRagged>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL(
-          (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), grid, dim3(TH),
-          0, st, static_cast<const T*>(scores), key_len, causal, static_cast<T*>(probs),
-          static_cast<T*>(out), keep_bits, slices, static_cast<int>(A), static_cast<int>(Sq),
-          static_cast<int>(Sk), scale, rng);
+          (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), dim3(sets),
+          dim3(TH), 0, st, static_cast<const T*>(scores), key_len, causal, static_cast<T*>(probs),
+          static_cast<T*>(out), keep_bits, slices, static_cast<int>(Sq), static_cast<int>(Sk), scale,
+          rng, sets_per_slice, heads, first_set);
     });
   };
   using std::integral_constant;
@@ -858,16 +929,16 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, dim3 grid, hipSt
 }
 
 template <typename T, int L, int C>
-static void attn_bwd_go(MaskSource mask, bool ragged, int threads, int grid, hipStream_t st, const void* dout,
+static void attn_bwd_go(MaskSource mask, bool ragged, int threads, uint32_t first_set, uint32_t sets, hipStream_t st, const void* dout,
                         const void* probs, const uint32_t* keep_bits, void* dscores, void* out_re,
                         int64_t rows, int64_t Sk, float scale, const RngArgs& rng) {
   auto go = [&](auto m, auto rag) {
     with_threads<L, decltype(rag)::value>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
-      hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, 1, decltype(m)::value, decltype(rag)::value, TH>), dim3(grid), dim3(TH),
+      hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, decltype(m)::value, decltype(rag)::value, TH>), dim3(sets), dim3(TH),
                          0, st, static_cast<const T*>(dout), static_cast<const T*>(probs), keep_bits,
                          static_cast<T*>(dscores), static_cast<T*>(out_re),
-                         static_cast<uint32_t>(rows), static_cast<int>(Sk), scale, rng);
+                         static_cast<uint32_t>(rows), static_cast<int>(Sk), scale, rng, first_set);
     });
   };
   using std::integral_constant;
@@ -910,32 +981,36 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
   const int bpc = tune_get(kTuneAttnFwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   const bool ragged = Sk % 8 != 0;
-  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnFwdMaxPieces));
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnFwdMaxPieces), false);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int slices = static_cast<int>(B * A);
     const int rr = sh.lanes > kWave || ragged
                        ? 1 : attn_rows(sh.ch, sh.lanes, vec, tune_get(kTuneAttnFwdRows));
     const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
     const int rows_per_set = (threads / sh.lanes) * rr;
-    const int64_t total_sets =
-        static_cast<int64_t>(slices) * ((Sq + rows_per_set - 1) / rows_per_set);
-    const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
-    const dim3 grid(static_cast<unsigned>(total_sets < cap ? total_sets : cap));
+    const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
+    const FastDiv heads(static_cast<uint32_t>(A));
+    const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice.d;
     const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);   \
-    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, grid, st, scores, key_len, causal, probs, out, keep_bits, slices, A, Sq, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);   \
+    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
   } while (0)
-    if (sh.lanes > kWave) {
-      TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
-    } else {
-      TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+    const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
+    for (int64_t done = 0; done < total_sets; done += cap) {
+      const uint32_t first = static_cast<uint32_t>(done);
+      const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));
+      if (sh.lanes > kWave) {
+        TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
+      } else {
+        TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+      }
     }
 #undef TEMPO_LAUNCH
     return launch_status();
   }
-  const int grid = row_grid(rows, kWave, bpc);
+  const int grid = row_grid(rows, bpc);
   if (dt == TEMPO_F32)
     hipLaunchKernelGGL((attn_fwd_generic_kernel<float>), dim3(grid), dim3(kThreads), 0, st,
                        static_cast<const float*>(scores), key_len, causal,
@@ -968,26 +1043,31 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
   const int bpc = tune_get(kTuneAttnBwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   const bool ragged = Sk % 8 != 0;
-  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces));
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces), true);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
-    const int grid = row_grid(rows, sh.lanes, bpc, 1, threads);
+    const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
-    else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, grid, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
+    else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
   } while (0)
-    if (sh.lanes > kWave) {
-      TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
-    } else {
-      TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+    const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
+    for (int64_t done = 0; done < total_sets; done += cap) {
+      const uint32_t first = static_cast<uint32_t>(done);
+      const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));
+      if (sh.lanes > kWave) {
+        TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
+      } else {
+        TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+      }
     }
 #undef TEMPO_LAUNCH
     return launch_status();
   }
-  const int grid = row_grid(rows, kWave, bpc);
+  const int grid = row_grid(rows, bpc);
   auto go = [&](auto tag, auto m) {
     using T = decltype(tag);
     hipLaunchKernelGGL((attn_bwd_generic_kernel<T, decltype(m)::value>), dim3(grid),

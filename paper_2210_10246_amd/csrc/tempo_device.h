@@ -228,9 +228,26 @@ __device__ __forceinline__ float dpp_f32(float v) {
   return as_f32(dpp_u32<CTRL>(as_u32(v)));
 }
 
+// The values of the lanes 16 (32) away, added to or compared with the lane's own: v_permlane16_swap
+// (v_permlane32_swap) exchanges the odd 16-lane rows of one register with the even rows of another
+// (the upper half with the lower half), so that of two copies of v each lane then holds both its own
+// and the other's value: a move and a swap on the vector ALU instead of an LDS round trip.
+template <int N, typename F>
+__device__ __forceinline__ float across_rows(float v, F&& f) {
+  static_assert(N == 16 || N == 32, "distance");
+  const uint32_t u = as_u32(v);
+  if constexpr (N == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return f(as_f32(p[0]), as_f32(p[1]));
+  } else {
+    const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return f(as_f32(p[0]), as_f32(p[1]));
+  }
+}
+
 // Butterfly reductions over groups of LANES consecutive lanes of a wave (LANES a power of
 // two, 4 <= LANES <= 64, groups aligned to LANES); every lane of the group ends with the
-// result.  Steps inside a 16-lane row use DPP, the steps across rows go through ds_bpermute.
+// result.  Steps inside a 16-lane row use DPP, the steps across rows v_permlane*_swap.
 template <int LANES>
 __device__ __forceinline__ float group_sum(float v) {
   static_assert(LANES >= 4 && LANES <= 64, "group size");
@@ -238,8 +255,9 @@ __device__ __forceinline__ float group_sum(float v) {
   v += dpp_f32<kDppXor2>(v);
   if (LANES >= 8) v += dpp_f32<kDppHalfMirror>(v);
   if (LANES >= 16) v += dpp_f32<kDppMirror>(v);
-  if (LANES >= 32) v += __shfl_xor(v, 16, kWave);
-  if (LANES >= 64) v += __shfl_xor(v, 32, kWave);
+  auto add = [](float a, float b) { return a + b; };
+  if (LANES >= 32) v = across_rows<16>(v, add);
+  if (LANES >= 64) v = across_rows<32>(v, add);
   return v;
 }
 template <int LANES>
@@ -249,8 +267,9 @@ __device__ __forceinline__ float group_max(float v) {
   v = fmaxf(v, dpp_f32<kDppXor2>(v));
   if (LANES >= 8) v = fmaxf(v, dpp_f32<kDppHalfMirror>(v));
   if (LANES >= 16) v = fmaxf(v, dpp_f32<kDppMirror>(v));
-  if (LANES >= 32) v = fmaxf(v, __shfl_xor(v, 16, kWave));
-  if (LANES >= 64) v = fmaxf(v, __shfl_xor(v, 32, kWave));
+  auto larger = [](float a, float b) { return fmaxf(a, b); };
+  if (LANES >= 32) v = across_rows<16>(v, larger);
+  if (LANES >= 64) v = across_rows<32>(v, larger);
   return v;
 }
 
@@ -333,6 +352,24 @@ __device__ __forceinline__ uint32_t merge_mask_word(uint32_t bits, int lane) {
   if (V == 4) w |= dpp_u32<kDppHalfMirror>(w);
   return w;
 }
+
+// n / d for 32-bit n by a multiplication (Granlund, Montgomery, PLDI'94, the round-up form): a
+// division by a run-time value is some 20 dependent instructions before a kernel's first load.
+struct FastDiv {
+  uint32_t d, m, s1, s2;
+  FastDiv() = default;
+  explicit FastDiv(uint32_t divisor) : d(divisor) {
+    int l = 0;
+    while (l < 32 && (uint64_t{1} << l) < d) ++l;
+    m = static_cast<uint32_t>(((uint64_t{1} << 32) * ((uint64_t{1} << l) - d)) / d + 1);
+    s1 = l < 1 ? l : 1;
+    s2 = l > 0 ? l - 1 : 0;
+  }
+  __host__ __device__ __forceinline__ uint32_t divide(uint32_t n) const {
+    const uint32_t t = static_cast<uint32_t>((static_cast<uint64_t>(m) * n) >> 32);
+    return (t + ((n - t) >> s1)) >> s2;
+  }
+};
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
