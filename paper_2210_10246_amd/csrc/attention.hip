@@ -757,7 +757,15 @@ constexpr int kRaggedMaxPieces = 4;
 constexpr bool is_ragged_shape(int lanes, int ch) {
   return ch <= kRaggedMaxPieces && !(lanes == 2 * kWave && ch == 2);
 }
-constexpr int ragged_threads(int lanes) { return lanes > 2 * kWave ? lanes : 2 * kWave; }
+
+// Fewest lanes a workgroup may have: a row's, and two rows' where a forward row takes two waves
+// (64x16x512x512 f32, three sets of buffers: 508-519 us, against 510-554 with one row per workgroup).
+constexpr int least_threads(int lanes, bool backward) {
+  return lanes <= kWave ? kWave : (backward ? lanes : 4 * kWave);
+}
+constexpr int ragged_threads(int lanes, bool backward) {
+  return lanes <= kWave ? 2 * kWave : least_threads(lanes, backward);
+}
 
 struct Shape {
   int lanes;
@@ -831,8 +839,8 @@ int attn_rows(int ch, int lanes, int vec, int tuned) {
 // gain 2-8 % (forward at every size, backward on tensors from 2 GB up, never a loss); single
 // waves do no better than two and lose 1-2 % in places.  So: two waves, and never fewer lanes
 // than a row takes.
-int group_threads(int lanes) {
-  const int least = lanes > kWave ? lanes : kWave;  // 64, 128 or 256
+int group_threads(int lanes, bool backward) {
+  const int least = least_threads(lanes, backward);  // 64, 128 or 256
   int want = tune_get(kTuneAttnThreads);
   want = want >= 256 ? 256 : (want >= 128 ? 128 : kWave);
   return want > least ? want : least;
@@ -878,18 +886,19 @@ int row_grid(int64_t rows, int blocks_per_cu) {
     default: return TEMPO_ERR_UNSUPPORTED;                                                 \
   }
 
-// Calls f with the workgroup size as a compile-time constant: 64, 128 or 256, at least L; with
-// FIXED the default size only.
-template <int L, bool FIXED, typename F>
+// Calls f with the workgroup size as a compile-time constant: 64, 128 or 256, at least
+// least_threads; with FIXED the default size only.
+template <int L, bool BACKWARD, bool FIXED, typename F>
 static void with_threads(int threads, F&& f) {
   using std::integral_constant;
   if constexpr (FIXED) {
-    return f(integral_constant<int, ragged_threads(L)>{});
+    return f(integral_constant<int, ragged_threads(L, BACKWARD)>{});
   } else {
-    if constexpr (L <= 64) {
+    constexpr int least = least_threads(L, BACKWARD);
+    if constexpr (least <= 64) {
       if (threads == 64) return f(integral_constant<int, 64>{});
     }
-    if constexpr (L <= 128) {
+    if constexpr (least <= 128) {
       if (threads == 128) return f(integral_constant<int, 128>{});
     }
     f(integral_constant<int, 256>{});
@@ -903,7 +912,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, uint32_t first_s
                         const FastDiv& sets_per_slice, int64_t Sq, int64_t Sk, float scale,
                         const RngArgs& rng) {
   auto go = [&](auto rows, auto w) {
-    with_threads<L, decltype(w)::value == kRagged>(threads, [&](auto th) {
+    with_threads<L, false, decltype(w)::value == kRagged>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL(
           (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), dim3(sets),
@@ -933,7 +942,7 @@ static void attn_bwd_go(MaskSource mask, bool ragged, int threads, uint32_t firs
                         const void* probs, const uint32_t* keep_bits, void* dscores, void* out_re,
                         int64_t rows, int64_t Sk, float scale, const RngArgs& rng) {
   auto go = [&](auto m, auto rag) {
-    with_threads<L, decltype(rag)::value>(threads, [&](auto th) {
+    with_threads<L, true, decltype(rag)::value>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, decltype(m)::value, decltype(rag)::value, TH>), dim3(sets), dim3(TH),
                          0, st, static_cast<const T*>(dout), static_cast<const T*>(probs), keep_bits,
@@ -986,7 +995,8 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const int slices = static_cast<int>(B * A);
     const int rr = sh.lanes > kWave || ragged
                        ? 1 : attn_rows(sh.ch, sh.lanes, vec, tune_get(kTuneAttnFwdRows));
-    const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
+    const int threads =
+        ragged ? ragged_threads(sh.lanes, false) : group_threads(sh.lanes, false);
     const int rows_per_set = (threads / sh.lanes) * rr;
     const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
     const FastDiv heads(static_cast<uint32_t>(A));
@@ -1045,7 +1055,8 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
   const bool ragged = Sk % 8 != 0;
   const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces), true);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
-    const int threads = ragged ? ragged_threads(sh.lanes) : group_threads(sh.lanes);
+    const int threads =
+        ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);
     const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
