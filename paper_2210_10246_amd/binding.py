@@ -1,4 +1,9 @@
-"""Thin ctypes binding of libtempo.so: same names as the C ABI, argument marshalling only.
+"""Thin binding of libtempo.so: same names as the C ABI, argument marshalling only.
+
+The calls go through _native.so (csrc/binding.cpp), which makes the checks below in native code and
+calls the C ABI on the current stream.  Whatever it does not take (an explicit stream, an argument
+that one of the checks refuses or that is no plain tensor) goes through the ctypes path here, which
+raises.
 
 Tensors are torch CUDA tensors (PyTorch supplies device memory and the stream; every step
 of the layers runs in the HIP kernels).  Outputs are written into tensors the caller passes.
@@ -54,6 +59,7 @@ _SIGNATURES = {
 }
 
 _lib = None
+_native = None  # the module _native.so, once load() has run
 
 
 class TempoError(RuntimeError):
@@ -63,8 +69,8 @@ class TempoError(RuntimeError):
 
 
 def load() -> ctypes.CDLL:
-    """Load libtempo.so (built in-tree by build.py); raises if it is missing."""
-    global _lib
+    """Load libtempo.so and _native.so (built in-tree by build.py); raises if one is missing."""
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(
@@ -74,6 +80,8 @@ def load() -> ctypes.CDLL:
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
+        from . import _native as native
+        _native = native
         _lib = lib
     return _lib
 
@@ -154,6 +162,10 @@ def tempo_copy_streams(reads, writes, stream=None):
 
 def tempo_gelu_fwd(x, y, mask, kind="erf", stream=None):
     """(y, mask) = GELU*(x); y may be x."""
+    if stream is None and _native is not None:
+        status = _native.tempo_gelu_fwd(x, y, mask, kind)
+        if status is not None:
+            return _check(status, "tempo_gelu_fwd")
     n = x.numel()
     dt = _act_dtype("x", x)
     _want("y", y, x.dtype, n)
@@ -164,6 +176,10 @@ def tempo_gelu_fwd(x, y, mask, kind="erf", stream=None):
 
 def tempo_gelu_bwd(dy, y, mask, dx, kind="erf", stream=None):
     """dx = dy * GELU'(GELU*^-1(y, mask)); dx may be dy."""
+    if stream is None and _native is not None:
+        status = _native.tempo_gelu_bwd(dy, y, mask, dx, kind)
+        if status is not None:
+            return _check(status, "tempo_gelu_bwd")
     n = y.numel()
     dt = _act_dtype("y", y)
     _want("dy", dy, y.dtype, n)
@@ -175,6 +191,10 @@ def tempo_gelu_bwd(dy, y, mask, dx, kind="erf", stream=None):
 
 def tempo_silu_fwd(x, y, mask, stream=None):
     """(y, mask) = SiLU*(x); y may be x."""
+    if stream is None and _native is not None:
+        status = _native.tempo_silu_fwd(x, y, mask)
+        if status is not None:
+            return _check(status, "tempo_silu_fwd")
     n = x.numel()
     dt = _act_dtype("x", x)
     _want("y", y, x.dtype, n)
@@ -185,6 +205,10 @@ def tempo_silu_fwd(x, y, mask, stream=None):
 
 def tempo_silu_bwd(dy, y, mask, dx, stream=None):
     """dx = dy * SiLU'(SiLU*^-1(y, mask)); dx may be dy."""
+    if stream is None and _native is not None:
+        status = _native.tempo_silu_bwd(dy, y, mask, dx)
+        if status is not None:
+            return _check(status, "tempo_silu_bwd")
     n = y.numel()
     dt = _act_dtype("y", y)
     _want("dy", dy, y.dtype, n)
@@ -195,6 +219,10 @@ def tempo_silu_bwd(dy, y, mask, dx, stream=None):
 
 
 def tempo_layernorm_fwd(x, gamma, beta, y, rstd, mean=None, eps=1e-5, stream=None):
+    if stream is None and _native is not None:
+        status = _native.tempo_layernorm_fwd(x, gamma, beta, y, rstd, mean, eps)
+        if status is not None:
+            return _check(status, "tempo_layernorm_fwd")
     M = x.shape[-1]
     N = x.numel() // M if M else 0
     dt = _act_dtype("x", x)
@@ -213,6 +241,10 @@ def tempo_layernorm_bwd_workspace_bytes(N: int, M: int) -> int:
 
 
 def tempo_layernorm_bwd(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, workspace, stream=None):
+    if stream is None and _native is not None:
+        status = _native.tempo_layernorm_bwd(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, workspace)
+        if status is not None:
+            return _check(status, "tempo_layernorm_bwd")
     M = y.shape[-1]
     N = y.numel() // M if M else 0
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
@@ -232,6 +264,10 @@ def tempo_layernorm_bwd(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, workspace, 
 
 def tempo_layernorm_bwd_static(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, stream=None):
     """tempo_layernorm_bwd with the library's static scratch array as workspace."""
+    if stream is None and _native is not None:
+        status = _native.tempo_layernorm_bwd_static(dy, y, gamma, beta, rstd, dx, dgamma, dbeta)
+        if status is not None:
+            return _check(status, "tempo_layernorm_bwd_static")
     M = y.shape[-1]
     N = y.numel() // M if M else 0
     dt = _act_dtype("y", y)
@@ -249,6 +285,11 @@ def tempo_layernorm_bwd_static(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, stre
 
 def tempo_attn_softmax_dropout_fwd(scores, key_len, causal, probs, out, keep_bits, p, seed, offset,
                                    stream=None):
+    if stream is None and _native is not None:
+        status = _native.tempo_attn_softmax_dropout_fwd(scores, key_len, causal, probs, out,
+                                                        keep_bits, p, seed, offset)
+        if status is not None:
+            return _check(status, "tempo_attn_softmax_dropout_fwd")
     B, A, Sq, Sk = scores.shape
     n = scores.numel()
     dt = _act_dtype("scores", scores)
@@ -263,6 +304,11 @@ def tempo_attn_softmax_dropout_fwd(scores, key_len, causal, probs, out, keep_bit
 
 
 def tempo_attn_softmax_dropout_bwd(dout, probs, keep_bits, dscores, out_recomputed, p, stream=None):
+    if stream is None and _native is not None:
+        status = _native.tempo_attn_softmax_dropout_bwd(dout, probs, keep_bits, dscores,
+                                                        out_recomputed, p)
+        if status is not None:
+            return _check(status, "tempo_attn_softmax_dropout_bwd")
     B, A, Sq, Sk = probs.shape
     n = probs.numel()
     dt = _act_dtype("probs", probs)
@@ -279,6 +325,11 @@ def tempo_attn_softmax_dropout_bwd(dout, probs, keep_bits, dscores, out_recomput
 def tempo_attn_softmax_dropout_bwd_bytemask(dout, probs, keep_bytes, dscores, out_recomputed, p,
                                             stream=None):
     """Backward reading a mask of one byte per element (uint8 or bool tensor; non-zero = kept)."""
+    if stream is None and _native is not None:
+        status = _native.tempo_attn_softmax_dropout_bwd_bytemask(dout, probs, keep_bytes, dscores,
+                                                                 out_recomputed, p)
+        if status is not None:
+            return _check(status, "tempo_attn_softmax_dropout_bwd_bytemask")
     B, A, Sq, Sk = probs.shape
     n = probs.numel()
     dt = _act_dtype("probs", probs)
@@ -295,6 +346,11 @@ def tempo_attn_softmax_dropout_bwd_bytemask(dout, probs, keep_bytes, dscores, ou
 
 def tempo_attn_softmax_dropout_bwd_regen(dout, probs, dscores, out_recomputed, p, seed, offset,
                                          stream=None):
+    if stream is None and _native is not None:
+        status = _native.tempo_attn_softmax_dropout_bwd_regen(dout, probs, dscores, out_recomputed,
+                                                              p, seed, offset)
+        if status is not None:
+            return _check(status, "tempo_attn_softmax_dropout_bwd_regen")
     B, A, Sq, Sk = probs.shape
     n = probs.numel()
     dt = _act_dtype("probs", probs)
