@@ -804,7 +804,7 @@ Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
 // Shape for rows of Sk elements; ch == 0: too long for the register-resident kernels.
 // Rows longer than a wave take as many waves as give a lane a single piece, while that leaves few
 // lanes idle (an eighth of them at most forward, where the vector ALU counts, a quarter backward);
-// longer ones take four waves forward.  One wave with several pieces per lane against this, us:
+// longer ones take four waves.  One wave with several pieces per lane against this, us:
 // 64x16x512x512 f32 547 -> 520 forward, 706 -> 695 backward; 8x12x1024x1024 bf16 causal backward
 // 134 -> 129; 1x16x2048 bf16 forward 72 -> 68; 2x12x3072 bf16 causal forward 206 -> 202; with more idle
 // lanes it loses (640 bf16 columns forward: 45 -> 53).  Ragged rows gain more (1001 f32: 363 -> 304
@@ -820,9 +820,28 @@ Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
     const bool two_ragged_bf16 = ragged && vec == 8 && wide == 2 * kWave;
     if (p > kWave && p <= kThreads && p * 8 >= wide * (backward ? 6 : 7) && !two_ragged_bf16)
       return {wide, 1};
-    if (!backward && p > kThreads) return {kThreads, (p + kThreads - 1) / kThreads};
+    if (p > kThreads) return {kThreads, (p + kThreads - 1) / kThreads};
   }
   return pick_wide_shape(p, 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
+}
+
+// Dynamic LDS that no kernel reads: it keeps the workgroups that are resident on a compute unit to
+// those that move about kFlightPieces pieces of each tensor at once.  The backward streams two
+// tensors in and two out, and the more waves have loads under way beyond that, the worse the memory
+// system does: at 32 and at 18-20 resident waves of one piece per lane, us: 8x12x1024x1024 bf16 129
+// and 124; 16x16x512x512 bf16 89 and 86; 64x16x512x512 f32 703 and 691; 2 pieces per lane, 32 and 12
+// waves: 16x4096x4096 bf16 378 and 347; 16x2048x2048 f32 189 and 173.  Fewer than 12 waves lose again.
+// Rows that leave a third of the lanes idle move less per wave and stay unlimited.
+// The forward is bound by the vector ALU in bfloat16 and wants all waves (3072 columns, causal: 201 us,
+// 255 at 16 waves); in float32 rows of several pieces per lane gain (16x2048x2048: 137 -> 131).
+constexpr int kFlightPieces = 18 * kWave;
+constexpr int kLdsPerCu = 160 * 1024;
+size_t flight_lds_bytes(const Shape& sh, int pieces, int threads, int least_waves) {
+  const int pieces_per_wave = std::max(1, pieces * kWave / sh.lanes);
+  const int waves = std::max(least_waves, (kFlightPieces + pieces_per_wave - 1) / pieces_per_wave);
+  const int groups = (waves + threads / kWave - 1) / (threads / kWave);
+  if (groups > 12 || waves >= 26) return 0;      // as good as all that fit
+  return kLdsPerCu / groups / 256 * 256 - 1280;  // less the static LDS; one more would not fit
 }
 
 // Rows a lane group of the forward kernel fetches at once: 2 (if the knob allows) when a
@@ -906,7 +925,7 @@ static void with_threads(int threads, F&& f) {
 }
 
 template <typename T, int L, int C>
-static void attn_fwd_go(int rr, MaskLayout layout, int threads, uint32_t first_set, uint32_t sets, hipStream_t st,
+static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint32_t first_set, uint32_t sets, hipStream_t st,
                         const void* scores, const int32_t* key_len, int causal, void* probs,
                         void* out, uint32_t* keep_bits, int slices, const FastDiv& heads,
                         const FastDiv& sets_per_slice, int64_t Sq, int64_t Sk, float scale,
@@ -916,7 +935,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, uint32_t first_s
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL(
           (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), dim3(sets),
-          dim3(TH), 0, st, static_cast<const T*>(scores), key_len, causal, static_cast<T*>(probs),
+          dim3(TH), lds, st, static_cast<const T*>(scores), key_len, causal, static_cast<T*>(probs),
           static_cast<T*>(out), keep_bits, slices, static_cast<int>(Sq), static_cast<int>(Sk), scale,
           rng, sets_per_slice, heads, first_set);
     });
@@ -938,14 +957,14 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, uint32_t first_s
 }
 
 template <typename T, int L, int C>
-static void attn_bwd_go(MaskSource mask, bool ragged, int threads, uint32_t first_set, uint32_t sets, hipStream_t st, const void* dout,
+static void attn_bwd_go(MaskSource mask, bool ragged, int threads, size_t lds, uint32_t first_set, uint32_t sets, hipStream_t st, const void* dout,
                         const void* probs, const uint32_t* keep_bits, void* dscores, void* out_re,
                         int64_t rows, int64_t Sk, float scale, const RngArgs& rng) {
   auto go = [&](auto m, auto rag) {
     with_threads<L, true, decltype(rag)::value>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
       hipLaunchKernelGGL((attn_bwd_kernel<T, L, C, decltype(m)::value, decltype(rag)::value, TH>), dim3(sets), dim3(TH),
-                         0, st, static_cast<const T*>(dout), static_cast<const T*>(probs), keep_bits,
+                         lds, st, static_cast<const T*>(dout), static_cast<const T*>(probs), keep_bits,
                          static_cast<T*>(dscores), static_cast<T*>(out_re),
                          static_cast<uint32_t>(rows), static_cast<int>(Sk), scale, rng, first_set);
     });
@@ -1001,11 +1020,13 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
     const FastDiv heads(static_cast<uint32_t>(A));
     const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice.d;
+    const size_t lds = dt == TEMPO_F32 && sh.ch > 2
+                           ? flight_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads, 12) : 0;
     const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);   \
-    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);   \
+    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
   } while (0)
     const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
     for (int64_t done = 0; done < total_sets; done += cap) {
@@ -1058,12 +1079,13 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
     const int threads =
         ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);
     const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
+    const size_t lds = flight_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads, 12);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
-    else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
+    if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, lds, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
+    else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, lds, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
   } while (0)
     const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
     for (int64_t done = 0; done < total_sets; done += cap) {
