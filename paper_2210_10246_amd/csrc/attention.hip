@@ -832,8 +832,6 @@ Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
 // and 124; 16x16x512x512 bf16 89 and 86; 64x16x512x512 f32 703 and 691; 2 pieces per lane, 32 and 12
 // waves: 16x4096x4096 bf16 378 and 347; 16x2048x2048 f32 189 and 173.  Fewer than 12 waves lose again.
 // Rows that leave a third of the lanes idle move less per wave and stay unlimited.
-// The forward is bound by the vector ALU in bfloat16 and wants all waves (3072 columns, causal: 201 us,
-// 255 at 16 waves); in float32 rows of several pieces per lane gain (16x2048x2048: 137 -> 131).
 constexpr int kFlightPieces = 18 * kWave;
 constexpr int kLdsPerCu = 160 * 1024;
 size_t flight_lds_bytes(const Shape& sh, int pieces, int threads, int least_waves) {
@@ -842,6 +840,16 @@ size_t flight_lds_bytes(const Shape& sh, int pieces, int threads, int least_wave
   const int groups = (waves + threads / kWave - 1) / (threads / kWave);
   if (groups > 12 || waves >= 26) return 0;      // as good as all that fit
   return kLdsPerCu / groups / 256 * 256 - 1280;  // less the static LDS; one more would not fit
+}
+
+// The same for the float32 forward (one tensor in, two out), whose vector work leaves room: rows that
+// fill their wave with one piece per lane 26-28 waves (64x16x256x256: 137 -> 133 us), three and four pieces
+// per lane 12 and 8 waves (8x3072x3072: 159 -> 152; 8x4096x4096: 284 -> 267).  The bfloat16 forward is
+// bound by the vector ALU and wants all waves (3072 columns, causal: 201 us, 255 at 16 waves).
+size_t fwd_f32_lds_bytes(const Shape& sh, int pieces, int threads) {
+  if (sh.ch == 1 && sh.lanes <= kWave && threads == 2 * kWave && pieces * 8 >= sh.lanes * 7)
+    return 11 * 1024;
+  return sh.ch > 2 ? flight_lds_bytes(sh, pieces, threads, sh.ch == 3 ? 12 : 8) : 0;
 }
 
 // Rows a lane group of the forward kernel fetches at once: 2 (if the knob allows) when a
@@ -1020,8 +1028,8 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
     const FastDiv heads(static_cast<uint32_t>(A));
     const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice.d;
-    const size_t lds = dt == TEMPO_F32 && sh.ch > 2
-                           ? flight_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads, 12) : 0;
+    const size_t lds =
+        dt == TEMPO_F32 ? fwd_f32_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads) : 0;
     const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
