@@ -62,7 +62,9 @@ __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int
 // must cover every batch).  LOOP = true: workgroups walk the batches grid-stride, fetching the
 // next batch before they compute on the current one, and load gamma/beta once: for long rows
 // the parameters (8 bytes per column from L2) otherwise outweigh the row itself.
-// RAG: rows of any length that is no multiple of the piece (see piece_col).
+// RAG: rows of any length that is no multiple of the piece (see piece_col): 16-byte accesses at
+// element-aligned addresses, columns on fixed lanes.  Bound by memory like the aligned rows: 8192 x 1001
+// f32 15.1 -> 13.1 us against element-wise accesses (1000 columns: 13.2), 4096 x 4100 bf16 40.6 -> 16.8.
 template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
     const T* x, const float* __restrict__ gamma, const float* __restrict__ beta, T* y,
@@ -258,6 +260,8 @@ __global__ __launch_bounds__(256) void ln_fwd_generic_kernel(
 // compute on the current one; the column sums stay in registers across batches, so the LDS
 // tree and the partial store are paid once per workgroup however many rows it walks.
 // RAG: rows of any length that is no multiple of the piece (see piece_col), parameters in registers.
+// 8192 x 1001 f32 50.3 -> 25.0 us against element-wise accesses with a division per element (1000
+// columns: 22.4), 4096 x 4100 bf16 98.9 -> 28.5.
 template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     const T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
