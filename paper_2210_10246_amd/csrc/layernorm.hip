@@ -53,6 +53,11 @@ __device__ __forceinline__ void store_col_sums(float* p, int ch, int chunks, int
     store_floats_any<V>(p + ch * V, v);
   }
 }
+// Whether a division by gamma may be done by multiplication with its reciprocal: neither that nor a
+// residual leaves the range of float32.
+__device__ __forceinline__ bool is_tame(float gamma) {
+  return fabsf(gamma) >= 0x1p-60f && fabsf(gamma) <= 0x1p60f;
+}
 // Length of a row of column sums in LDS: whole 16-byte pieces.
 __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int64_t{3}; }
 
@@ -259,9 +264,9 @@ __global__ __launch_bounds__(256) void ln_fwd_generic_kernel(
 // LOOP = true: workgroups walk the batches grid-stride and fetch the next batch before they
 // compute on the current one; the column sums stay in registers across batches, so the LDS
 // tree and the partial store are paid once per workgroup however many rows it walks.
-// RAG: rows of any length that is no multiple of the piece (see piece_col), parameters in registers.
-// 8192 x 1001 f32 50.3 -> 25.0 us against element-wise accesses with a division per element (1000
-// columns: 22.4), 4096 x 4100 bf16 98.9 -> 28.5.
+// RAG: rows of any length that is no multiple of the piece (see piece_col), parameters in registers,
+// and xhat as the quotient (y - beta) / gamma itself.  8192 x 1001 f32 50.0 -> 24.9 us against
+// element-wise accesses (1000 columns: 22.4), 4096 x 4100 bf16 97.8 -> 29.5.
 template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     const T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   __shared__ float2 red[2][kBwdWaves];
   static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
   int flip = 0;
-  // gamma, 1/gamma and beta/gamma of the lane's columns live in its registers when that share
+  // gamma, 1/gamma and beta/gamma (beta if RAG) of the lane's columns live in its registers when that share
   // is at most 24 columns; otherwise in LDS (the first 3*M floats; the
   // same memory is reused by the reduction tree at the end), where every row re-reads the three
   // vectors twice: at 8 waves per compute unit that is microseconds of LDS time per batch.
@@ -329,6 +334,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   float rs[R];
   fetch(base, rd, ry, rs);
   // parameters after the first rows are on their way
+  bool tame = true;  // every gamma of the lane is
   if constexpr (kRegParams) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -350,7 +356,15 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
         // for each of its columns in every workgroup, and the IEEE division costs four times as much
         const float est = __builtin_amdgcn_rcpf(r_ga[c][i]);
         r_rg[c][i] = fmaf(fmaf(-r_ga[c][i], est, 1.0f), est, est);
-        r_bg[c][i] = be[i] * r_rg[c][i];
+        if constexpr (RAG) {
+          r_bg[c][i] = be[i];
+          // waits for beta here: first used inside the loop, it would make the loop wait for every
+          // load under way, the rows fetched ahead included (8192 x 1001 f32: 38 -> 42 us)
+          asm volatile("" : "+v"(r_bg[c][i]));
+          tame = tame && is_tame(r_ga[c][i]);
+        } else {
+          r_bg[c][i] = be[i] * r_rg[c][i];
+        }
       }
     }
   } else {
@@ -363,6 +377,32 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     }
     lds_barrier();
   }
+  // xhat of a piece.  The fused form loses 2^-24 |beta / gamma| to the rounding of beta / gamma; ragged
+  // rows subtract first and divide: the product with the reciprocal, one residual step, which rounds it as
+  // a division does, and the division's own treatment of infinities.  Forward + backward, us, fused / this /
+  // a division per element: 8192 x 1001 f32 38.3 / 38.6 / 38.5, bf16 25.4 / 26.3 / 28.1; 4096 x 4100 bf16
+  // 45.4 / 46.5 / 50.2.
+  const bool wave_tame = __builtin_amdgcn_ballot_w64(!tame) == 0;  // scalar: a branch, not a select
+  auto xhat = [&](const float (&y8)[V], const float (&ga)[V], const float (&rg)[V], const float (&bg)[V],
+                  float (&h)[V]) {
+    if constexpr (!RAG) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) h[i] = fmaf(y8[i], rg[i], -bg[i]);
+    } else {
+      auto quotient = [](float d, float g, float rcp) {
+        const float q = d * rcp;
+        return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-g, q, d), rcp, q), g, d);
+      };
+      if (wave_tame) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) h[i] = quotient(y8[i] - bg[i], ga[i], rg[i]);
+      } else {  // per column, so that the two lanes which share one find the same value
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+          h[i] = is_tame(ga[i]) ? quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
+      }
+    }
+  };
   while (base < N) {
     const int64_t next = base + static_cast<int64_t>(gridDim.x) * batch_rows;
     Raw<T> nd[R][CH], ny[R][CH];  // unused (and eliminated) without LOOP
@@ -397,18 +437,19 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
             load_floats<V>(p_rg + ch * V, rg);
             load_floats<V>(p_bg + ch * V, bg);
           }
+          float h[V];
+          xhat(y8, ga, rg, bg, h);
 #pragma unroll
           for (int i = 0; i < V; ++i) {
-            const float h = fmaf(y8[i], rg[i], -bg[i]);  // xhat = (y - beta) / gamma
             const float q = d8[i] * ga[i];
             if (!RAG || i >= piece_dup<RAG, V>(ch, chunks, M)) {
-              c1[r] = fmaf(q, h, c1[r]);
+              c1[r] = fmaf(q, h[i], c1[r]);
               c2[r] += q;
             }
-            acc_g[c][i] = fmaf(d8[i], h, acc_g[c][i]);
+            acc_g[c][i] = fmaf(d8[i], h[i], acc_g[c][i]);
             acc_b[c][i] += d8[i];
             if constexpr (kKeep) {
-              k_h[r][c][i] = h;
+              k_h[r][c][i] = h[i];
               k_q[r][c][i] = q;
             }
           }
@@ -452,11 +493,10 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
               load_floats<V>(p_rg + ch * V, rg);
               load_floats<V>(p_bg + ch * V, bg);
             }
+            float h[V];
+            xhat(y8, ga, rg, bg, h);
 #pragma unroll
-            for (int i = 0; i < V; ++i) {
-              const float h = fmaf(y8[i], rg[i], -bg[i]);
-              o[i] = rs[r] * (d8[i] * ga[i] - fmaf(h, c1[r], c2[r]));
-            }
+            for (int i = 0; i < V; ++i) o[i] = rs[r] * (d8[i] * ga[i] - fmaf(h[i], c1[r], c2[r]));
           }
           stg_piece<RAG>(dx + row * M + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(o));
         }

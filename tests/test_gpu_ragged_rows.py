@@ -137,3 +137,28 @@ def test_layernorm_ragged_rows(B, M, N, dt):
         assert all((g == 7).all() for g in (g0, g1, g2, g3))
         runs.append((dxd, dgd, dbd))
     assert all(torch.equal(a, b) for a, b in zip(*runs))     # fixed summation order
+
+
+@pytest.mark.parametrize("extremes", [False, True])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N", [(5, 40), (63, 70), (255, 17), (511, 2100), (1001, 300), (2047, 300), (4097, 20), (8191, 9)])
+def test_layernorm_backward_where_beta_is_much_larger_than_gamma(B, M, N, dt, extremes):
+    """xhat = (y - beta) / gamma: the subtraction cancels, so it has to come first.  It is exact or
+    rounded once and the quotient within two units in the last place, whatever beta / gamma is;
+    subtracting beta / gamma from y / gamma instead is off by 2^-24 |beta / gamma|, here 6e-4."""
+    rng = np.random.default_rng(M)
+    gamma = O.round_to_dtype(0.01 * (1 + 0.1 * rng.standard_normal(M)), "f32")
+    beta = O.round_to_dtype(100 * (1 + 0.1 * rng.standard_normal(M)), "f32")
+    if extremes:  # columns whose gamma has no float32 reciprocal, or one close to the end of the range
+        gamma[M // 2], beta[M // 2] = 2.0 ** -130, 0.0
+        gamma[M // 3], beta[M // 3] = 2.0 ** 100, 0.0
+    x = O.round_to_dtype(rng.standard_normal((N, M)), dt)
+    y, rstd, _ = O.layernorm_fwd(x, gamma, beta, 1e-5, dt)
+    dy = stored(rng, (N, M), dt)
+    refs = O.layernorm_bwd(dy, y, gamma, beta, rstd, dt)
+    dxd = dev(dy, dt)
+    dgd, dbd = torch.empty(M, device="cuda"), torch.empty(M, device="cuda")
+    ws = torch.empty(B.tempo_layernorm_bwd_workspace_bytes(N, M), dtype=torch.uint8, device="cuda")
+    B.tempo_layernorm_bwd(dxd, dev(y, dt), dev(gamma, "f32"), dev(beta, "f32"), dev(rstd, "f32"), dxd, dgd, dbd, ws)
+    for name, got, ref, d in zip(("dx", "dgamma", "dbeta"), (dxd, dgd, dbd), refs, (dt, "f32", "f32")):
+        assert rel_err(host(got), ref) <= TOL[d], name
