@@ -434,7 +434,11 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
       }
     }
     sum = row_reduce<LANES, false>(sum, red[1]);
-    const float rinv = (sum > 0.0f) ? __builtin_amdgcn_rcpf(sum) : 0.0f;
+    // 1 / sum by the hardware estimate; ragged rows add a Newton step, which rounds it like a division
+    // (16x16x333x333 bf16 forward + backward: 87.6 us without it, 87.7 with it)
+    float est = __builtin_amdgcn_rcpf(sum);
+    if constexpr (RAG) est = fmaf(fmaf(-sum, est, 1.0f), est, est);
+    const float rinv = (sum > 0.0f) ? est : 0.0f;
     const uint64_t group0 = static_cast<uint64_t>(base) >> 3;  // aligned rows: whole groups
     constexpr bool kFlags = !RAG && V == 8;  // keep decisions as flag words
     uint32_t bits[CH];

@@ -162,3 +162,15 @@ def test_layernorm_backward_where_beta_is_much_larger_than_gamma(B, M, N, dt, ex
     B.tempo_layernorm_bwd(dxd, dev(y, dt), dev(gamma, "f32"), dev(beta, "f32"), dev(rstd, "f32"), dxd, dgd, dbd, ws)
     for name, got, ref, d in zip(("dx", "dgamma", "dbeta"), (dxd, dgd, dbd), refs, (dt, "f32", "f32")):
         assert rel_err(host(got), ref) <= TOL[d], name
+
+
+@pytest.mark.parametrize("Sk", [31, 255, 333, 1001])
+def test_attention_probabilities_of_equal_scores_are_correctly_rounded(B, Sk):
+    """Equal scores: every exponential is 1 and the sum of a causal row's i + 1 of them exact, so P is
+    1 / (i + 1) to the last bit if the reciprocal is correctly rounded."""
+    s = torch.zeros(1, 1, Sk, Sk, device="cuda")
+    P = torch.empty_like(s)
+    md = torch.empty(B.mask_words(s.numel()), dtype=torch.int32, device="cuda")
+    B.tempo_attn_softmax_dropout_fwd(s, None, True, P, None, md, 0.1, 1, 2)
+    want = torch.tril((1.0 / torch.arange(1, Sk + 1, dtype=torch.float64)).float()[:, None].expand(Sk, Sk))
+    assert torch.equal(P[0, 0].cpu(), want)
