@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "launch_split.h"
 #include "tempo_device.h"
 #include "tempo_host.h"
 
@@ -880,7 +881,7 @@ int group_threads(int lanes, bool backward) {
 // Workgroups of the any-length kernels: one wave per row, rows beyond the cap in a loop.
 int row_grid(int64_t rows, int blocks_per_cu) {
   const int64_t want = (rows + kThreads / kWave - 1) / (kThreads / kWave);
-  const int64_t cap = static_cast<int64_t>(compute_units()) * blocks_per_cu;
+  const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * blocks_per_cu, kThreads);
   return static_cast<int>(std::max<int64_t>(1, std::min(want, cap)));
 }
 
@@ -1040,7 +1041,7 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);   \
     else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
   } while (0)
-    const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
+    const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * bpc, threads);
     for (int64_t done = 0; done < total_sets; done += cap) {
       const uint32_t first = static_cast<uint32_t>(done);
       const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));
@@ -1099,7 +1100,7 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
     if (dt == TEMPO_F32) attn_bwd_go<float, L, C>(mask, ragged, threads, lds, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);   \
     else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, lds, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
   } while (0)
-    const int64_t cap = static_cast<int64_t>(compute_units()) * bpc;
+    const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * bpc, threads);
     for (int64_t done = 0; done < total_sets; done += cap) {
       const uint32_t first = static_cast<uint32_t>(done);
       const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));

@@ -181,3 +181,24 @@ def test_attention_beyond_2_32_elements(B, Sk):
     B.tempo_attn_softmax_dropout_bwd_regen(dout, P, dS_b, None, p, seed, offset)
     torch.cuda.synchronize()
     assert all(torch.equal(dS[b, a], dS_b[b, a]) for b in range(Bn) for a in range(A))
+
+
+def test_attention_of_2_24_workgroups_of_256_lanes(B):
+    """2^32 lanes, one more than HIP takes in one launch: the call is split, and the result is that of
+    workgroups of 64 lanes."""
+    s = _normal((1 << 24) * 8, 1.0, 7).view(4096, 4096, 1, 8)      # 2^24 slices of one row
+    old = B.tempo_get_launch_param(14)
+    got = []
+    try:
+        for lanes in (256, 64):
+            B.tempo_set_launch_param(14, lanes)
+            P, out = torch.zeros_like(s), torch.zeros_like(s)
+            md = torch.zeros(B.mask_words(s.numel()), dtype=torch.int32, device="cuda")
+            B.tempo_attn_softmax_dropout_fwd(s, None, False, P, out, md, 0.1, 3, 4)
+            got.append((P, out, md))
+    finally:
+        B.tempo_set_launch_param(14, old)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    ref = torch.softmax(s[-1].float(), -1)
+    assert float((got[0][0][-1].float() - ref).abs().max()) <= 2.0 ** -8
