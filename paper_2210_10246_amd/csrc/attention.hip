@@ -1042,17 +1042,20 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
   } while (0)
     const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * bpc, threads);
-    for (int64_t done = 0; done < total_sets; done += cap) {
-      const uint32_t first = static_cast<uint32_t>(done);
-      const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));
-      if (sh.lanes > kWave) {
-        TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
-      } else {
-        TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
-      }
-    }
+    tempo_status status = TEMPO_OK;
+    split_launch(total_sets, cap, [&](uint32_t first, uint32_t sets) {
+      status = [&]() -> tempo_status {
+        if (sh.lanes > kWave) {
+          TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
+        } else {
+          TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+        }
+        return launch_status();
+      }();
+      return status == TEMPO_OK;
+    });
 #undef TEMPO_LAUNCH
-    return launch_status();
+    return status;
   }
   const int grid = row_grid(rows, bpc);
   if (dt == TEMPO_F32)
@@ -1101,17 +1104,20 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
     else attn_bwd_go<bf16_t, L, C>(mask, ragged, threads, lds, first, sets, st, dout, probs, keep_bits, dscores, out_re, rows, Sk, scale, rng);                  \
   } while (0)
     const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * bpc, threads);
-    for (int64_t done = 0; done < total_sets; done += cap) {
-      const uint32_t first = static_cast<uint32_t>(done);
-      const uint32_t sets = static_cast<uint32_t>(std::min(cap, total_sets - done));
-      if (sh.lanes > kWave) {
-        TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
-      } else {
-        TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
-      }
-    }
+    tempo_status status = TEMPO_OK;
+    split_launch(total_sets, cap, [&](uint32_t first, uint32_t sets) {
+      status = [&]() -> tempo_status {
+        if (sh.lanes > kWave) {
+          TEMPO_ATTN_WIDE_DISPATCH(TEMPO_LAUNCH)
+        } else {
+          TEMPO_ATTN_DISPATCH(TEMPO_LAUNCH)
+        }
+        return launch_status();
+      }();
+      return status == TEMPO_OK;
+    });
 #undef TEMPO_LAUNCH
-    return launch_status();
+    return status;
   }
   const int grid = row_grid(rows, bpc);
   auto go = [&](auto tag, auto m) {

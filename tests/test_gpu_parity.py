@@ -596,6 +596,49 @@ def test_mask_does_not_depend_on_launch_shape(B):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Bn,A,Sq,Sk", [(3, 7, 601, 64), (3, 7, 601, 61), (2, 3, 131, 1024), (2, 3, 131, 1001)])
+def test_attn_split_into_several_launches(B, Bn, A, Sq, Sk, dt):
+    """Knobs 4 and 5 at one workgroup per compute unit split a call into four launches or more, the last
+    one partly filled (on 256 units); nothing in the result depends on it."""
+    rng = np.random.default_rng(Sk)
+    s = stored(rng, (Bn, A, Sq, Sk), dt, 0.5)
+    sd, dod = dev(s, dt), dev(stored(rng, s.shape, dt), dt)
+    kd = torch.from_numpy(np.array([Sk, Sk * 2 // 3, 5])[:Bn].astype(np.int32)).cuda()
+    results = []
+    old = [B.tempo_get_launch_param(k) for k in (4, 5)]
+    try:
+        for caps in (old, (1, 1)):
+            for k, cap in zip((4, 5), caps):
+                B.tempo_set_launch_param(k, cap)
+            r = []
+            for key_len, causal in ((kd, False), (None, True)):
+                Pd, od = torch.full_like(sd, 3.0), torch.full_like(sd, 3.0)
+                md = torch.full((B.mask_words(s.size),), -1, dtype=torch.int32, device="cuda")
+                B.tempo_attn_softmax_dropout_fwd(sd, key_len, causal, Pd, od, md, 0.1, 42, 7)
+                r += [Pd, od, md]
+            kept = torch.empty(s.size, dtype=torch.uint8, device="cuda")
+            B.tempo_mask_bits_to_bytes(md, kept, s.size)
+            for source in ("bits", "regen", "bytes"):
+                dsd, ord_ = torch.full_like(dod, 3.0), torch.full_like(dod, 3.0)
+                if source == "bits":
+                    B.tempo_attn_softmax_dropout_bwd(dod, Pd, md, dsd, ord_, 0.1)
+                elif source == "regen":
+                    B.tempo_attn_softmax_dropout_bwd_regen(dod, Pd, dsd, ord_, 0.1, 42, 7)
+                else:
+                    B.tempo_attn_softmax_dropout_bwd_bytemask(dod, Pd, kept, dsd, ord_, 0.1)
+                r += [dsd, ord_]
+            results.append(r)
+    finally:
+        for k, v in zip((4, 5), old):
+            B.tempo_set_launch_param(k, v)
+    for i, (a, b) in enumerate(zip(*results)):
+        assert torch.equal(a, b), i
+    assert np.array_equal(words(results[0][2]), O.pack_bits(O.dropout_keep(s.size, np.float32(0.1), 42, 7)))
+    ds = results[1][6:]
+    assert torch.equal(ds[0], ds[2]) and torch.equal(ds[0], ds[4])
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_attn_row_over_one_or_several_waves(B, dt):
     """Long rows: the same result whether one wave or 2-4 waves own a row (knob 8); the second
     lane group of the last row set has no row when Sq is odd."""

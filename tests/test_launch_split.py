@@ -39,3 +39,17 @@ def test_the_attention_launches_are_bounded_by_it():
         text = f.read()
     caps = re.findall(r"const int64_t cap = ([^;]*);", text)
     assert [("most_groups(" in c) for c in caps if "bpc" in c or "blocks_per_cu" in c] == [True] * 3
+
+
+@pytest.mark.parametrize("total,cap", [(1, 1), (7, 3), (9, 3), (256, 257), (257, 256), ((1 << 32) - 1, (1 << 24) - 1)])
+def test_split_covers_every_workgroup_once(program, total, cap):
+    *pairs, ok = program("split", total, cap, 1 << 40)
+    firsts, counts = pairs[::2], pairs[1::2]
+    assert ok == 1
+    assert firsts == [sum(counts[:i]) for i in range(len(counts))]
+    assert sum(counts) == total and 0 < min(counts) and max(counts) <= cap
+
+
+def test_split_ends_at_the_first_refused_launch(program):
+    assert program("split", 10, 4, 4) == [0, 4, 4, 4, 0]
+    assert program("split", 10, 4, 0) == [0, 4, 0]
