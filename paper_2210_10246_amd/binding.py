@@ -3,7 +3,7 @@
 The calls go through _native.so (csrc/binding.cpp), which makes the checks below in native code and
 calls the C ABI on the current stream.  Whatever it does not take (an explicit stream, an argument
 that one of the checks refuses or that is no plain tensor) goes through the ctypes path here, which
-raises.
+raises; so does every call if _native.so cannot be loaded, at 8-10 us of Python each.
 
 Tensors are torch CUDA tensors (PyTorch supplies device memory and the stream; every step
 of the layers runs in the HIP kernels).  Outputs are written into tensors the caller passes.
@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -59,7 +60,7 @@ _SIGNATURES = {
 }
 
 _lib = None
-_native = None  # the module _native.so, once load() has run
+_native = None  # the module _native.so, once load() has run and found it
 
 
 class TempoError(RuntimeError):
@@ -69,7 +70,7 @@ class TempoError(RuntimeError):
 
 
 def load() -> ctypes.CDLL:
-    """Load libtempo.so and _native.so (built in-tree by build.py); raises if one is missing."""
+    """Load libtempo.so (built in-tree by build.py), raising if it is missing, and _native.so."""
     global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
@@ -80,8 +81,12 @@ def load() -> ctypes.CDLL:
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
-        from . import _native as native
-        _native = native
+        try:
+            from . import _native as native
+            _native = native
+        except ImportError as e:  # not built, or for another torch
+            warnings.warn(f"_native.so: {e}; calls go through ctypes, which is slower: build it with "
+                          "`python -m paper_2210_10246_amd.build`", RuntimeWarning)
         _lib = lib
     return _lib
 

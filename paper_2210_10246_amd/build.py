@@ -30,20 +30,31 @@ def _compile(src: str, obj_dir: str) -> str:
     return obj
 
 
-def _build_native() -> None:
-    """binding.cpp: host code against torch's headers; finds libtempo.so beside itself."""
+def _build_native() -> bool:
+    """binding.cpp: host code against torch's headers; finds libtempo.so beside itself.  Needs a host
+    compiler and Python's headers, which libtempo.so does not: without them there is no _native.so, not
+    even an older one, and the binding makes its calls through ctypes."""
     import torch
     root = os.path.dirname(torch.__file__)
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-isystem", os.path.join(root, "include"), "-isystem", "/opt/rocm/include",
            "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "binding.cpp"), "-o", NATIVE_PATH, LIB_PATH, "-Wl,-rpath,$ORIGIN",
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"g++ failed on binding.cpp:\n{r.stderr[-6000:]}")
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        failed, said = r.returncode != 0, r.stderr
+    except OSError as e:
+        failed, said = True, str(e)
+    if said:
+        print(f"binding.cpp:\n{said[-6000:]}", file=sys.stderr)
+    if failed:
+        if os.path.exists(NATIVE_PATH):
+            os.remove(NATIVE_PATH)
+        print("_native.so was not built: the Python binding makes its calls through ctypes", file=sys.stderr)
+    return not failed
 
 
 def build_library(verbose: bool = True) -> str:

@@ -1,6 +1,11 @@
 """Host-side checks of the Python binding and the modules that need no GPU: the binding refuses
 tensors whose dtype or size the C ABI would misread, before anything reaches the device, and
 the LayerNorm module keeps its parameters in float32 whatever the model is cast to."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -67,3 +72,40 @@ def test_layernorm_module_keeps_float32_parameters_under_casts():
     assert layer.ln1.weight.dtype == torch.float32
     ln = InplaceLayerNorm(8).double()
     assert ln.weight.dtype == torch.float32
+
+
+def test_binding_works_without_its_native_half(tmp_path):
+    """libtempo.so alone is enough: the calls go through ctypes, with a warning that says what to build."""
+    here = os.path.dirname(os.path.abspath(B.__file__))
+    package = tmp_path / "paper_2210_10246_amd"
+    shutil.copytree(here, package, ignore=shutil.ignore_patterns("*.so", "_build", "csrc", "__pycache__"))
+    os.symlink(B.LIB_PATH, package / "libtempo.so")
+    code = """
+import warnings
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2210_10246_amd import binding as B
+    lib = B.load()
+assert B.load() is lib and B._native is None
+assert [w.category for w in seen] == [RuntimeWarning] and "paper_2210_10246_amd.build" in str(seen[0].message)
+assert B.tempo_layernorm_bwd_workspace_bytes(8, 64) > 0
+import torch
+x = torch.zeros(64)
+try:
+    B.tempo_gelu_fwd(x, x, torch.zeros(2, dtype=torch.int32))
+except ValueError as e:
+    assert "contiguous CUDA" in str(e)
+else:
+    raise AssertionError("a CPU tensor was taken")
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=tmp_path, timeout=300)
+
+
+def test_build_without_a_host_compiler_leaves_no_old_native_half(tmp_path, monkeypatch, capsys):
+    from paper_2210_10246_amd import build
+    old = tmp_path / "_native.so"
+    old.write_text("of an earlier build")
+    monkeypatch.setattr(build, "NATIVE_PATH", str(old))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    assert build._build_native() is False
+    assert not old.exists() and "ctypes" in capsys.readouterr().err
