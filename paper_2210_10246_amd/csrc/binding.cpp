@@ -48,6 +48,10 @@ uint32_t* mask_words(PyObject* o, int64_t n) {
 
 float real(PyObject* o) {
   if (PyFloat_Check(o)) return static_cast<float>(PyFloat_AS_DOUBLE(o));
+  if (PyLong_CheckExact(o)) {
+    const double v = PyLong_AsDouble(o);
+    if (!PyErr_Occurred()) return static_cast<float>(v);
+  }
   throw NotPlain{};
 }
 uint64_t bits64(PyObject* o) {
