@@ -756,11 +756,12 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_generic_kernel(
 
 constexpr int kMaxPieces = 1024;  // 4 per lane of 4 waves
 
-// Shapes of the ragged rows (row_shape never takes others, whatever the knobs say), in workgroups of
-// two waves (of the row's four where it takes four).
+// Shapes of the ragged rows (no others are taken, whatever the knobs say: ragged_shapes_exist()), in
+// workgroups of two waves (of the row's four where it takes four).  vec: elements per piece.
 constexpr int kRaggedMaxPieces = 4;
-constexpr bool is_ragged_shape(int lanes, int ch) {
-  return ch <= kRaggedMaxPieces && !(lanes == 2 * kWave && ch == 2);
+constexpr bool is_ragged_shape(int lanes, int ch, int vec, bool backward) {
+  if (lanes == 2 * kWave) return ch == 1 && vec == 4;
+  return ch <= (backward && lanes == kWave ? 3 : kRaggedMaxPieces);
 }
 
 // Fewest lanes a workgroup may have: a row's, and two rows' where a forward row takes two waves
@@ -780,11 +781,11 @@ struct Shape {
 // One piece per lane while the row fits in a wave (every access of a wave is then one
 // contiguous run of 16-byte pieces), more pieces per lane for longer rows.  min_lanes: 4 for
 // bfloat16, 8 for float32 (the lanes that share a mask word).  ch == 0: row too long.
-Shape pick_shape(int pieces, int min_lanes) {
+constexpr Shape pick_shape(int pieces, int min_lanes) {
   int lanes = min_lanes;
   while (lanes < 64 && lanes < pieces) lanes <<= 1;
   const int need = (pieces + lanes - 1) / lanes;
-  static const int allowed[] = {1, 2, 3, 4, 6, 8, 12, 16};
+  constexpr int allowed[] = {1, 2, 3, 4, 6, 8, 12, 16};
   for (int a : allowed)
     if (a >= need) return {lanes, lanes == 64 || a == 1 ? a : 0};
   return {0, 0};
@@ -792,7 +793,7 @@ Shape pick_shape(int pieces, int min_lanes) {
 
 // A row whose pieces per lane on one wave would exceed max_ch is spread over 2 or 4 waves (at
 // most 4 pieces per lane there).
-Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
+constexpr Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
   const Shape one = pick_shape(pieces, min_lanes);
   if (one.lanes == kWave && (one.ch == 0 || one.ch > max_ch)) {
     for (int lanes = 2 * kWave; lanes <= kThreads; lanes *= 2) {
@@ -815,11 +816,7 @@ Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
 // lanes it loses (640 bf16 columns forward: 45 -> 53).  Ragged rows gain more (1001 f32: 363 -> 304
 // both ways), but two waves of bfloat16 lose 5 % (901 columns: 143 -> 151).  Several short rows per
 // wave with three pieces per lane lose a third wherever rows are not whole 128-byte lines.
-Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
-  const bool ragged = Sk % 8 != 0;
-  const int64_t pieces = (Sk + vec - 1) / vec;
-  if (pieces > kMaxPieces) return {0, 0};
-  const int p = static_cast<int>(pieces);
+constexpr Shape shape_of(int p, bool ragged, int vec, int max_ch, bool backward) {
   if (ragged || max_ch <= kRaggedMaxPieces) {
     const int wide = p <= 2 * kWave ? 2 * kWave : kThreads;
     const bool two_ragged_bf16 = ragged && vec == 8 && wide == 2 * kWave;
@@ -829,6 +826,20 @@ Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
   }
   return pick_wide_shape(p, 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
 }
+Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
+  const int64_t pieces = (Sk + vec - 1) / vec;
+  if (pieces > kMaxPieces) return {0, 0};
+  return shape_of(static_cast<int>(pieces), Sk % 8 != 0, vec, max_ch, backward);
+}
+constexpr bool ragged_shapes_exist(int vec, bool backward) {
+  for (int p = 1; p <= kMaxPieces; ++p) {
+    const Shape sh = shape_of(p, true, vec, 1, backward);
+    if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, backward)) return false;
+  }
+  return true;
+}
+static_assert(ragged_shapes_exist(4, false) && ragged_shapes_exist(4, true), "float32");
+static_assert(ragged_shapes_exist(8, false) && ragged_shapes_exist(8, true), "bfloat16");
 
 // Dynamic LDS that no kernel reads: it keeps the workgroups that are resident on a compute unit to
 // those that move about kFlightPieces pieces of each tensor at once.  The backward streams two
@@ -962,7 +973,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint
       return go(integral_constant<int, 2>{}, bytes);
     }
   }
-  if constexpr (is_ragged_shape(L, C)) {
+  if constexpr (is_ragged_shape(L, C, Store<T>::kVec, false)) {
     if (layout == kRagged) return go(integral_constant<int, 1>{}, integral_constant<MaskLayout, kRagged>{});
   }
   if (layout == kWords) return go(integral_constant<int, 1>{}, words);
@@ -986,7 +997,7 @@ static void attn_bwd_go(MaskSource mask, bool ragged, int threads, size_t lds, u
   const integral_constant<MaskSource, kMaskBytes> bytes{};
   const integral_constant<MaskSource, kMaskBools> bools{};
   const integral_constant<MaskSource, kMaskRegen> regen{};
-  if constexpr (is_ragged_shape(L, C)) {
+  if constexpr (is_ragged_shape(L, C, Store<T>::kVec, true)) {
     if (ragged) {
       if (mask == kMaskBytes) return go(bytes, std::true_type{});
       if (mask == kMaskBools) return go(bools, std::true_type{});

@@ -197,8 +197,9 @@ __device__ __forceinline__ float block_sum_256(float v, float* lds) {
   return (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
-// Any M: one workgroup per row, scalar accesses.  KC > 0: rows of at most 256 * KC columns, held in
-// registers and read once.  KC == 0: any length, x re-read from cache for each pass.
+// Any M (fewer columns than a piece, or more than the register-resident kernels hold): one workgroup per
+// row, scalar accesses.  KC > 0: rows of at most 256 * KC columns, held in registers and read once.
+// KC == 0: any length, x re-read from cache for each pass.
 template <typename T, int KC>
 __global__ __launch_bounds__(256) void ln_fwd_generic_kernel(
     const T* x, const float* __restrict__ gamma, const float* __restrict__ beta, T* y,
@@ -789,9 +790,9 @@ struct Shape {
 // whole wave per row counts as unpadded while at most a third of its lanes' pieces are
 // padding; one row per wave lets a lane group fetch up to 4 rows at once, which there is
 // worth more than the idle lanes (measured at 384 and 768 columns; the forward loses by it).
-Shape pick_shape(int pieces, bool full_wave) {
-  static const int wide[] = {1, 2, 3, 4, 6, 8, 12, 16};  // 64 lanes
-  static const int narrow[] = {1, 2, 3};                 // 32 and 16 lanes
+constexpr Shape pick_shape(int pieces, bool full_wave) {
+  constexpr int wide[] = {1, 2, 3, 4, 6, 8, 12, 16};  // 64 lanes
+  constexpr int narrow[] = {1, 2, 3};                 // 32 and 16 lanes
   Shape best = {0, 0};
   int best_waste = 1 << 30;
   for (int lanes = 64; lanes >= 16; lanes >>= 1) {
@@ -815,7 +816,7 @@ Shape pick_shape(int pieces, bool full_wave) {
 
 // A row whose pieces per lane on one wave would exceed max_ch is spread over 2 or 4 waves (at
 // most 4 pieces per lane there).
-Shape widen_shape(Shape one, int pieces, int max_ch, int max_lanes) {
+constexpr Shape widen_shape(Shape one, int pieces, int max_ch, int max_lanes) {
   if (one.ch == 0 || (one.lanes == kWave && one.ch > max_ch)) {  // no one-wave shape, or too many pieces
     for (int lanes = 2 * kWave; lanes <= max_lanes; lanes *= 2) {
       const int need = (pieces + lanes - 1) / lanes;
@@ -869,17 +870,36 @@ constexpr int max_rows() {
   return L > 64 ? 1 : ((C <= 2 && L == 64) ? 4 : (C <= 4 ? 2 : 1));
 }
 
-// Shapes that ragged rows are dispatched to: those that the default knobs lead to.
+// Most pieces a row may have in the register-resident kernels.
+constexpr int max_fast_pieces(int vec) { return vec == 4 ? kMaxFastPiecesF32 : kMaxFastPieces; }
+// Shape for rows of `pieces` pieces of vec elements; ch == 0: too long.
+// Backward: four waves whose lanes would own more than 24 columns each (parameters in LDS, read twice per
+// element) give the row to all eight waves, which halves the columns per lane and keeps the parameters
+// in registers.
+constexpr Shape shape_of(int pieces, int vec, int max_ch, bool backward) {
+  const Shape sh = widen_shape(pick_shape(pieces, backward), pieces, max_ch, 256);
+  return backward && sh.lanes == 256 && sh.ch * vec > 24 ? Shape{kBwdThreads, sh.ch / 2} : sh;
+}
+
+// Shapes that ragged rows are dispatched to (no others: ragged_shapes_exist()).
 constexpr int kRaggedFwdMaxPieces = 4;
 constexpr int kRaggedBwdMaxPieces = 3;
-template <typename T>
-constexpr bool is_ragged_shape(bool backward, int lanes, int ch) {
-  constexpr bool f32 = std::is_same<T, float>::value;
-  const int most = backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces;
-  if (lanes <= kWave) return ch <= most;
-  if (lanes <= 256) return ch <= most || (f32 && (backward ? ch <= 6 : ch <= 8));
-  return backward;
+constexpr bool is_ragged_shape(int lanes, int ch, int vec, bool backward) {
+  if (lanes < kWave) return ch != 2;
+  if (lanes == kWave) return ch <= (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces);
+  if (lanes > 256) return backward;
+  return backward ? ch == 2 || ch == 3 || (lanes == 256 && vec == 4 && ch <= 6 && ch >= 4)
+                  : ch == 3 || ch == 4 || (lanes == 256 && vec == 4 && ch > 4);
 }
+constexpr bool ragged_shapes_exist(int vec, bool backward) {
+  for (int p = 2; p <= max_fast_pieces(vec); ++p) {
+    const Shape sh = shape_of(p, vec, backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces, backward);
+    if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, backward)) return false;
+  }
+  return true;
+}
+static_assert(ragged_shapes_exist(4, false) && ragged_shapes_exist(4, true), "float32");
+static_assert(ragged_shapes_exist(8, false) && ragged_shapes_exist(8, true), "bfloat16");
 
 template <typename T, int L, int C>
 static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, const void* x, const float* gamma,
@@ -895,7 +915,7 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
                          static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps);
     };
     auto go = [&](auto rows, auto lp) {
-      if constexpr (is_ragged_shape<T>(false, L, C)) {
+      if constexpr (is_ragged_shape(L, C, Store<T>::kVec, false)) {
         if (ragged) return launch(rows, lp, std::true_type{});
       }
       launch(rows, lp, std::false_type{});
@@ -922,17 +942,12 @@ static bool is_ragged(int64_t M, tempo_dtype dt) { return M % (dt == TEMPO_F32 ?
 
 static bool fast_shape(int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   const int vec = dt == TEMPO_F32 ? 4 : 8;
-  if (M < vec || (M + vec - 1) / vec > (dt == TEMPO_F32 ? kMaxFastPiecesF32 : kMaxFastPieces))
-    return false;
+  if (M < vec || (M + vec - 1) / vec > max_fast_pieces(vec)) return false;
   const int pieces = static_cast<int>((M + vec - 1) / vec);
   const bool ragged = is_ragged(M, dt);
   const int max_ch = ragged ? (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces)
                             : tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces);
-  *sh = widen_shape(pick_shape(pieces, backward), pieces, max_ch, 256);
-  // Backward: four waves whose lanes would own more than 24 columns each (parameters in LDS,
-  // read twice per element) give the row to all eight waves, which halves the columns per lane
-  // and keeps the parameters in registers.
-  if (backward && sh->lanes == 256 && sh->ch * vec > 24) *sh = {kBwdThreads, sh->ch / 2};
+  *sh = shape_of(pieces, vec, max_ch, backward);
   return sh->ch != 0;
 }
 
@@ -987,9 +1002,8 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
                          st, static_cast<const T*>(x), gamma, beta, static_cast<T*>(y), rstd, mean, N,
                          M, eps);
     };
-    auto by_length = [&](auto tag) {  // columns per thread held in registers: 8, 20, or none
-      if (M <= 256 * 8) go(tag, std::integral_constant<int, 8>{});
-      else if (M <= 256 * 20) go(tag, std::integral_constant<int, 20>{});
+    auto by_length = [&](auto tag) {  // columns per thread held in registers: 1 (short rows) or none
+      if (M <= 256) go(tag, std::integral_constant<int, 1>{});
       else go(tag, std::integral_constant<int, 0>{});
     };
     if (dt == TEMPO_F32) by_length(float{});
@@ -1090,7 +1104,7 @@ static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStre
                          static_cast<T*>(dx), workspace, N, static_cast<int>(M));
     };
     auto go = [&](auto rows, auto loop) {
-      if constexpr (is_ragged_shape<T>(true, L, C)) {
+      if constexpr (is_ragged_shape(L, C, Store<T>::kVec, true)) {
         if (ragged) return launch(rows, loop, std::true_type{});
       }
       launch(rows, loop, std::false_type{});
@@ -1178,9 +1192,8 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
                          st, static_cast<const T*>(dy), static_cast<const T*>(y), gamma, beta, rstd,
                          static_cast<T*>(dx), workspace, N, M);
     };
-    auto by_length = [&](auto tag) {  // columns per thread held in registers: 8, 20, or none
-      if (M <= 256 * 8) go(tag, std::integral_constant<int, 8>{});
-      else if (M <= 256 * 20) go(tag, std::integral_constant<int, 20>{});
+    auto by_length = [&](auto tag) {  // columns per thread held in registers: 1 (short rows) or none
+      if (M <= 256) go(tag, std::integral_constant<int, 1>{});
       else go(tag, std::integral_constant<int, 0>{});
     };
     if (dt == TEMPO_F32) by_length(float{});
