@@ -87,10 +87,11 @@ def _sample_rows(rng, rows, row_len, extra=()):
     return np.unique(pick[(pick >= 0) & (pick < rows)])
 
 
-@pytest.mark.parametrize("M", [4096, 4100])       # register-resident rows / the any-length kernels
+# register-resident rows, those at any element's address, the any-length kernels
+@pytest.mark.parametrize("M", [4096, 4100, 8200])
 def test_layernorm_beyond_2_32_elements(B, M):
     dt = "bf16"
-    N = (1 << 20) + 3
+    N = (1 << (20 if M < 8192 else 19)) + 3
     assert N * M > 1 << 32
     x = _normal(N * M, 1.0, 3).view(N, M)
     rng = np.random.default_rng(3)
@@ -129,10 +130,11 @@ def test_layernorm_beyond_2_32_elements(B, M):
     assert rel_err(W.as_f64(db), W.as_f64(db64)) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("Sk", [4128, 4100])      # register-resident rows / the any-length kernels
+# register-resident rows, those at any element's address, the any-length kernels
+@pytest.mark.parametrize("Sk", [4128, 4100, 8200])
 def test_attention_beyond_2_32_elements(B, Sk):
     dt = "bf16"
-    Bn, A, Sq = 2, 16, 32768
+    Bn, A, Sq = 2, 16, 32768 if Sk < 8192 else 16384
     rows, n = Bn * A * Sq, Bn * A * Sq * Sk
     assert n > 1 << 32
     p, seed, offset = 0.1, 0x5EED0000FEEDBEEF, (1 << 40) + 3

@@ -210,10 +210,12 @@ def test_gelu_round_trip_against_input_based_gradient(B, dt, kind):
 LN_SHAPES = [(256, 768), (5, 1024), (37, 768), (3, 8), (9, 64), (7, 100), (4, 4096), (3, 2048),
              (2, 4104), (1, 1), (6, 1536), (300, 1024), (3, 3072), (1030, 256),
              # beyond 4096 columns: register-resident up to 8192 (float32 with 6 or 8 pieces per
-             # lane), the any-shape kernels beyond and for rows that are not whole pieces
+             # lane), the any-shape kernels beyond
              (5, 8192), (70, 6144), (300, 5120), (2, 8200), (3, 8190), (600, 7168),
-             # any-shape backward: column sums in registers (up to 2048 and up to 5120 columns) / in memory
-             (1500, 1001), (2000, 4100), (3, 9300)]
+             # rows that are not whole pieces, and the any-shape kernels with more rows than one
+             (1500, 1001), (2000, 4100), (3, 9300),
+             # the any-shape kernels: rows shorter than a piece, more rows than workgroups
+             (2500, 3), (1100, 8200)]
 
 
 @pytest.mark.parametrize("eps", [1e-12, 1e-5])
@@ -404,12 +406,16 @@ ATTN_CASES = [
     (2, 1, 5, 1544, "padding", 0.1),   # long row ending inside a mask word
     (2, 2, 64, 160, "padding", 0.0),   # p = 0: everything kept
     (1, 1, 70, 1, "none", 0.1),
-    # rows of any length held in registers by one wave (4, 16 or 32 chunks of 64 elements), the
-    # keep bits of 448 elements drawn together; and the any-length kernels beyond 2048
+    # rows of any length held in registers, their keep bytes drawn into LDS
     (1, 1, 70, 449, "none", 0.3),
     (2, 1, 5, 1001, "causal", 0.1),
     (1, 2, 3, 1543, "padding", 0.1),
     (1, 1, 3, 2055, "none", 0.1),
+    # the any-length kernels (beyond 4096 keys in float32, 8192 in bfloat16), which draw the keep bits of
+    # 448 elements together
+    (1, 2, 3, 8200, "causal", 0.1),
+    (2, 1, 3, 8193, "padding", 0.1),
+    (1, 1, 2, 9001, "none", 0.3),
 ]
 
 
@@ -639,17 +645,22 @@ def test_attn_split_into_several_launches(B, Bn, A, Sq, Sk, dt):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-def test_attn_row_over_one_or_several_waves(B, dt):
+# in 16-byte pieces: the default shape is whole waves of one piece at 256 and (bf16) 128; the knob leads to
+# one, two and four waves of one to four pieces a lane at 150 and 200, to two waves of three pieces at 352 (knob
+# at 5) and of four at 500 (knob at 6)
+@pytest.mark.parametrize("pieces", [None, 150, 200, 352, 500])
+def test_attn_row_over_one_or_several_waves(B, dt, pieces):
     """Long rows: the same result whether one wave or 2-4 waves own a row (knob 8); the second
     lane group of the last row set has no row when Sq is odd."""
     rng = np.random.default_rng(8)
-    s = stored(rng, (1, 2, 5, 1024), dt, 0.125)
-    key_len = np.array([1000], dtype=np.int32)
+    Sk = 1024 if pieces is None else pieces * (4 if dt == "f32" else 8)
+    s = stored(rng, (1, 2, 5, Sk), dt, 0.125)
+    key_len = np.array([Sk - 24], dtype=np.int32)
     P_ref, out_ref, K_ref = O.attn_softmax_dropout_fwd(s, key_len, False, np.float32(0.1), 3, 4, dt)
     sd, kd = dev(s, dt), torch.from_numpy(key_len).cuda()
     old = B.tempo_get_launch_param(8)
     try:
-        for max_pieces in (1, 2, 4, 16):
+        for max_pieces in (1, 2, 4, 5, 6, 16):
             B.tempo_set_launch_param(8, max_pieces)
             Pd, od = torch.full_like(sd, 3.0), torch.full_like(sd, 3.0)
             md = torch.full((B.mask_words(s.size),), -1, dtype=torch.int32, device="cuda")
@@ -667,7 +678,7 @@ def test_attn_row_over_one_or_several_waves(B, dt):
     md = torch.from_numpy(O.pack_bits(K_ref).view(np.int32)).cuda()
     old = B.tempo_get_launch_param(9)
     try:
-        for max_pieces in (1, 2, 4, 16):
+        for max_pieces in (1, 2, 4, 5, 6, 16):
             B.tempo_set_launch_param(9, max_pieces)
             for regen in (False, True):
                 dsd, ord_ = torch.full_like(dod, 3.0), torch.full_like(dod, 3.0)
