@@ -816,30 +816,37 @@ constexpr Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
 // lanes it loses (640 bf16 columns forward: 45 -> 53).  Ragged rows gain more (1001 f32: 363 -> 304
 // both ways), but two waves of bfloat16 lose 5 % (901 columns: 143 -> 151).  Several short rows per
 // wave with three pieces per lane lose a third wherever rows are not whole 128-byte lines.
-constexpr Shape shape_of(int p, bool ragged, int vec, int max_ch, bool backward) {
+// A causal forward (rows of whole groups) takes half the waves with two pieces per lane, since a lane skips
+// only pieces of its own that are masked.  One piece / two pieces, us: bf16 2x12x1792x1792 83.5 / 70,
+// 12x2048x2048 50 / 47, 5x16x896x896 66 / 61; f32 9x16x448x448 55.6 / 53.4, 2x16x1024x1024 61.3 / 60.6.
+// The backward has one shape whatever its mask comes from: the same sums in the same order.
+enum RowUse { kForward, kForwardCausal, kBackward };
+constexpr Shape shape_of(int p, bool ragged, int vec, int max_ch, RowUse use) {
+  const bool backward = use == kBackward;
   if (ragged || max_ch <= kRaggedMaxPieces) {
     const int wide = p <= 2 * kWave ? 2 * kWave : kThreads;
     const bool two_ragged_bf16 = ragged && vec == 8 && wide == 2 * kWave;
     if (p > kWave && p <= kThreads && p * 8 >= wide * (backward ? 6 : 7) && !two_ragged_bf16)
-      return {wide, 1};
+      return use == kForwardCausal && !ragged && max_ch >= 2 ? Shape{wide / 2, 2} : Shape{wide, 1};
     if (p > kThreads) return {kThreads, (p + kThreads - 1) / kThreads};
   }
   return pick_wide_shape(p, 32 / vec, ragged ? kRaggedMaxPieces : max_ch);
 }
-Shape row_shape(int64_t Sk, int vec, int max_ch, bool backward) {
+Shape row_shape(int64_t Sk, int vec, int max_ch, RowUse use) {
   const int64_t pieces = (Sk + vec - 1) / vec;
   if (pieces > kMaxPieces) return {0, 0};
-  return shape_of(static_cast<int>(pieces), Sk % 8 != 0, vec, max_ch, backward);
+  return shape_of(static_cast<int>(pieces), Sk % 8 != 0, vec, max_ch, use);
 }
-constexpr bool ragged_shapes_exist(int vec, bool backward) {
+constexpr bool ragged_shapes_exist(int vec) {
   for (int p = 1; p <= kMaxPieces; ++p) {
-    const Shape sh = shape_of(p, true, vec, 1, backward);
-    if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, backward)) return false;
+    for (RowUse use : {kForward, kForwardCausal, kBackward}) {
+      const Shape sh = shape_of(p, true, vec, 1, use);
+      if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, use == kBackward)) return false;
+    }
   }
   return true;
 }
-static_assert(ragged_shapes_exist(4, false) && ragged_shapes_exist(4, true), "float32");
-static_assert(ragged_shapes_exist(8, false) && ragged_shapes_exist(8, true), "bfloat16");
+static_assert(ragged_shapes_exist(4) && ragged_shapes_exist(8), "float32 and bfloat16");
 
 // Dynamic LDS that no kernel reads: it keeps the workgroups that are resident on a compute unit to
 // those that move about kFlightPieces pieces of each tensor at once.  The backward streams two
@@ -1033,7 +1040,7 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
   const int bpc = tune_get(kTuneAttnFwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   const bool ragged = Sk % 8 != 0;
-  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnFwdMaxPieces), false);
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnFwdMaxPieces), causal ? kForwardCausal : kForward);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int slices = static_cast<int>(B * A);
     const int rr = sh.lanes > kWave || ragged
@@ -1101,7 +1108,7 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
   const int bpc = tune_get(kTuneAttnBwdBlocksPerCu);
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   const bool ragged = Sk % 8 != 0;
-  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces), true);
+  const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces), kBackward);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int threads =
         ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);

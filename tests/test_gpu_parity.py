@@ -411,6 +411,14 @@ ATTN_CASES = [
     (2, 1, 5, 1001, "causal", 0.1),
     (1, 2, 3, 1543, "padding", 0.1),
     (1, 1, 3, 2055, "none", 0.1),
+    # the edges of the shapes of a causal forward, which takes half the waves (in 16-byte pieces: 113, 225, 226,
+    # 257, 258), and of longer rows
+    (1, 1, 40, 904, "causal", 0.1),
+    (1, 2, 20, 1800, "causal", 0.1),
+    (1, 1, 19, 1032, "causal", 0.1),
+    (1, 1, 5, 2056, "none", 0.1),
+    (2, 1, 3, 1536, "padding", 0.1),
+    (1, 1, 3, 3080, "causal", 0.1),
     # the any-length kernels (beyond 4096 keys in float32, 8192 in bfloat16), which draw the keep bits of
     # 448 elements together
     (1, 2, 3, 8200, "causal", 0.1),
