@@ -848,31 +848,46 @@ constexpr bool ragged_shapes_exist(int vec) {
 }
 static_assert(ragged_shapes_exist(4) && ragged_shapes_exist(8), "float32 and bfloat16");
 
-// Dynamic LDS that no kernel reads: it keeps the workgroups that are resident on a compute unit to
-// those that move about kFlightPieces pieces of each tensor at once.  The backward streams two
-// tensors in and two out, and the more waves have loads under way beyond that, the worse the memory
-// system does: at 32 and at 18-20 resident waves of one piece per lane, us: 8x12x1024x1024 bf16 129
-// and 124; 16x16x512x512 bf16 89 and 86; 64x16x512x512 f32 703 and 691; 2 pieces per lane, 32 and 12
-// waves: 16x4096x4096 bf16 378 and 347; 16x2048x2048 f32 189 and 173.  Fewer than 12 waves lose again.
-// Rows that leave a third of the lanes idle move less per wave and stay unlimited.
-constexpr int kFlightPieces = 18 * kWave;
+// Dynamic LDS that no kernel reads: it keeps the waves that are resident on a compute unit to `waves`
+// (rounded up to whole workgroups; 0 and 26 or more: as many as fit, which is as good).
 constexpr int kLdsPerCu = 160 * 1024;
-size_t flight_lds_bytes(const Shape& sh, int pieces, int threads, int least_waves) {
-  const int pieces_per_wave = std::max(1, pieces * kWave / sh.lanes);
-  const int waves = std::max(least_waves, (kFlightPieces + pieces_per_wave - 1) / pieces_per_wave);
+size_t residency_lds_bytes(int waves, int threads) {
   const int groups = (waves + threads / kWave - 1) / (threads / kWave);
-  if (groups > 12 || waves >= 26) return 0;      // as good as all that fit
+  if (waves == 0 || waves >= 26 || groups > 12) return 0;
   return kLdsPerCu / groups / 256 * 256 - 1280;  // less the static LDS; one more would not fit
 }
+int pieces_per_wave(const Shape& sh, int pieces) { return std::max(1, pieces * kWave / sh.lanes); }
 
-// The same for the float32 forward (one tensor in, two out), whose vector work leaves room: rows that
-// fill their wave with one piece per lane 26-28 waves (64x16x256x256: 137 -> 133 us), three and four pieces
-// per lane 12 and 8 waves (8x3072x3072: 159 -> 152; 8x4096x4096: 284 -> 267).  The bfloat16 forward is
-// bound by the vector ALU and wants all waves (3072 columns, causal: 201 us, 255 at 16 waves).
-size_t fwd_f32_lds_bytes(const Shape& sh, int pieces, int threads) {
-  if (sh.ch == 1 && sh.lanes <= kWave && threads == 2 * kWave && pieces * 8 >= sh.lanes * 7)
-    return 11 * 1024;
-  return sh.ch > 2 ? flight_lds_bytes(sh, pieces, threads, sh.ch == 3 ? 12 : 8) : 0;
+// Resident waves of the backward: those that move about 18 pieces per lane of a wave of each tensor at once.  It
+// streams two tensors in and two out, and the more waves have loads under way beyond that, the worse the memory
+// system does: at 32 and at 18-20 resident waves of one piece per lane, us: 8x12x1024x1024 bf16 129
+// and 124; 16x16x512x512 bf16 89 and 86; 2 pieces per lane, 32 and 12 waves: 16x4096x4096 bf16 378 and 347;
+// 16x2048x2048 f32 189 and 173.  Fewer than 12 waves lose again.  Rows that leave a third of the lanes idle
+// move less per wave and stay unlimited.
+int bwd_waves(const Shape& sh, int pieces) {
+  const int per_wave = pieces_per_wave(sh, pieces);
+  return std::max(12, (18 * kWave + per_wave - 1) / per_wave);
+}
+
+// Dynamic LDS of the float32 forward (one tensor in, two out), whose vector work leaves room for the
+// same.  All waves / this, us: one piece per lane of one wave at 28 waves, 64x16x256x256 132 / 129; one wave of
+// three pieces at 20, 5x16x640x640 causal 59 / 59.5 and padded 64.7 / 64.4 (12: 62.8, 66.4), of four at 12, 4x16x800x800
+// 86 / 85, padded 82.3 / 80, causal 75 / 74 (8: 87.6, 87.3, 83.8).  Four waves: rows of which much is masked
+// keep fewer loads under way per wave and want more of them.  Three pieces: 12 waves, 8x3072x3072 159 / 150;
+// causal 20, 8x3072x3072 145 / 133, 12x2560x2560 136 / 138 (12: 134, 150).  Four pieces: 8 waves where the
+// lanes are full, 8x4096x4096 284 / 268; 12 where they are not, 4x3200x3200 91 / 83 (8: 87), and causal,
+// 4x4096x4096 135 / 122 (8: 125).
+// The bfloat16 forward is bound by the vector ALU and wants all waves (3072 columns, causal: 201 us, 255
+// at 16 waves).
+size_t fwd_f32_lds_bytes(const Shape& sh, int pieces, int threads, bool causal, bool padded) {
+  const bool one_wave = sh.lanes <= kWave;
+  const int per_wave = pieces_per_wave(sh, pieces);
+  if (sh.ch == 1 && one_wave && threads == 2 * kWave && pieces * 8 >= sh.lanes * 7)
+    return 11 * 1024;  // 28 waves
+  if (sh.ch == 3) return residency_lds_bytes(one_wave || causal ? 20 : 12, threads);
+  if (sh.ch == 4)
+    return residency_lds_bytes(one_wave || causal || per_wave <= (padded ? 240 : 224) ? 12 : 8, threads);
+  return 0;
 }
 
 // Rows a lane group of the forward kernel fetches at once: 2 (if the knob allows) when a
@@ -1051,8 +1066,8 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
     const FastDiv heads(static_cast<uint32_t>(A));
     const int64_t total_sets = static_cast<int64_t>(slices) * sets_per_slice.d;
-    const size_t lds =
-        dt == TEMPO_F32 ? fwd_f32_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads) : 0;
+    const int pieces = static_cast<int>((Sk + vec - 1) / vec);
+    const size_t lds = dt == TEMPO_F32 ? fwd_f32_lds_bytes(sh, pieces, threads, causal != 0, key_len != nullptr) : 0;
     const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
@@ -1113,7 +1128,8 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
     const int threads =
         ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);
     const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
-    const size_t lds = flight_lds_bytes(sh, static_cast<int>((Sk + vec - 1) / vec), threads, 12);
+    const int pieces = static_cast<int>((Sk + vec - 1) / vec);
+    const size_t lds = residency_lds_bytes(bwd_waves(sh, pieces), threads);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
 #define TEMPO_LAUNCH(L, C)                                                                   \
