@@ -764,8 +764,9 @@ constexpr bool is_ragged_shape(int lanes, int ch, int vec, bool backward) {
   return ch <= (backward && lanes == kWave ? 3 : kRaggedMaxPieces);
 }
 
-// Fewest lanes a workgroup may have: a row's, and two rows' where a forward row takes two waves
-// (64x16x512x512 f32, three sets of buffers: 508-519 us, against 510-554 with one row per workgroup).
+// Fewest lanes a workgroup may have: a row's, and two rows' where a forward row takes two waves.  One row /
+// two rows per workgroup, us: 32x16x1024x1024 bf16 518-542 / 497-519 by buffers, 16x16x505x505 f32 142 / 135,
+// 64x16x512x512 f32 506-545 / 516-528; 12x1024x1024 bf16 causal, on half the chip, 14.3 / 14.7.
 constexpr int least_threads(int lanes, bool backward) {
   return lanes <= kWave ? kWave : (backward ? lanes : 4 * kWave);
 }
@@ -858,14 +859,25 @@ size_t residency_lds_bytes(int waves, int threads) {
 }
 int pieces_per_wave(const Shape& sh, int pieces) { return std::max(1, pieces * kWave / sh.lanes); }
 
-// Resident waves of the backward: those that move about 18 pieces per lane of a wave of each tensor at once.  It
-// streams two tensors in and two out, and the more waves have loads under way beyond that, the worse the memory
-// system does: at 32 and at 18-20 resident waves of one piece per lane, us: 8x12x1024x1024 bf16 129
-// and 124; 16x16x512x512 bf16 89 and 86; 2 pieces per lane, 32 and 12 waves: 16x4096x4096 bf16 378 and 347;
-// 16x2048x2048 f32 189 and 173.  Fewer than 12 waves lose again.  Rows that leave a third of the lanes idle
-// move less per wave and stay unlimited.
-int bwd_waves(const Shape& sh, int pieces) {
+// Resident waves of the backward.  It streams two tensors in and two out, and the more waves have loads
+// under way, the worse the memory system does, until they are too few.  All waves / this, us:
+//  - one piece per lane, 18 waves where the lanes are full: 8x12x1024x1024 bf16 causal 130 / 126, 16x16x512x512
+//    bf16 88 / 85, 64x16x256x256 f32 175 / 173 (64x16x512x512 f32: as much faster as slower, by buffers), and
+//    20 or 24 at three quarters or five eighths: 25x16x384x384 bf16 80.5 / 76.7, 36x16x320x320 79.5 / 77.5;
+//  - several pieces, 12 waves: 16x4096x4096 bf16 373 / 350, 16x2048x2048 f32 causal 188 / 172, 8x3072x3072 f32
+//    210 / 196.  More on four waves with idle lanes.  Two pieces: 16, or 20 with a stored mask, 2x12 causal
+//    slices of 2304, 2816 and 3072 bf16 columns 169, 250, 304 / 166, 246, 294 (12: 194, 271, 310), with the bits
+//    drawn again 168, 250, 299 / 162, 242, 289.  Three pieces: 16, 4x5120x5120 bf16 141.5 / 137 (12: 140.5),
+//    and with the bits drawn again all, 4x6144x6144 bf16 199 (12: 207);
+//  - ragged rows of one piece pay at 23 waves what aligned ones gain: 23x16x333x333 bf16 62.3 / 63.7.
+int bwd_waves(const Shape& sh, int pieces, bool regen, bool ragged) {
   const int per_wave = pieces_per_wave(sh, pieces);
+  if (!ragged) {
+    if (sh.ch == 1) return std::max(18, (15 * kWave + per_wave - 1) / per_wave);
+    if (sh.lanes == kThreads && sh.ch == 2)
+      return per_wave <= 88 && !regen ? 20 : (per_wave <= 96 ? 16 : 12);
+    if (sh.lanes == kThreads && sh.ch == 3) return regen ? 0 : (per_wave <= 160 ? 16 : 12);
+  }
   return std::max(12, (18 * kWave + per_wave - 1) / per_wave);
 }
 
@@ -1129,7 +1141,7 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
         ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);
     const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
     const int pieces = static_cast<int>((Sk + vec - 1) / vec);
-    const size_t lds = residency_lds_bytes(bwd_waves(sh, pieces), threads);
+    const size_t lds = residency_lds_bytes(bwd_waves(sh, pieces, regen, ragged), threads);
     const MaskSource mask =
         regen ? kMaskRegen : (bools ? kMaskBools : (Sk % 32 == 0 ? kMaskWords : kMaskBytes));
 #define TEMPO_LAUNCH(L, C)                                                                   \
