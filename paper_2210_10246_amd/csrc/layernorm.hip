@@ -741,14 +741,13 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
   const int slice = threadIdx.x / kFinVecLanes;
   const int64_t j2 = static_cast<int64_t>(blockIdx.x) * kFinCols + q * 4;  // index into [2][M]
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (j2 + 4 <= 2 * M) {
+  auto add_up = [&](auto load) {  // load(address, four values)
     const float* p0 = partial + j2;
     int p = slice;
     for (; p + 7 * kFinSlices < parts; p += 8 * kFinSlices) {
       float v[8][4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        load_cols<ANY, 4>(p0 + static_cast<size_t>(p + u * kFinSlices) * 2 * M, v[u]);
+      for (int u = 0; u < 8; ++u) load(p0 + static_cast<size_t>(p + u * kFinSlices) * 2 * M, v[u]);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
 #pragma unroll
@@ -757,15 +756,19 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
     }
     for (; p < parts; p += kFinSlices) {
       float v[4];
-      load_cols<ANY, 4>(p0 + static_cast<size_t>(p) * 2 * M, v);
+      load(p0 + static_cast<size_t>(p) * 2 * M, v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) s[i] += v[i];
     }
-  } else if (ANY && j2 < 2 * M) {  // 2 * M - j2 is 2: the sums of two columns
-    for (int p = slice; p < parts; p += kFinSlices) {
-      s[0] += partial[static_cast<size_t>(p) * 2 * M + j2];
-      s[1] += partial[static_cast<size_t>(p) * 2 * M + j2 + 1];
-    }
+  };
+  if (j2 + 4 <= 2 * M) {
+    add_up([](const float* p, float (&v)[4]) { load_cols<ANY, 4>(p, v); });
+  } else if (ANY && j2 < 2 * M) {  // 2 * M - j2 is 2: the sums of two columns, as many loads under way
+    add_up([](const float* p, float (&v)[4]) {
+      v[0] = p[0];
+      v[1] = p[1];
+      v[2] = v[3] = 0.0f;
+    });
   }
   store_floats<4>(&lds[slice][q * 4], s);
   lds_barrier();
