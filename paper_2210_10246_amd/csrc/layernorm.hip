@@ -53,11 +53,10 @@ __device__ __forceinline__ void store_col_sums(float* p, int ch, int chunks, int
     store_floats_any<V>(p + ch * V, v);
   }
 }
-// Whether a division by gamma may be done by multiplication with its reciprocal: neither that nor a
-// residual leaves the range of float32.
-__device__ __forceinline__ bool is_tame(float gamma) {
-  return fabsf(gamma) >= 0x1p-60f && fabsf(gamma) <= 0x1p60f;
-}
+// A division by gamma may be done by multiplication with its reciprocal if neither that nor a residual
+// leaves the range of float32: if |gamma| is in 2^-60 .. 2^60, here its offset in that range.
+constexpr uint32_t kTameLow = (127u - 60u) << 24, kTameRange = 120u << 24;
+__device__ __forceinline__ uint32_t tame_offset(float gamma) { return (as_u32(gamma) << 1) - kTameLow; }
 // Length of a row of column sums in LDS: whole 16-byte pieces.
 __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int64_t{3}; }
 
@@ -335,7 +334,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   float rs[R];
   fetch(base, rd, ry, rs);
   // parameters after the first rows are on their way
-  bool tame = true;  // every gamma of the lane is
+  uint32_t offset = 0;  // the largest of the lane's gammas
   if constexpr (kRegParams) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -362,7 +361,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
           // waits for beta here: first used inside the loop, it would make the loop wait for every
           // load under way, the rows fetched ahead included (8192 x 1001 f32: 38 -> 42 us)
           asm volatile("" : "+v"(r_bg[c][i]));
-          tame = tame && is_tame(r_ga[c][i]);
+          offset = max(offset, tame_offset(r_ga[c][i]));
         } else {
           r_bg[c][i] = be[i] * r_rg[c][i];
         }
@@ -383,7 +382,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   // a division does, and the division's own treatment of infinities.  Forward + backward, us, fused / this /
   // a division per element: 8192 x 1001 f32 38.3 / 38.6 / 38.5, bf16 25.4 / 26.3 / 28.1; 4096 x 4100 bf16
   // 45.4 / 46.5 / 50.2.
-  const bool wave_tame = __builtin_amdgcn_ballot_w64(!tame) == 0;  // scalar: a branch, not a select
+  const bool wave_tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // scalar: a branch, not a select
   auto xhat = [&](const float (&y8)[V], const float (&ga)[V], const float (&rg)[V], const float (&bg)[V],
                   float (&h)[V]) {
     if constexpr (!RAG) {
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
       } else {  // per column, so that the two lanes which share one find the same value
 #pragma unroll
         for (int i = 0; i < V; ++i)
-          h[i] = is_tame(ga[i]) ? quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
+          h[i] = tame_offset(ga[i]) <= kTameRange ? quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
       }
     }
   };
@@ -878,26 +877,39 @@ constexpr int max_fast_pieces(int vec) { return vec == 4 ? kMaxFastPiecesF32 : k
 // Shape for rows of `pieces` pieces of vec elements; ch == 0: too long.
 // Backward: four waves whose lanes would own more than 24 columns each (parameters in LDS, read twice per
 // element) give the row to all eight waves, which halves the columns per lane and keeps the parameters
-// in registers.
-constexpr Shape shape_of(int pieces, int vec, int max_ch, bool backward) {
+// in registers.  Ragged rows, whose columns also hold a quotient:
+//  - so do those of 24 columns in float32, which do not fit the registers: 8000x5001 138 -> 89 us, 2000x4097
+//    38 -> 27; in bfloat16 they do, and eight waves lose (8000x5001 56 -> 66);
+//  - several rows per wave with three pieces per lane end in long reductions: a row per wave instead.  f32
+//    64x129 6.8 -> 4.9, 4000x129 9.0 -> 7.0, 65536x129 28 -> 25 (2000x323 9.6 -> 10.7); bf16 64x515 8.8 -> 6.8,
+//    4000x515 13.4 -> 9.9, 16384x515 19.0 -> 19.2, and not beyond: 65536x515 49 -> 54.  many: 64 rows per compute unit
+//    and more.
+constexpr Shape shape_of(int pieces, int vec, int max_ch, bool backward, bool ragged, bool many) {
   const Shape sh = widen_shape(pick_shape(pieces, backward), pieces, max_ch, 256);
-  return backward && sh.lanes == 256 && sh.ch * vec > 24 ? Shape{kBwdThreads, sh.ch / 2} : sh;
+  if (backward && sh.lanes == 256 && sh.ch * vec > 24) return {kBwdThreads, sh.ch / 2};
+  if (backward && ragged) {
+    if (sh.lanes == 256 && sh.ch == 6) return {kBwdThreads, 4};
+    if (sh.lanes < kWave && sh.ch == 3 && (vec == 4 || !many)) return {kWave, (pieces + kWave - 1) / kWave};
+  }
+  return sh;
 }
 
 // Shapes that ragged rows are dispatched to (no others: ragged_shapes_exist()).
 constexpr int kRaggedFwdMaxPieces = 4;
 constexpr int kRaggedBwdMaxPieces = 3;
 constexpr bool is_ragged_shape(int lanes, int ch, int vec, bool backward) {
-  if (lanes < kWave) return ch != 2;
+  if (lanes < kWave) return ch == 1 || (ch == 3 && !(backward && vec == 4));
   if (lanes == kWave) return ch <= (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces);
   if (lanes > 256) return backward;
-  return backward ? ch == 2 || ch == 3 || (lanes == 256 && vec == 4 && ch <= 6 && ch >= 4)
+  return backward ? ch == 2 || ch == 3 || (lanes == 256 && vec == 4 && ch == 4)
                   : ch == 3 || ch == 4 || (lanes == 256 && vec == 4 && ch > 4);
 }
 constexpr bool ragged_shapes_exist(int vec, bool backward) {
   for (int p = 2; p <= max_fast_pieces(vec); ++p) {
-    const Shape sh = shape_of(p, vec, backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces, backward);
-    if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, backward)) return false;
+    for (bool many : {false, true}) {
+      const Shape sh = shape_of(p, vec, backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces, backward, true, many);
+      if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, backward)) return false;
+    }
   }
   return true;
 }
@@ -943,14 +955,14 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
 
 static bool is_ragged(int64_t M, tempo_dtype dt) { return M % (dt == TEMPO_F32 ? 4 : 8) != 0; }
 
-static bool fast_shape(int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
+static bool fast_shape(int64_t N, int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   if (M < vec || (M + vec - 1) / vec > max_fast_pieces(vec)) return false;
   const int pieces = static_cast<int>((M + vec - 1) / vec);
   const bool ragged = is_ragged(M, dt);
   const int max_ch = ragged ? (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces)
                             : tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces);
-  *sh = shape_of(pieces, vec, max_ch, backward);
+  *sh = shape_of(pieces, vec, max_ch, backward, ragged, N >= int64_t{64} * compute_units());
   return sh->ch != 0;
 }
 
@@ -961,7 +973,7 @@ tempo_status launch_layernorm_fwd(const void* x, const float* gamma, const float
                                   tempo_dtype dt, hipStream_t st) {
   Shape sh;
   int64_t cap = static_cast<int64_t>(compute_units()) * tune_get(kTuneLnFwdBlocksPerCu);
-  if (fast_shape(M, dt, false, &sh)) {
+  if (fast_shape(N, M, dt, false, &sh)) {
     // rows per lane group, if the knob allows more than one: 4 for rows of one piece per lane, 2
     // for two pieces, so that a lane has 4 pieces in flight (and as many fetched ahead when the
     // workgroups loop); rows of one piece also take one more workgroup per compute unit.
@@ -1150,7 +1162,7 @@ struct BwdLaunch {
 };
 static BwdLaunch bwd_launch(int64_t N, int64_t M, tempo_dtype dt) {
   BwdLaunch b;
-  b.fast = fast_shape(M, dt, true, &b.sh);
+  b.fast = fast_shape(N, M, dt, true, &b.sh);
   // rows that are no multiple of a piece: one slot per row up to kMaxRaggedSlots, for either kernel
   const int per_row = static_cast<int>(N > kMaxRaggedSlots ? kMaxRaggedSlots : (N < 1 ? 1 : N));
   if (b.fast) {

@@ -100,7 +100,9 @@ def test_attention_ragged_rows(B, Sk, Sq, dt):
 LN_ROWS = [(4, 5), (5, 40), (7, 9), (9, 3), (63, 70), (65, 130), (127, 9), (129, 4100), (255, 17), (258, 1030),
            (385, 33), (511, 2100), (513, 41), (770, 700), (1001, 1300), (1023, 19), (1025, 600), (1535, 300),
            (1537, 20), (2047, 300), (2049, 9), (3070, 7), (3073, 300), (4095, 5), (4097, 260), (4100, 270),
-           (6145, 3), (8191, 270)]
+           (6145, 3), (8191, 270),
+           # fewer and more than 64 rows per compute unit (the row shapes of the backward differ), eight waves per row
+           (259, 64), (515, 700), (515, 16400), (5003, 300)]
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
