@@ -1060,6 +1060,16 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
                              void* out, uint32_t* keep_bits, int64_t B, int64_t A, int64_t Sq,
                              int64_t Sk, float p, uint64_t seed, uint64_t offset, tempo_dtype dt,
                              hipStream_t st) {
+  // A workgroup's rows are of one slice.  Where no causal mask tells the rows of a slice apart, those of a
+  // batch (of the call, without key_len) count as one: few rows per slice would leave most of the workgroup
+  // idle (2^24 slices of one row of one bf16 element: 8.5 ms, 0.41 this way; 1024x16x1x333 17.4 us, 13.8).
+  if (Sq == 1) causal = 0;  // the only row sees every key
+  const int64_t alike = key_len ? A * Sq : B * A * Sq;
+  if (!causal && alike <= int64_t{1} << 30) {
+    if (!key_len) B = 1;
+    A = 1;
+    Sq = alike;
+  }
   const int64_t rows = B * A * Sq;
   const int64_t rows_per_batch = A * Sq;
   const float scale = 1.0f / (1.0f - p);

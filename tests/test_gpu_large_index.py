@@ -188,7 +188,8 @@ def test_attention_beyond_2_32_elements(B, Sk):
 def test_attention_of_2_24_workgroups_of_256_lanes(B):
     """2^32 lanes, one more than HIP takes in one launch: the call is split, and the result is that of
     workgroups of 64 lanes."""
-    s = _normal((1 << 24) * 8, 1.0, 7).view(4096, 4096, 1, 8)      # 2^24 slices of one row
+    s = _normal((1 << 24) * 16, 1.0, 7).view(4096, 4096, 2, 8)     # 2^24 slices of two rows, which a causal
+                                                                   # mask tells apart: a workgroup each
     old = B.tempo_get_launch_param(14)
     got = []
     try:
@@ -196,11 +197,11 @@ def test_attention_of_2_24_workgroups_of_256_lanes(B):
             B.tempo_set_launch_param(14, lanes)
             P, out = torch.zeros_like(s), torch.zeros_like(s)
             md = torch.zeros(B.mask_words(s.numel()), dtype=torch.int32, device="cuda")
-            B.tempo_attn_softmax_dropout_fwd(s, None, False, P, out, md, 0.1, 3, 4)
+            B.tempo_attn_softmax_dropout_fwd(s, None, True, P, out, md, 0.1, 3, 4)
             got.append((P, out, md))
     finally:
         B.tempo_set_launch_param(14, old)
     for a, b in zip(*got):
         assert torch.equal(a, b)
-    ref = torch.softmax(s[-1].float(), -1)
-    assert float((got[0][0][-1].float() - ref).abs().max()) <= 2.0 ** -8
+    ref = torch.softmax(s[-1, :, 1].float(), -1)                   # the second row sees every key
+    assert float((got[0][0][-1, :, 1].float() - ref).abs().max()) <= 2.0 ** -8

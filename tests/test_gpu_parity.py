@@ -411,6 +411,12 @@ ATTN_CASES = [
     (2, 1, 5, 1001, "causal", 0.1),
     (1, 2, 3, 1543, "padding", 0.1),
     (1, 1, 3, 2055, "none", 0.1),
+    # few rows per slice, which share workgroups with those of other heads and batches
+    (3, 5, 1, 61, "padding", 0.1),
+    (3, 5, 1, 64, "causal", 0.1),
+    (4, 3, 3, 333, "padding", 0.1),
+    (2, 7, 1, 24, "none", 0.1),
+    (5, 2, 2, 1024, "zero_len", 0.1),
     # the edges of the shapes of a causal forward, which takes half the waves (in 16-byte pieces: 113, 225, 226,
     # 257, 258), and of longer rows
     (1, 1, 40, 904, "causal", 0.1),
