@@ -867,7 +867,7 @@ int pieces_per_wave(const Shape& sh, int pieces) { return std::max(1, pieces * k
 //  - several pieces, 12 waves: 16x4096x4096 bf16 373 / 350, 16x2048x2048 f32 causal 188 / 172, 8x3072x3072 f32
 //    210 / 196.  More on four waves with idle lanes.  Two pieces: 16, or 20 with a stored mask, 2x12 causal
 //    slices of 2304, 2816 and 3072 bf16 columns 169, 250, 304 / 166, 246, 294 (12: 194, 271, 310), with the bits
-//    drawn again 168, 250, 299 / 162, 242, 289.  Three pieces: 16, 4x5120x5120 bf16 141.5 / 137 (12: 140.5),
+//    drawn again 168, 250, 299 / 162, 242, 289 (the last at 12).  Three pieces: 16, 4x5120x5120 bf16 141.5 / 137 (12: 140.5),
 //    and with the bits drawn again all, 4x6144x6144 bf16 199 (12: 207);
 //  - ragged rows of one piece pay at 23 waves what aligned ones gain: 23x16x333x333 bf16 62.3 / 63.7.
 int bwd_waves(const Shape& sh, int pieces, bool regen, bool ragged) {
@@ -875,7 +875,7 @@ int bwd_waves(const Shape& sh, int pieces, bool regen, bool ragged) {
   if (!ragged) {
     if (sh.ch == 1) return std::max(18, (15 * kWave + per_wave - 1) / per_wave);
     if (sh.lanes == kThreads && sh.ch == 2)
-      return per_wave <= 88 && !regen ? 20 : (per_wave <= 96 ? 16 : 12);
+      return per_wave <= 88 && !regen ? 20 : (per_wave < 96 || (per_wave == 96 && !regen) ? 16 : 12);
     if (sh.lanes == kThreads && sh.ch == 3) return regen ? 0 : (per_wave <= 160 ? 16 : 12);
   }
   return std::max(12, (18 * kWave + per_wave - 1) / per_wave);
