@@ -132,7 +132,7 @@ __device__ __forceinline__ u32x4 apply_keep(u32x4 w, uint32_t bits) {
 
 
 // Element `off` of p, p the same for the whole wave: a scalar address and a 32-bit offset.  (The
-// offsets stay inside one set of rows: at most 32 rows of 8192 elements.)
+// offsets stay inside one set of rows: at most 64 rows of a piece per lane, or fewer of up to 8192 elements.)
 template <typename T>
 __device__ __forceinline__ T* at_offset(T* p, uint32_t off) {
   using Byte = std::conditional_t<std::is_const<T>::value, const char, char>;
@@ -233,7 +233,7 @@ __device__ __forceinline__ uint32_t load_keep_bits(const uint32_t* keep_bits, in
 // where a lane takes the 8-bit window that starts at its piece.  One generator call per 8 elements,
 // as on the aligned path.
 // Measured, forward + backward: bfloat16 16x16x333x333 under a padding mask 198 us element by element,
-// 94 us this way (aligned rows of 336 elements: 81); 8x12x1001x1001 557 -> 254 us (regen).
+// 84 us this way (aligned rows of 336 elements: 76); 8x12x1001x1001 557 -> 240 us (regen).
 // Rows shorter than a piece (SHORT: only the kernels with the fewest lanes per row take them) are
 // read and written element by element; `fill` stands for the rest of the piece.
 template <typename T, bool RAG, bool SHORT>

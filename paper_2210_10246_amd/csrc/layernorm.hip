@@ -265,8 +265,8 @@ __global__ __launch_bounds__(256) void ln_fwd_generic_kernel(
 // compute on the current one; the column sums stay in registers across batches, so the LDS
 // tree and the partial store are paid once per workgroup however many rows it walks.
 // RAG: rows of any length that is no multiple of the piece (see piece_col), parameters in registers,
-// and xhat as the quotient (y - beta) / gamma itself.  8192 x 1001 f32 50.0 -> 24.9 us against
-// element-wise accesses (1000 columns: 22.4), 4096 x 4100 bf16 97.8 -> 29.5.
+// and xhat as the quotient (y - beta) / gamma itself.  8192 x 1001 f32 50.0 -> 23.7 us against
+// element-wise accesses (1000 columns: 22.4), 4096 x 4100 bf16 97.8 -> 28.5.
 template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     const T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
@@ -379,9 +379,8 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   }
   // xhat of a piece.  The fused form loses 2^-24 |beta / gamma| to the rounding of beta / gamma; ragged
   // rows subtract first and divide: the product with the reciprocal, one residual step, which rounds it as
-  // a division does, and the division's own treatment of infinities.  Forward + backward, us, fused / this /
-  // a division per element: 8192 x 1001 f32 38.3 / 38.6 / 38.5, bf16 25.4 / 26.3 / 28.1; 4096 x 4100 bf16
-  // 45.4 / 46.5 / 50.2.
+  // a division does, and the division's own treatment of infinities.  What this / a division per element takes
+  // beyond the fused form, us: 8192 x 1001 f32 0.3 / 0.2, bf16 0.9 / 2.7; 4096 x 4100 bf16 1.1 / 4.8.
   const bool wave_tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // scalar: a branch, not a select
   auto xhat = [&](const float (&y8)[V], const float (&ga)[V], const float (&rg)[V], const float (&bg)[V],
                   float (&h)[V]) {

@@ -25,7 +25,7 @@ enum TuneKey {
   kTuneLnBwdMaxPieces = 11,     // and layernorm_bwd
   kTuneLnBwdLoopBlocksPerCu = 12,  // layernorm_bwd: workgroups per CU beyond which they loop
   kTuneGeluFwdSmallGroupsFrom = 13,  // bf16 gelu/silu fwd: Mi elements from which 512-lane groups
-  kTuneAttnThreads = 14,        // attn fwd / bwd: lanes per workgroup (64, 128 or 256; at least one row's)
+  kTuneAttnThreads = 14,        // attn fwd / bwd: lanes per workgroup (64, 128 or 256; at least a row's, two where a forward row takes two waves)
   kTuneGeluF32Threads = 15,     // float32 gelu/silu: lanes per workgroup (64, 128, 256; 1 = per kernel)
   kTuneCount = 16
 };
