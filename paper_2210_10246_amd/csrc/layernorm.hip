@@ -741,20 +741,34 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   auto add_up = [&](auto load) {  // load(address, four values)
     const float* p0 = partial + j2;
+    auto at = [&](int p) { return p0 + static_cast<size_t>(p) * 2 * M; };
     int p = slice;
     for (; p + 7 * kFinSlices < parts; p += 8 * kFinSlices) {
       float v[8][4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) load(p0 + static_cast<size_t>(p + u * kFinSlices) * 2 * M, v[u]);
+      for (int u = 0; u < 8; ++u) load(at(p + u * kFinSlices), v[u]);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] += v[u][i];
       }
     }
-    for (; p < parts; p += kFinSlices) {
+    // The rest all at once too: with 250 partials the last slices have 7, and cost 1.5 us when they added
+    // them up one memory latency after the other (2000 x 1024 bf16 backward 10.2 -> 8.7 us).
+    if (p + kFinSlices < parts) {
+      float v[7][4];
+#pragma unroll
+      for (int u = 0; u < 7; ++u)
+        if (p + u * kFinSlices < parts) load(at(p + u * kFinSlices), v[u]);
+#pragma unroll
+      for (int u = 0; u < 7; ++u) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (p + u * kFinSlices < parts) s[i] += v[u][i];
+      }
+    } else if (p < parts) {
       float v[4];
-      load(p0 + static_cast<size_t>(p) * 2 * M, v);
+      load(at(p), v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) s[i] += v[i];
     }
@@ -880,7 +894,7 @@ constexpr int max_fast_pieces(int vec) { return vec == 4 ? kMaxFastPiecesF32 : k
 //  - so do those of 24 columns in float32, which do not fit the registers: 8000x5001 138 -> 89 us, 2000x4097
 //    38 -> 27; in bfloat16 they do, and eight waves lose (8000x5001 56 -> 66);
 //  - several rows per wave with three pieces per lane end in long reductions: a row per wave instead.  f32
-//    64x129 6.8 -> 4.9, 4000x129 9.0 -> 7.0, 65536x129 28 -> 25 (2000x323 9.6 -> 10.7); bf16 64x515 8.8 -> 6.8,
+//    64x129 6.8 -> 4.9, 4000x129 9.0 -> 7.0, 65536x129 28 -> 25; bf16 64x515 8.8 -> 6.8,
 //    4000x515 13.4 -> 9.9, 16384x515 19.0 -> 19.2, and not beyond: 65536x515 49 -> 54.  many: 64 rows per compute unit
 //    and more.
 constexpr Shape shape_of(int pieces, int vec, int max_ch, bool backward, bool ragged, bool many) {
