@@ -346,11 +346,12 @@ constexpr uint32_t kAbsentX = 0xF149F149u;  // two bf16 of about -2.5e30: mask b
 template <int KIND, int K, int THREADS>
 __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, bf16_t* y,
                                                                    uint32_t* __restrict__ mask,
-                                                                   int64_t n) {
+                                                                   int64_t n, int64_t kept) {
   __shared__ uint32_t lut[2 * TEMPO_GELU_LUT_N];
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t q_base = static_cast<int64_t>(blockIdx.x) * (THREADS * K) + threadIdx.x;
   const bool full = (static_cast<int64_t>(blockIdx.x) + 1) * (THREADS * K) * 8 <= n;
+  const bool cached = static_cast<int64_t>(blockIdx.x) * (THREADS * K) * 8 < kept;
   u32x4 w[K];
   if (full) {  // whole tile inside the tensor: straight-line loads
 #pragma unroll
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, 
     // every lane of the wave takes part in the merge; absent chunks contribute zero bits
     const uint32_t word = merge_mask_word<8>(byte, lane);
     if (full) {
-      stg_stream(y + q * 8, yw);
+      stg_kept<false>(y + q * 8, yw, cached);
       if ((lane & 3) == 0) mask[q >> 2] = word;
     } else {
       const int64_t left = n - q * 8;
@@ -450,6 +451,14 @@ int tile_grid(int64_t n, int k, int threads) {  // float32 pieces of 4 elements
   return static_cast<int>((n_pieces + per_block - 1) / per_block);
 }
 
+// Part of y that the bfloat16 forward leaves in the Infinity Cache.  Forward + backward / forward alone, us,
+// all streamed -> the first 64 MiB kept: 8192x4096 60.6 -> 58.8 / 25.1 -> 25.3, 32768x2048 silu 113.6 -> 111.6 /
+// 47.5 -> 46.6, 8192x12288 167.8 -> 166.2 / 71.1 -> 68.8.  All 128 MiB of the second: 108.8 / 50.5, a
+// forward alone loses; so it does below 60 MiB (50 MiB 50.4 -> 49.4 / 20.4 -> 21.0; 16 MiB 18.4 -> 18.4 / 6.3 -> 7.9).  The
+// float32 backward has other bounds than memory and gains nothing at any size.
+constexpr int kKeptFromMiB = 60;
+constexpr int kKeptMiB = 64;
+
 int pick_k(int tuned) { return tuned >= 4 ? 4 : (tuned >= 2 ? 2 : 1); }
 
 }  // namespace
@@ -493,17 +502,18 @@ tempo_status launch_gelu_fwd(const void* x, void* y, uint32_t* mask, int64_t n, 
                              int kind, hipStream_t st) {
   const int k = pick_k(tune_get(kTuneGeluFwdChunks));
   if (dt == TEMPO_BF16) {
+    const int64_t kept = kept_elements(n, 2, kKeptFromMiB, kKeptMiB);
     // large tensors: half-size workgroups with half the pieces per lane
     const bool small_groups = n >= tune_get(kTuneGeluFwdSmallGroupsFrom) * int64_t{1048576} && k >= 2;
     with_kind_k(kind, small_groups ? k / 2 : k, [&](auto kd, auto kk) {
       constexpr int KD = decltype(kd)::value, KK = decltype(kk)::value;
       if (small_groups)
         hipLaunchKernelGGL((gelu_fwd_lut_kernel<KD, KK, 512>), dim3(lut_grid(n, KK, 512)), dim3(512),
-                           0, st, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y), mask, n);
+                           0, st, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y), mask, n, kept);
       else
         hipLaunchKernelGGL((gelu_fwd_lut_kernel<KD, KK, 1024>), dim3(lut_grid(n, KK, 1024)),
                            dim3(1024), 0, st, static_cast<const bf16_t*>(x),
-                           static_cast<bf16_t*>(y), mask, n);
+                           static_cast<bf16_t*>(y), mask, n, kept);
     });
     return launch_status();
   }

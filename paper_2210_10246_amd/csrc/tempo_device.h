@@ -116,6 +116,22 @@ __device__ __forceinline__ void stg_piece(void* p, u32x4 v) {
   if constexpr (ANY) stg_stream_any(p, v);
   else stg_stream(p, v);
 }
+// The same for a forward's output that the backward reads again: `cached` stores it without the
+// streaming hint.  Streaming accesses take no room in the 256 MiB Infinity Cache, so what is stored this
+// way is still there when the backward comes, if the cached part fits; a kernel that has just
+// filled the L2s with such stores then waits for them to be written out (2-3 us).  Which part pays is
+// the launchers' rule (kept_elements()).  `cached` is the same for the whole wave.
+template <bool ANY>
+__device__ __forceinline__ void stg_kept(void* p, u32x4 v, bool cached) {
+  if (cached) {
+    asm volatile("");  // these two keep the compiler from making one store of both, which loses the hint
+    if constexpr (ANY) *reinterpret_cast<u32x4_any*>(p) = v;
+    else *reinterpret_cast<u32x4*>(p) = v;
+    asm volatile("");
+  } else {
+    stg_piece<ANY>(p, v);
+  }
+}
 template <typename T>
 __device__ __forceinline__ void load_piece(const T* p, float (&v)[Store<T>::kVec]) {
   Store<T>::unpack(ldg_stream(p), v);
