@@ -19,6 +19,9 @@ namespace {
 constexpr int kFwdThreads = 256;
 constexpr int kBwdWaves = 8;
 constexpr int kBwdThreads = kBwdWaves * kWave;
+// ln_bwd_few_kernel: lanes per workgroup, and those of them side by side on a row's columns.
+constexpr int kFewThreads = 512;
+constexpr int kFewColLanes = 4;
 // Rows of more than 1024 pieces in bfloat16 (8192 columns: 4 pieces per lane of 4 waves) or 2048
 // pieces in float32 (8192 columns: 6 or 8 pieces per lane of 4 waves, float32 only, whose pieces
 // need half the registers per column) take the generic kernels.  Dynamic LDS of the backward: the column sums' slots (all
@@ -57,6 +60,18 @@ __device__ __forceinline__ void store_col_sums(float* p, int ch, int chunks, int
 // leaves the range of float32: if |gamma| is in 2^-60 .. 2^60, here its offset in that range.
 constexpr uint32_t kTameLow = (127u - 60u) << 24, kTameRange = 120u << 24;
 __device__ __forceinline__ uint32_t tame_offset(float gamma) { return (as_u32(gamma) << 1) - kTameLow; }
+// 1 / g by the hardware estimate and one Newton step (within 1 ulp): a lane does this for each of its columns
+// in every workgroup, and the IEEE division costs four times as much.
+__device__ __forceinline__ float reciprocal(float g) {
+  const float est = __builtin_amdgcn_rcpf(g);
+  return fmaf(fmaf(-g, est, 1.0f), est, est);
+}
+// d / g for a tame g: the product with the reciprocal, one residual step, which rounds it as a division
+// does, and the division's own treatment of infinities.
+__device__ __forceinline__ float tame_quotient(float d, float g, float rcp) {
+  const float q = d * rcp;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-g, q, d), rcp, q), g, d);
+}
 // Length of a row of column sums in LDS: whole 16-byte pieces.
 __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int64_t{3}; }
 
@@ -353,10 +368,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
       }
 #pragma unroll
       for (int i = 0; i < V; ++i) {
-        // reciprocal by the hardware estimate and one Newton step (within 1 ulp): a lane does this
-        // for each of its columns in every workgroup, and the IEEE division costs four times as much
-        const float est = __builtin_amdgcn_rcpf(r_ga[c][i]);
-        r_rg[c][i] = fmaf(fmaf(-r_ga[c][i], est, 1.0f), est, est);
+        r_rg[c][i] = reciprocal(r_ga[c][i]);
         if constexpr (RAG) {
           r_bg[c][i] = be[i];
           // waits for beta here: first used inside the loop, it would make the loop wait for every
@@ -379,8 +391,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     lds_barrier();
   }
   // xhat of a piece.  The fused form loses 2^-24 |beta / gamma| to the rounding of beta / gamma; ragged
-  // rows subtract first and divide: the product with the reciprocal, one residual step, which rounds it as
-  // a division does, and the division's own treatment of infinities.  What this / a division per element takes
+  // rows subtract first and divide (tame_quotient).  What this / a division per element takes
   // beyond the fused form, us: 8192 x 1001 f32 0.3 / 0.2, bf16 0.9 / 2.7; 4096 x 4100 bf16 1.1 / 4.8.
   const bool wave_tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // scalar: a branch, not a select
   auto xhat = [&](const float (&y8)[V], const float (&ga)[V], const float (&rg)[V], const float (&bg)[V],
@@ -389,17 +400,13 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
 #pragma unroll
       for (int i = 0; i < V; ++i) h[i] = fmaf(y8[i], rg[i], -bg[i]);
     } else {
-      auto quotient = [](float d, float g, float rcp) {
-        const float q = d * rcp;
-        return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-g, q, d), rcp, q), g, d);
-      };
       if (wave_tame) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) h[i] = quotient(y8[i] - bg[i], ga[i], rg[i]);
+        for (int i = 0; i < V; ++i) h[i] = tame_quotient(y8[i] - bg[i], ga[i], rg[i]);
       } else {  // per column, so that the two lanes which share one find the same value
 #pragma unroll
         for (int i = 0; i < V; ++i)
-          h[i] = tame_offset(ga[i]) <= kTameRange ? quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
+          h[i] = tame_offset(ga[i]) <= kTameRange ? tame_quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
       }
     }
   };
@@ -796,6 +803,170 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
   }
 }
 
+// xhat of a piece from its output, as ln_bwd_kernel computes it: y / gamma - beta / gamma of aligned rows,
+// the quotient of ragged ones.
+template <bool RAG, int V>
+struct Xhat {
+  float ga[V], rg[V], bg[V];  // RAG: bg is beta
+  bool tame;
+  __device__ __forceinline__ Xhat(const float (&gamma)[V], const float (&beta)[V]) {
+    uint32_t offset = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      ga[i] = gamma[i];
+      rg[i] = reciprocal(gamma[i]);
+      bg[i] = RAG ? beta[i] : beta[i] * rg[i];
+      offset = max(offset, tame_offset(gamma[i]));
+    }
+    tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // the wave's: a branch, not a select
+  }
+  __device__ __forceinline__ void operator()(const float (&y8)[V], float (&h)[V]) const {
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      if constexpr (!RAG) h[i] = fmaf(y8[i], rg[i], -bg[i]);
+      else if (tame || tame_offset(ga[i]) <= kTameRange) h[i] = tame_quotient(y8[i] - bg[i], ga[i], rg[i]);
+      else h[i] = (y8[i] - bg[i]) / ga[i];
+    }
+  }
+};
+
+// Few rows: the whole backward in one launch.  The first col_blocks workgroups own 64 bytes of columns each
+// (4 lanes x a piece, 128 rows at a time) and walk all rows for dgamma and dbeta, which need no row sums; the
+// others own rows (LANES lanes, CH pieces per lane) and write dx.  dy and y are read twice, the second
+// time from a cache; in return there are no partials and no second dispatch.  In place (dx is dy) the two halves
+// are launched one after the other; `first` is the launch's first workgroup.
+// Bound by latency: a launch that does nothing takes 1.7 us, and a wave alone on its SIMD 4-8 cycles an
+// instruction, so that the column walk has one row per lane under way and the next fetched: with 2, 4 or 8 rows
+// unrolled 64x768 f32 takes 3.0, 3.5 and 5.3 us (256 lanes) instead of 2.9.
+template <typename T, int LANES, int CH, bool RAG>
+__global__ __launch_bounds__(kFewThreads) void ln_bwd_few_kernel(
+    const T* dy, const T* y, const float* __restrict__ gamma,
+    const float* __restrict__ beta, const float* __restrict__ rstd, T* dx,
+    float* __restrict__ dgamma, float* __restrict__ dbeta, int N, int M, int col_blocks, int first) {
+  constexpr int V = Store<T>::kVec;
+  constexpr int kWaves = kFewThreads / kWave;
+  const int chunks = RAG ? (M + V - 1) / V : M / V;
+  auto load = [](const T* p) {  // cached: the other half of the grid reads it too
+    if constexpr (RAG) return *reinterpret_cast<const u32x4_any*>(p);
+    else return *reinterpret_cast<const u32x4*>(p);
+  };
+  const int block = first + static_cast<int>(blockIdx.x);
+  if (block < col_blocks) {
+    constexpr int kSlices = kFewThreads / kFewColLanes;
+    static_assert(kFewColLanes == 4, "the sums over a wave's lanes below");
+    __shared__ float sums[kWaves][kFewColLanes][2 * V];
+    const int t = threadIdx.x % kFewColLanes;
+    const int slice = threadIdx.x / kFewColLanes;
+    const int ch = block * kFewColLanes + t;
+    float acc[2 * V];
+#pragma unroll
+    for (int i = 0; i < 2 * V; ++i) acc[i] = 0.0f;
+    if (ch < chunks && slice < N) {
+      const int col = piece_col<RAG, V>(ch, chunks, M);
+      int64_t e = static_cast<int64_t>(slice) * M + col;
+      u32x4 d = load(dy + e), o = load(y + e);
+      float ga[V], be[V];
+      load_cols<RAG, V>(gamma + col, ga);
+      load_cols<RAG, V>(beta + col, be);
+      const Xhat<RAG, V> xhat(ga, be);
+      for (int row = slice; row < N; row += kSlices) {
+        u32x4 next_d = d, next_o = o;
+        e += static_cast<int64_t>(kSlices) * M;
+        if (row + kSlices < N) {
+          next_d = load(dy + e);
+          next_o = load(y + e);
+        }
+        float d8[V], y8[V], h[V];
+        Store<T>::unpack(d, d8);
+        Store<T>::unpack(o, y8);
+        xhat(y8, h);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          acc[i] = fmaf(d8[i], h[i], acc[i]);
+          acc[V + i] += d8[i];
+        }
+        d = next_d;
+        o = next_o;
+      }
+    }
+    // over the 16 lanes of the wave that own the same piece, then over the waves
+    auto add = [](float a, float b) { return a + b; };
+#pragma unroll
+    for (int i = 0; i < 2 * V; ++i) {
+      acc[i] += dpp_f32<kDppRor4>(acc[i]);
+      acc[i] += dpp_f32<kDppRor8>(acc[i]);
+      acc[i] = across_rows<32>(across_rows<16>(acc[i], add), add);
+    }
+    if ((threadIdx.x & (kWave - 1)) < kFewColLanes) {
+#pragma unroll
+      for (int i = 0; i < 2 * V; ++i) sums[threadIdx.x / kWave][t][i] = acc[i];
+    }
+    lds_barrier();
+    const int k = threadIdx.x / (2 * V), i = threadIdx.x % (2 * V);
+    const int sum_ch = block * kFewColLanes + k;
+    if (k < kFewColLanes && sum_ch < chunks && i % V >= piece_dup<RAG, V>(sum_ch, chunks, M)) {
+      float s = sums[0][k][i];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) s += sums[w][k][i];
+      (i < V ? dgamma : dbeta)[piece_col<RAG, V>(sum_ch, chunks, M) + i % V] = s;
+    }
+    return;
+  }
+  constexpr int kGroups = kFewThreads / LANES;
+  __shared__ float2 red[kWaves];
+  const int t = threadIdx.x % LANES;
+  const int row = (block - col_blocks) * kGroups + threadIdx.x / LANES;
+  const bool live = row < N;  // a group of several waves walks on: the row sums hold a barrier
+  if (LANES <= kWave && !live) return;
+  const int64_t e = static_cast<int64_t>(row) * M;
+  u32x4 d[CH], o[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int ch = c * LANES + t;
+    if (live && ch < chunks) {
+      d[c] = load(dy + e + piece_col<RAG, V>(ch, chunks, M));
+      o[c] = load(y + e + piece_col<RAG, V>(ch, chunks, M));
+    }
+  }
+  const float rs = live ? rstd[row] : 0.0f;
+  float h[CH][V], q[CH][V];
+  float c1 = 0.0f, c2 = 0.0f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int ch = c * LANES + t;
+    if (live && ch < chunks) {
+      float ga[V], be[V], d8[V], y8[V];
+      load_cols<RAG, V>(gamma + piece_col<RAG, V>(ch, chunks, M), ga);
+      load_cols<RAG, V>(beta + piece_col<RAG, V>(ch, chunks, M), be);
+      Store<T>::unpack(d[c], d8);
+      Store<T>::unpack(o[c], y8);
+      Xhat<RAG, V>(ga, be)(y8, h[c]);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        q[c][i] = d8[i] * ga[i];
+        if (!RAG || i >= piece_dup<RAG, V>(ch, chunks, M)) {
+          c1 = fmaf(q[c][i], h[c][i], c1);
+          c2 += q[c][i];
+        }
+      }
+    }
+  }
+  row_sum2<LANES>(c1, c2, red);
+  const float inv_m = 1.0f / static_cast<float>(M);
+  c1 *= inv_m;
+  c2 *= inv_m;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int ch = c * LANES + t;
+    if (live && ch < chunks) {
+      float r[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) r[i] = rs * (q[c][i] - fmaf(h[c][i], c1, c2));
+      stg_piece<RAG>(dx + e + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(r));
+    }
+  }
+}
+
 struct Shape {
   int lanes;
   int ch;
@@ -1175,6 +1346,71 @@ static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStre
   }
 }
 
+// Most rows that ln_bwd_few_kernel takes: a column's rows are walked in steps of 128.  Forward + backward, two
+// launches / one, us: f32 x 768 at 64, 256, 512, 640, 768 and 1024 rows 8.6, 9.0, 9.9, 10.1, 10.4, 10.8 / 6.2, 6.9,
+// 8.6, 9.1, 9.8, 10.8; bf16 x 1024 at 256, 512 and 1024 8.9, 9.4, 10.6 / 6.5, 8.5, 11.2; f32 x 4096 at 256 and 768
+// 14.2, 20.9 / 11.1, 21.6; x 1001 at 512 f32 11.2 / 9.7, bf16 11.2 / 9.9.
+constexpr int64_t kFewRows = 640;
+static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
+// Lanes and pieces per lane of a row in ln_bwd_few_kernel: a wave while that leaves at most four pieces, else
+// four waves.
+constexpr Shape few_shape(int pieces) {
+  for (int ch = 1; ch <= 4; ++ch)
+    if (pieces <= ch * kWave) return {kWave, ch};
+  for (int ch : {2, 3, 4, 6, 8})
+    if (pieces <= ch * 4 * kWave) return {4 * kWave, ch};
+  return {0, 0};
+}
+static bool few_rows(int64_t N, int64_t M, tempo_dtype dt) {
+  const int vec = dt == TEMPO_F32 ? 4 : 8;
+  return N >= 1 && N <= kFewRows && M >= vec && (M + vec - 1) / vec <= max_fast_pieces(vec);
+}
+template <typename T>
+static tempo_status ln_bwd_few(bool ragged, bool in_place, hipStream_t st, const void* dy, const void* y, const float* gamma,
+                               const float* beta, const float* rstd, void* dx, float* dgamma, float* dbeta, int64_t N,
+                               int64_t M) {
+  const int pieces = static_cast<int>((M + Store<T>::kVec - 1) / Store<T>::kVec);
+  const Shape sh = few_shape(pieces);
+  const int col_blocks = (pieces + kFewColLanes - 1) / kFewColLanes;
+  const int groups = kFewThreads / sh.lanes;
+  const int grid = col_blocks + static_cast<int>((N + groups - 1) / groups);
+  auto go = [&](auto lanes, auto ch) {
+    auto launch = [&](auto rag, int first, int count) {
+      hipLaunchKernelGGL((ln_bwd_few_kernel<T, decltype(lanes)::value, decltype(ch)::value, decltype(rag)::value>),
+                         dim3(count), dim3(kFewThreads), 0, st, static_cast<const T*>(dy), static_cast<const T*>(y),
+                         gamma, beta, rstd, static_cast<T*>(dx), dgamma, dbeta, static_cast<int>(N),
+                         static_cast<int>(M), col_blocks, first);
+      return launch_status();
+    };
+    auto halves = [&](auto rag) {
+      if (!in_place) return launch(rag, 0, grid);
+      const tempo_status columns = launch(rag, 0, col_blocks);
+      return columns != TEMPO_OK ? columns : launch(rag, col_blocks, grid - col_blocks);
+    };
+    return ragged ? halves(std::true_type{}) : halves(std::false_type{});
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, kWave> wave{};
+  constexpr integral_constant<int, 4 * kWave> waves{};
+  switch (sh.lanes * 100 + sh.ch) {
+    case 6401: return go(wave, integral_constant<int, 1>{});
+    case 6402: return go(wave, integral_constant<int, 2>{});
+    case 6403: return go(wave, integral_constant<int, 3>{});
+    case 6404: return go(wave, integral_constant<int, 4>{});
+    case 25602: return go(waves, integral_constant<int, 2>{});
+    case 25603: return go(waves, integral_constant<int, 3>{});
+    case 25604: return go(waves, integral_constant<int, 4>{});
+  }
+  if constexpr (std::is_same<T, float>::value) {
+    if (sh.ch == 6) return go(waves, integral_constant<int, 6>{});
+    if (sh.ch == 8) return go(waves, integral_constant<int, 8>{});
+  }
+  return TEMPO_ERR_UNSUPPORTED;
+}
+
 // Everything a backward launch depends on, taken from the knobs once: the workspace check and
 // the launch of one call always see the same plan.
 struct BwdLaunch {
@@ -1211,6 +1447,24 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
                                   int64_t N, int64_t M, tempo_dtype dt, hipStream_t st) {
   const BwdLaunch b = bwd_launch(N, M, dt);
   if (workspace_bytes < slot_bytes(b, M)) return TEMPO_ERR_WORKSPACE;
+  if (few_rows(N, M, dt)) {
+    const int64_t act = N * M * (dt == TEMPO_F32 ? 4 : 2), par = M * 4;
+    const bool in_place = overlap(dx, act, dy, act) || overlap(dx, act, y, act);
+    // dgamma or dbeta in the place of an input: left to the row kernel, which has read it all before they are written
+    bool apart = true;
+    auto keep_apart = [&](const void* in, int64_t bytes) {
+      apart = apart && !overlap(dgamma, par, in, bytes) && !overlap(dbeta, par, in, bytes);
+    };
+    keep_apart(dy, act);
+    keep_apart(y, act);
+    keep_apart(gamma, par);
+    keep_apart(beta, par);
+    keep_apart(rstd, N * 4);
+    if (apart)
+      return dt == TEMPO_F32
+                 ? ln_bwd_few<float>(is_ragged(M, dt), in_place, st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M)
+                 : ln_bwd_few<bf16_t>(is_ragged(M, dt), in_place, st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M);
+  }
   int grid = b.plan.grid;
   if (b.fast) {
     const Shape sh = b.sh;
