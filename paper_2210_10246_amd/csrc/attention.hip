@@ -344,17 +344,18 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
     T* __restrict__ out, uint32_t* __restrict__ keep_bits, int slices, int Sq, int Sk, float scale,
     RngArgs rng, FastDiv sets_per_slice, FastDiv heads, uint32_t first_set, int64_t kept) {
   static_assert(THREADS % LANES == 0 && THREADS % kWave == 0, "whole lane groups, whole waves");
+  constexpr bool kOneWave = butterfly_lanes(LANES) == LANES;  // a row inside one wave: no barriers
   constexpr int kGroups = THREADS / LANES;
   constexpr int V = Store<T>::kVec;
   int g = threadIdx.x / LANES;
-  if constexpr (LANES >= kWave) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
+  if constexpr (LANES % kWave == 0) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
   const int t = threadIdx.x % LANES;
   constexpr bool RAG = MASK == kRagged;
   constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
   const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
   const int64_t total_pieces = static_cast<int64_t>(slices) * Sq * pieces;
-  __shared__ float red[2][THREADS / kWave];
-  static_assert(LANES <= kWave || R == 1, "rows over several waves: one row per group");
+  __shared__ float red[2][kOneWave ? 1 : THREADS / butterfly_lanes(LANES)];
+  static_assert(kOneWave || R == 1, "rows over several waves: one row per group");
   static_assert(!RAG || R == 1, "ragged rows: one row per group");
   __shared__ uint8_t keep_lds[RAG ? kGroups : 1][RAG ? keep_row_bytes(LANES * CH * V) : 1];
 
@@ -388,14 +389,14 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
     if (limit[0] >= 0)
       draw_row_keep<LANES>(keep_row, base, g * Sk, Sk, t, rng, keep_bits,
                            static_cast<int64_t>(slices) * Sq * Sk);
-    if constexpr (LANES <= kWave) wave_lds_fence();  // else the reductions' barriers order it
+    if constexpr (kOneWave) wave_lds_fence();  // else the reductions' barriers order it
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     // no row: uniform over the lane group; a group of several waves walks on (no loads, no
     // stores) because the reductions below hold workgroup barriers
     const bool live = limit[r] >= 0;
-    if (LANES <= kWave && !live) continue;
+    if (kOneWave && !live) continue;
     const uint32_t row_off = static_cast<uint32_t>(g + r * kGroups) * Sk;  // elements from base
     float v[CH][V];
     float mx = -INFINITY;
@@ -537,14 +538,15 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
     uint32_t first_set) {
   static_assert(THREADS % LANES == 0 && THREADS % kWave == 0, "whole lane groups, whole waves");
   static_assert(!RAG || MASK != kMaskWords, "ragged rows: no whole words");
+  constexpr bool kOneWave = butterfly_lanes(LANES) == LANES;
   constexpr int kGroups = THREADS / LANES;
   constexpr int V = Store<T>::kVec;
   int g = threadIdx.x / LANES;
-  if constexpr (LANES >= kWave) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
+  if constexpr (LANES % kWave == 0) g = __builtin_amdgcn_readfirstlane(g);  // row math stays scalar
   const int t = threadIdx.x % LANES;
   constexpr bool SHORT = takes_short_rows(RAG, LANES, V);
   const int pieces = RAG ? (Sk + V - 1) / V : Sk / V;
-  __shared__ float red[THREADS / kWave];
+  __shared__ float red[kOneWave ? 1 : THREADS / butterfly_lanes(LANES)];
   constexpr bool kDraw = RAG && MASK == kMaskRegen;  // the keep bytes of the rows, drawn into LDS
   __shared__ uint8_t keep_lds[kDraw ? kGroups : 1][kDraw ? keep_row_bytes(LANES * CH * V) : 1];
 
@@ -576,7 +578,7 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
   if constexpr (kDraw) {
     uint8_t* const keep_row = keep_lds[g];
     if (live) draw_row_keep<LANES>(keep_row, base, row_off, Sk, t, rng, nullptr, 0);
-    if constexpr (LANES <= kWave) wave_lds_fence();
+    if constexpr (kOneWave) wave_lds_fence();
     else lds_barrier();
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(THREADS) void attn_bwd_kernel(
   } else if constexpr (MASK == kMaskRegen) {  // every lane takes part: lane pairs share draws
     lane_keep_bits<T, LANES, CH>(static_cast<uint64_t>(base) >> 3, row_off / V, t, rng, bits);
   }
-  if (LANES <= kWave && !live) return;
+  if (kOneWave && !live) return;
   float dp[CH][V], pr[CH][V];
   float dot = 0.0f;
 #pragma unroll
@@ -758,22 +760,26 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_generic_kernel(
 
 constexpr int kMaxPieces = 1024;  // 4 per lane of 4 waves
 
-// Shapes of the ragged rows (no others are taken, whatever the knobs say: ragged_shapes_exist()), in
-// workgroups of two waves (of the row's four where it takes four).  vec: elements per piece.
-constexpr int kRaggedMaxPieces = 4;
-constexpr bool is_ragged_shape(int lanes, int ch, int vec, bool backward) {
-  if (lanes == 2 * kWave) return ch == 1 && vec == 4;
-  return ch <= (backward && lanes == kWave ? 3 : kRaggedMaxPieces);
+constexpr int kRaggedMaxPieces = 4;  // per lane
+
+// Rows of one piece per lane on a number of lanes that is no power of two (odd_shape()) lie across the waves
+// of a workgroup, which takes as many rows as fill whole waves.
+constexpr bool is_odd(int lanes) { return (lanes & (lanes - 1)) != 0; }
+constexpr int odd_threads(int lanes) {
+  const int low = lanes & -lanes;
+  return lanes / low * (low > kWave ? low : kWave);
 }
 
 // Fewest lanes a workgroup may have: a row's, and two rows' where a forward row takes two waves.  One row /
 // two rows per workgroup, us: 32x16x1024x1024 bf16 518-542 / 497-519 by buffers, 16x16x505x505 f32 142 / 135,
 // 64x16x512x512 f32 506-545 / 516-528; 12x1024x1024 bf16 causal, on half the chip, 14.3 / 14.7.
 constexpr int least_threads(int lanes, bool backward) {
+  if (is_odd(lanes)) return odd_threads(lanes);
   return lanes <= kWave ? kWave : (backward ? lanes : 4 * kWave);
 }
-constexpr int ragged_threads(int lanes, bool backward) {
-  return lanes <= kWave ? 2 * kWave : least_threads(lanes, backward);
+// Lanes per workgroup of the ragged rows and of those on an odd number of lanes, whatever the knob says.
+constexpr int fixed_threads(int lanes, bool backward) {
+  return lanes <= kWave && !is_odd(lanes) ? 2 * kWave : least_threads(lanes, backward);
 }
 
 struct Shape {
@@ -824,9 +830,47 @@ constexpr Shape pick_wide_shape(int pieces, int min_lanes, int max_ch) {
 // 12x2048x2048 50 / 47, 5x16x896x896 66 / 61; f32 9x16x448x448 55.6 / 53.4, 2x16x1024x1024 61.3 / 60.6.
 // The backward has one shape whatever its mask comes from: the same sums in the same order.
 enum RowUse { kForward, kForwardCausal, kBackward };
+
+// Lanes that are no power of two, where those would leave a quarter of the lanes idle or more: the vector ALU, which
+// bounds the bfloat16 forward, works for idle lanes too, and the backward keeps fewer loads under way per wave.  The
+// price is a workgroup barrier per row sum.  Power of two / this, us:
+//  - 12 (bfloat16 only: 8 lanes share a float32 mask word), 24 and 48 lanes for 9..12, 17..24 and 33..48 pieces, both
+//    ways: bf16 48x16x80x80 17.5 / 17.0, 32x16x150x150 39.6 / 35.2, 16x16x333x333 padded 83.2 / 74.8, 16x16x384x384 89.3 /
+//    84.4; f32 32x16x96x96 26.5 / 26.0, 32x16x150x150 66.9 / 60.2;
+//  - backward on 96 lanes for 65..96 pieces, bf16 8x16x520x520 55.3 / 49.4, 8x16x765x765 117 / 106, 8x16x768x768 99.6 /
+//    99.0, f32 16x16x333x333 86.9 / 80.3; 160 for 129..160, bf16 2x16x1101x1101 63.2 / 55.1, 1280 70.9 / 69.0; 192 for
+//    161..192, bf16 1400 93.5 / 88.8, f32 4x16x701x701 93.1 / 87.9, but bf16 1501 106 / 115; 224 for 193..224 of bf16
+//    ragged, 1701 148 / 131, not aligned, 1792 133.1 / 133.1, nor f32, 800 107 / 108.5; 320 for 257..320, bf16 2x8x2100x2100
+//    105 / 96, 2560 140.0 / 138.7; 384 up to 352, bf16 2700 166 / 159, f32 2x16x1401x1401 174 / 168, not when full, bf16
+//    3072 195.5 / 200.5;
+//  - the bfloat16 forward without a causal mask, whose pieces a lane skips, only next to full lanes: 96 from 89 pieces,
+//    8x16x744x744 80.9 / 74.6 (704: 65.5 / 65.5, 520: 43.0 / 44.7); 192 of aligned rows, 2x16x1400x1400 72.7 / 68.4 (1501:
+//    80.4 / 81.8); 224 from 209, 1700 124 / 117 (1600: 86 / 92).  160, 320 and 384 lanes lose (1200 padded 47.6 / 56.1), and
+//    so does float32 from 96 lanes up (4x16x600x600 47.4 / 51.1).
+constexpr Shape odd_shape(int p, bool ragged, int vec, RowUse use) {
+  const bool bf16 = vec == 8;
+  if (p > 8 && p <= 12 && bf16) return {12, 1};
+  if (p > 16 && p <= 24) return {24, 1};
+  if (p > 32 && p <= 48) return {48, 1};
+  if (use == kBackward) {
+    if (p > 64 && p <= 96) return {96, 1};
+    if (p > 128 && p <= 160) return {160, 1};
+    if (p > 160 && p <= 192 && !(bf16 && ragged)) return {192, 1};
+    if (p > 192 && p <= 224 && bf16 && ragged) return {224, 1};
+    if (p > 256 && p <= 320) return {320, 1};
+    if (p > 320 && p <= 352) return {384, 1};
+  } else if (use == kForward && bf16) {
+    if (p > 88 && p <= 96) return {96, 1};
+    if (p > 160 && p <= 192 && !ragged) return {192, 1};
+    if (p > 208 && p <= 224) return {224, 1};
+  }
+  return {0, 0};
+}
 constexpr Shape shape_of(int p, bool ragged, int vec, int max_ch, RowUse use) {
   const bool backward = use == kBackward;
   if (ragged || max_ch <= kRaggedMaxPieces) {
+    const Shape odd = odd_shape(p, ragged, vec, use);
+    if (odd.ch != 0) return odd;
     const int wide = p <= 2 * kWave ? 2 * kWave : kThreads;
     const bool two_ragged_bf16 = ragged && vec == 8 && wide == 2 * kWave;
     if (p > kWave && p <= kThreads && p * 8 >= wide * (backward ? 6 : 7) && !two_ragged_bf16)
@@ -840,11 +884,22 @@ Shape row_shape(int64_t Sk, int vec, int max_ch, RowUse use) {
   if (pieces > kMaxPieces) return {0, 0};
   return shape_of(static_cast<int>(pieces), Sk % 8 != 0, vec, max_ch, use);
 }
+// Whether rows come to a shape: all that ragged rows and odd numbers of lanes have kernels for.  (Aligned rows on a
+// power of two come to any, by the knobs.)
+constexpr bool has_kernel(int lanes, int ch, int vec, bool ragged, bool backward) {
+  if (!ragged && !is_odd(lanes)) return true;
+  for (int p = 1; p <= kMaxPieces; ++p) {
+    for (RowUse use : {kForward, kForwardCausal, kBackward}) {
+      const Shape sh = shape_of(p, ragged, vec, 1, use);
+      if (sh.lanes == lanes && sh.ch == ch && (use == kBackward) == backward) return true;
+    }
+  }
+  return false;
+}
 constexpr bool ragged_shapes_exist(int vec) {
   for (int p = 1; p <= kMaxPieces; ++p) {
     for (RowUse use : {kForward, kForwardCausal, kBackward}) {
-      const Shape sh = shape_of(p, true, vec, 1, use);
-      if (sh.ch == 0 || !is_ragged_shape(sh.lanes, sh.ch, vec, use == kBackward)) return false;
+      if (shape_of(p, true, vec, 1, use).ch == 0) return false;
     }
   }
   return true;
@@ -929,6 +984,7 @@ int kept_mib(int64_t n, tempo_dtype dt) { return dt == TEMPO_BF16 && n * 2 >= in
 // waves do no better than two and lose 1-2 % in places.  So: two waves, and never fewer lanes
 // than a row takes.
 int group_threads(int lanes, bool backward) {
+  if (is_odd(lanes)) return odd_threads(lanes);
   const int least = least_threads(lanes, backward);  // 64, 128 or 256
   int want = tune_get(kTuneAttnThreads);
   want = want >= 256 ? 256 : (want >= 128 ? 128 : kWave);
@@ -949,8 +1005,11 @@ int row_grid(int64_t rows, int blocks_per_cu) {
   switch (sh.lanes * 100 + sh.ch) {                                                        \
     case 401: LAUNCH(4, 1); break;                                                         \
     case 801: LAUNCH(8, 1); break;                                                         \
+    case 1201: LAUNCH(12, 1); break;                                                       \
     case 1601: LAUNCH(16, 1); break;                                                       \
+    case 2401: LAUNCH(24, 1); break;                                                       \
     case 3201: LAUNCH(32, 1); break;                                                       \
+    case 4801: LAUNCH(48, 1); break;                                                       \
     case 6401: LAUNCH(64, 1); break;                                                       \
     case 6402: LAUNCH(64, 2); break;                                                       \
     case 6403: LAUNCH(64, 3); break;                                                       \
@@ -964,24 +1023,30 @@ int row_grid(int64_t rows, int blocks_per_cu) {
 
 #define TEMPO_ATTN_WIDE_DISPATCH(LAUNCH)                                                   \
   switch (sh.lanes * 100 + sh.ch) {                                                        \
+    case 9601: LAUNCH(96, 1); break;                                                       \
     case 12801: LAUNCH(128, 1); break;                                                     \
     case 12802: LAUNCH(128, 2); break;                                                     \
     case 12803: LAUNCH(128, 3); break;                                                     \
     case 12804: LAUNCH(128, 4); break;                                                     \
+    case 16001: LAUNCH(160, 1); break;                                                     \
+    case 19201: LAUNCH(192, 1); break;                                                     \
+    case 22401: LAUNCH(224, 1); break;                                                     \
     case 25601: LAUNCH(256, 1); break;                                                     \
     case 25602: LAUNCH(256, 2); break;                                                     \
     case 25603: LAUNCH(256, 3); break;                                                     \
     case 25604: LAUNCH(256, 4); break;                                                     \
+    case 32001: LAUNCH(320, 1); break;                                                     \
+    case 38401: LAUNCH(384, 1); break;                                                     \
     default: return TEMPO_ERR_UNSUPPORTED;                                                 \
   }
 
 // Calls f with the workgroup size as a compile-time constant: 64, 128 or 256, at least
-// least_threads; with FIXED the default size only.
+// least_threads; with FIXED and for odd numbers of lanes the only size.
 template <int L, bool BACKWARD, bool FIXED, typename F>
 static void with_threads(int threads, F&& f) {
   using std::integral_constant;
-  if constexpr (FIXED) {
-    return f(integral_constant<int, ragged_threads(L, BACKWARD)>{});
+  if constexpr (FIXED || is_odd(L)) {
+    return f(integral_constant<int, fixed_threads(L, BACKWARD)>{});
   } else {
     constexpr int least = least_threads(L, BACKWARD);
     if constexpr (least <= 64) {
@@ -1013,17 +1078,19 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint
   using std::integral_constant;
   const integral_constant<MaskLayout, kWords> words{};
   const integral_constant<MaskLayout, kBytes> bytes{};
-  if constexpr (C <= 2 && L <= kWave) {
+  if constexpr (C <= 2 && L <= kWave && !is_odd(L)) {
     if (rr == 2) {
       if (layout == kWords) return go(integral_constant<int, 2>{}, words);
       return go(integral_constant<int, 2>{}, bytes);
     }
   }
-  if constexpr (is_ragged_shape(L, C, Store<T>::kVec, false)) {
+  if constexpr (has_kernel(L, C, Store<T>::kVec, true, false)) {
     if (layout == kRagged) return go(integral_constant<int, 1>{}, integral_constant<MaskLayout, kRagged>{});
   }
-  if (layout == kWords) return go(integral_constant<int, 1>{}, words);
-  go(integral_constant<int, 1>{}, bytes);
+  if constexpr (has_kernel(L, C, Store<T>::kVec, false, false)) {
+    if (layout == kWords) return go(integral_constant<int, 1>{}, words);
+    go(integral_constant<int, 1>{}, bytes);
+  }
 }
 
 template <typename T, int L, int C>
@@ -1043,17 +1110,19 @@ static void attn_bwd_go(MaskSource mask, bool ragged, int threads, size_t lds, u
   const integral_constant<MaskSource, kMaskBytes> bytes{};
   const integral_constant<MaskSource, kMaskBools> bools{};
   const integral_constant<MaskSource, kMaskRegen> regen{};
-  if constexpr (is_ragged_shape(L, C, Store<T>::kVec, true)) {
+  if constexpr (has_kernel(L, C, Store<T>::kVec, true, true)) {
     if (ragged) {
       if (mask == kMaskBytes) return go(bytes, std::true_type{});
       if (mask == kMaskBools) return go(bools, std::true_type{});
       return go(regen, std::true_type{});
     }
   }
-  if (mask == kMaskWords) return go(integral_constant<MaskSource, kMaskWords>{}, std::false_type{});
-  if (mask == kMaskBytes) return go(bytes, std::false_type{});
-  if (mask == kMaskBools) return go(bools, std::false_type{});
-  go(regen, std::false_type{});
+  if constexpr (has_kernel(L, C, Store<T>::kVec, false, true)) {
+    if (mask == kMaskWords) return go(integral_constant<MaskSource, kMaskWords>{}, std::false_type{});
+    if (mask == kMaskBytes) return go(bytes, std::false_type{});
+    if (mask == kMaskBools) return go(bools, std::false_type{});
+    go(regen, std::false_type{});
+  }
 }
 
 static RngArgs make_rng(float p, uint64_t seed, uint64_t offset) {
@@ -1095,7 +1164,7 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const int rr = sh.lanes > kWave || ragged
                        ? 1 : attn_rows(sh.ch, sh.lanes, vec, tune_get(kTuneAttnFwdRows));
     const int threads =
-        ragged ? ragged_threads(sh.lanes, false) : group_threads(sh.lanes, false);
+        ragged ? fixed_threads(sh.lanes, false) : group_threads(sh.lanes, false);
     const int rows_per_set = (threads / sh.lanes) * rr;
     const FastDiv sets_per_slice(static_cast<uint32_t>((Sq + rows_per_set - 1) / rows_per_set));
     const FastDiv heads(static_cast<uint32_t>(A));
@@ -1162,7 +1231,7 @@ static tempo_status attn_bwd_any(const void* dout, const void* probs, const uint
   const Shape sh = row_shape(Sk, vec, tune_get(kTuneAttnBwdMaxPieces), kBackward);
   if (sh.ch != 0 && rows <= UINT32_MAX) {  // rows counted in 32 bits
     const int threads =
-        ragged ? ragged_threads(sh.lanes, true) : group_threads(sh.lanes, true);
+        ragged ? fixed_threads(sh.lanes, true) : group_threads(sh.lanes, true);
     const int64_t total_sets = (rows + threads / sh.lanes - 1) / (threads / sh.lanes);
     const int pieces = static_cast<int>((Sk + vec - 1) / vec);
     const size_t lds = residency_lds_bytes(bwd_waves(sh, pieces, regen, ragged), threads);

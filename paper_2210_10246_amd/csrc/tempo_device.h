@@ -309,27 +309,32 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// Lanes that reduce by butterflies alone: those of a row inside one wave, a wave of a row over several, the
+// largest power of two in rows of 24, 48 or 96 lanes, which lie across waves.
+constexpr int butterfly_lanes(int lanes) {
+  return lanes >= kWave && lanes % kWave == 0 ? kWave : (lanes & -lanes);
+}
+
 // Row reductions for rows owned by LANES consecutive threads of a workgroup.  A row inside
-// one wave: butterflies.  A row spread over LANES/64 waves: butterfly per wave, then one
-// exchange through `slots` (one entry per wave of the workgroup) behind a workgroup barrier, so
+// one wave: butterflies.  Any other: a butterfly per unit (butterfly_lanes), then one
+// exchange through `slots` (one entry per unit of the workgroup) behind a workgroup barrier, so
 // every thread of the workgroup has to make the call; consecutive calls must alternate between
 // two slot arrays (a fast wave may already write its next value while a slow one still reads).
 // Every lane of the row ends with the same result.
 template <int LANES, bool MAX>
 __device__ __forceinline__ float row_reduce(float v, float* slots) {
-  if constexpr (LANES <= kWave) {
-    return MAX ? group_max<LANES>(v) : group_sum<LANES>(v);
-  } else {
-    v = MAX ? group_max<kWave>(v) : group_sum<kWave>(v);
-    if ((threadIdx.x & (kWave - 1)) == 0) slots[threadIdx.x / kWave] = v;
+  constexpr int U = butterfly_lanes(LANES);
+  v = MAX ? group_max<U>(v) : group_sum<U>(v);
+  if constexpr (U < LANES) {
+    if (threadIdx.x % U == 0) slots[threadIdx.x / U] = v;
     lds_barrier();
-    constexpr int W = LANES / kWave;
+    constexpr int W = LANES / U;
     const int w0 = (threadIdx.x / LANES) * W;
-    float r = slots[w0];
+    v = slots[w0];
 #pragma unroll
-    for (int k = 1; k < W; ++k) r = MAX ? fmaxf(r, slots[w0 + k]) : r + slots[w0 + k];
-    return r;
+    for (int k = 1; k < W; ++k) v = MAX ? fmaxf(v, slots[w0 + k]) : v + slots[w0 + k];
   }
+  return v;
 }
 
 // Two sums at once (one barrier for both); slots holds two floats per wave of the workgroup.
