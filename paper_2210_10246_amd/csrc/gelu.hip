@@ -231,9 +231,9 @@ __global__ __launch_bounds__(THREADS) void gelu_bwd_kernel(const float* dy,  // 
 // 16 KiB forward, 32 KiB backward.  Per element this leaves a handful of integer ops, one
 // ds_read_b32 and one multiply, which keeps the vector ALU far below the memory time (the
 // cubic path above costs ~40 VALU ops per element, more than a bf16 element's share of HBM
-// time).  Workgroups of 1024 lanes own contiguous tiles of K pieces
+// time).  Workgroups own contiguous tiles of up to K pieces
 // per lane.
-constexpr int kLutBwdThreads = 1024;  // 512 is 2-5 % slower
+constexpr int kLutThreads = 1024;
 
 template <int WORDS, int THREADS>
 __device__ __forceinline__ void stage_lut(uint32_t* lds, const uint32_t* src) {
@@ -341,27 +341,41 @@ __device__ __forceinline__ void store_tail_bf16(bf16_t* p, int64_t left, const u
 
 constexpr uint32_t kAbsentX = 0xF149F149u;  // two bf16 of about -2.5e30: mask bit 0
 
-// THREADS lanes per workgroup: 1024, or 512 with half the pieces per lane for large tensors
-// (2-4 % faster from 130 MB of traffic up, 20 % slower at 70 MB).
-template <int KIND, int K, int THREADS>
+// A workgroup's pieces: THREADS*K of them, or with SPLIT the first `tile` (whole waves) of as many, so that the
+// grid gives every compute unit the same number of equal workgroups (lut_shape()).
+template <int K, int THREADS, bool SPLIT>
+struct LutTile {
+  int64_t first;  // the lane's first piece
+  bool full;      // the whole tile is inside the tensor
+  int waves_at, size;
+  __device__ __forceinline__ LutTile(int64_t n, int tile)
+      : waves_at(__builtin_amdgcn_readfirstlane(threadIdx.x & ~(kWave - 1))), size(SPLIT ? tile : THREADS * K) {
+    first = static_cast<int64_t>(blockIdx.x) * size + threadIdx.x;
+    full = (static_cast<int64_t>(blockIdx.x) + 1) * size * 8 <= n;
+  }
+  __device__ __forceinline__ bool has(int k) const { return !SPLIT || k * THREADS + waves_at < size; }
+};
+
+template <int KIND, int K, int THREADS, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, bf16_t* y,
                                                                    uint32_t* __restrict__ mask,
-                                                                   int64_t n, int64_t kept) {
+                                                                   int64_t n, int64_t kept, int tile_size) {
   __shared__ uint32_t lut[2 * TEMPO_GELU_LUT_N];
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t q_base = static_cast<int64_t>(blockIdx.x) * (THREADS * K) + threadIdx.x;
-  const bool full = (static_cast<int64_t>(blockIdx.x) + 1) * (THREADS * K) * 8 <= n;
-  const bool cached = static_cast<int64_t>(blockIdx.x) * (THREADS * K) * 8 < kept;
+  const LutTile<K, THREADS, SPLIT> tile(n, tile_size);
+  const bool cached = static_cast<int64_t>(blockIdx.x) * tile.size * 8 < kept;
   u32x4 w[K];
-  if (full) {  // whole tile inside the tensor: straight-line loads
+  if (tile.full) {  // straight-line loads
 #pragma unroll
-    for (int k = 0; k < K; ++k) w[k] = ldg_stream(x + (q_base + k * THREADS) * 8);
+    for (int k = 0; k < K; ++k)
+      if (tile.has(k)) w[k] = ldg_stream(x + (tile.first + k * THREADS) * 8);
   } else {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int64_t q = q_base + k * THREADS;
+      const int64_t q = tile.first + k * THREADS;
       const int64_t left = n - q * 8;
       w[k] = u32x4{kAbsentX, kAbsentX, kAbsentX, kAbsentX};
+      if (!tile.has(k)) continue;
       if (left >= 8) w[k] = ldg_stream(x + q * 8);
       else if (left > 0) w[k] = load_tail_bf16(x + q * 8, left, kAbsentX);
     }
@@ -369,13 +383,14 @@ __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, 
   stage_lut<2 * TEMPO_GELU_LUT_N, THREADS>(lut, GeluConst<KIND>::lut_fwd());
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const int64_t q = q_base + k * THREADS;
+    if (!tile.has(k)) continue;
+    const int64_t q = tile.first + k * THREADS;
     u32x4 yw;
     uint32_t byte;
     gelu_fwd_lut_chunk(w[k], lut, yw, byte);
     // every lane of the wave takes part in the merge; absent chunks contribute zero bits
     const uint32_t word = merge_mask_word<8>(byte, lane);
-    if (full) {
+    if (tile.full) {
       stg_kept<false>(y + q * 8, yw, cached);
       if ((lane & 3) == 0) mask[q >> 2] = word;
     } else {
@@ -387,20 +402,20 @@ __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, 
   }
 }
 
-template <int KIND, int K>
-__global__ __launch_bounds__(kLutBwdThreads) void gelu_bwd_lut_kernel(const bf16_t* dy,
+template <int KIND, int K, int THREADS, bool SPLIT>
+__global__ __launch_bounds__(THREADS) void gelu_bwd_lut_kernel(const bf16_t* dy,
                                                                    const bf16_t* __restrict__ y,
                                                                    const uint32_t* __restrict__ mask,
-                                                                   bf16_t* dx, int64_t n) {
+                                                                   bf16_t* dx, int64_t n, int tile_size) {
   __shared__ uint32_t lut[4 * TEMPO_GELU_LUT_N];
-  const int64_t q_base = static_cast<int64_t>(blockIdx.x) * (kLutBwdThreads * K) + threadIdx.x;
-  const bool full = (static_cast<int64_t>(blockIdx.x) + 1) * (kLutBwdThreads * K) * 8 <= n;
+  const LutTile<K, THREADS, SPLIT> tile(n, tile_size);
   u32x4 wy[K], wd[K];
   uint32_t mw[K];
-  if (full) {
+  if (tile.full) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int64_t q = q_base + k * kLutBwdThreads;
+      const int64_t q = tile.first + k * THREADS;
+      if (!tile.has(k)) continue;
       wd[k] = ldg_stream(dy + q * 8);
       wy[k] = ldg_stream(y + q * 8);
       mw[k] = __builtin_nontemporal_load(mask + (q >> 2));
@@ -408,10 +423,11 @@ __global__ __launch_bounds__(kLutBwdThreads) void gelu_bwd_lut_kernel(const bf16
   } else {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int64_t q = q_base + k * kLutBwdThreads;
+      const int64_t q = tile.first + k * THREADS;
       const int64_t left = n - q * 8;
       wy[k] = wd[k] = u32x4{0u, 0u, 0u, 0u};
       mw[k] = 0;
+      if (!tile.has(k)) continue;
       if (left >= 8) {
         wd[k] = ldg_stream(dy + q * 8);
         wy[k] = ldg_stream(y + q * 8);
@@ -422,13 +438,14 @@ __global__ __launch_bounds__(kLutBwdThreads) void gelu_bwd_lut_kernel(const bf16
       if (left > 0) mw[k] = mask[q >> 2];
     }
   }
-  stage_lut<4 * TEMPO_GELU_LUT_N, kLutBwdThreads>(lut, GeluConst<KIND>::lut_bwd());
+  stage_lut<4 * TEMPO_GELU_LUT_N, THREADS>(lut, GeluConst<KIND>::lut_bwd());
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const int64_t q = q_base + k * kLutBwdThreads;
+    if (!tile.has(k)) continue;
+    const int64_t q = tile.first + k * THREADS;
     const uint32_t byte = mw[k] >> (8 * static_cast<int>(q & 3));
     const u32x4 r = gelu_bwd_lut_chunk<GeluConst<KIND>::kLutLeftShift>(wy[k], wd[k], byte, lut);
-    if (full) {
+    if (tile.full) {
       stg_stream(dx + q * 8, r);
     } else {
       const int64_t left = n - q * 8;
@@ -438,12 +455,40 @@ __global__ __launch_bounds__(kLutBwdThreads) void gelu_bwd_lut_kernel(const bf16
   }
 }
 
-int lut_grid(int64_t n, int k, int threads) {
-  const int64_t n_chunks = (n + 7) / 8;
-  const int64_t per_block = static_cast<int64_t>(threads) * k;
-  return static_cast<int>((n_chunks + per_block - 1) / per_block);
+// Launch shape of the bfloat16 kernels.  Knobs 0 and 1 at another value than their defaults fix the pieces per lane
+// of workgroups of 1024 lanes.
+//  - Few elements: small workgroups, so that all compute units have one and a wave runs through less code.  4 (backward
+//    2) pieces per lane of 1024 lanes / 256 lanes of one piece, us: 32 Ki elements forward 3.8 / 2.0, backward 3.4 /
+//    2.1, 512 Ki 4.2 / 2.2 and 4.4 / 2.4; / 512 lanes forward 2 Mi 5.1 / 3.3, 4 Mi 5.5 / 4.4.
+//  - Where whole tiles give some compute units one workgroup more than the others, all wait for those: the tile
+//    shrinks until all have the same number (SPLIT).  Whole / split, forward: 8.8 Mi 10.1 / 6.6, 12 Mi 10.9 / 8.5, 14.7
+//    Mi 11.1 / 10.5, 20 Mi 16.3 / 15.0; not with a single workgroup each, 8 Mi 6.2 / 6.5.  Backward, whose lookups
+//    overlap less for the branches between the pieces, only up to three quarters of a tile per compute unit: 1.4 Mi
+//    4.9 / 3.8, 3 Mi 5.6 / 5.2, but 4 Mi 5.8 / 6.1, 14.7 Mi 18.1 / 19.3.
+//  - Forward from knob 13's 24 Mi: 512 lanes with half the pieces (2-4 % faster from 130 MB of traffic up, 20 % slower
+//    at 70 MB).
+struct LutShape {
+  int threads, k;
+  bool split;
+  int tile;  // pieces per workgroup
+};
+static LutShape lut_shape(bool forward, int64_t n, int k) {
+  const int64_t pieces = (n + 7) / 8;
+  auto whole = [](int threads, int k) { return LutShape{threads, k, false, threads * k}; };
+  if (forward && k >= 2 && n >= tune_get(kTuneGeluFwdSmallGroupsFrom) * int64_t{1048576}) return whole(512, k / 2);
+  if (k != (forward ? 4 : 2)) return whole(kLutThreads, k);
+  if (n <= int64_t{640} << 10) return whole(256, 1);
+  if (forward && n <= int64_t{4} << 20) return whole(512, 1);
+  const int64_t cus = compute_units(), most = kLutThreads * k;
+  const int64_t per_cu = (pieces + cus * most - 1) / (cus * most);
+  const int64_t even = (pieces + cus * per_cu - 1) / (cus * per_cu);
+  if (forward ? per_cu < 2 : (per_cu > 1 || even * 4 > most * 3)) return whole(kLutThreads, k);
+  const int tile = static_cast<int>((even + kWave - 1) / kWave * kWave);
+  return {kLutThreads, tile <= most / 2 ? k / 2 : k, true, tile};
 }
-
+static int lut_grid(int64_t n, const LutShape& sh) {
+  return static_cast<int>(((n + 7) / 8 + sh.tile - 1) / sh.tile);
+}
 
 int tile_grid(int64_t n, int k, int threads) {  // float32 pieces of 4 elements
   const int64_t n_pieces = (n + 3) / 4;
@@ -470,10 +515,10 @@ struct F32Shape {
   int threads;
   int k;
 };
-static F32Shape f32_shape(bool forward, int kind) {
+// Backward of up to 256 Ki elements one piece: 32 Ki 2.75 -> 2.3 us, 200 Ki 3.1 -> 2.8, but 300 Ki silu 3.4 -> 3.5.
+static F32Shape f32_shape(bool forward, int64_t n) {
   const int forced = tune_get(kTuneGeluF32Threads);
-  (void)kind;
-  if (forced == 1) return forward ? F32Shape{64, 1} : F32Shape{256, 2};
+  if (forced == 1) return forward ? F32Shape{64, 1} : F32Shape{256, n <= (256 << 10) ? 1 : 2};
   const int k = pick_k(tune_get(forward ? kTuneGeluFwdChunks : kTuneGeluBwdChunks));
   return {forced >= 256 ? 256 : (forced >= 128 ? 128 : 64), k};
 }
@@ -498,26 +543,45 @@ static void with_kind_k(int kind, int k, F&& f) {
   else with_k<kActSilu>(k, f);
 }
 
+// Calls f with the shape's lanes, pieces per lane and SPLIT as compile-time constants.
+template <typename F>
+static void with_lut_shape(const LutShape& sh, F&& f) {
+  using std::integral_constant;
+  auto pieces = [&](auto threads, auto split) {
+    if (sh.k == 1) f(threads, integral_constant<int, 1>{}, split);
+    else if (sh.k == 2) f(threads, integral_constant<int, 2>{}, split);
+    else f(threads, integral_constant<int, 4>{}, split);
+  };
+  if (sh.threads == 256) f(integral_constant<int, 256>{}, integral_constant<int, 1>{}, std::false_type{});
+  else if (sh.threads == 512 && sh.k == 1) f(integral_constant<int, 512>{}, integral_constant<int, 1>{}, std::false_type{});
+  else if (sh.threads == 512) f(integral_constant<int, 512>{}, integral_constant<int, 2>{}, std::false_type{});
+  else if (sh.split) pieces(integral_constant<int, kLutThreads>{}, std::true_type{});
+  else pieces(integral_constant<int, kLutThreads>{}, std::false_type{});
+}
+template <typename F>
+static void with_kind(int kind, F&& f) {
+  if (kind == TEMPO_GELU_ERF) f(std::integral_constant<int, TEMPO_GELU_ERF>{});
+  else if (kind == TEMPO_GELU_TANH) f(std::integral_constant<int, TEMPO_GELU_TANH>{});
+  else f(std::integral_constant<int, kActSilu>{});
+}
+
 tempo_status launch_gelu_fwd(const void* x, void* y, uint32_t* mask, int64_t n, tempo_dtype dt,
                              int kind, hipStream_t st) {
   const int k = pick_k(tune_get(kTuneGeluFwdChunks));
   if (dt == TEMPO_BF16) {
     const int64_t kept = kept_elements(n, 2, kKeptFromMiB, kKeptMiB);
-    // large tensors: half-size workgroups with half the pieces per lane
-    const bool small_groups = n >= tune_get(kTuneGeluFwdSmallGroupsFrom) * int64_t{1048576} && k >= 2;
-    with_kind_k(kind, small_groups ? k / 2 : k, [&](auto kd, auto kk) {
-      constexpr int KD = decltype(kd)::value, KK = decltype(kk)::value;
-      if (small_groups)
-        hipLaunchKernelGGL((gelu_fwd_lut_kernel<KD, KK, 512>), dim3(lut_grid(n, KK, 512)), dim3(512),
-                           0, st, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y), mask, n, kept);
-      else
-        hipLaunchKernelGGL((gelu_fwd_lut_kernel<KD, KK, 1024>), dim3(lut_grid(n, KK, 1024)),
-                           dim3(1024), 0, st, static_cast<const bf16_t*>(x),
-                           static_cast<bf16_t*>(y), mask, n, kept);
+    const LutShape sh = lut_shape(true, n, k);
+    with_kind(kind, [&](auto kd) {
+      with_lut_shape(sh, [&](auto th, auto kk, auto split) {
+        constexpr int TH = decltype(th)::value;
+        hipLaunchKernelGGL((gelu_fwd_lut_kernel<decltype(kd)::value, decltype(kk)::value, TH, decltype(split)::value>),
+                           dim3(lut_grid(n, sh)), dim3(TH), 0, st, static_cast<const bf16_t*>(x),
+                           static_cast<bf16_t*>(y), mask, n, kept, sh.tile);
+      });
     });
     return launch_status();
   }
-  const F32Shape sh = f32_shape(true, kind);
+  const F32Shape sh = f32_shape(true, n);
   with_kind_k(kind, sh.k, [&](auto kd, auto kk) {
     with_f32_threads(sh.threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
@@ -533,15 +597,18 @@ tempo_status launch_gelu_bwd(const void* dy, const void* y, const uint32_t* mask
                              int64_t n, tempo_dtype dt, int kind, hipStream_t st) {
   const int k = pick_k(tune_get(kTuneGeluBwdChunks));
   if (dt == TEMPO_BF16) {
-    with_kind_k(kind, k, [&](auto kd, auto kk) {
-      hipLaunchKernelGGL((gelu_bwd_lut_kernel<decltype(kd)::value, decltype(kk)::value>),
-                         dim3(lut_grid(n, k, kLutBwdThreads)), dim3(kLutBwdThreads), 0, st,
-                         static_cast<const bf16_t*>(dy), static_cast<const bf16_t*>(y), mask,
-                         static_cast<bf16_t*>(dx), n);
+    const LutShape sh = lut_shape(false, n, k);
+    with_kind(kind, [&](auto kd) {
+      with_lut_shape(sh, [&](auto th, auto kk, auto split) {
+        constexpr int TH = decltype(th)::value;
+        hipLaunchKernelGGL((gelu_bwd_lut_kernel<decltype(kd)::value, decltype(kk)::value, TH, decltype(split)::value>),
+                           dim3(lut_grid(n, sh)), dim3(TH), 0, st, static_cast<const bf16_t*>(dy),
+                           static_cast<const bf16_t*>(y), mask, static_cast<bf16_t*>(dx), n, sh.tile);
+      });
     });
     return launch_status();
   }
-  const F32Shape sh = f32_shape(false, kind);
+  const F32Shape sh = f32_shape(false, n);
   with_kind_k(kind, sh.k, [&](auto kd, auto kk) {
     with_f32_threads(sh.threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
