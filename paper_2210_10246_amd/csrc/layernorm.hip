@@ -287,7 +287,7 @@ template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     const T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ rstd, T* dx,
-    float* __restrict__ partial, int64_t N, int M) {
+    float* __restrict__ partial, int64_t N, int M, int slot_row) {
   extern __shared__ float lds[];  // bwd_lds_bytes(): the tree's [slots][2][M] floats, >= 3*M
   constexpr int kGroups = kBwdThreads / LANES;
   constexpr int V = Store<T>::kVec;
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
   const bool owner = lane < LANES;  // one copy per wave
   constexpr int kRowWaves = LANES > kWave ? LANES / kWave : 1;
   constexpr int S = kBwdWaves / kRowWaves;
-  float* out = partial + static_cast<size_t>(blockIdx.x) * 2 * M;
+  float* out = partial + static_cast<size_t>(blockIdx.x) * 2 * slot_row;
   if (static_cast<size_t>(S) * 2 * Ml * sizeof(float) <= kOneStepLdsBytes) {
     if constexpr (!kRegParams) lds_barrier();  // the parameters in LDS are no longer read
     if (owner) {
@@ -578,9 +578,9 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
           for (int i = 0; i < 4; ++i) v[k][i] += v[k + half][i];
         }
       }
-      if constexpr (RAG) {  // from LDS rows of Ml to slot rows of M floats
+      if (RAG && slot_row != Ml) {  // from LDS rows of Ml to slot rows of M floats
         const int col = j < Ml ? j : j - Ml;
-        float* o = out + (j < Ml ? 0 : M) + col;
+        float* o = out + (j < Ml ? 0 : slot_row) + col;
         if (col + 4 <= M) {
           store_floats_any<4>(o, v[0]);
         } else {
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
       const int ch = c * LANES + t;
       if (ch < chunks) {
         store_col_sums<RAG, !RAG, V>(out, ch, chunks, M, acc_g[c]);
-        store_col_sums<RAG, !RAG, V>(out + M, ch, chunks, M, acc_b[c]);
+        store_col_sums<RAG, !RAG, V>(out + slot_row, ch, chunks, M, acc_b[c]);
       }
     }
   }
@@ -730,10 +730,10 @@ __global__ __launch_bounds__(256) void ln_bwd_generic_kernel(
   }
 }
 
-// dgamma[j] = sum_p partial[p][0][j], dbeta[j] = sum_p partial[p][1][j].  A workgroup of 4 waves
-// owns 32 adjacent columns of the [2][M] row, 8 lanes x 4 floats; its 32 slices each add every
+// dgamma[j] = sum_p partial[p][0][j], dbeta[j] = sum_p partial[p][1][j], slots of [2][slot_row >= M].  A workgroup of
+// 4 waves owns 32 adjacent columns of the [2][slot_row] row, 8 lanes x 4 floats; its 32 slices each add every
 // 32nd partial (all loads of a lane are independent and issued together), then the slices are
-// combined through LDS in a fixed order.  ANY (M odd): slots start at any float's address and the
+// combined through LDS in a fixed order.  ANY (slot_row odd): slots start at any float's address and the
 // last 16-byte piece of a slot is half a piece.
 constexpr int kFinCols = 32;   // 128 contiguous bytes per partial row
 constexpr int kFinSlices = 32;
@@ -741,15 +741,15 @@ constexpr int kFinVecLanes = kFinCols / 4;
 template <bool ANY>
 __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kernel(
     const float* __restrict__ partial, float* __restrict__ dgamma, float* __restrict__ dbeta,
-    int parts, int64_t M) {
+    int parts, int64_t M, int64_t slot_row) {
   __shared__ float lds[kFinSlices][kFinCols + 4];
   const int q = threadIdx.x % kFinVecLanes;
   const int slice = threadIdx.x / kFinVecLanes;
-  const int64_t j2 = static_cast<int64_t>(blockIdx.x) * kFinCols + q * 4;  // index into [2][M]
+  const int64_t j2 = static_cast<int64_t>(blockIdx.x) * kFinCols + q * 4;  // index into [2][slot_row]
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   auto add_up = [&](auto load) {  // load(address, four values)
     const float* p0 = partial + j2;
-    auto at = [&](int p) { return p0 + static_cast<size_t>(p) * 2 * M; };
+    auto at = [&](int p) { return p0 + static_cast<size_t>(p) * 2 * slot_row; };
     int p = slice;
     for (; p + 7 * kFinSlices < parts; p += 8 * kFinSlices) {
       float v[8][4];
@@ -781,9 +781,9 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
       for (int i = 0; i < 4; ++i) s[i] += v[i];
     }
   };
-  if (j2 + 4 <= 2 * M) {
+  if (j2 + 4 <= 2 * slot_row) {
     add_up([](const float* p, float (&v)[4]) { load_cols<ANY, 4>(p, v); });
-  } else if (ANY && j2 < 2 * M) {  // 2 * M - j2 is 2: the sums of two columns, as many loads under way
+  } else if (ANY && j2 < 2 * slot_row) {  // 2 * slot_row - j2 is 2: the sums of two columns, as many loads under way
     add_up([](const float* p, float (&v)[4]) {
       v[0] = p[0];
       v[1] = p[1];
@@ -794,12 +794,12 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
   lds_barrier();
   const int col = threadIdx.x;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kFinCols + col;
-  if (col < kFinCols && j < 2 * M) {
+  if (col < kFinCols && (j < M || (j >= slot_row && j < slot_row + M))) {
     float tot = 0.0f;
 #pragma unroll
     for (int k = 0; k < kFinSlices; ++k) tot += lds[k][col];
     if (j < M) dgamma[j] = tot;
-    else dbeta[j - M] = tot;
+    else dbeta[j - slot_row] = tot;
   }
 }
 
@@ -1285,7 +1285,7 @@ static size_t bwd_lds_bytes(const Shape& sh, int64_t M, tempo_dtype dt) {
 template <typename T, int L, int C>
 static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStream_t st, const void* dy,
                      const void* y, const float* gamma, const float* beta, const float* rstd,
-                     void* dx, float* workspace, int64_t N, int64_t M) {
+                     void* dx, float* workspace, int64_t N, int64_t M, int slot_row) {
   int grid = plan.grid;
   if constexpr ((std::is_same<T, bf16_t>::value && C > 4 && L > kWave) ||
                 (L == kBwdThreads && C != (std::is_same<T, bf16_t>::value ? 2 : 4))) {
@@ -1310,7 +1310,7 @@ static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStre
       }
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBwdThreads), lds_bytes, st,
                          static_cast<const T*>(dy), static_cast<const T*>(y), gamma, beta, rstd,
-                         static_cast<T*>(dx), workspace, N, static_cast<int>(M));
+                         static_cast<T*>(dx), workspace, N, static_cast<int>(M), slot_row);
     };
     auto go = [&](auto rows, auto loop) {
       if constexpr (is_ragged_shape(L, C, Store<T>::kVec, true)) {
@@ -1466,14 +1466,19 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
                  : ln_bwd_few<bf16_t>(is_ragged(M, dt), in_place, st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M);
   }
   int grid = b.plan.grid;
+  // Ragged rows' slots in whole 16-byte pieces, if the workspace, which is sized in rows of M, has room for that: it
+  // nearly always is sized for more slots than the launch has workgroups.  Backward, us, slot rows of M / padded: f32
+  // 1000x1001 9.5 / 8.8, 2048x1023 10.8 / 9.5, 8192x1001 24.0 / 23.5; bf16 2048x1001 9.8 / 9.4, 4096x4095 28.6 / 26.9.
+  int64_t slot_row = M;
+  if (b.fast && grid * lds_row(M) <= b.slots * M) slot_row = lds_row(M);
   if (b.fast) {
     const Shape sh = b.sh;
     const size_t lds_bytes = bwd_lds_bytes(sh, M, dt);
     const BwdPlan plan = b.plan;
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) grid = ln_bwd_go<float, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);   \
-    else grid = ln_bwd_go<bf16_t, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M);                  \
+    if (dt == TEMPO_F32) grid = ln_bwd_go<float, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M, static_cast<int>(slot_row));   \
+    else grid = ln_bwd_go<bf16_t, L, C>(plan, is_ragged(M, dt), lds_bytes, st, dy, y, gamma, beta, rstd, dx, workspace, N, M, static_cast<int>(slot_row));                  \
   } while (0)
     TEMPO_LN_DISPATCH(TEMPO_LAUNCH)
 #undef TEMPO_LAUNCH
@@ -1492,10 +1497,10 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
     else by_length(bf16_t{});
   }
   if (hipGetLastError() != hipSuccess) return TEMPO_ERR_LAUNCH;
-  const int fgrid = static_cast<int>((2 * M + kFinCols - 1) / kFinCols);
-  auto finalize = M % 2 == 0 ? ln_bwd_finalize_kernel<false> : ln_bwd_finalize_kernel<true>;
+  const int fgrid = static_cast<int>((2 * slot_row + kFinCols - 1) / kFinCols);
+  auto finalize = slot_row % 2 == 0 ? ln_bwd_finalize_kernel<false> : ln_bwd_finalize_kernel<true>;
   hipLaunchKernelGGL(finalize, dim3(fgrid), dim3(kFinVecLanes * kFinSlices), 0, st, workspace,
-                     dgamma, dbeta, grid, M);
+                     dgamma, dbeta, grid, M, slot_row);
   return launch_status();
 }
 
