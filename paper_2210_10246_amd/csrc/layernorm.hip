@@ -84,7 +84,9 @@ __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int
 // RAG: rows of any length that is no multiple of the piece (see piece_col): 16-byte accesses at
 // element-aligned addresses, columns on fixed lanes.  Bound by memory like the aligned rows: 8192 x 1001
 // f32 15.1 -> 13.1 us against element-wise accesses (1000 columns: 13.2), 4096 x 4100 bf16 40.6 -> 16.8.
-template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
+// KEPT: the first kept_rows rows of y are stored for the backward to find in a cache (stg_kept); a kernel of
+// its own, since the branches cost the others 1-2 % (584 x 3008 f32 4.39 -> 4.48 us, 8192 x 1024 bf16 7.0 -> 7.1).
+template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG, bool KEPT>
 __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
     const T* x, const float* __restrict__ gamma, const float* __restrict__ beta, T* y,
     float* __restrict__ rstd_out, float* __restrict__ mean_out, int64_t N, int M, float eps,
@@ -180,7 +182,9 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
           float o[V];
 #pragma unroll
           for (int i = 0; i < V; ++i) o[i] = fmaf(v[c][i] * rs, ga[c][i], be[c][i]);
-          stg_kept<RAG>(y + row * M + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(o), base < kept_rows);
+          T* const to = y + row * M + piece_col<RAG, V>(ch, chunks, M);
+          if constexpr (KEPT) stg_kept<RAG>(to, Store<T>::pack(o), base < kept_rows);
+          else stg_piece<RAG>(to, Store<T>::pack(o));
         }
       }
       if (t == 0 && live) {
@@ -1116,12 +1120,18 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
   if constexpr ((std::is_same<T, bf16_t>::value && C > 4 && L > kWave) || L > kFwdThreads) {
     // shapes that exist for float32 only, or for the backward only (fast_shape never picks them here)
   } else {
-    auto launch = [&](auto rows, auto lp, auto rag) {
+    const int64_t kept_rows = kept_elements(N * M, sizeof(T), kKeptFromMiB, kKeptMiB) / M;
+    auto launch_as = [&](auto rows, auto lp, auto rag, auto kept) {
       hipLaunchKernelGGL((ln_fwd_kernel<T, L, C, decltype(rows)::value, decltype(lp)::value,
-                                        decltype(rag)::value>),
+                                        decltype(rag)::value, decltype(kept)::value>),
                          dim3(grid), dim3(kFwdThreads), 0, st, static_cast<const T*>(x), gamma, beta,
-                         static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps,
-                         kept_elements(N * M, sizeof(T), kKeptFromMiB, kKeptMiB) / M);
+                         static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps, kept_rows);
+    };
+    auto launch = [&](auto rows, auto lp, auto rag) {
+      if constexpr (decltype(lp)::value) {  // so many rows always loop, unless a knob says otherwise
+        if (kept_rows > 0) return launch_as(rows, lp, rag, std::true_type{});
+      }
+      launch_as(rows, lp, rag, std::false_type{});
     };
     auto go = [&](auto rows, auto lp) {
       if constexpr (is_ragged_shape(L, C, Store<T>::kVec, false)) {
