@@ -18,7 +18,8 @@ extern "C" {
  * reads the knobs it depends on once per call, so its workspace check and its launch always
  * agree; a knob changed between tempo_layernorm_bwd_workspace_bytes and the call can at worst
  * make that call return TEMPO_ERR_WORKSPACE.
- *   key 0 / 1: 16-byte pieces per lane in gelu_fwd / gelu_bwd (1, 2 or 4; float32: see key 15);
+ *   key 0 / 1: 16-byte pieces per lane in gelu_fwd / gelu_bwd (1, 2 or 4; float32: see key 15; at their defaults,
+ *   4 / 2, the bfloat16 kernels choose smaller workgroups or tiles for some sizes);
  *   key 13: tensor size in Mi elements from which the bfloat16 gelu/silu forward uses workgroups
  *   of 512 lanes with half the pieces per lane (65536: never);
  *   key 2, 4, 5: cap on workgroups per compute unit of layernorm_fwd, attn fwd, attn bwd
@@ -27,14 +28,15 @@ extern "C" {
  *   layernorm_fwd then takes 4 rows of one piece per lane, 2 of two pieces);
  *   key 8, 9, 10, 11: attn fwd / attn bwd / layernorm_fwd / layernorm_bwd: 16-byte pieces per
  *   lane above which a row is spread over 2 or 4 waves instead of one (16 or more: never; attn fwd /
- *   bwd up to 4: rows that then fill the lanes of 2 or 4 waves with one piece each take those, a causal
- *   forward from 2 half as many waves with two pieces);
+ *   bwd up to 4: rows that then fill the lanes of 2 or 4 waves, or 12, 24, 48, 96, 160, 192, 224, 320 or 384 lanes,
+ *   with one piece each take those, a causal forward from 2 half as many waves with two pieces);
  *   key 15: lanes per workgroup of the float32 gelu / silu kernels (64, 128 or 256, with the
  *   pieces per lane of keys 0 / 1; 1, the default: one wave of one piece per lane forward, four
  *   waves of two pieces backward);
  *   key 14: lanes per workgroup of attn fwd / bwd (64, 128 or 256; never fewer than a row's, or two rows'
- *   where a forward row takes two waves);
- *   key 3: rows each lane group of layernorm_bwd walks; key 12: workgroups per compute unit
+ *   where a forward row takes two waves; rows on 12, 24, 48, ... lanes have workgroups of their own size);
+ *   key 3: rows each lane group of layernorm_bwd walks (more than 640 rows; fewer take one launch that has no
+ *   knobs); key 12: workgroups per compute unit
  *   beyond which its workgroups loop over the rows; keys 3, 11 and 12 set its grid and the
  *   size of its workspace, so query tempo_layernorm_bwd_workspace_bytes after changing them.
  * Results never depend on these except the summation order of dgamma/dbeta and of the softmax

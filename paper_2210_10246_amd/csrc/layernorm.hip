@@ -6,7 +6,8 @@
 // Backward: same ownership; xhat is rebuilt from the OUTPUT as (y - beta)/gamma, the two row
 // sums are butterfly-reduced, and the column sums for dgamma/dbeta are carried in registers
 // across rows, tree-reduced over the workgroup through LDS in a fixed order and written as
-// one partial per workgroup; a second small kernel adds the partials in a fixed order.
+// one partial per workgroup; a second small kernel adds the partials in a fixed order.  Few rows take one
+// launch, in which workgroups that own columns walk all rows (ln_bwd_few_kernel).
 #include <atomic>
 #include <type_traits>
 
