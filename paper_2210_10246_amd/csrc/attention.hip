@@ -251,8 +251,8 @@ __device__ __forceinline__ u32x4 load_row_piece(const T* p, int Sk, u32x4 fill) 
   }
   return ldg_piece<RAG>(p);
 }
-template <typename T, bool RAG, bool SHORT, bool KEPT = false>
-__device__ __forceinline__ void store_row_piece(T* p, int Sk, u32x4 w, bool cached = false) {
+template <typename T, bool RAG, bool SHORT>
+__device__ __forceinline__ void store_row_piece(T* p, int Sk, u32x4 w) {
   constexpr int V = Store<T>::kVec;
   if constexpr (SHORT) {
     if (Sk < V) {
@@ -264,8 +264,7 @@ __device__ __forceinline__ void store_row_piece(T* p, int Sk, u32x4 w, bool cach
       return;
     }
   }
-  if constexpr (KEPT) stg_kept<RAG>(p, w, cached);
-  else stg_piece<RAG>(p, w);
+  stg_piece<RAG>(p, w);
 }
 constexpr bool takes_short_rows(bool ragged, int lanes, int vec) { return ragged && lanes * vec == 32; }
 // Keep bytes of a row of up to `elements` elements, whatever its alignment, and one more that a
@@ -342,7 +341,7 @@ template <typename T, int LANES, int CH, int R, MaskLayout MASK, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
     const T* scores, const int32_t* __restrict__ key_len, int causal, T* probs,
     T* __restrict__ out, uint32_t* __restrict__ keep_bits, int slices, int Sq, int Sk, float scale,
-    RngArgs rng, FastDiv sets_per_slice, FastDiv heads, uint32_t first_set, int64_t kept) {
+    RngArgs rng, FastDiv sets_per_slice, FastDiv heads, uint32_t first_set) {
   static_assert(THREADS % LANES == 0 && THREADS % kWave == 0, "whole lane groups, whole waves");
   constexpr bool kOneWave = butterfly_lanes(LANES) == LANES;  // a row inside one wave: no barriers
   constexpr int kGroups = THREADS / LANES;
@@ -367,7 +366,6 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
   // scalar base and a 32-bit offset.
   const int64_t base = row_offset(slice * static_cast<uint32_t>(Sq) + set0, Sk);
   const T* const s_base = scores + base;
-  const bool cached = base < kept;  // probs
   // limit = number of leading columns of the row that take part in the softmax; -1: no row
   int limit[R];
   Raw<T> raw[R][CH];
@@ -464,7 +462,7 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(
         // round P once, into the words that are stored; Out is computed from the stored P
         const u32x4 pw = Store<T>::pack(p8);
         Store<T>::unpack(pw, p8);
-        store_row_piece<T, RAG, SHORT, true>(at_offset(probs + base, row_off + col0), Sk, pw, cached);
+        store_row_piece<T, RAG, SHORT>(at_offset(probs + base, row_off + col0), Sk, pw);
 #pragma unroll
         for (int k = 0; k < V; ++k) o8[k] = p8[k] * scale;
         u32x4 ow = Store<T>::pack(o8);
@@ -968,16 +966,6 @@ int attn_rows(int ch, int lanes, int vec, int tuned) {
   return (vec == 8 && ch == 1 && lanes == kWave && tuned >= 2) ? 2 : 1;
 }
 
-// Probabilities the forward leaves in the Infinity Cache for the backward.  Forward + backward / forward alone in a
-// loop, us, all streamed -> the first 64 MiB kept: bf16 12x16x512x512 117.0 -> 114.2 / 53.0 -> 51.3, 16x16x500x500
-// padded 159.7 -> 154.9 / 69.2 -> 66.8; f32 8x16x512x512 149.0 -> 146.7 / 65.8 -> 63.8, 4x16x1000x1000 causal 288.7
-// -> 283.6 / 118.2 -> 112.3.  More gives the pass more and costs a forward alone: all of the second 150.4 / 80.5,
-// 96 MiB of the last 280.0 / 123.  Where it is few per cent of the forward, in bfloat16 from 160 MiB up, 192 MiB are
-// kept: 8x12x1024x1024 causal 207.7 -> 193.3 / 87.1 -> 90.0 (64 MiB: 203.3), 32x16x512x512 297.8 -> 283.3 / 139 -> 146.
-// Below 40 MiB the forward's wait for its L2s outweighs it: 8 MiB 12.4 -> 13.5, 32 MiB 42.5 -> 42.7.
-constexpr int kKeptFromMiB = 40;
-int kept_mib(int64_t n, tempo_dtype dt) { return dt == TEMPO_BF16 && n * 2 >= int64_t{160} << 20 ? 192 : 64; }
-
 // Lanes per workgroup of the register-resident kernels.  Small workgroups come and go
 // independently, which the memory system rewards: against workgroups of four waves, two waves
 // gain 2-8 % (forward at every size, backward on tensors from 2 GB up, never a loss); single
@@ -1064,7 +1052,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint
                         const void* scores, const int32_t* key_len, int causal, void* probs,
                         void* out, uint32_t* keep_bits, int slices, const FastDiv& heads,
                         const FastDiv& sets_per_slice, int64_t Sq, int64_t Sk, float scale,
-                        const RngArgs& rng, int64_t kept) {
+                        const RngArgs& rng) {
   auto go = [&](auto rows, auto w) {
     with_threads<L, false, decltype(w)::value == kRagged>(threads, [&](auto th) {
       constexpr int TH = decltype(th)::value;
@@ -1072,7 +1060,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint
           (attn_fwd_kernel<T, L, C, decltype(rows)::value, decltype(w)::value, TH>), dim3(sets),
           dim3(TH), lds, st, static_cast<const T*>(scores), key_len, causal, static_cast<T*>(probs),
           static_cast<T*>(out), keep_bits, slices, static_cast<int>(Sq), static_cast<int>(Sk), scale,
-          rng, sets_per_slice, heads, first_set, kept);
+          rng, sets_per_slice, heads, first_set);
     });
   };
   using std::integral_constant;
@@ -1172,12 +1160,10 @@ tempo_status launch_attn_fwd(const void* scores, const int32_t* key_len, int cau
     const int pieces = static_cast<int>((Sk + vec - 1) / vec);
     const size_t lds = dt == TEMPO_F32 ? fwd_f32_lds_bytes(sh, pieces, threads, causal != 0, key_len != nullptr) : 0;
     const MaskLayout layout = ragged ? kRagged : (Sk % 32 == 0 ? kWords : kBytes);
-    const int64_t kept =
-        kept_elements(rows * Sk, dt == TEMPO_F32 ? 4 : 2, kKeptFromMiB, kept_mib(rows * Sk, dt));
 #define TEMPO_LAUNCH(L, C)                                                                   \
   do {                                                                                       \
-    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng, kept);   \
-    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng, kept);                  \
+    if (dt == TEMPO_F32) attn_fwd_go<float, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);   \
+    else attn_fwd_go<bf16_t, L, C>(rr, layout, threads, lds, first, sets, st, scores, key_len, causal, probs, out, keep_bits, slices, heads, sets_per_slice, Sq, Sk, scale, rng);                  \
   } while (0)
     const int64_t cap = most_groups(static_cast<int64_t>(compute_units()) * bpc, threads);
     tempo_status status = TEMPO_OK;

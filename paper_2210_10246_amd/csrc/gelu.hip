@@ -359,11 +359,10 @@ struct LutTile {
 template <int KIND, int K, int THREADS, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, bf16_t* y,
                                                                    uint32_t* __restrict__ mask,
-                                                                   int64_t n, int64_t kept, int tile_size) {
+                                                                   int64_t n, int tile_size) {
   __shared__ uint32_t lut[2 * TEMPO_GELU_LUT_N];
   const int lane = threadIdx.x & (kWave - 1);
   const LutTile<K, THREADS, SPLIT> tile(n, tile_size);
-  const bool cached = static_cast<int64_t>(blockIdx.x) * tile.size * 8 < kept;
   u32x4 w[K];
   if (tile.full) {  // straight-line loads
 #pragma unroll
@@ -391,7 +390,7 @@ __global__ __launch_bounds__(THREADS) void gelu_fwd_lut_kernel(const bf16_t* x, 
     // every lane of the wave takes part in the merge; absent chunks contribute zero bits
     const uint32_t word = merge_mask_word<8>(byte, lane);
     if (tile.full) {
-      stg_kept<false>(y + q * 8, yw, cached);
+      stg_stream(y + q * 8, yw);
       if ((lane & 3) == 0) mask[q >> 2] = word;
     } else {
       const int64_t left = n - q * 8;
@@ -496,14 +495,6 @@ int tile_grid(int64_t n, int k, int threads) {  // float32 pieces of 4 elements
   return static_cast<int>((n_pieces + per_block - 1) / per_block);
 }
 
-// Part of y that the bfloat16 forward leaves in the Infinity Cache.  Forward + backward / forward alone, us,
-// all streamed -> the first 64 MiB kept: 8192x4096 60.6 -> 58.8 / 25.1 -> 25.3, 32768x2048 silu 113.6 -> 111.6 /
-// 47.5 -> 46.6, 8192x12288 167.8 -> 166.2 / 71.1 -> 68.8.  All 128 MiB of the second: 108.8 / 50.5, a
-// forward alone loses; so it does below 60 MiB (50 MiB 50.4 -> 49.4 / 20.4 -> 21.0; 16 MiB 18.4 -> 18.4 / 6.3 -> 7.9).  The
-// float32 backward has other bounds than memory and gains nothing at any size.
-constexpr int kKeptFromMiB = 60;
-constexpr int kKeptMiB = 64;
-
 int pick_k(int tuned) { return tuned >= 4 ? 4 : (tuned >= 2 ? 2 : 1); }
 
 }  // namespace
@@ -569,14 +560,13 @@ tempo_status launch_gelu_fwd(const void* x, void* y, uint32_t* mask, int64_t n, 
                              int kind, hipStream_t st) {
   const int k = pick_k(tune_get(kTuneGeluFwdChunks));
   if (dt == TEMPO_BF16) {
-    const int64_t kept = kept_elements(n, 2, kKeptFromMiB, kKeptMiB);
     const LutShape sh = lut_shape(true, n, k);
     with_kind(kind, [&](auto kd) {
       with_lut_shape(sh, [&](auto th, auto kk, auto split) {
         constexpr int TH = decltype(th)::value;
         hipLaunchKernelGGL((gelu_fwd_lut_kernel<decltype(kd)::value, decltype(kk)::value, TH, decltype(split)::value>),
                            dim3(lut_grid(n, sh)), dim3(TH), 0, st, static_cast<const bf16_t*>(x),
-                           static_cast<bf16_t*>(y), mask, n, kept, sh.tile);
+                           static_cast<bf16_t*>(y), mask, n, sh.tile);
       });
     });
     return launch_status();

@@ -85,13 +85,10 @@ __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int
 // RAG: rows of any length that is no multiple of the piece (see piece_col): 16-byte accesses at
 // element-aligned addresses, columns on fixed lanes.  Bound by memory like the aligned rows: 8192 x 1001
 // f32 15.1 -> 13.1 us against element-wise accesses (1000 columns: 13.2), 4096 x 4100 bf16 40.6 -> 16.8.
-// KEPT: the first kept_rows rows of y are stored for the backward to find in a cache (stg_kept); a kernel of
-// its own, since the branches cost the others 1-2 % (584 x 3008 f32 4.39 -> 4.48 us, 8192 x 1024 bf16 7.0 -> 7.1).
-template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG, bool KEPT>
+template <typename T, int LANES, int CH, int R, bool LOOP, bool RAG>
 __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
     const T* x, const float* __restrict__ gamma, const float* __restrict__ beta, T* y,
-    float* __restrict__ rstd_out, float* __restrict__ mean_out, int64_t N, int M, float eps,
-    int64_t kept_rows) {
+    float* __restrict__ rstd_out, float* __restrict__ mean_out, int64_t N, int M, float eps) {
   constexpr int kGroups = kFwdThreads / LANES;
   constexpr int V = Store<T>::kVec;
   const int g = threadIdx.x / LANES;
@@ -183,9 +180,7 @@ __global__ __launch_bounds__(kFwdThreads) void ln_fwd_kernel(
           float o[V];
 #pragma unroll
           for (int i = 0; i < V; ++i) o[i] = fmaf(v[c][i] * rs, ga[c][i], be[c][i]);
-          T* const to = y + row * M + piece_col<RAG, V>(ch, chunks, M);
-          if constexpr (KEPT) stg_kept<RAG>(to, Store<T>::pack(o), base < kept_rows);
-          else stg_piece<RAG>(to, Store<T>::pack(o));
+          stg_piece<RAG>(y + row * M + piece_col<RAG, V>(ch, chunks, M), Store<T>::pack(o));
         }
       }
       if (t == 0 && live) {
@@ -1106,14 +1101,6 @@ constexpr bool ragged_shapes_exist(int vec, bool backward) {
 static_assert(ragged_shapes_exist(4, false) && ragged_shapes_exist(4, true), "float32");
 static_assert(ragged_shapes_exist(8, false) && ragged_shapes_exist(8, true), "bfloat16");
 
-// Part of y that the forward leaves in the Infinity Cache.  Forward + backward / forward alone, us, all streamed
-// -> the first 64 MiB kept: bf16 32768x1024 63.5 -> 61.9 / 25.4 -> 25.3, f32 16384x1024 62.1 -> 60.4 / 24.3 -> 24.2,
-// 32768x1024 116.7 -> 112.3 / 46.3 -> 44.8, 20000x1001 78.1 -> 75.7 / 30.5 -> 29.5.  All 128 MiB of the third:
-// 109.2 / 48.1, a forward alone loses; so it does below 60 MiB (bf16 24576x1024 51.1 -> 50.8 / 20.6 -> 21.8, f32
-// 8192x1024 35.1 -> 34.7 / 12.6 -> 13.5).
-constexpr int kKeptFromMiB = 60;
-constexpr int kKeptMiB = 64;
-
 template <typename T, int L, int C>
 static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, const void* x, const float* gamma,
                       const float* beta, void* y, float* rstd, float* mean, int64_t N, int64_t M,
@@ -1121,18 +1108,11 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
   if constexpr ((std::is_same<T, bf16_t>::value && C > 4 && L > kWave) || L > kFwdThreads) {
     // shapes that exist for float32 only, or for the backward only (fast_shape never picks them here)
   } else {
-    const int64_t kept_rows = kept_elements(N * M, sizeof(T), kKeptFromMiB, kKeptMiB) / M;
-    auto launch_as = [&](auto rows, auto lp, auto rag, auto kept) {
-      hipLaunchKernelGGL((ln_fwd_kernel<T, L, C, decltype(rows)::value, decltype(lp)::value,
-                                        decltype(rag)::value, decltype(kept)::value>),
-                         dim3(grid), dim3(kFwdThreads), 0, st, static_cast<const T*>(x), gamma, beta,
-                         static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps, kept_rows);
-    };
     auto launch = [&](auto rows, auto lp, auto rag) {
-      if constexpr (decltype(lp)::value) {  // so many rows always loop, unless a knob says otherwise
-        if (kept_rows > 0) return launch_as(rows, lp, rag, std::true_type{});
-      }
-      launch_as(rows, lp, rag, std::false_type{});
+      hipLaunchKernelGGL((ln_fwd_kernel<T, L, C, decltype(rows)::value, decltype(lp)::value,
+                                        decltype(rag)::value>),
+                         dim3(grid), dim3(kFwdThreads), 0, st, static_cast<const T*>(x), gamma, beta,
+                         static_cast<T*>(y), rstd, mean, N, static_cast<int>(M), eps);
     };
     auto go = [&](auto rows, auto lp) {
       if constexpr (is_ragged_shape(L, C, Store<T>::kVec, false)) {

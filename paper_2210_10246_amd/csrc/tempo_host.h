@@ -32,16 +32,6 @@ enum TuneKey {
 int tune_get(TuneKey k);
 int compute_units();
 
-// Leading elements of a forward's output that are stored without the streaming hint, for the backward
-// to find them in the Infinity Cache: the first `most` MiB of outputs of at least `from` MiB, none of those
-// beyond 768 MiB, of which that would be too little to show (attention f32 64x16x512x512: 1 GiB, within 0.6 % either way).
-// The launchers' figures are of passes and forwards over three sets of buffers; a forward alone over buffers that are not
-// seen again pays 2-7 % for the part (bf16 8192x4096 GELU 24.9 -> 26.5 us, 8x12x1024x1024 causal attention 87 -> 91).
-inline int64_t kept_elements(int64_t n, int64_t element_bytes, int64_t from, int64_t most) {
-  const int64_t bytes = n * element_bytes;
-  return bytes < (from << 20) || bytes > (int64_t{768} << 20) ? 0 : (most << 20) / element_bytes;
-}
-
 inline tempo_status launch_status() {
   return hipGetLastError() == hipSuccess ? TEMPO_OK : TEMPO_ERR_LAUNCH;
 }

@@ -1,5 +1,5 @@
-"""Outputs of which a part is stored for the backward to find in the cache (the rest streamed): a call that
-mixes the two store kinds gives the bits of calls too small for it, at aligned and ragged rows."""
+"""A forward over a large tensor gives the bits of forwards over its parts, whatever launch shapes the two sizes
+take, at aligned and ragged rows."""
 import pytest
 import torch
 
@@ -16,7 +16,6 @@ def _x(shape, dtype, seed=3):
     return torch.randn(shape, generator=g, device="cuda", dtype=torch.float32).to(dtype)
 
 
-# y of 60 MiB and more keeps its first 64 MiB: a boundary inside the tensor, none, and the smallest
 @pytest.mark.parametrize("dtype,mib", [(torch.bfloat16, 61), (torch.bfloat16, 71), (torch.float32, 61), (torch.float32, 90)])
 @pytest.mark.parametrize("cols", [1024, 1003])
 def test_layernorm_fwd(dtype, mib, cols):
@@ -31,7 +30,7 @@ def test_layernorm_fwd(dtype, mib, cols):
         return y, rstd
 
     y, rstd = fwd(x)
-    step = rows // 4 // 8 * 8            # quarters: under 60 MiB, 16-byte aligned
+    step = rows // 4 // 8 * 8            # quarters, 16-byte aligned
     for r in range(0, rows, step):
         ys, rs = fwd(x[r:r + step])
         assert torch.equal(y[r:r + step], ys) and torch.equal(rstd[r:r + step], rs)
@@ -54,7 +53,6 @@ def test_gelu_fwd_bf16(mib):
         assert torch.equal(y[e:e + step], ys) and torch.equal(mask[e // 32:e // 32 + ms.numel()], ms)
 
 
-# probabilities of 40 MiB and more keep their first 64 MiB, of 160 MiB and more in bf16 192 MiB
 @pytest.mark.parametrize("dtype,heads,seq", [(torch.bfloat16, 150, 840), (torch.bfloat16, 100, 333), (torch.float32, 30, 1024),
                                              (torch.float32, 120, 333), (torch.bfloat16, 20, 2600)])
 @pytest.mark.parametrize("causal", [False, True])
@@ -69,7 +67,7 @@ def test_attention_fwd(dtype, heads, seq, causal):
         return probs, out, keep
 
     probs, out, keep = fwd(scores, p)
-    step = 8                             # heads: whole groups of 8 elements, under 40 MiB up to 840 columns
+    step = 8                             # heads: whole groups of 8 elements
     for h in range(0, heads, step):
         part = scores[:, h:h + step].contiguous()
         assert torch.equal(probs[:, h:h + step], fwd(part, 0.0)[0])
