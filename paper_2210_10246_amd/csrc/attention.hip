@@ -836,15 +836,21 @@ enum RowUse { kForward, kForwardCausal, kBackward };
 //    ways: bf16 48x16x80x80 17.5 / 17.0, 32x16x150x150 39.6 / 35.2, 16x16x333x333 padded 83.2 / 74.8, 16x16x384x384 89.3 /
 //    84.4; f32 32x16x96x96 26.5 / 26.0, 32x16x150x150 66.9 / 60.2;
 //  - backward on 96 lanes for 65..96 pieces, bf16 8x16x520x520 55.3 / 49.4, 8x16x765x765 117 / 106, 8x16x768x768 99.6 /
-//    99.0, f32 16x16x333x333 86.9 / 80.3; 160 for 129..160, bf16 2x16x1101x1101 63.2 / 55.1, 1280 70.9 / 69.0; 192 for
-//    161..192, bf16 1400 93.5 / 88.8, f32 4x16x701x701 93.1 / 87.9, but bf16 1501 106 / 115; 224 for 193..224 of bf16
-//    ragged, 1701 148 / 131, not aligned, 1792 133.1 / 133.1, nor f32, 800 107 / 108.5; 320 for 257..320, bf16 2x8x2100x2100
-//    105 / 96, 2560 140.0 / 138.7; 384 up to 352, bf16 2700 166 / 159, f32 2x16x1401x1401 174 / 168, not when full, bf16
-//    3072 195.5 / 200.5;
-//  - the bfloat16 forward without a causal mask, whose pieces a lane skips, only next to full lanes: 96 from 89 pieces,
-//    8x16x744x744 80.9 / 74.6 (704: 65.5 / 65.5, 520: 43.0 / 44.7); 192 of aligned rows, 2x16x1400x1400 72.7 / 68.4 (1501:
-//    80.4 / 81.8); 224 from 209, 1700 124 / 117 (1600: 86 / 92).  160, 320 and 384 lanes lose (1200 padded 47.6 / 56.1), and
-//    so does float32 from 96 lanes up (4x16x600x600 47.4 / 51.1).
+//    99.0, f32 16x16x333x333 86.9 / 80.3; 160 for 129..160, bf16 2x16x1101x1101 63.2 / 55.1, 1280 70.9 / 69.0; 224
+//    for 193..224 of bf16 ragged, 1701 148 / 131, not aligned, 1792 133.1 / 133.1, nor f32, 800 107 / 108.5; 320 for 257..320,
+//    bf16 2x8x2100x2100 105 / 96, 2560 140.0 / 138.7; 384 for 321..352 of ragged rows, bf16 2700 166 / 159, f32
+//    2x16x1401x1401 174 / 168;
+//  - the bfloat16 forward without a causal mask, whose pieces a lane skips, on 96 lanes from 89 pieces, 8x16x744x744
+//    80.9 / 74.6 (704: 65.5 / 65.5, 520: 43.0 / 44.7).
+// The same as a mean of the ratio over two dozen sizes of 0.3 to 38 M elements each, below 3 M / above, since every size
+// at which the workgroups just exceed what is resident loses up to 17 % and others gain as much:
+//  - taken: 12..48 lanes forward 0.83-1.00 / 0.87-0.94, backward 0.89-1.00 / 0.91-0.99; backward on 96 0.87-0.98 /
+//    0.90-0.97, 160 0.81-1.00 / 0.89-0.98, 320 0.89-1.00 / 0.92-1.00, 224 0.94 / 0.92 with the mask stored, 1.00 / 1.02 drawn
+//    again, 384 ragged 0.92 / 0.94 and 0.99 / 0.99; forward on 96 0.87-0.91 / 0.96-1.02;
+//  - not taken: forward on 192 0.94 / 1.06-1.09 (2x4x1360x1360 1.26-1.29), 224 0.92-0.99 / 0.97-1.04 (2x1728x1728 1.20-1.23),
+//    160, 320 and 384 (1200 padded 47.6 / 56.1 us) and of float32 from 96 up (4x16x600x600 47.4 / 51.1); backward on 192,
+//    float32 0.96 / 0.97 stored, 1.05-1.09 / 0.98 drawn again (up to 1.26), bf16 aligned 0.97 / 0.98 and 1.02 / 1.01 (up to 1.16),
+//    ragged 1501 106 / 115 us; aligned backward on 384 1.01 and 1.03 (3072, full, 195.5 / 200.5 us).
 constexpr Shape odd_shape(int p, bool ragged, int vec, RowUse use) {
   const bool bf16 = vec == 8;
   if (p > 8 && p <= 12 && bf16) return {12, 1};
@@ -853,14 +859,11 @@ constexpr Shape odd_shape(int p, bool ragged, int vec, RowUse use) {
   if (use == kBackward) {
     if (p > 64 && p <= 96) return {96, 1};
     if (p > 128 && p <= 160) return {160, 1};
-    if (p > 160 && p <= 192 && !(bf16 && ragged)) return {192, 1};
     if (p > 192 && p <= 224 && bf16 && ragged) return {224, 1};
     if (p > 256 && p <= 320) return {320, 1};
-    if (p > 320 && p <= 352) return {384, 1};
+    if (p > 320 && p <= 352 && ragged) return {384, 1};
   } else if (use == kForward && bf16) {
     if (p > 88 && p <= 96) return {96, 1};
-    if (p > 160 && p <= 192 && !ragged) return {192, 1};
-    if (p > 208 && p <= 224) return {224, 1};
   }
   return {0, 0};
 }
@@ -1017,7 +1020,6 @@ int row_grid(int64_t rows, int blocks_per_cu) {
     case 12803: LAUNCH(128, 3); break;                                                     \
     case 12804: LAUNCH(128, 4); break;                                                     \
     case 16001: LAUNCH(160, 1); break;                                                     \
-    case 19201: LAUNCH(192, 1); break;                                                     \
     case 22401: LAUNCH(224, 1); break;                                                     \
     case 25601: LAUNCH(256, 1); break;                                                     \
     case 25602: LAUNCH(256, 2); break;                                                     \

@@ -1,4 +1,4 @@
-"""Attention rows on 12, 24, 48, 96, 160, 192, 224, 320 and 384 lanes, several of which lie across the waves of a
+"""Attention rows on 12, 24, 48, 96, 160, 224, 320 and 384 lanes, several of which lie across the waves of a
 workgroup: both ends of every range of pieces per row, ragged and aligned, with row counts that leave
 lane groups of the last workgroup without a row.  The checks are those of the ragged rows: the oracle, every mask
 source, in place, guard words behind every output."""
