@@ -36,7 +36,7 @@ extern "C" {
  *   key 14: lanes per workgroup of attn fwd / bwd (64, 128 or 256; never fewer than a row's, or two rows'
  *   where a forward row takes two waves; rows on 12, 24, 48, ... lanes have workgroups of their own size);
  *   key 3: rows each lane group of layernorm_bwd walks (up to 640 rows, 320 of the longest, take one launch that has no
- *   knobs unless an output lies in the place of an input); key 12: workgroups per compute unit
+ *   knobs); key 12: workgroups per compute unit
  *   beyond which its workgroups loop over the rows; keys 3, 11 and 12 set its grid and the
  *   size of its workspace, so query tempo_layernorm_bwd_workspace_bytes after changing them.
  * Results never depend on these except the summation order of dgamma/dbeta and of the softmax

@@ -832,9 +832,9 @@ struct Xhat {
 
 // Few rows: the whole backward in one launch.  The first col_blocks workgroups own 64 bytes of columns each
 // (4 lanes x a piece, 128 rows at a time) and walk all rows for dgamma and dbeta, which need no row sums; the
-// others own rows (LANES lanes, CH pieces per lane) and write dx, which may not lie in the place of an
-// input.  dy and y are read twice, the second time from a cache; in return there are no partials and no second
-// dispatch.
+// others own rows (LANES lanes, CH pieces per lane) and write dx.  dy and y are read twice, the second
+// time from a cache; in return there are no partials and no second dispatch.  In place (dx is dy) the two halves
+// are launched one after the other; `first` is the launch's first workgroup.
 // Bound by latency: a launch that does nothing takes 1.7 us, and a wave alone on its SIMD 4-8 cycles an
 // instruction, so that the column walk has one row per lane under way and the next fetched: with 2, 4 or 8 rows
 // unrolled 64x768 f32 takes 3.0, 3.5 and 5.3 us (256 lanes) instead of 2.9.
@@ -842,7 +842,7 @@ template <typename T, int LANES, int CH, bool RAG>
 __global__ __launch_bounds__(kFewThreads) void ln_bwd_few_kernel(
     const T* dy, const T* y, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ rstd, T* dx,
-    float* __restrict__ dgamma, float* __restrict__ dbeta, int N, int M, int col_blocks) {
+    float* __restrict__ dgamma, float* __restrict__ dbeta, int N, int M, int col_blocks, int first) {
   constexpr int V = Store<T>::kVec;
   constexpr int kWaves = kFewThreads / kWave;
   const int chunks = RAG ? (M + V - 1) / V : M / V;
@@ -850,7 +850,7 @@ __global__ __launch_bounds__(kFewThreads) void ln_bwd_few_kernel(
     if constexpr (RAG) return *reinterpret_cast<const u32x4_any*>(p);
     else return *reinterpret_cast<const u32x4*>(p);
   };
-  const int block = static_cast<int>(blockIdx.x);
+  const int block = first + static_cast<int>(blockIdx.x);
   if (block < col_blocks) {
     constexpr int kSlices = kFewThreads / kFewColLanes;
     static_assert(kFewColLanes == 4, "the sums over a wave's lanes below");
@@ -1342,8 +1342,10 @@ static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStre
 // f32 256x768 5.7 / 3.0, 640x768 6.6 / 4.5, 640x1001 7.3 / 6.7, 640x4096 14.0 / 12.7, 640x6144 18.4 / 16.8, 320x8187 18.4 /
 // 18.1, 384x8187 18.6 / 20.5, 640x8187 22.5 / 30.3, 320x6143 14.3 / 13.6, 384x6143 14.5 / 15.0, 640x5001 17.0 / 17.8, 576x6148
 // 17.3 / 18.1, 640x8192 20.9 / 23.7; bf16 256x1024 6.0 / 2.9, 640x1024 6.5 / 3.4, 640x4096 12.1 / 7.8, 640x8191 19.5 / 19.3.
-// Beyond 640 rows, forward + backward: f32 1024x768 10.8 / 10.8, 768x4096 20.9 / 21.6, bf16 1024x1024 10.6 / 11.2.  In place (dx is dy or y) the columns would have to be summed
-// before dx is written, in a launch of their own: f32 256x768 5.7 / 6.8, 640x8192 20.7 / 27.4, bf16 640x1024 6.3 / 9.4.
+// Beyond 640 rows, forward + backward: f32 1024x768 10.8 / 10.8, 768x4096 20.9 / 21.6, bf16 1024x1024 10.6 / 11.2.  In place the columns have to be summed before dx is written, in a
+// launch of their own, which only 64 rows and the longer bfloat16 ones gain by (f32 64x768 5.6 / 5.4, 256x768 5.7 / 6.8,
+// 640x4096 14.0 / 16.7, bf16 640x1024 6.3 / 9.4, 256x4096 8.9 / 7.6); the rule is the same, for dx, dgamma and dbeta to have
+// the bits of the call apart.
 constexpr int64_t kFewRows = 640;
 constexpr int64_t kFewLongRows = 320;  // float32, of more than 4096 columns if ragged, of more than 6144 if not
 static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
@@ -1365,7 +1367,7 @@ static bool few_rows(int64_t N, int64_t M, tempo_dtype dt) {
   return N >= 1 && N <= (is_long ? kFewLongRows : kFewRows) && M >= vec && (M + vec - 1) / vec <= max_fast_pieces(vec);
 }
 template <typename T>
-static tempo_status ln_bwd_few(bool ragged, hipStream_t st, const void* dy, const void* y, const float* gamma,
+static tempo_status ln_bwd_few(bool ragged, bool in_place, hipStream_t st, const void* dy, const void* y, const float* gamma,
                                const float* beta, const float* rstd, void* dx, float* dgamma, float* dbeta, int64_t N,
                                int64_t M) {
   const int pieces = static_cast<int>((M + Store<T>::kVec - 1) / Store<T>::kVec);
@@ -1374,14 +1376,19 @@ static tempo_status ln_bwd_few(bool ragged, hipStream_t st, const void* dy, cons
   const int groups = kFewThreads / sh.lanes;
   const int grid = col_blocks + static_cast<int>((N + groups - 1) / groups);
   auto go = [&](auto lanes, auto ch) {
-    auto launch = [&](auto rag) {
+    auto launch = [&](auto rag, int first, int count) {
       hipLaunchKernelGGL((ln_bwd_few_kernel<T, decltype(lanes)::value, decltype(ch)::value, decltype(rag)::value>),
-                         dim3(grid), dim3(kFewThreads), 0, st, static_cast<const T*>(dy), static_cast<const T*>(y),
+                         dim3(count), dim3(kFewThreads), 0, st, static_cast<const T*>(dy), static_cast<const T*>(y),
                          gamma, beta, rstd, static_cast<T*>(dx), dgamma, dbeta, static_cast<int>(N),
-                         static_cast<int>(M), col_blocks);
+                         static_cast<int>(M), col_blocks, first);
       return launch_status();
     };
-    return ragged ? launch(std::true_type{}) : launch(std::false_type{});
+    auto halves = [&](auto rag) {
+      if (!in_place) return launch(rag, 0, grid);
+      const tempo_status columns = launch(rag, 0, col_blocks);
+      return columns != TEMPO_OK ? columns : launch(rag, col_blocks, grid - col_blocks);
+    };
+    return ragged ? halves(std::true_type{}) : halves(std::false_type{});
   };
   using std::integral_constant;
   constexpr integral_constant<int, kWave> wave{};
@@ -1440,9 +1447,9 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
   if (workspace_bytes < slot_bytes(b, M)) return TEMPO_ERR_WORKSPACE;
   if (few_rows(N, M, dt)) {
     const int64_t act = N * M * (dt == TEMPO_F32 ? 4 : 2), par = M * 4;
-    // outputs in the place of an input: left to the row kernel, which has read all of a row before it writes the row's
-    // dx, and everything before dgamma and dbeta
-    bool apart = !overlap(dx, act, dy, act) && !overlap(dx, act, y, act);
+    const bool in_place = overlap(dx, act, dy, act) || overlap(dx, act, y, act);
+    // dgamma or dbeta in the place of an input: left to the row kernel, which has read it all before they are written
+    bool apart = true;
     auto keep_apart = [&](const void* in, int64_t bytes) {
       apart = apart && !overlap(dgamma, par, in, bytes) && !overlap(dbeta, par, in, bytes);
     };
@@ -1453,8 +1460,8 @@ tempo_status launch_layernorm_bwd(const void* dy, const void* y, const float* ga
     keep_apart(rstd, N * 4);
     if (apart)
       return dt == TEMPO_F32
-                 ? ln_bwd_few<float>(is_ragged(M, dt), st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M)
-                 : ln_bwd_few<bf16_t>(is_ragged(M, dt), st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M);
+                 ? ln_bwd_few<float>(is_ragged(M, dt), in_place, st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M)
+                 : ln_bwd_few<bf16_t>(is_ragged(M, dt), in_place, st, dy, y, gamma, beta, rstd, dx, dgamma, dbeta, N, M);
   }
   int grid = b.plan.grid;
   // Ragged rows' slots in whole 16-byte pieces, if the workspace, which is sized in rows of M, has room for that: it

@@ -1,5 +1,5 @@
-"""LayerNorm backward of few rows: one launch where the outputs are apart from the inputs, the row kernel with its
-partial sums where dx is dy or dgamma is gamma.  All against float64, at the edges of the column walk's steps
+"""LayerNorm backward of few rows: one launch where dx is apart from dy, two where it is dy, and the row kernel with
+its partial sums where dgamma is an input too.  All against float64, at the edges of the column walk's steps
 (128 rows), of the row shapes and of the rule (640 rows, 320 of the longest float32 ones)."""
 import pytest
 import torch
@@ -69,10 +69,9 @@ def test_layernorm_bwd(M, N, dt):
 
 # Where one launch is slower, the row kernel has to run: it adds dgamma and dbeta in an order of its own, so that their
 # bits tell.  Its bits come from a call that is always its own, the one with dgamma in gamma's place.
-@pytest.mark.parametrize("dt,N,M,in_place", [
-    ("f32", 64, 768, True), ("f32", 640, 1001, True), ("bf16", 256, 1024, True), ("bf16", 640, 4100, True),
-    ("f32", 321, 6148, False), ("f32", 640, 8192, False), ("f32", 321, 4097, False), ("f32", 640, 8191, False)])
-def test_row_kernel_where_it_is_faster(dt, N, M, in_place):
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("N,M", [(321, 6148), (640, 8192), (321, 4097), (640, 8191)])
+def test_long_float32_rows_take_the_row_kernel(N, M, in_place, dt="f32"):
     gamma, beta, y, dy, rstd = inputs(M, N, dt)
     ws = torch.empty(B.tempo_layernorm_bwd_workspace_bytes(N, M), dtype=torch.uint8, device="cuda")
 
