@@ -1,10 +1,11 @@
 """Attention rows on 12, 24, 48, 96, 160, 224, 320 and 384 lanes, several of which lie across the waves of a
 workgroup: both ends of every range of pieces per row, ragged and aligned, with row counts that leave
-lane groups of the last workgroup without a row.  The checks are those of the ragged rows: the oracle, every mask
-source, in place, guard words behind every output."""
+lane groups of the last workgroup without a row, under every mask: a causal forward has shapes of its own.
+The checks are those of the ragged rows: the oracle, every source of the keep bits, in place, guard words behind
+every output."""
 import pytest
 
-from test_gpu_ragged_rows import B, test_attention_ragged_rows as check  # noqa: F401
+from test_gpu_ragged_rows import B, check_attention  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -13,9 +14,10 @@ PIECES = [8, 9, 12, 13, 16, 17, 24, 25, 33, 48, 49, 65, 88, 89, 96, 97, 129, 160
           257, 320, 321, 352, 353]
 
 
+@pytest.mark.parametrize("mask", ["none", "padding", "causal"])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("cut", [0, 3])     # elements short of whole pieces
 @pytest.mark.parametrize("pieces", PIECES)
-def test_attention(B, pieces, cut, dt):
+def test_attention(B, pieces, cut, dt, mask):
     rows = 13 if pieces <= 48 else (5 if pieces <= 224 else 2)
-    check(B, pieces * (8 if dt == "bf16" else 4) - cut, rows, dt)
+    check_attention(B, pieces * (8 if dt == "bf16" else 4) - cut, rows, dt, mask)

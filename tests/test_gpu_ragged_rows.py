@@ -54,11 +54,15 @@ ATTN_ROWS = [(1, 33), (3, 21), (5, 13), (7, 9), (9, 7), (15, 3), (31, 5), (33, 9
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("Sk,Sq", ATTN_ROWS)
 def test_attention_ragged_rows(B, Sk, Sq, dt):
+    check_attention(B, Sk, Sq, dt, {1: "causal", 3: "padding"}.get(Sk % 4, "none"))
+
+
+def check_attention(B, Sk, Sq, dt, mask):
     rng = np.random.default_rng(Sk)
     shape = (2, 1, Sq, Sk)
     p, seed, offset = np.float32(0.2), 0x123456789ABC, 5
-    causal = Sk % 4 == 1
-    key_len = np.array([Sk, max(1, Sk * 2 // 3)], dtype=np.int32) if Sk % 4 == 3 else None
+    causal = mask == "causal"
+    key_len = np.array([Sk, max(1, Sk * 2 // 3)], dtype=np.int32) if mask == "padding" else None
     s = stored(rng, shape, dt, 0.5)
     P_ref, out_ref, K_ref = O.attn_softmax_dropout_fwd(s, key_len, causal, p, seed, offset, dt)
     sd = dev(s, dt)
