@@ -1140,13 +1140,16 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
 
 static bool is_ragged(int64_t M, tempo_dtype dt) { return M % (dt == TEMPO_F32 ? 4 : 8) != 0; }
 
+// Longest rows whose column sums fit the LDS of a compute unit when a wave owns a row: half of the waves' sums at once.
+constexpr int64_t kOneWaveBwdColumns = 160 * 1024 / (kBwdWaves / 2 * 2 * sizeof(float));
 static bool fast_shape(int64_t N, int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   if (M < vec || (M + vec - 1) / vec > max_fast_pieces(vec)) return false;
   const int pieces = static_cast<int>((M + vec - 1) / vec);
   const bool ragged = is_ragged(M, dt);
-  const int max_ch = ragged ? (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces)
-                            : tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces);
+  int max_ch = ragged ? (backward ? kRaggedBwdMaxPieces : kRaggedFwdMaxPieces)
+                      : tune_get(backward ? kTuneLnBwdMaxPieces : kTuneLnFwdMaxPieces);
+  if (backward && M > kOneWaveBwdColumns && max_ch > 4) max_ch = 4;  // several waves, whatever the knob says
   *sh = shape_of(pieces, vec, max_ch, backward, ragged, N >= int64_t{64} * compute_units());
   return sh->ch != 0;
 }
