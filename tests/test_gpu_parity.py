@@ -215,7 +215,9 @@ LN_SHAPES = [(256, 768), (5, 1024), (37, 768), (3, 8), (9, 64), (7, 100), (4, 40
              # rows that are not whole pieces, and the any-shape kernels with more rows than one
              (1500, 1001), (2000, 4100), (3, 9300),
              # the any-shape kernels: rows shorter than a piece, more rows than workgroups
-             (2500, 3), (1100, 8200)]
+             (2500, 3), (1100, 8200),
+             # more rows than the backward takes in one launch
+             (641, 64), (700, 768), (1100, 1024), (650, 3072), (645, 8192)]
 
 
 @pytest.mark.parametrize("eps", [1e-12, 1e-5])
@@ -286,8 +288,8 @@ def test_layernorm_bwd(B, shape, dt):
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(37, 2048), (5, 3072), (9, 4096), (3, 1032), (600, 1536),
-                                   # more rows than the backward takes in one launch; a wave's column sums would not fit the LDS
-                                   (642, 6144), (641, 8192)])
+                                   # more rows than the backward takes in one launch, which has no knobs
+                                   (643, 1032), (701, 1536), (645, 2048), (703, 3072), (1030, 4096), (642, 6144), (641, 8192)])
 def test_layernorm_row_over_one_or_several_waves(B, shape, dt):
     """Long rows: the same results whether one wave or 2-4 waves own a row (knobs 10, 11),
     with row counts that leave lane groups without a row in the last batch."""

@@ -147,7 +147,9 @@ def test_layernorm_ragged_rows(B, M, N, dt):
 
 @pytest.mark.parametrize("extremes", [False, True])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("M,N", [(5, 40), (63, 70), (255, 17), (511, 2100), (1001, 300), (2047, 300), (4097, 20), (8191, 9)])
+@pytest.mark.parametrize("M,N", [(5, 40), (63, 70), (255, 17), (511, 2100), (1001, 300), (2047, 300), (4097, 20), (8191, 9),
+                                 # more rows than the backward takes in one launch
+                                 (9, 700), (63, 1000), (257, 650), (1001, 700), (2047, 645), (4097, 650), (8191, 641)])
 def test_layernorm_backward_where_beta_is_much_larger_than_gamma(B, M, N, dt, extremes):
     """xhat = (y - beta) / gamma: the subtraction cancels, so it has to come first.  It is exact or
     rounded once and the quotient within two units in the last place, whatever beta / gamma is;
