@@ -338,6 +338,24 @@ __device__ __forceinline__ void store_tail_bf16(bf16_t* p, int64_t left, const u
   for (int i = 0; i < left; ++i)
     p[i].bits = static_cast<uint16_t>((i & 1) ? (t[i >> 1] >> 16) : (t[i >> 1] & 0xFFFFu));
 }
+// The same with the elements under way together, for the backward, which has two of them to load: one after the
+// other they were what a launch of equal workgroups waited for last (2267029 elements 6.0 -> 4.8 us, 300007 3.9 -> 2.4).
+// The forward's straight-line path loses 4-6 % beside this code (4.1 M elements 4.7 -> 5.0 us).
+__device__ __forceinline__ u32x4 load_tail_together(const bf16_t* p, int64_t left) {
+  uint32_t e[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    e[i] = 0;
+    if (i < 7 && i < left) e[i] = p[i].bits;
+  }
+  return u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+}
+__device__ __forceinline__ void store_tail_together(bf16_t* p, int64_t left, const u32x4 v) {
+  const uint32_t t[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int i = 0; i < 7; ++i)
+    if (i < left) p[i].bits = static_cast<uint16_t>((i & 1) ? (t[i >> 1] >> 16) : (t[i >> 1] & 0xFFFFu));
+}
 
 constexpr uint32_t kAbsentX = 0xF149F149u;  // two bf16 of about -2.5e30: mask bit 0
 
@@ -431,8 +449,8 @@ __global__ __launch_bounds__(THREADS) void gelu_bwd_lut_kernel(const bf16_t* dy,
         wd[k] = ldg_stream(dy + q * 8);
         wy[k] = ldg_stream(y + q * 8);
       } else if (left > 0) {
-        wd[k] = load_tail_bf16(dy + q * 8, left, 0u);
-        wy[k] = load_tail_bf16(y + q * 8, left, 0u);
+        wd[k] = load_tail_together(dy + q * 8, left);
+        wy[k] = load_tail_together(y + q * 8, left);
       }
       if (left > 0) mw[k] = mask[q >> 2];
     }
@@ -449,7 +467,7 @@ __global__ __launch_bounds__(THREADS) void gelu_bwd_lut_kernel(const bf16_t* dy,
     } else {
       const int64_t left = n - q * 8;
       if (left >= 8) stg_stream(dx + q * 8, r);
-      else if (left > 0) store_tail_bf16(dx + q * 8, left, r);
+      else if (left > 0) store_tail_together(dx + q * 8, left, r);
     }
   }
 }

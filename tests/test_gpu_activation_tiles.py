@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 KI, MI = 1 << 10, 1 << 20
 SIZES = [8, 2041, 640 * KI, 640 * KI + 1, 3 * MI, 3 * MI + 517, 4 * MI, 4 * MI + 1, 8 * MI, 8 * MI + 8, 9 * MI + 3, 5003 * 3072,
-         16 * MI, 16 * MI + 1, 17 * MI + 511, 24 * MI - 1, 24 * MI]
+         16 * MI, 16 * MI + 1, 17 * MI + 511, 24 * MI - 1, 24 * MI] + [2267024 + left for left in range(8)]
 GUARD = 64
 
 
