@@ -33,7 +33,7 @@ extern "C" {
  *   with one piece each take those, a causal forward from 2 half as many waves with two pieces);
  *   key 15: lanes per workgroup of the float32 gelu / silu kernels (64, 128 or 256, with the
  *   pieces per lane of keys 0 / 1; 1, the default: one wave of one piece per lane forward, four
- *   waves of two pieces backward);
+ *   waves of two pieces backward, of one piece from 1 to 256 Ki elements);
  *   key 14: lanes per workgroup of attn fwd / bwd (64, 128 or 256; never fewer than a row's, or two rows'
  *   where a forward row takes two waves; rows on 12, 24, 48, ... lanes have workgroups of their own size);
  *   key 3: rows each lane group of layernorm_bwd walks (up to 640 rows, 320 of the longest, take one launch that has no

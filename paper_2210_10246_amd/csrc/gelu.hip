@@ -524,10 +524,11 @@ struct F32Shape {
   int threads;
   int k;
 };
-// Backward of up to 256 Ki elements one piece: 32 Ki 2.75 -> 2.3 us, 200 Ki 3.1 -> 2.8, but 300 Ki silu 3.4 -> 3.5.
+// Backward of up to 256 Ki elements one piece: 32 Ki 2.75 -> 2.3 us, 200 Ki 3.1 -> 2.8, but 300 Ki silu 3.4 -> 3.5, and
+// 1.9 -> 2.1 where one workgroup takes all (up to 1 Ki).
 static F32Shape f32_shape(bool forward, int64_t n) {
   const int forced = tune_get(kTuneGeluF32Threads);
-  if (forced == 1) return forward ? F32Shape{64, 1} : F32Shape{256, n <= (256 << 10) ? 1 : 2};
+  if (forced == 1) return forward ? F32Shape{64, 1} : F32Shape{256, n > 1024 && n <= (256 << 10) ? 1 : 2};
   const int k = pick_k(tune_get(forward ? kTuneGeluFwdChunks : kTuneGeluBwdChunks));
   return {forced >= 256 ? 256 : (forced >= 128 ? 128 : 64), k};
 }

@@ -1,6 +1,6 @@
-"""bfloat16 activations at sizes around every change of launch shape (small workgroups, tiles shrunk to the number of
-compute units): the values are looked up per bit pattern, so every shape gives the bits of the plain one (pieces
-per lane fixed by the knobs), with guard words behind every output."""
+"""Activations at sizes around every change of launch shape (small workgroups, tiles shrunk to the number of compute
+units): an element's values do not depend on its neighbours, so every shape gives the bits of the plain one (pieces
+and lanes fixed by the knobs), with guard words behind every output."""
 import pytest
 import torch
 
@@ -19,16 +19,29 @@ def guarded(n, dtype):
     return buf[:n], buf[n:]
 
 
+F32_SIZES = [1, 1021, 1024, 1025, 2047, 256 * KI - 1, 256 * KI, 256 * KI + 1, 300 * KI + 3]
+
+
 @pytest.mark.parametrize("kind", ["erf", "silu"])
 @pytest.mark.parametrize("n", SIZES)
 def test_every_shape_gives_the_same_bits(n, kind):
+    check(n, kind, torch.bfloat16, {0: 1, 1: 1})
+
+
+@pytest.mark.parametrize("kind", ["erf", "silu"])
+@pytest.mark.parametrize("n", F32_SIZES)
+def test_every_float32_shape_gives_the_same_bits(n, kind):
+    check(n, kind, torch.float32, {0: 4, 1: 4, 15: 64})
+
+
+def check(n, kind, dtype, plain):
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
-    x, dy = ((3 * torch.randn(n, generator=g, device="cuda")).to(torch.bfloat16) for _ in range(2))
+    x, dy = ((3 * torch.randn(n, generator=g, device="cuda")).to(dtype) for _ in range(2))
 
     def both():
-        (y, y_end), (mask, mask_end) = guarded(n, torch.bfloat16), guarded(B.mask_words(n), torch.int32)
-        dx, dx_end = guarded(n, torch.bfloat16)
+        (y, y_end), (mask, mask_end) = guarded(n, dtype), guarded(B.mask_words(n), torch.int32)
+        dx, dx_end = guarded(n, dtype)
         if kind == "silu":
             B.tempo_silu_fwd(x, y, mask)
             B.tempo_silu_bwd(dy, y, mask, dx)
@@ -39,12 +52,12 @@ def test_every_shape_gives_the_same_bits(n, kind):
         return y, mask, dx
 
     got = both()
-    old = B.tempo_get_launch_param(0), B.tempo_get_launch_param(1)
+    old = {key: B.tempo_get_launch_param(key) for key in plain}
     try:
-        B.tempo_set_launch_param(0, 1)
-        B.tempo_set_launch_param(1, 1)
+        for key, value in plain.items():
+            B.tempo_set_launch_param(key, value)
         want = both()
     finally:
-        B.tempo_set_launch_param(0, old[0])
-        B.tempo_set_launch_param(1, old[1])
+        for key, value in old.items():
+            B.tempo_set_launch_param(key, value)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
