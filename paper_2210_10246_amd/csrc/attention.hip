@@ -885,10 +885,10 @@ Shape row_shape(int64_t Sk, int vec, int max_ch, RowUse use) {
   if (pieces > kMaxPieces) return {0, 0};
   return shape_of(static_cast<int>(pieces), Sk % 8 != 0, vec, max_ch, use);
 }
-// Whether rows come to a shape: all that ragged rows and odd numbers of lanes have kernels for.  (Aligned rows on a
-// power of two come to any, by the knobs.)
+// Whether rows come to a shape: all that there are kernels for.  (Aligned rows on a power of two come to any from 32
+// elements, by the knobs.)
 constexpr bool has_kernel(int lanes, int ch, int vec, bool ragged, bool backward) {
-  if (!ragged && !is_odd(lanes)) return true;
+  if (!ragged && !is_odd(lanes)) return lanes * vec >= 32;
   for (int p = 1; p <= kMaxPieces; ++p) {
     for (RowUse use : {kForward, kForwardCausal, kBackward}) {
       const Shape sh = shape_of(p, ragged, vec, 1, use);
@@ -1068,7 +1068,7 @@ static void attn_fwd_go(int rr, MaskLayout layout, int threads, size_t lds, uint
   using std::integral_constant;
   const integral_constant<MaskLayout, kWords> words{};
   const integral_constant<MaskLayout, kBytes> bytes{};
-  if constexpr (C <= 2 && L <= kWave && !is_odd(L)) {
+  if constexpr (std::is_same<T, bf16_t>::value && C == 1 && L == kWave) {  // attn_rows()
     if (rr == 2) {
       if (layout == kWords) return go(integral_constant<int, 2>{}, words);
       return go(integral_constant<int, 2>{}, bytes);

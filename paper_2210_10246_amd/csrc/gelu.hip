@@ -501,7 +501,7 @@ static LutShape lut_shape(bool forward, int64_t n, int k) {
   const int64_t even = (pieces + cus * per_cu - 1) / (cus * per_cu);
   if (forward ? per_cu < 2 : (per_cu > 1 || even * 4 > most * 3)) return whole(kLutThreads, k);
   const int tile = static_cast<int>((even + kWave - 1) / kWave * kWave);
-  return {kLutThreads, tile <= most / 2 ? k / 2 : k, true, tile};
+  return {kLutThreads, tile <= most / 2 ? k / 2 : k, true, tile};  // k forward: more than half a tile each of two or more
 }
 static int lut_grid(int64_t n, const LutShape& sh) {
   return static_cast<int>(((n + 7) / 8 + sh.tile - 1) / sh.tile);
@@ -553,20 +553,27 @@ static void with_kind_k(int kind, int k, F&& f) {
   else with_k<kActSilu>(k, f);
 }
 
-// Calls f with the shape's lanes, pieces per lane and SPLIT as compile-time constants.
-template <typename F>
+// Calls f with the shape's lanes, pieces per lane and SPLIT as compile-time constants: those that lut_shape() gives
+// the direction.
+template <bool FORWARD, typename F>
 static void with_lut_shape(const LutShape& sh, F&& f) {
   using std::integral_constant;
-  auto pieces = [&](auto threads, auto split) {
-    if (sh.k == 1) f(threads, integral_constant<int, 1>{}, split);
-    else if (sh.k == 2) f(threads, integral_constant<int, 2>{}, split);
-    else f(threads, integral_constant<int, 4>{}, split);
-  };
-  if (sh.threads == 256) f(integral_constant<int, 256>{}, integral_constant<int, 1>{}, std::false_type{});
-  else if (sh.threads == 512 && sh.k == 1) f(integral_constant<int, 512>{}, integral_constant<int, 1>{}, std::false_type{});
-  else if (sh.threads == 512) f(integral_constant<int, 512>{}, integral_constant<int, 2>{}, std::false_type{});
-  else if (sh.split) pieces(integral_constant<int, kLutThreads>{}, std::true_type{});
-  else pieces(integral_constant<int, kLutThreads>{}, std::false_type{});
+  constexpr integral_constant<int, 1> one{};
+  constexpr integral_constant<int, 2> two{};
+  constexpr integral_constant<int, 4> four{};
+  constexpr integral_constant<int, kLutThreads> all{};
+  constexpr std::false_type whole{};
+  constexpr std::true_type split{};
+  if (sh.threads == 256) return f(integral_constant<int, 256>{}, one, whole);
+  if constexpr (FORWARD) {
+    constexpr integral_constant<int, 512> half{};
+    if (sh.threads == 512) return sh.k == 1 ? f(half, one, whole) : f(half, two, whole);
+    if (sh.split) return f(all, four, split);
+  } else {
+    if (sh.split) return sh.k == 1 ? f(all, one, split) : f(all, two, split);
+  }
+  if (sh.k == 1) return f(all, one, whole);
+  sh.k == 2 ? f(all, two, whole) : f(all, four, whole);
 }
 template <typename F>
 static void with_kind(int kind, F&& f) {
@@ -581,7 +588,7 @@ tempo_status launch_gelu_fwd(const void* x, void* y, uint32_t* mask, int64_t n, 
   if (dt == TEMPO_BF16) {
     const LutShape sh = lut_shape(true, n, k);
     with_kind(kind, [&](auto kd) {
-      with_lut_shape(sh, [&](auto th, auto kk, auto split) {
+      with_lut_shape<true>(sh, [&](auto th, auto kk, auto split) {
         constexpr int TH = decltype(th)::value;
         hipLaunchKernelGGL((gelu_fwd_lut_kernel<decltype(kd)::value, decltype(kk)::value, TH, decltype(split)::value>),
                            dim3(lut_grid(n, sh)), dim3(TH), 0, st, static_cast<const bf16_t*>(x),
@@ -608,7 +615,7 @@ tempo_status launch_gelu_bwd(const void* dy, const void* y, const uint32_t* mask
   if (dt == TEMPO_BF16) {
     const LutShape sh = lut_shape(false, n, k);
     with_kind(kind, [&](auto kd) {
-      with_lut_shape(sh, [&](auto th, auto kk, auto split) {
+      with_lut_shape<false>(sh, [&](auto th, auto kk, auto split) {
         constexpr int TH = decltype(th)::value;
         hipLaunchKernelGGL((gelu_bwd_lut_kernel<decltype(kd)::value, decltype(kk)::value, TH, decltype(split)::value>),
                            dim3(lut_grid(n, sh)), dim3(TH), 0, st, static_cast<const bf16_t*>(dy),

@@ -1030,10 +1030,8 @@ constexpr Shape widen_shape(Shape one, int pieces, int max_ch, int max_lanes) {
     case 6412: LAUNCH(64, 12); break;                                                      \
     case 6416: LAUNCH(64, 16); break;                                                      \
     case 3201: LAUNCH(32, 1); break;                                                       \
-    case 3202: LAUNCH(32, 2); break;                                                       \
     case 3203: LAUNCH(32, 3); break;                                                       \
     case 1601: LAUNCH(16, 1); break;                                                       \
-    case 1602: LAUNCH(16, 2); break;                                                       \
     case 1603: LAUNCH(16, 3); break;                                                       \
     case 12801: LAUNCH(128, 1); break;                                                     \
     case 12802: LAUNCH(128, 2); break;                                                     \
@@ -1281,9 +1279,10 @@ static int ln_bwd_go(const BwdPlan& plan, bool ragged, size_t lds_bytes, hipStre
                      const void* y, const float* gamma, const float* beta, const float* rstd,
                      void* dx, float* workspace, int64_t N, int64_t M, int slot_row) {
   int grid = plan.grid;
-  if constexpr ((std::is_same<T, bf16_t>::value && C > 4 && L > kWave) ||
+  if constexpr ((std::is_same<T, bf16_t>::value && ((C > 4 && L > kWave) || (C == 16 && L == kWave))) ||
+                (L == 4 * kWave && C * Store<T>::kVec > 24) ||
                 (L == kBwdThreads && C != (std::is_same<T, bf16_t>::value ? 2 : 4))) {
-    return grid;  // shapes that exist for the other dtype only
+    return grid;  // shapes that exist for the other dtype or the forward only
   } else {
     auto launch = [&](auto rows, auto loop, auto rag) {
       auto kernel = ln_bwd_kernel<T, L, C, decltype(rows)::value, decltype(loop)::value,
