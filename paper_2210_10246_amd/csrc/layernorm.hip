@@ -73,6 +73,21 @@ __device__ __forceinline__ float tame_quotient(float d, float g, float rcp) {
   const float q = d * rcp;
   return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-g, q, d), rcp, q), g, d);
 }
+// Whether all of a wave's gammas are tame: scalar, so that the choice is a branch and not a select.
+__device__ __forceinline__ bool all_tame(uint32_t offset) {
+  return __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;
+}
+// xhat of an element from the stored output.  The fused form loses 2^-24 |beta / gamma| to the rounding of
+// beta / gamma; ragged rows subtract first and divide (tame_quotient).  What this / a division per element takes
+// beyond the fused form, us: 8192 x 1001 f32 0.3 / 0.2, bf16 0.9 / 2.7; 4096 x 4100 bf16 1.1 / 4.8.
+// wave_tame: all_tame(); if not, the choice is per column, so that the two lanes which share one find the same value.
+// (Per element: as a loop over the piece with the branch around it the few-row kernel spills, f32 64x4100 4.0 -> 5.9 us.)
+template <bool RAG>
+__device__ __forceinline__ float xhat_of(float y, float ga, float rg, float bg, bool wave_tame) {
+  if constexpr (!RAG) return fmaf(y, rg, -bg);
+  if (wave_tame || tame_offset(ga) <= kTameRange) return tame_quotient(y - bg, ga, rg);
+  return (y - bg) / ga;
+}
 // Length of a row of column sums in LDS: whole 16-byte pieces.
 __host__ __device__ constexpr int64_t lds_row(int64_t M) { return (M + 3) & ~int64_t{3}; }
 
@@ -390,24 +405,15 @@ __global__ __launch_bounds__(kBwdThreads) void ln_bwd_kernel(
     }
     lds_barrier();
   }
-  // xhat of a piece.  The fused form loses 2^-24 |beta / gamma| to the rounding of beta / gamma; ragged
-  // rows subtract first and divide (tame_quotient).  What this / a division per element takes
-  // beyond the fused form, us: 8192 x 1001 f32 0.3 / 0.2, bf16 0.9 / 2.7; 4096 x 4100 bf16 1.1 / 4.8.
-  const bool wave_tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // scalar: a branch, not a select
+  const bool wave_tame = all_tame(offset);
   auto xhat = [&](const float (&y8)[V], const float (&ga)[V], const float (&rg)[V], const float (&bg)[V],
                   float (&h)[V]) {
-    if constexpr (!RAG) {
+    if (!RAG || wave_tame) {
 #pragma unroll
-      for (int i = 0; i < V; ++i) h[i] = fmaf(y8[i], rg[i], -bg[i]);
+      for (int i = 0; i < V; ++i) h[i] = xhat_of<RAG>(y8[i], ga[i], rg[i], bg[i], true);
     } else {
-      if (wave_tame) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) h[i] = tame_quotient(y8[i] - bg[i], ga[i], rg[i]);
-      } else {  // per column, so that the two lanes which share one find the same value
-#pragma unroll
-        for (int i = 0; i < V; ++i)
-          h[i] = tame_offset(ga[i]) <= kTameRange ? tame_quotient(y8[i] - bg[i], ga[i], rg[i]) : (y8[i] - bg[i]) / ga[i];
-      }
+      for (int i = 0; i < V; ++i) h[i] = xhat_of<RAG>(y8[i], ga[i], rg[i], bg[i], false);
     }
   };
   while (base < N) {
@@ -803,11 +809,10 @@ __global__ __launch_bounds__(kFinVecLanes* kFinSlices) void ln_bwd_finalize_kern
   }
 }
 
-// xhat of a piece from its output, as ln_bwd_kernel computes it: y / gamma - beta / gamma of aligned rows,
-// the quotient of ragged ones.
+// The columns of a piece and xhat of its rows.
 template <bool RAG, int V>
 struct Xhat {
-  float ga[V], rg[V], bg[V];  // RAG: bg is beta
+  float ga[V], rg[V], bg[V];
   bool tame;
   __device__ __forceinline__ Xhat(const float (&gamma)[V], const float (&beta)[V]) {
     uint32_t offset = 0;
@@ -818,15 +823,11 @@ struct Xhat {
       bg[i] = RAG ? beta[i] : beta[i] * rg[i];
       offset = max(offset, tame_offset(gamma[i]));
     }
-    tame = __builtin_amdgcn_ballot_w64(offset > kTameRange) == 0;  // the wave's: a branch, not a select
+    tame = all_tame(offset);
   }
   __device__ __forceinline__ void operator()(const float (&y8)[V], float (&h)[V]) const {
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-      if constexpr (!RAG) h[i] = fmaf(y8[i], rg[i], -bg[i]);
-      else if (tame || tame_offset(ga[i]) <= kTameRange) h[i] = tame_quotient(y8[i] - bg[i], ga[i], rg[i]);
-      else h[i] = (y8[i] - bg[i]) / ga[i];
-    }
+    for (int i = 0; i < V; ++i) h[i] = xhat_of<RAG>(y8[i], ga[i], rg[i], bg[i], tame);
   }
 };
 
