@@ -833,15 +833,15 @@ enum RowUse { kForward, kForwardCausal, kBackward };
 // bounds the bfloat16 forward, works for idle lanes too, and the backward keeps fewer loads under way per wave.  The
 // price is a workgroup barrier per row sum.  Power of two / this, us:
 //  - 12 (bfloat16 only: 8 lanes share a float32 mask word), 24 and 48 lanes for 9..12, 17..24 and 33..48 pieces, both
-//    ways: bf16 48x16x80x80 17.5 / 17.0, 32x16x150x150 39.6 / 35.2, 16x16x333x333 padded 83.2 / 74.8, 16x16x384x384 89.3 /
-//    84.4; f32 32x16x96x96 26.5 / 26.0, 32x16x150x150 66.9 / 60.2;
+//    ways: bf16 48x16x80x80 17.5 / 16.4, 32x16x150x150 38.9 / 34.3, 16x16x333x333 padded 84.5 / 75.2, 16x16x384x384 91.7 /
+//    88.2; f32 32x16x96x96 26.7 / 25.8, 32x16x150x150 67.9 / 60.8;
 //  - backward on 96 lanes for 65..96 pieces, bf16 8x16x520x520 55.3 / 49.4, 8x16x765x765 117 / 106, 8x16x768x768 99.6 /
 //    99.0, f32 16x16x333x333 86.9 / 80.3; 160 for 129..160, bf16 2x16x1101x1101 63.2 / 55.1, 1280 70.9 / 69.0; 224
 //    for 193..224 of bf16 ragged, 1701 148 / 131, not aligned, 1792 133.1 / 133.1, nor f32, 800 107 / 108.5; 320 for 257..320,
 //    bf16 2x8x2100x2100 105 / 96, 2560 140.0 / 138.7; 384 for 321..352 of ragged rows, bf16 2700 166 / 159, f32
 //    2x16x1401x1401 174 / 168;
 //  - the bfloat16 forward without a causal mask, whose pieces a lane skips, on 96 lanes from 89 pieces, 8x16x744x744
-//    80.9 / 74.6 (704: 65.5 / 65.5, 520: 43.0 / 44.7).
+//    89.8 / 79.1 (704 columns the same, 520 4 % slower).
 // The same as a mean of the ratio over two dozen sizes of 0.3 to 38 M elements each, below 3 M / above, since every size
 // at which the workgroups just exceed what is resident loses up to 17 % and others gain as much:
 //  - taken: 12..48 lanes forward 0.83-1.00 / 0.87-0.94, backward 0.89-1.00 / 0.91-0.99; backward on 96 0.87-0.98 /
