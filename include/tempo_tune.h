@@ -28,7 +28,7 @@ extern "C" {
  *   layernorm_fwd then takes 4 rows of one piece per lane, 2 of two pieces);
  *   key 8, 9, 10, 11: attn fwd / attn bwd / layernorm_fwd / layernorm_bwd: 16-byte pieces per
  *   lane above which a row is spread over 2 or 4 waves instead of one (16 or more: never, but for layernorm_bwd of more
- *   than 5120 columns, whose sums would not fit; attn fwd /
+ *   than 5088 columns, whose sums would not fit; attn fwd /
  *   bwd up to 4: rows that then fill the lanes of 2 or 4 waves, or 12, 24, 48, 96, 160, 224, 320 or 384 lanes,
  *   with one piece each take those, a causal forward from 2 half as many waves with two pieces);
  *   key 15: lanes per workgroup of the float32 gelu / silu kernels (64, 128 or 256, with the

@@ -81,7 +81,7 @@ __device__ __forceinline__ bool all_tame(uint32_t offset) {
 // beta / gamma; ragged rows subtract first and divide (tame_quotient).  What this / a division per element takes
 // beyond the fused form, us: 8192 x 1001 f32 0.3 / 0.2, bf16 0.9 / 2.7; 4096 x 4100 bf16 1.1 / 4.8.
 // wave_tame: all_tame(); if not, the choice is per column, so that the two lanes which share one find the same value.
-// (Per element: as a loop over the piece with the branch around it the few-row kernel spills, f32 64x4100 4.0 -> 5.9 us.)
+// (Per element: with a loop over the piece inside the branch the few-row kernel is slower, f32 64x4100 4.0 -> 5.9 us.)
 template <bool RAG>
 __device__ __forceinline__ float xhat_of(float y, float ga, float rg, float bg, bool wave_tame) {
   if constexpr (!RAG) return fmaf(y, rg, -bg);
@@ -1139,8 +1139,9 @@ static void ln_fwd_go(int rr, bool loop, bool ragged, int grid, hipStream_t st, 
 
 static bool is_ragged(int64_t M, tempo_dtype dt) { return M % (dt == TEMPO_F32 ? 4 : 8) != 0; }
 
-// Longest rows whose column sums fit the LDS of a compute unit when a wave owns a row: half of the waves' sums at once.
-constexpr int64_t kOneWaveBwdColumns = 160 * 1024 / (kBwdWaves / 2 * 2 * sizeof(float));
+// Longest rows whose column sums fit the LDS of a compute unit when a wave owns a row: half of the waves' sums at once,
+// beside 1 KiB for what the kernel declares itself.
+constexpr int64_t kOneWaveBwdColumns = 159 * 1024 / (kBwdWaves / 2 * 2 * sizeof(float));  // 5088
 static bool fast_shape(int64_t N, int64_t M, tempo_dtype dt, bool backward, Shape* sh) {
   const int vec = dt == TEMPO_F32 ? 4 : 8;
   if (M < vec || (M + vec - 1) / vec > max_fast_pieces(vec)) return false;

@@ -289,7 +289,8 @@ def test_layernorm_bwd(B, shape, dt):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(37, 2048), (5, 3072), (9, 4096), (3, 1032), (600, 1536),
                                    # more rows than the backward takes in one launch, which has no knobs
-                                   (643, 1032), (701, 1536), (645, 2048), (703, 3072), (1030, 4096), (642, 6144), (641, 8192)])
+                                   (643, 1032), (701, 1536), (645, 2048), (703, 3072), (1030, 4096), (642, 6144), (641, 8192),
+                                   (650, 5080), (650, 5088), (650, 5096), (650, 5120)])
 def test_layernorm_row_over_one_or_several_waves(B, shape, dt):
     """Long rows: the same results whether one wave or 2-4 waves own a row (knobs 10, 11),
     with row counts that leave lane groups without a row in the last batch."""
