@@ -379,3 +379,22 @@ def tempo_mask_bytes_to_bits(bytes_, bits, n, stream=None):
     _want("bytes", bytes_, torch.uint8, at_least=n)
     _check(load().tempo_mask_bytes_to_bits(_ptr(bytes_), _ptr(bits), n, _stream(stream)),
            "tempo_mask_bytes_to_bits")
+
+
+def encoder_fwd(*args):
+    """One native call for the forward of modules.TempoEncoderLayer (csrc/binding.cpp names the arguments): what its backward
+    needs, or None if the call was not made."""
+    r = _native.tempo_encoder_fwd(*args)
+    if r is None:
+        return None
+    _check(r[0], "encoder_fwd")
+    return r[1:]
+
+
+def encoder_bwd(*args):
+    """The same for the backward: the gradients of x and the parameters."""
+    r = _native.tempo_encoder_bwd(*args)
+    if r is None:
+        raise ValueError("encoder_bwd: a gradient or a kept tensor is not what the forward left")
+    _check(r[0], "encoder_bwd")
+    return r[1:]

@@ -11,7 +11,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libtempo.so")
-SOURCES = ("api.hip", "gelu.hip", "layernorm.hip", "attention.hip", "mask.hip")
+SOURCES = ("api.hip", "gelu.hip", "layernorm.hip", "attention.hip", "mask.hip", "matmul.hip", "encoder.hip")
 NATIVE_PATH = os.path.join(HERE, "_native.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -8,10 +8,13 @@
 // is no float or int.  Nothing has happened then, and binding.py goes through its own checks, which
 // raise what they always raised.
 #include <Python.h>
+#include <ATen/ops/empty.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/tempo.h"
+#include "encoder.h"
 
 namespace {
 
@@ -225,6 +228,202 @@ TEMPO_METHOD(attn_softmax_dropout_bwd_bytemask) {  // dout, probs, keep_bytes, d
   });
 }
 
+// ---- the encoder layer of modules.py ---------------------------------------------------------------------------
+// A float32 tensor of these sizes beside x.
+float* beside(const at::Tensor& x, PyObject* o, std::initializer_list<int64_t> sizes) {
+  const at::Tensor& t = tensor(o);
+  if (t.scalar_type() != at::kFloat || t.device() != x.device() || t.sizes() != at::IntArrayRef(sizes) || t.is_neg()) throw NotPlain{};
+  return static_cast<float*>(pointer(t));
+}
+constexpr int kEncoderParams = 12;
+// The layer of x with heads, eps1, eps2, p, seed, offset and kind at a[0 .. 6], and its parameters at w.
+tempo_encoder encoder(const at::Tensor& x, PyObject* const* a, PyObject* const* w) {
+  tempo_encoder e{};
+  if (x.scalar_type() != at::kFloat || x.dim() != 3 || x.is_neg() || x.device().index() != c10::hip::current_device()) throw NotPlain{};
+  e.x = static_cast<float*>(pointer(x));
+  e.batch = x.size(0);
+  e.seq = x.size(1);
+  e.hidden = x.size(2);
+  if (!PyLong_CheckExact(a[0])) throw NotPlain{};
+  e.heads = PyLong_AsLongLong(a[0]);
+  e.eps1 = real(a[1]);
+  e.eps2 = real(a[2]);
+  e.p = real(a[3]);
+  e.seed = bits64(a[4]);
+  e.offset = bits64(a[5]);
+  e.kind = gelu_kind(a[6]);
+  const at::Tensor& w1 = tensor(w[4]);
+  if (w1.dim() != 2) throw NotPlain{};
+  e.ffn = w1.size(0);
+  const int64_t H = e.hidden, F = e.ffn;
+  e.wqkv = beside(x, w[0], {3 * H, H});
+  e.bqkv = beside(x, w[1], {3 * H});
+  e.wproj = beside(x, w[2], {H, H});
+  e.bproj = beside(x, w[3], {H});
+  e.w1 = beside(x, w[4], {F, H});
+  e.b1 = beside(x, w[5], {F});
+  e.w2 = beside(x, w[6], {H, F});
+  e.b2 = beside(x, w[7], {H});
+  e.gamma1 = beside(x, w[8], {H});
+  e.beta1 = beside(x, w[9], {H});
+  e.gamma2 = beside(x, w[10], {H});
+  e.beta2 = beside(x, w[11], {H});
+  if (!tempo_encoder_takes(&e)) throw NotPlain{};
+  return e;
+}
+float* data(const at::Tensor& t) { return t.defined() ? static_cast<float*>(t.data_ptr()) : nullptr; }
+// (status, tensors), an undefined one as None
+template <size_t N>
+PyObject* result(tempo_status status, const at::Tensor* const (&t)[N]) {
+  PyObject* r = PyTuple_New(N + 1);
+  if (!r) return nullptr;
+  PyTuple_SET_ITEM(r, 0, PyLong_FromLong(status));
+  for (size_t i = 0; i < N; ++i) PyTuple_SET_ITEM(r, i + 1, THPVariable_Wrap(*t[i]));  // None for an undefined one
+  return r;
+}
+
+// x, key_len, heads, eps1, eps2, p, seed, offset, kind, 12 parameters -> status and what the backward needs
+TEMPO_METHOD(encoder_fwd) {
+  if (nargs != 9 + kEncoderParams) Py_RETURN_NONE;
+  at::Tensor qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2;
+  tempo_status status;
+  try {
+    const at::Tensor& x = tensor(a[0]);
+    tempo_encoder e = encoder(x, a + 2, a + 9);
+    if (a[1] != Py_None) {
+      const at::Tensor& k = tensor(a[1]);
+      if (k.scalar_type() != at::kInt || k.numel() != e.batch || k.device() != x.device()) throw NotPlain{};
+      e.key_len = static_cast<int32_t*>(pointer(k));
+    }
+    const int64_t B = e.batch, S = e.seq, T = B * S, n = B * e.heads * S * S;
+    const auto floats = x.options().requires_grad(false), words = floats.dtype(at::kInt);
+    qkv = at::empty({T, 3 * e.hidden}, floats);
+    probs = at::empty({B, e.heads, S, S}, floats);
+    at::Tensor out = at::empty({B, e.heads, S, S}, floats);
+    keep = at::empty({(n + 31) / 32}, words);
+    ctxt = at::empty({T, e.hidden}, floats);
+    y1 = at::empty({T, e.hidden}, floats);
+    rstd1 = at::empty({T}, floats);
+    h = at::empty({T, e.ffn}, floats);
+    side = at::empty({(T * e.ffn + 31) / 32}, words);
+    y2 = at::empty({B, S, e.hidden}, floats);
+    rstd2 = at::empty({T}, floats);
+    e.qkv = data(qkv);
+    e.probs = data(probs);
+    e.keep = reinterpret_cast<uint32_t*>(keep.data_ptr());
+    e.ctxt = data(ctxt);
+    e.y1 = data(y1);
+    e.rstd1 = data(rstd1);
+    e.h = data(h);
+    e.side = reinterpret_cast<uint32_t*>(side.data_ptr());
+    e.y2 = data(y2);
+    e.rstd2 = data(rstd2);
+    void* st = stream();
+    PyThreadState* state = PyEval_SaveThread();
+    status = tempo_encoder_fwd(&e, data(out), st);
+    PyEval_RestoreThread(state);
+  } catch (...) {
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
+  const at::Tensor* all[] = {&qkv, &probs, &keep, &ctxt, &y1, &rstd1, &h, &side, &y2, &rstd2};
+  return result(status, all);
+}
+
+// dy, wanted (bits: x, then the parameters), x, heads, eps1, eps2, p, seed, offset, kind, 12 parameters, and of
+// encoder_fwd qkv, probs, keep or None, ctxt, y1, rstd1, h, side, y2, rstd2 -> status and the 13 gradients
+TEMPO_METHOD(encoder_bwd) {
+  if (nargs != 10 + kEncoderParams + 10) Py_RETURN_NONE;
+  at::Tensor dx, dw[kEncoderParams];
+  tempo_status status = TEMPO_OK;
+  try {
+    const at::Tensor& x = tensor(a[2]);
+    tempo_encoder e = encoder(x, a + 3, a + 10);
+    PyObject* const* kept = a + 10 + kEncoderParams;
+    const int64_t B = e.batch, S = e.seq, T = B * S, H = e.hidden, F = e.ffn, n = B * e.heads * S * S;
+    const float* dy = beside(x, a[0], {B, S, H});
+    const uint64_t wanted = bits64(a[1]);
+    e.qkv = beside(x, kept[0], {T, 3 * H});
+    e.probs = beside(x, kept[1], {B, e.heads, S, S});
+    if (kept[2] != Py_None) e.keep = mask_words(kept[2], n);
+    e.ctxt = beside(x, kept[3], {T, H});
+    e.y1 = beside(x, kept[4], {T, H});
+    e.rstd1 = beside(x, kept[5], {T});
+    e.h = beside(x, kept[6], {T, F});
+    e.side = mask_words(kept[7], T * F);
+    e.y2 = beside(x, kept[8], {B, S, H});
+    e.rstd2 = beside(x, kept[9], {T});
+    auto want = [&](int first, int last) { return (wanted >> first & ((uint64_t{2} << (last - first)) - 1)) != 0; };
+    const auto floats = x.options().requires_grad(false);
+    auto grad = [&](int i, at::IntArrayRef sizes) { return data(dw[i] = at::empty(sizes, floats)); };
+    tempo_encoder_grads g{};
+    at::Tensor ds = at::empty({T, H}, floats), dh, dy1;
+    at::Tensor workspace = at::empty({static_cast<int64_t>(tempo_layernorm_bwd_workspace_bytes(T, H))}, floats.dtype(at::kByte));
+    const size_t workspace_bytes = workspace.numel();
+    void* st = stream();
+    auto run = [&](auto&& call) {
+      if (status != TEMPO_OK) return;
+      PyThreadState* state = PyEval_SaveThread();
+      status = call();
+      PyEval_RestoreThread(state);
+    };
+    // bits: 0 x, 1 2 qkv, 3 4 proj, 5 6 fc1, 7 8 fc2, 9 10 ln1, 11 12 ln2
+    const bool attention = want(0, 2), first = want(0, 4) || want(9, 10);
+    g.dgamma2 = grad(10, {H});
+    g.dbeta2 = grad(11, {H});
+    if (want(7, 8)) {
+      g.dw2 = grad(6, {H, F});
+      g.db2 = grad(7, {H});
+    }
+    if (want(5, 6)) {
+      g.dw1 = grad(4, {F, H});
+      g.db1 = grad(5, {F});
+    }
+    if (first) dy1 = at::empty({T, H}, floats);
+    if (first || g.dw1) dh = at::empty({T, F}, floats);
+    run([&] {
+      return tempo_encoder_bwd_ffn(&e, &g, dy, data(ds), data(dh), data(dy1), workspace.data_ptr(), workspace_bytes, st);
+    });
+    dh.reset();
+    if (first) {
+      g.dgamma1 = grad(8, {H});
+      g.dbeta1 = grad(9, {H});
+      run([&] {
+        return tempo_encoder_bwd_norm(&e, &g, data(dy1), data(ds), workspace.data_ptr(), workspace_bytes, st);
+      });
+    }
+    workspace.reset();
+    if (want(0, 4)) {
+      at::Tensor dctxt, dqkv, dout, out;
+      if (want(3, 4)) {
+        g.dwproj = grad(2, {H, H});
+        g.dbproj = grad(3, {H});
+      }
+      if (attention) {
+        dctxt = dy1;  // has been read
+        dqkv = at::empty({T, 3 * H}, floats);
+        dout = at::empty({B, e.heads, S, S}, floats);
+        out = at::empty({B, e.heads, S, S}, floats);
+        if (want(1, 2)) {
+          g.dwqkv = grad(0, {3 * H, H});
+          g.dbqkv = grad(1, {3 * H});
+        }
+        if (want(0, 0)) g.dx = data(dx = at::empty({B, S, H}, floats));
+      }
+      run([&] {
+        return tempo_encoder_bwd_attention(&e, &g, data(ds), data(dctxt), data(dqkv), data(dout), data(out), st);
+      });
+    }
+    for (int i = 0; i < kEncoderParams; ++i)
+      if (!want(i + 1, i + 1)) dw[i].reset();
+  } catch (...) {
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
+  const at::Tensor* all[] = {&dx, dw, dw + 1, dw + 2, dw + 3, dw + 4, dw + 5, dw + 6, dw + 7, dw + 8, dw + 9, dw + 10, dw + 11};
+  return result(status, all);
+}
+
 #define TEMPO_ENTRY(name) {"tempo_" #name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {TEMPO_ENTRY(gelu_fwd),
                          TEMPO_ENTRY(gelu_bwd),
@@ -237,6 +436,8 @@ PyMethodDef methods[] = {TEMPO_ENTRY(gelu_fwd),
                          TEMPO_ENTRY(attn_softmax_dropout_bwd),
                          TEMPO_ENTRY(attn_softmax_dropout_bwd_regen),
                          TEMPO_ENTRY(attn_softmax_dropout_bwd_bytemask),
+                         TEMPO_ENTRY(encoder_fwd),
+                         TEMPO_ENTRY(encoder_bwd),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

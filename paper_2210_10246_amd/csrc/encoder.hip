@@ -1,0 +1,158 @@
+// The launches of encoder.h.  Heads are taken from and put into the [T, 3 hidden] and [T, hidden] layouts by the
+// strides of the products, and residuals, biases, 1 / sqrt(d) and the sums for the bias gradients are part of them: no
+// copies, no elementwise passes beside the three layers.
+#include <cmath>
+
+#include "encoder.h"
+#include "matmul.h"
+
+namespace tempo {
+namespace {
+
+struct Sizes {
+  int64_t T, H, F, S, d;
+  int B, A;
+  explicit Sizes(const tempo_encoder& e)
+      : T(e.batch * e.seq), H(e.hidden), F(e.ffn), S(e.seq), d(e.hidden / e.heads), B(static_cast<int>(e.batch)),
+        A(static_cast<int>(e.heads)) {}
+};
+
+MatSide rows_of(const float* p, int64_t ld, int64_t outer = 0, int64_t inner = 0) { return {p, ld, outer, inner, false}; }
+MatSide columns_of(const float* p, int64_t ld, int64_t outer = 0, int64_t inner = 0) { return {p, ld, outer, inner, true}; }
+
+Matmul product(MatSide a, MatSide b, float* c, int64_t ldc, int64_t M, int64_t N, int64_t K) {
+  return {a, b, c, ldc, 0, 0, nullptr, nullptr, nullptr, 1.0f, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 1, 1};
+}
+// One product per head.
+Matmul per_head(const Sizes& z, MatSide a, MatSide b, float* c, int64_t ldc, int64_t c_outer, int64_t c_inner, int64_t N,
+                int64_t K) {
+  Matmul g = product(a, b, c, ldc, z.S, N, K);
+  g.c_outer = c_outer;
+  g.c_inner = c_inner;
+  g.batch = z.B * z.A;
+  g.inner = z.A;
+  return g;
+}
+// y = x w^T + bias (+ add)
+Matmul linear(const float* x, const float* w, const float* bias, const float* add, float* y, int64_t T, int64_t out, int64_t in) {
+  Matmul g = product(rows_of(x, in), rows_of(w, in), y, out, T, out, in);
+  g.bias = bias;
+  g.add = add;
+  return g;
+}
+// dx = dy w (+ add)
+Matmul linear_dx(const float* dy, const float* w, const float* add, float* dx, int64_t T, int64_t out, int64_t in) {
+  Matmul g = product(rows_of(dy, out), columns_of(w, in), dx, in, T, in, out);
+  g.add = add;
+  return g;
+}
+// dw = dy^T x and db = the column sums of dy
+Matmul linear_dw(const float* dy, const float* x, float* dw, float* db, int64_t T, int64_t out, int64_t in) {
+  Matmul g = product(columns_of(dy, out), columns_of(x, in), dw, in, out, in, T);
+  g.a_sums = db;
+  return g;
+}
+
+struct Run {
+  hipStream_t st;
+  tempo_status status = TEMPO_OK;
+  void operator()(tempo_status s) {
+    if (status == TEMPO_OK) status = s;
+  }
+  void operator()(const Matmul& g) {
+    if (status == TEMPO_OK) status = launch_matmul(g, st);
+  }
+};
+
+}  // namespace
+}  // namespace tempo
+
+using namespace tempo;
+
+int tempo_encoder_takes(const tempo_encoder* e) {
+  const Sizes z(*e);
+  if (z.T < 1 || z.H < 1 || z.F < 1 || z.A < 1 || z.H % z.A != 0) return 0;
+  if (z.H % 4 != 0 || z.F % 4 != 0 || z.d % 4 != 0) return 0;
+  const int64_t most = int64_t{1} << 30;  // sizes and tiles are counted in 32 bits
+  if (z.T > most / (3 * z.H) || z.T > most / z.F || z.F > most / z.H || z.S > 32768 ||
+      e->batch * e->heads > most / (z.S * z.S))
+    return 0;
+  // Multiplications of the four layers' weights, forward.  Below, the launches, copies and host time that go count for more than
+  // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 911 / 233, 8 x 128 x 1024 953 / 810,
+  // 8 x 256 x 1024 (26e9) 1575 / 1538, 32 x 256 x 512 (26e9) 1834 / 1789, but 16 x 256 x 1024 (52e9) 2938 / 3132.
+  return z.T * (4 * z.H * z.H + 2 * z.H * z.F) <= int64_t{26} * 1000 * 1000 * 1000;
+}
+
+tempo_status tempo_encoder_fwd(const tempo_encoder* e, float* out, void* hip_stream) {
+  const Sizes z(*e);
+  const int64_t H = z.H, S = z.S, d = z.d, L = 3 * H;
+  const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(d)));
+  Run run{static_cast<hipStream_t>(hip_stream)};
+  run(linear(e->x, e->wqkv, e->bqkv, nullptr, e->qkv, z.T, L, H));
+  Matmul scores = per_head(z, rows_of(e->qkv, L, S * L, d), rows_of(e->qkv + H, L, S * L, d), e->probs, S, z.A * S * S, S * S, S, d);
+  scores.alpha = scale;
+  run(scores);
+  if (run.status == TEMPO_OK)
+    run(tempo_attn_softmax_dropout_fwd(e->probs, e->key_len, 0, e->probs, out, e->keep, e->batch, e->heads, S, S, e->p,
+                                       e->seed, e->offset, TEMPO_F32, hip_stream));
+  run(per_head(z, rows_of(out, S, z.A * S * S, S * S), columns_of(e->qkv + 2 * H, L, S * L, d), e->ctxt, H, S * H, d, d, S));
+  run(linear(e->ctxt, e->wproj, e->bproj, e->x, e->y1, z.T, H, H));
+  if (run.status == TEMPO_OK)
+    run(tempo_layernorm_fwd(e->y1, e->gamma1, e->beta1, e->y1, e->rstd1, nullptr, z.T, H, e->eps1, TEMPO_F32, hip_stream));
+  run(linear(e->y1, e->w1, e->b1, nullptr, e->h, z.T, z.F, H));
+  if (run.status == TEMPO_OK) run(tempo_gelu_fwd(e->h, e->h, e->side, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
+  run(linear(e->h, e->w2, e->b2, e->y1, e->y2, z.T, H, z.F));
+  if (run.status == TEMPO_OK)
+    run(tempo_layernorm_fwd(e->y2, e->gamma2, e->beta2, e->y2, e->rstd2, nullptr, z.T, H, e->eps2, TEMPO_F32, hip_stream));
+  return run.status;
+}
+
+tempo_status tempo_encoder_bwd_ffn(const tempo_encoder* e, const tempo_encoder_grads* g, const float* dy, float* ds2,
+                                   float* dh, float* dy1, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  const Sizes z(*e);
+  Run run{static_cast<hipStream_t>(hip_stream)};
+  run(tempo_layernorm_bwd(dy, e->y2, e->gamma2, e->beta2, e->rstd2, ds2, g->dgamma2, g->dbeta2, workspace, workspace_bytes,
+                          z.T, z.H, TEMPO_F32, hip_stream));
+  if (g->dw2) run(linear_dw(ds2, e->h, g->dw2, g->db2, z.T, z.H, z.F));
+  if (!dy1 && !g->dw1) return run.status;
+  run(linear_dx(ds2, e->w2, nullptr, dh, z.T, z.H, z.F));
+  if (run.status == TEMPO_OK) run(tempo_gelu_bwd(dh, e->h, e->side, dh, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
+  if (g->dw1) run(linear_dw(dh, e->y1, g->dw1, g->db1, z.T, z.F, z.H));
+  if (dy1) run(linear_dx(dh, e->w1, ds2, dy1, z.T, z.F, z.H));
+  return run.status;
+}
+
+tempo_status tempo_encoder_bwd_norm(const tempo_encoder* e, const tempo_encoder_grads* g, const float* dy1, float* ds1,
+                                    void* workspace, size_t workspace_bytes, void* hip_stream) {
+  const Sizes z(*e);
+  return tempo_layernorm_bwd(dy1, e->y1, e->gamma1, e->beta1, e->rstd1, ds1, g->dgamma1, g->dbeta1, workspace,
+                             workspace_bytes, z.T, z.H, TEMPO_F32, hip_stream);
+}
+
+tempo_status tempo_encoder_bwd_attention(const tempo_encoder* e, const tempo_encoder_grads* g, const float* ds1,
+                                         float* dctxt, float* dqkv, float* dout, float* out, void* hip_stream) {
+  const Sizes z(*e);
+  const int64_t H = z.H, S = z.S, d = z.d, L = 3 * H, SS = S * S;
+  const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(d)));
+  Run run{static_cast<hipStream_t>(hip_stream)};
+  if (g->dwproj) run(linear_dw(ds1, e->ctxt, g->dwproj, g->dbproj, z.T, H, H));
+  if (!dctxt) return run.status;
+  run(linear_dx(ds1, e->wproj, nullptr, dctxt, z.T, H, H));
+  run(per_head(z, rows_of(dctxt, H, S * H, d), rows_of(e->qkv + 2 * H, L, S * L, d), dout, S, z.A * SS, SS, S, d));
+  if (run.status == TEMPO_OK) {
+    if (e->keep)
+      run(tempo_attn_softmax_dropout_bwd(dout, e->probs, e->keep, dout, out, e->batch, e->heads, S, S, e->p, TEMPO_F32, hip_stream));
+    else
+      run(tempo_attn_softmax_dropout_bwd_regen(dout, e->probs, dout, out, e->batch, e->heads, S, S, e->p, e->seed,
+                                               e->offset, TEMPO_F32, hip_stream));
+  }
+  run(per_head(z, columns_of(out, S, z.A * SS, SS), columns_of(dctxt, H, S * H, d), dqkv + 2 * H, L, S * L, d, d, S));
+  Matmul dq = per_head(z, rows_of(dout, S, z.A * SS, SS), columns_of(e->qkv + H, L, S * L, d), dqkv, L, S * L, d, d, S);
+  Matmul dk = per_head(z, columns_of(dout, S, z.A * SS, SS), columns_of(e->qkv, L, S * L, d), dqkv + H, L, S * L, d, d, S);
+  dq.alpha = dk.alpha = scale;
+  run(dq);
+  run(dk);
+  if (g->dwqkv) run(linear_dw(dqkv, e->x, g->dwqkv, g->dbqkv, z.T, L, H));
+  if (g->dx) run(linear_dx(dqkv, e->wqkv, ds1, g->dx, z.T, L, H));
+  return run.status;
+}

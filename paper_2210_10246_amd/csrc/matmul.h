@@ -1,0 +1,33 @@
+// Float32 matrix products of the encoder layer (no HIP in here beyond the stream).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "../../include/tempo.h"
+
+namespace tempo {
+
+// One operand of a product: element (row, k) at p[row * ld + k], or at p[k * ld + row] if k_major.  The slice b of a
+// batch starts (b / inner) * outer_stride + (b % inner) * inner_stride elements further on.
+struct MatSide {
+  const float* p;
+  int64_t ld;
+  int64_t outer_stride, inner_stride;
+  bool k_major;
+};
+
+// c[m][n] = alpha * sum_k a(m, k) b(n, k) + bias[n] + add[m][n]
+struct Matmul {
+  MatSide a, b;
+  float* c;
+  int64_t ldc, c_outer, c_inner;
+  const float* bias;   // [N] or null
+  const float* add;    // laid out as c, or null; may be c
+  float* a_sums;       // [M]: sum_k a(m, k), or null (k-major a, a single slice)
+  float alpha;
+  int M, N, K, batch, inner;
+};
+tempo_status launch_matmul(const Matmul& g, hipStream_t st);
+
+}  // namespace tempo

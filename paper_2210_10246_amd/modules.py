@@ -15,7 +15,10 @@ from __future__ import annotations
 import math
 
 import torch
+import torch.nn.functional as F
 from torch import nn
+from torch.autograd import forward_ad
+from torch.nn.modules import module
 
 from . import binding as B
 
@@ -170,6 +173,64 @@ class TempoAttentionCore(nn.Module):
                                       self.store_mask)
 
 
+class _EncoderLayerFn(torch.autograd.Function):
+    """The whole layer, whose forward has been made (_native.tempo_encoder_fwd): keeps what the layers of the general path
+    keep.  The backward is one native call too."""
+
+    @staticmethod
+    def forward(ctx, made, setting, key_len, store_mask, x, *params):
+        qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = made
+        ctx.setting, ctx.key_len = setting, key_len
+        ctx.key_len_version = _version(key_len)
+        ctx.store_mask = store_mask
+        kept = (qkv, probs) + ((keep,) if store_mask else ()) + (ctxt, y1, rstd1, h, side, y2, rstd2)
+        ctx.save_for_backward(x, *params, *kept)
+        return y2
+
+    @staticmethod
+    def backward(ctx, dy):
+        x, *rest = ctx.saved_tensors
+        params, kept = rest[:12], rest[12:]
+        needed = ctx.needs_input_grad[4:]
+        if torch.is_grad_enabled():              # create_graph: the gradients of the general path
+            return (None,) * 4 + _differentiable_grads(ctx, dy, x, params, needed)
+        if not ctx.store_mask:
+            kept.insert(2, None)
+        wanted = sum(1 << i for i, n in enumerate(needed) if n)
+        r = B.encoder_bwd(dy.contiguous(), wanted, x, *ctx.setting, *params, *kept)
+        return (None,) * 4 + r
+
+
+def _version(t):
+    return None if t is None or t.is_inference() else t._version
+
+
+def _differentiable_grads(ctx, dy, x, params, needed):
+    heads, eps1, eps2, p, seed, offset, kind = ctx.setting
+    if _version(ctx.key_len) != ctx.key_len_version:
+        raise RuntimeError("key_len has been modified since the forward")
+    wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = params
+
+    def core(scores, v):
+        return _AttentionCoreFn.apply(scores, v, ctx.key_len, False, p, seed, offset, ctx.store_mask)
+
+    ctxt = _attention(F.linear(x, wqkv, bqkv), heads, core)
+    y1 = _InplaceLayerNormFn.apply(x + F.linear(ctxt, wproj, bproj), g1, be1, eps1)
+    h = _InplaceGELUFn.apply(F.linear(y1, w1, b1), kind)
+    out = _InplaceLayerNormFn.apply(y1 + F.linear(h, w2, b2), g2, be2, eps2)
+    inputs = [t for t, n in zip((x, *params), needed) if n]
+    grads = iter(torch.autograd.grad(out, inputs, dy, create_graph=True))
+    return tuple(next(grads) if n else None for n in needed)
+
+
+def _attention(qkv, heads, core):
+    Bn, S, L = qkv.shape
+    d = L // 3 // heads
+    q, k, v = qkv.view(Bn, S, 3, heads, d).permute(2, 0, 3, 1, 4)
+    scores = torch.matmul(q, k.transpose(-1, -2)) * (1.0 / math.sqrt(d))
+    return core(scores, v.contiguous()).permute(0, 2, 1, 3).reshape(Bn, S, heads * d)
+
+
 class TempoEncoderLayer(nn.Module):
     """A post-LN BERT encoder layer built from the three memory-reduced layers (Fig. 1 of the
     paper); hidden-state dropouts are left out (they are not part of the method)."""
@@ -188,11 +249,43 @@ class TempoEncoderLayer(nn.Module):
         self.core = TempoAttentionCore(p_attn)
 
     def forward(self, x, key_len=None):
-        Bn, S, H = x.shape
-        d = H // self.heads
-        q, k, v = self.qkv(x).view(Bn, S, 3, self.heads, d).permute(2, 0, 3, 1, 4)
-        scores = torch.matmul(q, k.transpose(-1, -2)) * (1.0 / math.sqrt(d))
-        ctxt = self.core(scores, v.contiguous(), key_len)
-        ctxt = ctxt.permute(0, 2, 1, 3).reshape(Bn, S, H)
+        out = self._as_one(x, key_len)
+        if out is not None:
+            return out
+        ctxt = _attention(self.qkv(x), self.heads, lambda scores, v: self.core(scores, v, key_len))
         x = self.ln1(x + self.proj(ctxt))
         return self.ln2(x + self.fc2(self.act(self.fc1(x))))
+
+    def _as_one(self, x, key_len):
+        """The layer as one native call each way, or None where anything could see or change its parts: hooks, other
+        modules in their places, autocast, function transforms, tracing, dispatch and function modes, forward-mode AD,
+        tensor subclasses, other types and layouts."""
+        if type(x) not in _PLAIN or x.dtype != torch.float32 or not x.is_cuda or B.load() is None or B._native is None:
+            return None
+        if (torch.is_autocast_enabled() or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
+                or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
+                or torch.compiler.is_compiling() or torch.jit.is_tracing() or module._has_any_global_hook()):
+            return None
+        parts = self._modules
+        for name, kind in _PARTS:
+            m = parts.get(name)
+            if (type(m) is not kind or m._forward_hooks or m._forward_pre_hooks or m._backward_hooks
+                    or m._backward_pre_hooks or "forward" in m.__dict__):
+                return None
+        qkv, proj, fc1, fc2, ln1, ln2, core = (parts[n] for n in ("qkv", "proj", "fc1", "fc2", "ln1", "ln2", "core"))
+        params = (qkv.weight, qkv.bias, proj.weight, proj.bias, fc1.weight, fc1.bias, fc2.weight, fc2.bias,
+                  ln1.weight, ln1.bias, ln2.weight, ln2.bias)
+        setting = (self.heads, ln1.eps, ln2.eps, core.p if core.training else 0.0, core.seed, core.offset + 1,
+                   parts["act"].kind)
+        made = B.encoder_fwd(x, key_len, *setting, *params)
+        if made is None:
+            return None
+        core.offset += 1
+        if not torch.is_grad_enabled():
+            return made[8]
+        return _EncoderLayerFn.apply(made, setting, key_len, core.store_mask, x, *params)
+
+
+_PLAIN = (torch.Tensor, nn.Parameter)
+_PARTS = (("qkv", nn.Linear), ("proj", nn.Linear), ("fc1", nn.Linear), ("fc2", nn.Linear), ("ln1", InplaceLayerNorm),
+          ("ln2", InplaceLayerNorm), ("act", InplaceGELU), ("core", TempoAttentionCore))

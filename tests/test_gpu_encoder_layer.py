@@ -1,0 +1,187 @@
+"""TempoEncoderLayer as one native call each way against the same layer made of its parts: outputs, gradients, and which of
+the two routes a call takes."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2210_10246_amd import binding, modules
+    binding.load()
+    return modules
+
+
+@pytest.fixture
+def taken(M, monkeypatch):
+    """Whether each call of the layer so far was made as one."""
+    made, fwd = [], M.B.encoder_fwd
+
+    def spy(*args):
+        r = fwd(*args)
+        made.append(r is not None)
+        return r
+    monkeypatch.setattr(M.B, "encoder_fwd", spy)
+    return made
+
+
+def layer_of(M, hidden, heads, ffn, **kw):
+    torch.manual_seed(11)
+    layer = M.TempoEncoderLayer(hidden, heads, ffn, eps=1e-5, **kw).cuda().train()
+    with torch.no_grad():
+        for ln in (layer.ln1, layer.ln2):
+            ln.weight.add_(0.1 * torch.randn_like(ln.weight))
+            ln.bias.add_(0.1 * torch.randn_like(ln.bias))
+    return layer
+
+
+def inputs(batch, seq, hidden):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    x, dy = (torch.randn(batch, seq, hidden, generator=g, device="cuda") for _ in range(2))
+    return x.requires_grad_(), dy
+
+
+def step(layer, x, dy, key_len=None, wanted=None):
+    layer.core.offset = 4
+    out = layer(x, key_len)
+    wanted = [x, *layer.parameters()] if wanted is None else wanted
+    return [out.detach(), *torch.autograd.grad(out, wanted, dy)]
+
+
+def parts(M, monkeypatch, *args):
+    with monkeypatch.context() as m:
+        m.setattr(M.TempoEncoderLayer, "_as_one", lambda *a: None)
+        return step(*args)
+
+
+# Tiles of 32 and 64 rows, columns and steps of k of 16, 32 and 64: one short of them, whole, one more; head sizes and
+# sequences that are no multiple of a piece's 4, and the smallest ones.
+@pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [
+    (1, 1, 32, 2, 64), (2, 31, 64, 4, 100), (3, 33, 96, 3, 36), (1, 65, 128, 2, 512), (2, 130, 40, 5, 44), (5, 7, 192, 12, 768),
+    (1, 64, 64, 1, 4), (3, 63, 12, 3, 260), (2, 256, 256, 4, 1024), (4, 97, 512, 8, 2048), (1, 3, 1024, 16, 4096)])
+@pytest.mark.parametrize("padded", [False, True])
+def test_one_call_matches_the_parts(M, monkeypatch, taken, batch, seq, hidden, heads, ffn, padded):
+    layer = layer_of(M, hidden, heads, ffn, p_attn=0.1)
+    x, dy = inputs(batch, seq, hidden)
+    key_len = torch.arange(seq, seq - batch, -1, device="cuda", dtype=torch.int32).clamp(min=1) if padded else None
+    got = step(layer, x, dy, key_len)
+    assert taken == [True] and layer.core.offset == 5
+    want = parts(M, monkeypatch, layer, x, dy, key_len)
+    # float32 sums of up to 4096 products in another order: about sqrt(4096) 2^-24 = 4e-6 of the result's norm, and what
+    # five products in a row make of it; an absolute 1e-6 for the key bias, whose gradient is 0 but for rounding
+    for i, (a, b) in enumerate(zip(got, want)):
+        assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5, i
+
+
+@pytest.mark.parametrize("kind,store,training", [("tanh", True, True), ("erf", False, True), ("erf", True, False)])
+def test_options_reach_the_kernels(M, monkeypatch, taken, kind, store, training):
+    layer = layer_of(M, 128, 2, 256)
+    layer.act.kind, layer.core.store_mask = kind, store
+    layer.train(training)
+    x, dy = inputs(2, 50, 128)
+    got = step(layer, x, dy)
+    assert taken == [True]
+    for a, b in zip(got, parts(M, monkeypatch, layer, x, dy)):
+        assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5
+
+
+def test_gradients_of_a_part_of_the_inputs(M):
+    """Whatever is asked for has the bits it has when everything is."""
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(3, 20, 64)
+    every = [x, *layer.parameters()]
+    full = step(layer, x, dy)[1:]
+    for names in ([0], [2], [3, 4], [5], [7, 8], [9], [11, 12], [0, 6], [1, 10]):
+        for t in every:
+            t.requires_grad_(any(t is every[i] for i in names))
+        got = step(layer, x, dy, None, [every[i] for i in names])[1:]
+        for i, g in zip(names, got):
+            assert torch.equal(g, full[i]), names
+    for t in every:
+        t.requires_grad_(True)
+
+
+def test_without_gradients(M, taken):
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(2, 9, 64)
+    want = step(layer, x, dy)[0]
+    for mode in (torch.no_grad, torch.inference_mode):
+        with mode():
+            layer.core.offset = 4
+            assert torch.equal(layer(x), want)
+    assert taken == [True] * 3
+
+
+def test_calls_that_are_made_of_the_parts(M, monkeypatch, taken):
+    """Whatever could see or change the layer's parts, or that the kernels do not take."""
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(2, 8, 64)
+    want = step(layer, x, dy)
+    assert taken == [True]
+    taken.clear()
+    seen = []
+    hook = layer.fc1.register_forward_hook(lambda m, i, o: seen.append(o.shape))
+    got = step(layer, x, dy)
+    hook.remove()
+    assert seen == [(2, 8, 128)] and torch.allclose(got[0], want[0], atol=1e-5)
+    with torch.autocast("cuda", dtype=torch.bfloat16):
+        layer(x)
+    proj, layer.proj = layer.proj, torch.nn.Sequential(layer.proj)
+    step(layer, x, dy, None, [x])
+    layer.proj = proj
+    step(layer, x.transpose(0, 1).contiguous().transpose(0, 1).detach().requires_grad_(), dy, None, list(layer.parameters()))
+    with torch.device("cuda"):                   # a function mode
+        step(layer, x, dy)
+    assert not any(taken)
+    # gradients that are differentiated again: the parts' own
+    out = layer(x)
+    (g,) = torch.autograd.grad(out, [layer.fc2.weight], dy, create_graph=True)
+    with monkeypatch.context() as m:
+        m.setattr(M.TempoEncoderLayer, "_as_one", lambda *a: None)
+        layer.core.offset -= 1
+        (h,) = torch.autograd.grad(layer(x), [layer.fc2.weight], dy, create_graph=True)
+    assert g.requires_grad == h.requires_grad and torch.equal(g, h)
+
+
+def test_odd_heads_are_made_of_the_parts(M, taken):
+    layer = layer_of(M, 66, 3, 128)              # 22 columns a head
+    x, dy = inputs(2, 8, 66)
+    step(layer, x, dy)
+    assert taken == [False]
+
+
+def test_hooks_on_what_is_kept(M, taken):
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(2, 40, 64)
+    want = step(layer, x, dy)
+    with torch.autograd.graph.save_on_cpu():
+        got = step(layer, x, dy)
+    assert taken == [True, True]
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+def test_replays_of_a_captured_step(M, taken):
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(2, 40, 64)
+    want = step(layer, x, dy)
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(st):
+        step(layer, x, dy)
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            got = step(layer, x, dy)
+        for _ in range(3):
+            for t in got:
+                t.zero_()
+            graph.replay()
+            st.synchronize()
+            for a, b in zip(got, want):
+                assert torch.equal(a, b)
+            step(layer, x, dy)
+    assert all(taken)
