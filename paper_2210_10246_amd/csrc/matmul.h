@@ -29,5 +29,7 @@ struct Matmul {
   int M, N, K, batch, inner;
 };
 tempo_status launch_matmul(const Matmul& g, hipStream_t st);
+// g (k-major b only) and one or two products of one size with two k-major operands, none of which needs another.
+tempo_status launch_matmul_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st);
 
 }  // namespace tempo

@@ -92,25 +92,40 @@ __device__ __forceinline__ int full_steps(const Matmul& g, bool akm, bool bkm, i
 }
 
 // A workgroup owns BM x BN elements of c.  Each of its waves owns 32 x 32 of them for a KS-th of every KT values of k.
-constexpr int matmul_threads(int BM, int BN, int KS) { return kWave * (BM / kTile) * (BN / kTile) * KS; }
-template <bool AKM, bool BKM, int BM, int BN, int KS, int KT, int DEPTH>
-__global__ __launch_bounds__(matmul_threads(BM, BN, KS)) void matmul_kernel(Matmul g, int tiles_m, int tiles_n) {
-  constexpr int kWavesM = BM / kTile, kWavesN = BN / kTile;
-  constexpr int kThreads = matmul_threads(BM, BN, KS);
-  constexpr int KW = KT / KS;
-  static_assert(KW % 8 == 0, "whole steps of 8");
+template <bool AKM_, bool BKM_, int BM_, int BN_, int KS_, int KT_, int DEPTH_>
+struct Config {
+  static constexpr bool AKM = AKM_, BKM = BKM_;
+  static constexpr int BM = BM_, BN = BN_, KS = KS_, KT = KT_, DEPTH = DEPTH_;
+  static constexpr int kWavesM = BM / kTile, kWavesN = BN / kTile;
+  static constexpr int kThreads = kWave * kWavesM * kWavesN * KS;
   using A = Stage<AKM, BM, KT, kThreads, DEPTH>;
   using B = Stage<BKM, BN, KT, kThreads, DEPTH>;
-  constexpr int kBuffer = A::kFloats + B::kFloats;
-  constexpr int kExchange = KS > 1 ? KS * kWavesM * kWavesN * 16 * kWave : 0;
-  __shared__ __attribute__((aligned(16))) float lds[2 * kBuffer > kExchange ? 2 * kBuffer : kExchange];
-  __shared__ float sums[KS][BM];
+  static constexpr int kBuffer = A::kFloats + B::kFloats;
+  static constexpr int kExchange = KS > 1 ? KS * kWavesM * kWavesN * 16 * kWave : 0;
+  static constexpr int kStaged = 2 * kBuffer > kExchange ? 2 * kBuffer : kExchange;
+  static constexpr int kLds = kStaged + (AKM ? KS * BM : 0);  // floats
+  static int64_t tiles(const Matmul& g) { return int64_t{(g.M + BM - 1) / BM} * ((g.N + BN - 1) / BN) * g.batch; }
+};
+
+// Tile `block` of `total`, in the order of the launch.
+template <typename C>
+__device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int total, float* lds) {
+  constexpr bool AKM = C::AKM, BKM = C::BKM;
+  constexpr int BM = C::BM, BN = C::BN, KS = C::KS, KT = C::KT, DEPTH = C::DEPTH;
+  constexpr int kWavesM = C::kWavesM, kThreads = C::kThreads;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  constexpr int KW = KT / KS;
+  static_assert(KW % 8 == 0, "whole steps of 8");
+  using A = typename C::A;
+  using B = typename C::B;
+  constexpr int kBuffer = C::kBuffer;
+  float* const sums = lds + C::kStaged;  // AKM: [KS][BM]
 
   // Neighbouring workgroups go to different XCDs, each of which has its own L2: every XCD takes a run of tiles, which
   // share columns of c.
   constexpr int kXcds = 8;
-  const int total = gridDim.x, xcd = blockIdx.x % kXcds, each = total / kXcds, more = total % kXcds;
-  const int tile = xcd * each + min(xcd, more) + static_cast<int>(blockIdx.x) / kXcds;
+  const int xcd = block % kXcds, each = total / kXcds, more = total % kXcds;
+  const int tile = xcd * each + min(xcd, more) + block / kXcds;
   const int slice = tile / (tiles_m * tiles_n), in_slice = tile % (tiles_m * tiles_n);
   const int n0 = in_slice / tiles_m * BN, m0 = in_slice % tiles_m * BM;
   const int outer = slice / g.inner, inner = slice % g.inner;
@@ -209,7 +224,7 @@ __global__ __launch_bounds__(matmul_threads(BM, BN, KS)) void matmul_kernel(Matm
     if (g.a_sums && n0 == 0) {  // uniform over the workgroup
       float v = (asum[0] + asum[1]) + (asum[2] + asum[3]);
       v = across_rows<32>(v, [](float x, float y) { return x + y; });
-      if (wn == 0 && half == 0) sums[ks][wm * kTile + l32] = v;
+      if (wn == 0 && half == 0) sums[ks * BM + wm * kTile + l32] = v;
     }
   }
   // Register r of a lane is element (m = lane % 32, n = 8 (r / 4) + 4 (lane / 32) + r % 4) of the wave's 32 x 32: four
@@ -260,22 +275,53 @@ __global__ __launch_bounds__(matmul_threads(BM, BN, KS)) void matmul_kernel(Matm
   if constexpr (AKM) {
     if (g.a_sums && n0 == 0) {
       for (int i = threadIdx.x; i < BM && m0 + i < g.M; i += kThreads) {
-        float v = sums[0][i];
+        float v = sums[i];
 #pragma unroll
-        for (int s = 1; s < KS; ++s) v += sums[s][i];
+        for (int s = 1; s < KS; ++s) v += sums[s * BM + i];
         g.a_sums[m0 + i] = v;
       }
     }
   }
 }
 
-template <bool AKM, bool BKM, int BM, int BN, int KS, int KT, int DEPTH>
+template <typename C>
+__global__ __launch_bounds__(C::kThreads) void matmul_kernel(Matmul g) {
+  __shared__ __attribute__((aligned(16))) float lds[C::kLds];
+  matmul_tile<C>(g, blockIdx.x, gridDim.x, lds);
+}
+template <typename C>
 tempo_status go(const Matmul& g, hipStream_t st) {
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  hipLaunchKernelGGL((matmul_kernel<AKM, BKM, BM, BN, KS, KT, DEPTH>), dim3(tiles_m * tiles_n * g.batch),
-                     dim3(matmul_threads(BM, BN, KS)), 0, st, g, tiles_m, tiles_n);
+  hipLaunchKernelGGL((matmul_kernel<C>), dim3(C::tiles(g)), dim3(C::kThreads), 0, st, g);
   return launch_status();
 }
+
+// Products that need nothing of each other in one launch: g, and one or two of the same size.
+template <typename C, typename D>
+__global__ __launch_bounds__(C::kThreads) void matmul_group_kernel(Matmul g, Matmul h0, Matmul h1, int g_tiles, int h_tiles) {
+  static_assert(C::kThreads == D::kThreads, "one workgroup size");
+  __shared__ __attribute__((aligned(16))) float lds[C::kLds > D::kLds ? C::kLds : D::kLds];
+  const int block = blockIdx.x;
+  if (block < g_tiles) return matmul_tile<C>(g, block, g_tiles, lds);
+  const int rest = block - g_tiles;
+  if (rest < h_tiles) matmul_tile<D>(h0, rest, h_tiles, lds);
+  else matmul_tile<D>(h1, rest - h_tiles, h_tiles, lds);
+}
+template <typename C, typename D>
+tempo_status go_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st) {
+  const int64_t g_tiles = C::tiles(g), h_tiles = D::tiles(h0);
+  hipLaunchKernelGGL((matmul_group_kernel<C, D>), dim3(g_tiles + (h1 ? 2 : 1) * h_tiles), dim3(C::kThreads), 0, st, g, h0,
+                     h1 ? *h1 : h0, static_cast<int>(g_tiles), static_cast<int>(h_tiles));
+  return launch_status();
+}
+
+template <bool AKM, bool BKM>
+using Large = Config<AKM, BKM, 64, 64, 1, 16, 4>;
+template <bool AKM, bool BKM>
+using Middle = Config<AKM, BKM, 64, 32, 2, 32, 4>;
+template <bool AKM, bool BKM>
+using Small = Config<AKM, BKM, 32, 32, 4, 32, 4>;
+template <bool AKM, bool BKM>
+using SmallLong = Config<AKM, BKM, 32, 32, 8, 64, 4>;
 
 // Tiles of 64 x 64, 64 x 32 or 32 x 32 elements: whichever gives the compute unit with the most of them the least to do,
 // where a smaller tile takes 8 % (12 % with two k-major operands) more time for its elements, and a workgroup alone on its
@@ -297,12 +343,12 @@ tempo_status by_shape(const Matmul& g, hipStream_t st) {
     return r * (bm * bn / 1024) * (100 + percent) + (bm * bn / 1024) * 15;
   };
   const int64_t large = cost(64, 64, 0), middle = cost(64, 32, small), least = cost(32, 32, 2 * small);
-  if (large <= middle && large <= least) return go<AKM, BKM, 64, 64, 1, 16, 4>(g, st);
-  if (middle <= least) return go<AKM, BKM, 64, 32, 2, 32, 4>(g, st);
+  if (large <= middle && large <= least) return go<Large<AKM, BKM>>(g, st);
+  if (middle <= least) return go<Middle<AKM, BKM>>(g, st);
   if constexpr (!AKM) {
-    if (rounds(32, 32) == 1 && g.K >= (BKM ? 512 : 2560)) return go<AKM, BKM, 32, 32, 8, 64, 4>(g, st);
+    if (rounds(32, 32) == 1 && g.K >= (BKM ? 512 : 2560)) return go<SmallLong<AKM, BKM>>(g, st);
   }
-  return go<AKM, BKM, 32, 32, 4, 32, 4>(g, st);
+  return go<Small<AKM, BKM>>(g, st);
 }
 
 }  // namespace
@@ -312,15 +358,28 @@ tempo_status launch_matmul(const Matmul& g, hipStream_t st) {
   if (g.a.k_major) return g.b.k_major ? by_shape<true, true>(g, st) : TEMPO_ERR_UNSUPPORTED;
   return g.b.k_major ? by_shape<false, true>(g, st) : by_shape<false, false>(g, st);
 }
-#ifdef PROBE
-int compute_units() { return 256; }
-extern "C" __attribute__((visibility("default"))) int tempo_probe_matmul(
-    const float* a, int64_t lda, int akm, const float* b, int64_t ldb, int bkm, float* c, int64_t ldc, const float* bias,
-    const float* add, float* a_sums, float alpha, int M, int N, int K, int batch, int64_t as, int64_t bs, int64_t cs,
-    void* st) {
-  Matmul g{{a, lda, as, 0, akm != 0}, {b, ldb, bs, 0, bkm != 0}, c, ldc, cs, 0, bias, add, a_sums, alpha, M, N, K, batch, 1};
-  return launch_matmul(g, static_cast<hipStream_t>(st));
+// The tile of each by how many of 64 x 64 it has per compute unit: together they are some per compute unit, and the sizes
+// that suit a product by itself (by_shape()) are too small or too large.  us apart / with the product of the rows in large,
+// middle, small tiles and the others' tile this gives: dx and dw of a [256, 768] x [768, 3072] layer (192 and 576 tiles) 37.0 /
+// 28.7, 30.3, 32.3; [256, 768] x [768, 768] (48, 144) 16.7 / 20.7, 13.9, 10.9; [128, 768] x [768, 3072] (96, 576) 26.1 / 24.3, 18.0,
+// 21.3; [512, 1024] x [1024, 3072] (128, 768) 69.5 / 77.1, 63.6, 66.4; [2048, 1024] x [1024, 4096] (512, 1024) 305 / 301, 327,
+// 341.  The others' tile, large / middle / small: (48, 576) 31.3 / 32.4 / 33.9; (48, 144) 13.4 / 10.9 / 11.3; (64, 64) 17.5 / 12.7 /
+// 10.0.  Three products of 24 heads of 128 x 128 x 64 11.1 / 6.3.
+tempo_status launch_matmul_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st) {
+  if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || h0.M <= 0 || h0.N <= 0 || h0.batch <= 0) return TEMPO_ERR_UNSUPPORTED;
+  using GL = Large<false, true>;
+  using GM = Middle<false, true>;
+  using GS = Small<false, true>;
+  using HL = Large<true, true>;
+  using HM = Middle<true, true>;
+  using HS = Small<true, true>;
+  const int64_t cus = compute_units(), g_tiles = GL::tiles(g), h_tiles = HL::tiles(h0);
+  if (g_tiles * 8 >= cus * 5)
+    return h_tiles >= cus ? go_group<GL, HL>(g, h0, h1, st) : go_group<GL, HM>(g, h0, h1, st);
+  if (g_tiles * 16 >= cus * 5)
+    return h_tiles >= cus ? go_group<GM, HL>(g, h0, h1, st) : go_group<GM, HM>(g, h0, h1, st);
+  if (h_tiles >= cus) return go_group<GS, HL>(g, h0, h1, st);
+  return h_tiles * 8 >= cus * 3 ? go_group<GS, HM>(g, h0, h1, st) : go_group<GS, HS>(g, h0, h1, st);
 }
-#endif
 
 }  // namespace tempo
