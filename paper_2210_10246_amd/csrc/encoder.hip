@@ -1,6 +1,6 @@
 // The launches of encoder.h.  Heads are taken from and put into the [T, 3 hidden] and [T, hidden] layouts by the
 // strides of the products, and residuals, biases, 1 / sqrt(d) and the sums for the bias gradients are part of them: no
-// copies, no elementwise passes beside the three layers.
+// copies, no elementwise passes beside the three layers; GELU is part of the products around it.
 #include <cmath>
 
 #include "encoder.h"
@@ -51,6 +51,14 @@ Matmul linear_dw(const float* dy, const float* x, float* dw, float* db, int64_t 
   Matmul g = product(columns_of(dy, out), columns_of(x, in), dw, in, out, in, T);
   g.a_sums = db;
   return g;
+}
+
+// The layer's GELU behind (before, in the backward) a product.
+void with_gelu(Matmul& g, const tempo_encoder& e, Matmul::Act act) {
+  g.act = act;
+  g.kind = e.kind;
+  g.act_y = e.h;
+  g.side = reinterpret_cast<uint8_t*>(e.side);
 }
 
 struct Run {
@@ -106,8 +114,11 @@ tempo_status tempo_encoder_fwd(const tempo_encoder* e, float* out, void* hip_str
   run(linear(e->ctxt, e->wproj, e->bproj, e->x, e->y1, z.T, H, H));
   if (run.status == TEMPO_OK)
     run(tempo_layernorm_fwd(e->y1, e->gamma1, e->beta1, e->y1, e->rstd1, nullptr, z.T, H, e->eps1, TEMPO_F32, hip_stream));
-  run(linear(e->y1, e->w1, e->b1, nullptr, e->h, z.T, z.F, H));
-  if (run.status == TEMPO_OK) run(tempo_gelu_fwd(e->h, e->h, e->side, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
+  Matmul h = linear(e->y1, e->w1, e->b1, nullptr, e->h, z.T, z.F, H);
+  if (z.F % 8 == 0) with_gelu(h, *e, Matmul::kForward);
+  run(h);
+  if (z.F % 8 != 0 && run.status == TEMPO_OK)
+    run(tempo_gelu_fwd(e->h, e->h, e->side, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
   run(linear(e->h, e->w2, e->b2, e->y1, e->y2, z.T, H, z.F));
   if (run.status == TEMPO_OK)
     run(tempo_layernorm_fwd(e->y2, e->gamma2, e->beta2, e->y2, e->rstd2, nullptr, z.T, H, e->eps2, TEMPO_F32, hip_stream));
@@ -121,10 +132,12 @@ tempo_status tempo_encoder_bwd_ffn(const tempo_encoder* e, const tempo_encoder_g
   run(tempo_layernorm_bwd(dy, e->y2, e->gamma2, e->beta2, e->rstd2, ds2, g->dgamma2, g->dbeta2, workspace, workspace_bytes,
                           z.T, z.H, TEMPO_F32, hip_stream));
   const bool more = dy1 || g->dw1;
-  const Matmul dh2 = linear_dx(ds2, e->w2, nullptr, dh, z.T, z.H, z.F);
+  Matmul dh2 = linear_dx(ds2, e->w2, nullptr, dh, z.T, z.H, z.F);
+  const bool fused = g->dw2 && z.F % 8 == 0;  // grouped products only
+  if (fused) with_gelu(dh2, *e, Matmul::kBackward);
   run.backward(more ? &dh2 : nullptr, linear_dw(ds2, e->h, g->dw2, g->db2, z.T, z.H, z.F));
   if (!more) return run.status;
-  if (run.status == TEMPO_OK) run(tempo_gelu_bwd(dh, e->h, e->side, dh, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
+  if (!fused && run.status == TEMPO_OK) run(tempo_gelu_bwd(dh, e->h, e->side, dh, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
   const Matmul dx1 = linear_dx(dh, e->w1, ds2, dy1, z.T, z.F, z.H);
   run.backward(dy1 ? &dx1 : nullptr, linear_dw(dh, e->y1, g->dw1, g->db1, z.T, z.F, z.H));
   return run.status;

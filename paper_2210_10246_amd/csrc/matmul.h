@@ -27,6 +27,12 @@ struct Matmul {
   float* a_sums;       // [M]: sum_k a(m, k), or null (k-major a, a single slice)
   float alpha;
   int M, N, K, batch, inner;
+  // Float32 GELU of c, or its backward from the outputs act_y, laid out as c; side: the bits at or right of the minimum,
+  // written or read (N a multiple of 8, a single slice, no addend).
+  enum Act { kNone, kForward, kBackward } act = kNone;
+  tempo_gelu_kind kind = TEMPO_GELU_ERF;
+  const float* act_y = nullptr;
+  uint8_t* side = nullptr;
 };
 tempo_status launch_matmul(const Matmul& g, hipStream_t st);
 // g (k-major b only) and one or two products of one size with two k-major operands, none of which needs another.

@@ -7,9 +7,8 @@
 // heads of [128, 64] x [64, 128] 4.1 (8.0 and two copies).  At [2048, 1024] x [1024, 4096] 152 (112; 125).
 // Steps of k are fetched DEPTH + 2 ahead, written to LDS two ahead and read from there one ahead of the matrix instructions.
 // With one step fetched ahead and everything else in sequence [256, 768] x [768, 2304] takes 17.5, [256, 3072] x [3072, 768] 28.
+#include "gelu_f32.h"
 #include "matmul.h"
-#include "tempo_device.h"
-#include "tempo_host.h"
 
 namespace tempo {
 namespace {
@@ -108,8 +107,9 @@ struct Config {
 };
 
 // Tile `block` of `total`, in the order of the launch.
-template <typename C>
-__device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int total, float* lds) {
+// ACT, KIND: g.act and g.kind.  table: rows of the backward's cubics in LDS.
+template <typename C, int ACT, int KIND>
+__device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int total, float* lds, const f32x4* table) {
   constexpr bool AKM = C::AKM, BKM = C::BKM;
   constexpr int BM = C::BM, BN = C::BN, KS = C::KS, KT = C::KT, DEPTH = C::DEPTH;
   constexpr int kWavesM = C::kWavesM, kThreads = C::kThreads;
@@ -234,9 +234,30 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
   auto finish = [&](int q, f32x4 v) {
     const int n = n0 + wn * kTile + 8 * q + 4 * half;
     const int left = m < g.M ? g.N - n : 0;
-    if (left <= 0) return;
     const int64_t e = outer * g.c_outer + inner * g.c_inner + m * g.ldc + n;
     v *= g.alpha;
+    if constexpr (ACT == Matmul::kForward) {
+      // a group of both halves of the wave is 8 adjacent elements: a byte of the mask
+      if (g.bias && left > 0) v += *reinterpret_cast<const f32x4_word*>(g.bias + n);
+      uint32_t bits = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bits |= (v[i] >= as_f32(GeluConst<KIND>::xstar) ? 1u : 0u) << (4 * half + i);
+        v[i] = act_value<KIND>(v[i]);
+      }
+      const auto both = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+      if (left <= 0) return;
+      *reinterpret_cast<f32x4_word*>(g.c + e) = v;
+      if (half == 0) g.side[e >> 3] = static_cast<uint8_t>(both[0] | both[1]);
+      return;
+    }
+    if (left <= 0) return;
+    if constexpr (ACT == Matmul::kBackward) {
+      const f32x4 y = *reinterpret_cast<const f32x4_word*>(g.act_y + e);
+      const uint32_t bits = g.side[e >> 3] >> (4 * half);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] *= gelu_composite<KIND>(y[i], (bits >> i) & 1u, table);
+    }
     if (left >= 4) {
       if (g.bias) v += *reinterpret_cast<const f32x4_word*>(g.bias + n);
       if (g.add) v += *reinterpret_cast<const f32x4_word*>(g.add + e);
@@ -284,34 +305,59 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
   }
 }
 
-template <typename C>
+template <typename C, int ACT, int KIND>
 __global__ __launch_bounds__(C::kThreads) void matmul_kernel(Matmul g) {
   __shared__ __attribute__((aligned(16))) float lds[C::kLds];
-  matmul_tile<C>(g, blockIdx.x, gridDim.x, lds);
+  matmul_tile<C, ACT, KIND>(g, blockIdx.x, gridDim.x, lds, nullptr);
 }
 template <typename C>
 tempo_status go(const Matmul& g, hipStream_t st) {
-  hipLaunchKernelGGL((matmul_kernel<C>), dim3(C::tiles(g)), dim3(C::kThreads), 0, st, g);
-  return launch_status();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(C::tiles(g)), dim3(C::kThreads), 0, st, g);
+    return launch_status();
+  };
+  if (g.act == Matmul::kNone) return launch(matmul_kernel<C, Matmul::kNone, 0>);
+  if constexpr (!C::AKM && !C::BKM) {
+    if (g.act == Matmul::kForward)
+      return launch(g.kind == TEMPO_GELU_TANH ? matmul_kernel<C, Matmul::kForward, TEMPO_GELU_TANH>
+                                              : matmul_kernel<C, Matmul::kForward, TEMPO_GELU_ERF>);
+  }
+  return TEMPO_ERR_UNSUPPORTED;
 }
 
 // Products that need nothing of each other in one launch: g, and one or two of the same size.
-template <typename C, typename D>
+template <typename C, typename D, int ACT, int KIND>
 __global__ __launch_bounds__(C::kThreads) void matmul_group_kernel(Matmul g, Matmul h0, Matmul h1, int g_tiles, int h_tiles) {
   static_assert(C::kThreads == D::kThreads, "one workgroup size");
-  __shared__ __attribute__((aligned(16))) float lds[C::kLds > D::kLds ? C::kLds : D::kLds];
+  constexpr int kRows = ACT == Matmul::kBackward ? GeluConst<KIND>::kBwdRows : 0;
+  constexpr int kStaged = C::kLds > D::kLds ? C::kLds : D::kLds;
+  static_assert(kStaged % 4 == 0, "table rows of 16 bytes behind it");
+  __shared__ __attribute__((aligned(16))) float lds[kStaged + 4 * kRows];
   const int block = blockIdx.x;
-  if (block < g_tiles) return matmul_tile<C>(g, block, g_tiles, lds);
+  if (block < g_tiles) {
+    f32x4* const table = reinterpret_cast<f32x4*>(lds + kStaged);
+    if constexpr (ACT == Matmul::kBackward) {  // ordered by the barriers of the loop
+      for (int i = threadIdx.x; i < kRows; i += C::kThreads)
+        table[i] = *reinterpret_cast<const f32x4*>(GeluConst<KIND>::bwd_table()[i]);
+    }
+    return matmul_tile<C, ACT, KIND>(g, block, g_tiles, lds, table);
+  }
   const int rest = block - g_tiles;
-  if (rest < h_tiles) matmul_tile<D>(h0, rest, h_tiles, lds);
-  else matmul_tile<D>(h1, rest - h_tiles, h_tiles, lds);
+  if (rest < h_tiles) matmul_tile<D, Matmul::kNone, 0>(h0, rest, h_tiles, lds, nullptr);
+  else matmul_tile<D, Matmul::kNone, 0>(h1, rest - h_tiles, h_tiles, lds, nullptr);
 }
 template <typename C, typename D>
 tempo_status go_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st) {
   const int64_t g_tiles = C::tiles(g), h_tiles = D::tiles(h0);
-  hipLaunchKernelGGL((matmul_group_kernel<C, D>), dim3(g_tiles + (h1 ? 2 : 1) * h_tiles), dim3(C::kThreads), 0, st, g, h0,
-                     h1 ? *h1 : h0, static_cast<int>(g_tiles), static_cast<int>(h_tiles));
-  return launch_status();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g_tiles + (h1 ? 2 : 1) * h_tiles), dim3(C::kThreads), 0, st, g, h0, h1 ? *h1 : h0,
+                       static_cast<int>(g_tiles), static_cast<int>(h_tiles));
+    return launch_status();
+  };
+  if (g.act == Matmul::kNone) return launch(matmul_group_kernel<C, D, Matmul::kNone, 0>);
+  if (g.act != Matmul::kBackward) return TEMPO_ERR_UNSUPPORTED;
+  return launch(g.kind == TEMPO_GELU_TANH ? matmul_group_kernel<C, D, Matmul::kBackward, TEMPO_GELU_TANH>
+                                          : matmul_group_kernel<C, D, Matmul::kBackward, TEMPO_GELU_ERF>);
 }
 
 template <bool AKM, bool BKM>
