@@ -11,6 +11,7 @@
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/tempo.h"
@@ -336,6 +337,7 @@ TEMPO_METHOD(encoder_bwd) {
   if (nargs != 10 + kEncoderParams + 10) Py_RETURN_NONE;
   at::Tensor dx, dw[kEncoderParams];
   tempo_status status = TEMPO_OK;
+  HANDLE_TH_ERRORS  // out of memory, as torch raises it
   try {
     const at::Tensor& x = tensor(a[2]);
     tempo_encoder e = encoder(x, a + 3, a + 10);
@@ -416,12 +418,13 @@ TEMPO_METHOD(encoder_bwd) {
     }
     for (int i = 0; i < kEncoderParams; ++i)
       if (!want(i + 1, i + 1)) dw[i].reset();
-  } catch (...) {
+  } catch (const NotPlain&) {
     PyErr_Clear();
     Py_RETURN_NONE;
   }
   const at::Tensor* all[] = {&dx, dw, dw + 1, dw + 2, dw + 3, dw + 4, dw + 5, dw + 6, dw + 7, dw + 8, dw + 9, dw + 10, dw + 11};
   return result(status, all);
+  END_HANDLE_TH_ERRORS
 }
 
 #define TEMPO_ENTRY(name) {"tempo_" #name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(name)), METH_FASTCALL, nullptr}

@@ -88,9 +88,10 @@ int tempo_encoder_takes(const tempo_encoder* e) {
   const Sizes z(*e);
   if (z.T < 1 || z.H < 1 || z.F < 1 || z.A < 1 || z.H % z.A != 0) return 0;
   if (z.H % 4 != 0 || z.F % 4 != 0 || z.d % 4 != 0) return 0;
-  const int64_t most = int64_t{1} << 30;  // sizes and tiles are counted in 32 bits
+  // Sizes, tiles and lanes are counted in 32 bits: at most 2^20 + T A / 16 + B A tiles of 256 lanes in each of three products.
+  const int64_t most = int64_t{1} << 30;
   if (z.T > most / (3 * z.H) || z.T > most / z.F || z.F > most / z.H || z.S > 32768 ||
-      e->batch * e->heads > most / (z.S * z.S))
+      e->batch * e->heads > most / (z.S * z.S) || e->batch * e->heads > most >> 10 || z.T * z.A > most >> 6)
     return 0;
   // Multiplications of the four layers' weights, forward.  Below, the launches, copies and host time that go count for more than
   // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 911 / 233, 8 x 128 x 1024 953 / 810,

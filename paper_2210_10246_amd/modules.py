@@ -260,11 +260,13 @@ class TempoEncoderLayer(nn.Module):
         """The layer as one native call each way, or None where anything could see or change its parts: hooks, other
         modules in their places, autocast, function transforms, tracing, dispatch and function modes, forward-mode AD,
         tensor subclasses, other types and layouts."""
+        if torch.compiler.is_compiling():
+            return None
         if type(x) not in _PLAIN or x.dtype != torch.float32 or not x.is_cuda or B.load() is None or B._native is None:
             return None
         if (torch.is_autocast_enabled() or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
                 or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
-                or torch.compiler.is_compiling() or torch.jit.is_tracing() or module._has_any_global_hook()):
+                or torch.jit.is_tracing() or module._has_any_global_hook()):
             return None
         parts = self._modules
         for name, kind in _PARTS:
