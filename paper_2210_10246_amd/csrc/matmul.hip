@@ -147,7 +147,8 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  f32x4 asum = {0.0f, 0.0f, 0.0f, 0.0f};
+  // AKM: the sums of a, of a few steps and of all before, so that long columns do not add up in one chain
+  f32x4 asum = {0.0f, 0.0f, 0.0f, 0.0f}, asum_before = asum;
   constexpr int kFrags = KW / 8;
   f32x4 fa[2][kFrags], fb[2][kFrags];
   // No branch around the loads: behind one, the compiler waits for all that are under way.  Beyond the last step they
@@ -205,6 +206,10 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
     for (int s = 0; s < whole; s += DEPTH) {
 #pragma unroll
       for (int j = 0; j < DEPTH; ++j) one(j, s + j);
+      if constexpr (AKM) {
+        asum_before += asum;
+        asum = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
     }
 #pragma unroll
     for (int j = 0; j < DEPTH - 1; ++j) {
@@ -222,6 +227,7 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
 
   if constexpr (AKM) {
     if (g.a_sums && n0 == 0) {  // uniform over the workgroup
+      asum += asum_before;
       float v = (asum[0] + asum[1]) + (asum[2] + asum[3]);
       v = across_rows<32>(v, [](float x, float y) { return x + y; });
       if (wn == 0 && half == 0) sums[ks * BM + wm * kTile + l32] = v;

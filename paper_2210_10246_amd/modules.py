@@ -7,8 +7,10 @@ Only what is stashed for backward differs from the stock layers:
   TempoAttentionCore softmax -> dropout -> (. @ V) keeping the softmax output P and a 1-bit
                      mask; the dropout output is a transient in forward and is recomputed by
                      the backward kernel for the gradient of V (Sec. 3.3).
-Every arithmetic step of the three layers runs in the HIP kernels; the two matrix products
-around the attention sublayer are ordinary library GEMMs (torch.matmul).
+  TempoEncoderLayer  an encoder layer of the three: in float32 one native call each way on HIP
+                     kernels alone where nothing else can see its parts, else those parts
+Every arithmetic step of the three layers runs in the HIP kernels; the matrix products around
+them, where the layer is made of its parts, are ordinary library GEMMs (torch.matmul, nn.Linear).
 """
 from __future__ import annotations
 

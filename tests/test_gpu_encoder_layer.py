@@ -58,10 +58,12 @@ def parts(M, monkeypatch, *args):
 
 
 # Tiles of 32 and 64 rows, columns and steps of k of 16, 32 and 64: one short of them, whole, one more; head sizes and
-# sequences that are no multiple of a piece's 4, and the smallest ones.
+# sequences that are no multiple of a piece's 4, and the smallest ones.  The last four come to every tile size, alone and
+# in one launch with another.
 @pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [
     (1, 1, 32, 2, 64), (2, 31, 64, 4, 100), (3, 33, 96, 3, 36), (2, 33, 64, 2, 72), (1, 65, 128, 2, 512), (2, 130, 40, 5, 44), (5, 7, 192, 12, 768),
-    (1, 64, 64, 1, 4), (3, 63, 12, 3, 260), (2, 256, 256, 4, 1024), (4, 97, 512, 8, 2048), (1, 3, 1024, 16, 4096)])
+    (1, 64, 64, 1, 4), (3, 63, 12, 3, 260), (2, 256, 256, 4, 1024), (4, 97, 512, 8, 2048), (1, 3, 1024, 16, 4096),
+    (1, 128, 512, 8, 3072), (4, 256, 256, 4, 1024)])
 @pytest.mark.parametrize("padded", [False, True])
 def test_one_call_matches_the_parts(M, monkeypatch, taken, batch, seq, hidden, heads, ffn, padded):
     layer = layer_of(M, hidden, heads, ffn, p_attn=0.1)
