@@ -53,7 +53,9 @@ Matmul linear_dw(const float* dy, const float* x, float* dw, float* db, int64_t 
   return g;
 }
 
-// The layer's GELU behind (before, in the backward) a product.
+// The layer's GELU at the end of a product: the forward's of the first feed-forward layer, the backward's of the second one's
+// dx.  As launches of their own they took 4.5 us each at 2 x 128 x 768 and read and wrote [T, ffn] once more: a step 203.5 / 197.8
+// us, 8 x 256 x 768 1019 / 998.  The mask is bytes to the product: rows of a multiple of 8 columns.
 void with_gelu(Matmul& g, const tempo_encoder& e, Matmul::Act act) {
   g.act = act;
   g.kind = e.kind;
@@ -94,8 +96,9 @@ int tempo_encoder_takes(const tempo_encoder* e) {
       e->batch * e->heads > most / (z.S * z.S) || e->batch * e->heads > most >> 10 || z.T * z.A > most >> 6)
     return 0;
   // Multiplications of the four layers' weights, forward.  Below, the launches, copies and host time that go count for more than
-  // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 911 / 233, 8 x 128 x 1024 953 / 810,
-  // 8 x 256 x 1024 (26e9) 1575 / 1538, 32 x 256 x 512 (26e9) 1834 / 1789, but 16 x 256 x 1024 (52e9) 2938 / 3132.
+  // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 (2e9) 1094 / 278 (host time), 8 x 128 x 1024
+  // (13e9) 1106 / 775, 8 x 256 x 1024 (26e9) 1589 / 1553, 32 x 256 x 512 (26e9) 1896 / 1860; beyond, 16 x 256 x 768 (29e9)
+  // 1953 / 1924, 12 x 256 x 1024 (39e9) 2269 / 2326, 48 x 256 x 512 (39e9) 2742 / 2776, 16 x 256 x 1024 (52e9) 2890 / 3095.
   return z.T * (4 * z.H * z.H + 2 * z.H * z.F) <= int64_t{26} * 1000 * 1000 * 1000;
 }
 
