@@ -268,7 +268,7 @@ class TempoEncoderLayer(nn.Module):
             return None
         if (torch.is_autocast_enabled() or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
                 or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
-                or torch.jit.is_tracing() or module._has_any_global_hook()):
+                or torch.jit.is_tracing() or module._has_any_global_hook() or nn.Linear.forward is not _LINEAR):
             return None
         parts = self._modules
         for name, kind in _PARTS:
@@ -291,5 +291,6 @@ class TempoEncoderLayer(nn.Module):
 
 
 _PLAIN = (torch.Tensor, nn.Parameter)
+_LINEAR = nn.Linear.forward                      # what the products stand for
 _PARTS = (("qkv", nn.Linear), ("proj", nn.Linear), ("fc1", nn.Linear), ("fc2", nn.Linear), ("ln1", InplaceLayerNorm),
           ("ln2", InplaceLayerNorm), ("act", InplaceGELU), ("core", TempoAttentionCore))

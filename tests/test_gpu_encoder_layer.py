@@ -137,6 +137,10 @@ def test_calls_that_are_made_of_the_parts(M, monkeypatch, taken):
     step(layer, x.transpose(0, 1).contiguous().transpose(0, 1).detach().requires_grad_(), dy, None, list(layer.parameters()))
     with torch.device("cuda"):                   # a function mode
         step(layer, x, dy)
+    with monkeypatch.context() as m:
+        plain = torch.nn.Linear.forward
+        m.setattr(torch.nn.Linear, "forward", lambda self, t: 2 * plain(self, t))
+        assert not torch.allclose(step(layer, x, dy)[0], want[0], atol=1e-2)
     assert not any(taken)
     # gradients that are differentiated again: the parts' own
     out = layer(x)
