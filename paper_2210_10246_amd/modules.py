@@ -211,6 +211,9 @@ def _differentiable_grads(ctx, dy, x, params, needed):
     heads, eps1, eps2, p, seed, offset, kind = ctx.setting
     if _version(ctx.key_len) != ctx.key_len_version:
         raise RuntimeError("key_len has been modified since the forward")
+    # Aliases, which are inputs of this graph alone: x may depend on these parameters, and two of them may be the same tensor,
+    # whose gradients the caller's backward adds up.
+    x, *params = [t.view_as(t) for t in (x, *params)]
     wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = params
 
     def core(scores, v):
@@ -264,7 +267,7 @@ class TempoEncoderLayer(nn.Module):
         tensor subclasses, other types and layouts."""
         if torch.compiler.is_compiling():
             return None
-        if type(x) not in _PLAIN or x.dtype != torch.float32 or not x.is_cuda or B.load() is None or B._native is None:
+        if not _plain(x):
             return None
         if (torch.is_autocast_enabled() or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
                 or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
@@ -290,7 +293,13 @@ class TempoEncoderLayer(nn.Module):
         return _EncoderLayerFn.apply(made, setting, key_len, core.store_mask, x, *params)
 
 
-_PLAIN = (torch.Tensor, nn.Parameter)
+def _plain(x):
+    if type(x) not in (torch.Tensor, nn.Parameter) or x.dtype != torch.float32 or not x.is_cuda:
+        return False
+    B.load()
+    return B._native is not None
+
+
 _LINEAR = nn.Linear.forward                      # what the products stand for
 _PARTS = (("qkv", nn.Linear), ("proj", nn.Linear), ("fc1", nn.Linear), ("fc2", nn.Linear), ("ln1", InplaceLayerNorm),
           ("ln2", InplaceLayerNorm), ("act", InplaceGELU), ("core", TempoAttentionCore))
