@@ -87,14 +87,20 @@ struct Run {
 using namespace tempo;
 
 int tempo_encoder_takes(const tempo_encoder* e) {
-  const Sizes z(*e);
-  if (z.T < 1 || z.H < 1 || z.F < 1 || z.A < 1 || z.H % z.A != 0) return 0;
-  if (z.H % 4 != 0 || z.F % 4 != 0 || z.d % 4 != 0) return 0;
-  // Sizes, tiles and lanes are counted in 32 bits: at most 2^20 + T A / 16 + B A tiles of 256 lanes in each of three products.
   const int64_t most = int64_t{1} << 30;
-  if (z.T > most / (3 * z.H) || z.T > most / z.F || z.F > most / z.H || z.S > 32768 ||
-      e->batch * e->heads > most / (z.S * z.S) || e->batch * e->heads > most >> 10 || z.T * z.A > most >> 6)
-    return 0;
+  for (int64_t n : {e->batch, e->seq, e->hidden, e->heads, e->ffn})
+    if (n < 1 || n > most) return 0;
+  if (e->hidden % e->heads != 0) return 0;
+  const Sizes z(*e);
+  if (z.H % 4 != 0 || z.F % 4 != 0 || z.d % 4 != 0) return 0;
+  // Elements of every tensor; then tiles: sizes, tiles and lanes are counted in 32 bits, and a launch has up to three products
+  // of 256 lanes a tile, at least 32 x 32 elements each.
+  const int64_t slices = e->batch * e->heads;
+  if (z.T > most / (3 * z.H) || z.T > most / z.F || z.F > most / z.H || z.S > 32768 || slices > most / (z.S * z.S)) return 0;
+  auto tiles = [](int64_t M, int64_t N) { return (M + kTile - 1) / kTile * ((N + kTile - 1) / kTile); };
+  for (int64_t n : {tiles(z.T, 3 * z.H), tiles(z.T, z.F), tiles(3 * z.H, z.H), tiles(z.F, z.H), slices * tiles(z.S, z.S),
+                    slices * tiles(z.S, z.d)})
+    if (n > most / (kTile * kTile)) return 0;
   // Multiplications of the four layers' weights, forward.  Below, the launches, copies and host time that go count for more than
   // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 (2e9) 1094 / 278 (host time), 8 x 128 x 1024
   // (13e9) 1106 / 775, 8 x 256 x 1024 (26e9) 1589 / 1553, 32 x 256 x 512 (26e9) 1896 / 1860; beyond, 16 x 256 x 768 (29e9)

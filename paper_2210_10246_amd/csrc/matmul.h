@@ -8,6 +8,8 @@
 
 namespace tempo {
 
+constexpr int kTile = 32;  // rows and columns of a matrix instruction, and of the smallest tile
+
 // One operand of a product: element (row, k) at p[row * ld + k], or at p[k * ld + row] if k_major.  The slice b of a
 // batch starts (b / inner) * outer_stride + (b % inner) * inner_stride elements further on.
 struct MatSide {

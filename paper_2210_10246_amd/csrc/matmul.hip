@@ -16,8 +16,6 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef f32x4 f32x4_word __attribute__((aligned(4)));  // 16 bytes at any float's address
 
-constexpr int kTile = 32;  // rows and columns of a matrix instruction
-
 // R rows by KT values of k of one operand: DEPTH steps ahead in registers, then LDS.
 template <bool KM, int R, int KT, int THREADS, int DEPTH>
 struct Stage {

@@ -19,6 +19,9 @@ class Encoder(ctypes.Structure):
     ((16, 256, 1024, 16, 4096), 0),                                   # the library's products are faster
     ((2, 128, 66, 3, 256), 0), ((2, 128, 64, 4, 254), 0), ((2, 8, 64, 3, 256), 0),   # no whole pieces, no whole heads
     ((0, 8, 64, 4, 256), 0), ((2, 0, 64, 4, 256), 0),
+    ((2, 8, 64, 0, 256), 0), ((2, 8, 64, -4, 256), 0), ((2, 8, 64, 4 - (1 << 32), 256), 0), ((2, 8, 64, 4 + (1 << 32), 256), 0),
+    ((-2, -8, 64, 4, 256), 0), ((1 << 62, 4, 64, 4, 256), 0), ((2, 8, 1 << 62, 4, 256), 0),
+    ((1, 1, 4, 1, 1 << 25), 1), ((1, 1, 4, 1, 1 << 26), 0), ((1, 1, 80000, 1250, 4), 0),   # few rows, more tiles than are counted
     ((1 << 21, 1, 4, 1, 4), 0), ((1 << 19, 64, 8, 2, 8), 0), ((1, 40000, 64, 1, 64), 0),   # more tiles than are counted
 ])
 def test_sizes_the_one_call_takes(sizes, takes):
