@@ -17,7 +17,6 @@ from __future__ import annotations
 import math
 
 import torch
-import torch.nn.functional as F
 from torch import nn
 from torch.autograd import forward_ad
 from torch.nn.modules import module
@@ -29,16 +28,22 @@ def _words(n: int, device) -> torch.Tensor:
     return torch.empty(B.mask_words(n), dtype=torch.int32, device=device)
 
 
+# `made`, in the three functions below: what the forward has already made, which is then not run (x and scores give only their
+# place in the graph).
+
 class _InplaceGELUFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, kind):
-        x = x.contiguous()
-        y = torch.empty_like(x)
-        mask = _words(x.numel(), x.device)
-        if kind == "silu":
-            B.tempo_silu_fwd(x, y, mask)
+    def forward(ctx, x, kind, made=None):
+        if made is None:
+            x = x.contiguous()
+            y = torch.empty_like(x)
+            mask = _words(x.numel(), x.device)
+            if kind == "silu":
+                B.tempo_silu_fwd(x, y, mask)
+            else:
+                B.tempo_gelu_fwd(x, y, mask, kind)
         else:
-            B.tempo_gelu_fwd(x, y, mask, kind)
+            y, mask = made[0].detach(), made[1]
         ctx.kind = kind
         ctx.save_for_backward(y, mask)
         return y
@@ -52,7 +57,7 @@ class _InplaceGELUFn(torch.autograd.Function):
             B.tempo_silu_bwd(dy, y, mask, dx)
         else:
             B.tempo_gelu_bwd(dy, y, mask, dx, ctx.kind)
-        return dx, None
+        return dx, None, None
 
 
 class InplaceGELU(nn.Module):
@@ -76,13 +81,16 @@ class InplaceSiLU(nn.Module):
 
 class _InplaceLayerNormFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, gamma, beta, eps):
-        x = x.contiguous()
-        M = x.shape[-1]
-        N = x.numel() // M
-        y = torch.empty_like(x)
-        rstd = torch.empty(N, dtype=torch.float32, device=x.device)
-        B.tempo_layernorm_fwd(x, gamma, beta, y, rstd, None, eps)
+    def forward(ctx, x, gamma, beta, eps, made=None):
+        if made is None:
+            x = x.contiguous()
+            M = x.shape[-1]
+            N = x.numel() // M
+            y = torch.empty_like(x)
+            rstd = torch.empty(N, dtype=torch.float32, device=x.device)
+            B.tempo_layernorm_fwd(x, gamma, beta, y, rstd, None, eps)
+        else:
+            y, rstd = made[0].detach(), made[1]
         ctx.save_for_backward(y, gamma, beta, rstd)
         return y
 
@@ -98,7 +106,7 @@ class _InplaceLayerNormFn(torch.autograd.Function):
         ws = torch.empty(B.tempo_layernorm_bwd_workspace_bytes(N, M), dtype=torch.uint8,
                          device=y.device)
         B.tempo_layernorm_bwd(dy, y, gamma, beta, rstd, dx, dgamma, dbeta, ws)
-        return dx, dgamma, dbeta, None
+        return dx, dgamma, dbeta, None, None
 
 
 class InplaceLayerNorm(nn.Module):
@@ -130,19 +138,22 @@ class InplaceLayerNorm(nn.Module):
 
 class _AttentionCoreFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, scores, v, key_len, causal, p, seed, offset, store_mask):
-        scores = scores.contiguous()
-        probs = torch.empty_like(scores)
-        out = torch.empty_like(scores)          # transient: freed when forward returns
-        keep = _words(scores.numel(), scores.device)
-        B.tempo_attn_softmax_dropout_fwd(scores, key_len, causal, probs, out, keep, p, seed, offset)
+    def forward(ctx, scores, v, key_len, causal, p, seed, offset, store_mask, made=None):
+        if made is None:
+            scores = scores.contiguous()
+            probs = torch.empty_like(scores)
+            out = torch.empty_like(scores)      # transient: freed when forward returns
+            keep = _words(scores.numel(), scores.device)
+            B.tempo_attn_softmax_dropout_fwd(scores, key_len, causal, probs, out, keep, p, seed, offset)
+        else:
+            probs, keep = made[:2]
         ctx.rng = (p, seed, offset)
         ctx.store_mask = store_mask
         if store_mask:
             ctx.save_for_backward(probs, v, keep)
         else:                                   # the mask is a transient too: drawn again later
             ctx.save_for_backward(probs, v)
-        return torch.matmul(out, v)
+        return torch.matmul(out, v) if made is None else made[2].detach()
 
     @staticmethod
     def backward(ctx, dctx):
@@ -156,7 +167,7 @@ class _AttentionCoreFn(torch.autograd.Function):
         else:
             B.tempo_attn_softmax_dropout_bwd_regen(dout, probs, dscores, out_re, p, seed, offset)
         dv = torch.matmul(out_re.transpose(-1, -2), dctx)
-        return dscores, dv, None, None, None, None, None, None
+        return (dscores, dv) + (None,) * 7
 
 
 class TempoAttentionCore(nn.Module):
@@ -180,60 +191,90 @@ class _EncoderLayerFn(torch.autograd.Function):
     keep.  The backward is one native call too."""
 
     @staticmethod
-    def forward(ctx, made, setting, key_len, store_mask, x, *params):
+    def forward(ctx, made, setting, store_mask, x, *params):
         qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = made
-        ctx.setting, ctx.key_len = setting, key_len
-        ctx.key_len_version = _version(key_len)
-        ctx.store_mask = store_mask
-        kept = (qkv, probs) + ((keep,) if store_mask else ()) + (ctxt, y1, rstd1, h, side, y2, rstd2)
-        ctx.save_for_backward(x, *params, *kept)
+        ctx.setting, ctx.store_mask = setting, store_mask
+        ctx.save_for_backward(x, *params, qkv, probs, keep if store_mask else None, ctxt, y1, rstd1, h, side, y2, rstd2)
         return y2
 
     @staticmethod
     def backward(ctx, dy):
-        x, *rest = ctx.saved_tensors
-        params, kept = rest[:12], rest[12:]
-        needed = ctx.needs_input_grad[4:]
-        if torch.is_grad_enabled():              # create_graph: the gradients of the general path
-            return (None,) * 4 + _differentiable_grads(ctx, dy, x, params, needed)
-        if not ctx.store_mask:
-            kept.insert(2, None)
+        needed = ctx.needs_input_grad[3:]
+        if torch.is_grad_enabled():              # create_graph
+            return (None,) * 3 + _grads_of_parts(ctx, dy, needed)
         wanted = sum(1 << i for i, n in enumerate(needed) if n)
-        r = B.encoder_bwd(dy.contiguous(), wanted, x, *ctx.setting, *params, *kept)
-        return (None,) * 4 + r
+        x, *rest = ctx.saved_tensors
+        return (None,) * 3 + B.encoder_bwd(dy.contiguous(), wanted, x, *ctx.setting, *rest)
 
 
-def _version(t):
-    return None if t is None or t.is_inference() else t._version
+class _MadeLinearFn(torch.autograd.Function):
+    """y = x w^T + b, already made."""
+
+    @staticmethod
+    def forward(ctx, y, x, w, b):
+        ctx.save_for_backward(x, w)
+        return y.detach()
+
+    @staticmethod
+    def backward(ctx, dy):
+        x, w = ctx.saved_tensors
+        rows = dy.reshape(-1, dy.shape[-1])
+        dx = torch.matmul(dy, w) if ctx.needs_input_grad[1] else None
+        dw = torch.matmul(rows.t(), x.reshape(-1, x.shape[-1])) if ctx.needs_input_grad[2] else None
+        return None, dx, dw, rows.sum(0) if ctx.needs_input_grad[3] else None
 
 
-def _differentiable_grads(ctx, dy, x, params, needed):
-    heads, eps1, eps2, p, seed, offset, kind = ctx.setting
-    if _version(ctx.key_len) != ctx.key_len_version:
-        raise RuntimeError("key_len has been modified since the forward")
-    # Aliases, which are inputs of this graph alone: x may depend on these parameters, and two of them may be the same tensor,
-    # whose gradients the caller's backward adds up.
-    x, *params = [t.view_as(t) for t in (x, *params)]
-    wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = params
+class _MadeScoresFn(torch.autograd.Function):
+    """scale q k^T of every head, already made; only its place in the graph is needed."""
 
-    def core(scores, v):
-        return _AttentionCoreFn.apply(scores, v, ctx.key_len, False, p, seed, offset, ctx.store_mask)
+    @staticmethod
+    def forward(ctx, scores, q, k, scale):
+        ctx.scale = scale
+        ctx.save_for_backward(q, k)
+        return scores.detach()
 
-    ctxt = _attention(F.linear(x, wqkv, bqkv), heads, core)
-    y1 = _InplaceLayerNormFn.apply(x + F.linear(ctxt, wproj, bproj), g1, be1, eps1)
-    h = _InplaceGELUFn.apply(F.linear(y1, w1, b1), kind)
-    out = _InplaceLayerNormFn.apply(y1 + F.linear(h, w2, b2), g2, be2, eps2)
-    inputs = [t for t, n in zip((x, *params), needed) if n]
-    grads = iter(torch.autograd.grad(out, inputs, dy, create_graph=True))
+    @staticmethod
+    def backward(ctx, ds):
+        q, k = ctx.saved_tensors
+        ds = ds * ctx.scale
+        return None, torch.matmul(ds, k), torch.matmul(ds.transpose(-1, -2), q), None
+
+
+def _grads_of_parts(ctx, dy, needed):
+    """The gradients as the layer made of its parts gives them, connected to its inputs.  The graph of the parts is laid over what
+    the forward made: nothing of the forward runs again."""
+    heads, _, _, p, seed, offset, kind = ctx.setting
+    inputs, (qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2) = ctx.saved_tensors[:13], ctx.saved_tensors[13:]
+    Bn, S, H = dy.shape
+    d = H // heads
+
+    def value(t, *shape):     # t in that shape; zeros without memory where nothing looks at it
+        return dy.new_zeros(()).expand(shape) if t is None else t.reshape(shape)
+    with torch.enable_grad():
+        # Aliases, which are inputs of this graph alone: x may depend on these parameters, and two of them may be the same
+        # tensor, whose gradients the caller's backward adds up.
+        inputs = [t.view_as(t) for t in inputs]
+        x, wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = inputs
+
+        def core(q, k, v):
+            scores = _MadeScoresFn.apply(value(None, Bn, heads, S, S), q, k, 1.0 / math.sqrt(d))
+            made = (probs, keep, value(ctxt, Bn, S, heads, d).permute(0, 2, 1, 3))
+            return _AttentionCoreFn.apply(scores, v, None, False, p, seed, offset, ctx.store_mask, made)
+
+        rows = value(None, Bn, S, H)
+        a = _attention(_MadeLinearFn.apply(value(qkv, Bn, S, 3 * H), x, wqkv, bqkv), dy.shape, heads, core)
+        y1 = _InplaceLayerNormFn.apply(x + _MadeLinearFn.apply(rows, a, wproj, bproj), g1, be1, None,
+                                       (value(y1, Bn, S, H), rstd1))
+        h = _InplaceGELUFn.apply(_MadeLinearFn.apply(value(None, Bn, S, len(b1)), y1, w1, b1), kind, (value(h, Bn, S, len(b1)), side))
+        out = _InplaceLayerNormFn.apply(y1 + _MadeLinearFn.apply(rows, h, w2, b2), g2, be2, None, (y2, rstd2))
+    grads = iter(torch.autograd.grad(out, [t for t, n in zip(inputs, needed) if n], dy, create_graph=torch.is_grad_enabled()))
     return tuple(next(grads) if n else None for n in needed)
 
 
-def _attention(qkv, heads, core):
-    Bn, S, L = qkv.shape
-    d = L // 3 // heads
-    q, k, v = qkv.view(Bn, S, 3, heads, d).permute(2, 0, 3, 1, 4)
-    scores = torch.matmul(q, k.transpose(-1, -2)) * (1.0 / math.sqrt(d))
-    return core(scores, v.contiguous()).permute(0, 2, 1, 3).reshape(Bn, S, heads * d)
+def _attention(qkv, shape, heads, core):
+    Bn, S, H = shape
+    q, k, v = qkv.view(Bn, S, 3, heads, H // heads).permute(2, 0, 3, 1, 4)
+    return core(q, k, v.contiguous()).permute(0, 2, 1, 3).reshape(Bn, S, H)
 
 
 class TempoEncoderLayer(nn.Module):
@@ -257,7 +298,12 @@ class TempoEncoderLayer(nn.Module):
         out = self._as_one(x, key_len)
         if out is not None:
             return out
-        ctxt = _attention(self.qkv(x), self.heads, lambda scores, v: self.core(scores, v, key_len))
+
+        def core(q, k, v):
+            scores = torch.matmul(q, k.transpose(-1, -2)) * (1.0 / math.sqrt(q.shape[-1]))
+            return self.core(scores, v, key_len)
+        Bn, S, H = x.shape
+        ctxt = _attention(self.qkv(x), (Bn, S, H), self.heads, core)
         x = self.ln1(x + self.proj(ctxt))
         return self.ln2(x + self.fc2(self.act(self.fc1(x))))
 
@@ -290,7 +336,7 @@ class TempoEncoderLayer(nn.Module):
         core.offset += 1
         if not torch.is_grad_enabled():
             return made[8]
-        return _EncoderLayerFn.apply(made, setting, key_len, core.store_mask, x, *params)
+        return _EncoderLayerFn.apply(made, setting, core.store_mask, x, *params)
 
 
 def _plain(x):
