@@ -72,12 +72,9 @@ struct Run {
   void operator()(const Matmul& g) {
     if (status == TEMPO_OK) status = launch_matmul(g, st);
   }
-  // A layer's dx and, if wanted, its dw: either needs only dy.
-  void backward(const Matmul* dx, const Matmul& dw) {
-    if (status != TEMPO_OK) return;
-    if (dx && dw.c) status = launch_matmul_group(*dx, dw, nullptr, st);
-    else if (dx) status = launch_matmul(*dx, st);
-    else if (dw.c) status = launch_matmul(dw, st);
+  // A layer's dx and dw, either of which may not be wanted: no c.
+  void backward(const Matmul& dx, const Matmul& dw) {
+    if (status == TEMPO_OK && (dx.c || dw.c)) status = launch_matmul_group(dx, dw, nullptr, st);
   }
 };
 
@@ -142,14 +139,12 @@ tempo_status tempo_encoder_bwd_ffn(const tempo_encoder* e, const tempo_encoder_g
   run(tempo_layernorm_bwd(dy, e->y2, e->gamma2, e->beta2, e->rstd2, ds2, g->dgamma2, g->dbeta2, workspace, workspace_bytes,
                           z.T, z.H, TEMPO_F32, hip_stream));
   const bool more = dy1 || g->dw1;
-  Matmul dh2 = linear_dx(ds2, e->w2, nullptr, dh, z.T, z.H, z.F);
-  const bool fused = g->dw2 && z.F % 8 == 0;  // grouped products only
-  if (fused) with_gelu(dh2, *e, Matmul::kBackward);
-  run.backward(more ? &dh2 : nullptr, linear_dw(ds2, e->h, g->dw2, g->db2, z.T, z.H, z.F));
+  Matmul dh2 = linear_dx(ds2, e->w2, nullptr, more ? dh : nullptr, z.T, z.H, z.F);
+  if (z.F % 8 == 0) with_gelu(dh2, *e, Matmul::kBackward);
+  run.backward(dh2, linear_dw(ds2, e->h, g->dw2, g->db2, z.T, z.H, z.F));
   if (!more) return run.status;
-  if (!fused && run.status == TEMPO_OK) run(tempo_gelu_bwd(dh, e->h, e->side, dh, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
-  const Matmul dx1 = linear_dx(dh, e->w1, ds2, dy1, z.T, z.F, z.H);
-  run.backward(dy1 ? &dx1 : nullptr, linear_dw(dh, e->y1, g->dw1, g->db1, z.T, z.F, z.H));
+  if (z.F % 8 != 0 && run.status == TEMPO_OK) run(tempo_gelu_bwd(dh, e->h, e->side, dh, z.T * z.F, TEMPO_F32, e->kind, hip_stream));
+  run.backward(linear_dx(dh, e->w1, ds2, dy1, z.T, z.F, z.H), linear_dw(dh, e->y1, g->dw1, g->db1, z.T, z.F, z.H));
   return run.status;
 }
 
@@ -166,8 +161,7 @@ tempo_status tempo_encoder_bwd_attention(const tempo_encoder* e, const tempo_enc
   const int64_t H = z.H, S = z.S, d = z.d, L = 3 * H, SS = S * S;
   const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(d)));
   Run run{static_cast<hipStream_t>(hip_stream)};
-  const Matmul dc = linear_dx(ds1, e->wproj, nullptr, dctxt, z.T, H, H);
-  run.backward(dctxt ? &dc : nullptr, linear_dw(ds1, e->ctxt, g->dwproj, g->dbproj, z.T, H, H));
+  run.backward(linear_dx(ds1, e->wproj, nullptr, dctxt, z.T, H, H), linear_dw(ds1, e->ctxt, g->dwproj, g->dbproj, z.T, H, H));
   if (!dctxt) return run.status;
   run(per_head(z, rows_of(dctxt, H, S * H, d), rows_of(e->qkv + 2 * H, L, S * L, d), dout, S, z.A * SS, SS, S, d));
   if (run.status == TEMPO_OK) {
@@ -182,7 +176,6 @@ tempo_status tempo_encoder_bwd_attention(const tempo_encoder* e, const tempo_enc
   Matmul dk = per_head(z, columns_of(dout, S, z.A * SS, SS), columns_of(e->qkv, L, S * L, d), dqkv + H, L, S * L, d, d, S);
   dq.alpha = dk.alpha = scale;
   if (run.status == TEMPO_OK) run(launch_matmul_group(dq, dk, &dv, run.st));
-  const Matmul dx = linear_dx(dqkv, e->wqkv, ds1, g->dx, z.T, L, H);
-  run.backward(g->dx ? &dx : nullptr, linear_dw(dqkv, e->x, g->dwqkv, g->dbqkv, z.T, L, H));
+  run.backward(linear_dx(dqkv, e->wqkv, ds1, g->dx, z.T, L, H), linear_dw(dqkv, e->x, g->dwqkv, g->dbqkv, z.T, L, H));
   return run.status;
 }

@@ -37,7 +37,8 @@ struct Matmul {
   uint8_t* side = nullptr;
 };
 tempo_status launch_matmul(const Matmul& g, hipStream_t st);
-// g (k-major b only) and one or two products of one size with two k-major operands, none of which needs another.
+// g (k-major b only) and one or two products of one size with two k-major operands, none of which needs another.  g or h0
+// may have no c: it is not computed, and the other gets the bits that it has beside it.
 tempo_status launch_matmul_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st);
 
 }  // namespace tempo

@@ -321,7 +321,7 @@ tempo_status go(const Matmul& g, hipStream_t st) {
     return launch_status();
   };
   if (g.act == Matmul::kNone) return launch(matmul_kernel<C, Matmul::kNone, 0>);
-  if constexpr (!C::AKM && !C::BKM) {
+  if constexpr (!C::BKM) {
     if (g.act == Matmul::kForward)
       return launch(g.kind == TEMPO_GELU_TANH ? matmul_kernel<C, Matmul::kForward, TEMPO_GELU_TANH>
                                               : matmul_kernel<C, Matmul::kForward, TEMPO_GELU_ERF>);
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(C::kThreads) void matmul_group_kernel(Matmul g, Mat
   static_assert(kStaged % 4 == 0, "table rows of 16 bytes behind it");
   __shared__ __attribute__((aligned(16))) float lds[kStaged + 4 * kRows];
   const int block = blockIdx.x;
-  if (block < g_tiles) {
+  if (block < g_tiles) {  // none of it if g is not computed
     f32x4* const table = reinterpret_cast<f32x4*>(lds + kStaged);
     if constexpr (ACT == Matmul::kBackward) {  // ordered by the barriers of the loop
       for (int i = threadIdx.x; i < kRows; i += C::kThreads)
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(C::kThreads) void matmul_group_kernel(Matmul g, Mat
 }
 template <typename C, typename D>
 tempo_status go_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st) {
-  const int64_t g_tiles = C::tiles(g), h_tiles = D::tiles(h0);
+  const int64_t g_tiles = g.c ? C::tiles(g) : 0, h_tiles = h0.c ? D::tiles(h0) : 0;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(g_tiles + (h1 ? 2 : 1) * h_tiles), dim3(C::kThreads), 0, st, g, h0, h1 ? *h1 : h0,
                        static_cast<int>(g_tiles), static_cast<int>(h_tiles));
@@ -374,42 +374,39 @@ template <bool AKM, bool BKM>
 using SmallLong = Config<AKM, BKM, 32, 32, 8, 64, 4>;
 
 // Tiles of 64 x 64, 64 x 32 or 32 x 32 elements: whichever gives the compute unit with the most of them the least to do,
-// where a smaller tile takes 8 % (12 % with two k-major operands) more time for its elements, and a workgroup alone on its
-// compute unit 15 %.  us with 64 x 64 / 64 x 32 / 32 x 32 tiles: [256, 768] x [768, 2304] 18.8 / 17.9 / 15.2, [512, 1024] x
-// [1024, 3072] 38.6 / 31.5 / 33.7, [1024, 768] x [768, 3072] 43.8 / 46.8 / 49.6; [2304, 256] x [256, 768], both k-major, 14.9 /
-// 17.1 / 16.3, [3072, 1024] x [1024, 768] 57.5 / 54.1 / 57.8.  Where each compute unit has at most one 32 x 32 tile with
-// many values of k, 8 instead of 4 waves share those: [256, 3072] x [3072, 768] k-major 23.5 / 19.7, 768 values 8.4 / 7.9,
-// but 7.7 / 8.3 with rows of k side by side and, 2048 values, 15.4 / 15.5.  Larger tiles per wave or workgroup (64 x 128, 128 x
-// 128) gain 5 % on [2048, 1024] x [1024, 4096] and lose everywhere below.
-template <bool AKM, bool BKM>
+// where a smaller tile takes 8 % more time for its elements, and a workgroup alone on its compute unit 15 %.  us with 64 x 64 /
+// 64 x 32 / 32 x 32 tiles: [256, 768] x [768, 2304] 18.8 / 17.9 / 15.2, [512, 1024] x [1024, 3072] 38.6 / 31.5 / 33.7, [1024, 768]
+// x [768, 3072] 43.8 / 46.8 / 49.6.  Where each compute unit has at most one 32 x 32 tile with many values of k, 8 instead of 4
+// waves share those: [256, 3072] x [3072, 768] k-major 23.5 / 19.7, 768 values 8.4 / 7.9, but 7.7 / 8.3 with rows of k side by side
+// and, 2048 values, 15.4 / 15.5.  Larger tiles per wave or workgroup (64 x 128, 128 x 128) gain 5 % on [2048, 1024] x [1024, 4096]
+// and lose everywhere below.
+template <bool BKM>
 tempo_status by_shape(const Matmul& g, hipStream_t st) {
   const int64_t cus = compute_units();
   auto rounds = [&](int bm, int bn) {
     return (int64_t{(g.M + bm - 1) / bm} * ((g.N + bn - 1) / bn) * g.batch + cus - 1) / cus;
   };
-  const int small = AKM ? 12 : 8;
   auto cost = [&](int bm, int bn, int percent) {
     const int64_t r = rounds(bm, bn);
     return r * (bm * bn / 1024) * (100 + percent) + (bm * bn / 1024) * 15;
   };
-  const int64_t large = cost(64, 64, 0), middle = cost(64, 32, small), least = cost(32, 32, 2 * small);
-  if (large <= middle && large <= least) return go<Large<AKM, BKM>>(g, st);
-  if (middle <= least) return go<Middle<AKM, BKM>>(g, st);
-  if constexpr (!AKM) {
-    if (rounds(32, 32) == 1 && g.K >= (BKM ? 512 : 2560)) return go<SmallLong<AKM, BKM>>(g, st);
-  }
-  return go<Small<AKM, BKM>>(g, st);
+  const int64_t large = cost(64, 64, 0), middle = cost(64, 32, 8), least = cost(32, 32, 16);
+  if (large <= middle && large <= least) return go<Large<false, BKM>>(g, st);
+  if (middle <= least) return go<Middle<false, BKM>>(g, st);
+  if (rounds(32, 32) == 1 && g.K >= (BKM ? 512 : 2560)) return go<SmallLong<false, BKM>>(g, st);
+  return go<Small<false, BKM>>(g, st);
 }
 
 }  // namespace
 
 tempo_status launch_matmul(const Matmul& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return TEMPO_OK;
-  if (g.a.k_major) return g.b.k_major ? by_shape<true, true>(g, st) : TEMPO_ERR_UNSUPPORTED;
-  return g.b.k_major ? by_shape<false, true>(g, st) : by_shape<false, false>(g, st);
+  if (g.a.k_major) return TEMPO_ERR_UNSUPPORTED;  // in groups only
+  return g.b.k_major ? by_shape<true>(g, st) : by_shape<false>(g, st);
 }
 // The tile of each by how many of 64 x 64 it has per compute unit: together they are some per compute unit, and the sizes
-// that suit a product by itself (by_shape()) are too small or too large.  us apart / with the product of the rows in large,
+// that suit a product by itself (by_shape()) are too small or too large.  The rule counts both also where one of them is not
+// computed: tiles decide in which order the products of an element add up, and so its bits.  us apart / with the product of the rows in large,
 // middle, small tiles and the others' tile this gives: dx and dw of a [256, 768] x [768, 3072] layer (192 and 576 tiles) 37.0 /
 // 28.7, 30.3, 32.3; [256, 768] x [768, 768] (48, 144) 16.7 / 20.7, 13.9, 10.9; [128, 768] x [768, 3072] (96, 576) 26.1 / 24.3, 18.0,
 // 21.3; [512, 1024] x [1024, 3072] (128, 768) 69.5 / 77.1, 63.6, 66.4; [2048, 1024] x [1024, 4096] (512, 1024) 305 / 301, 327,

@@ -90,10 +90,13 @@ def test_options_reach_the_kernels(M, monkeypatch, taken, kind, store, training)
         assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5
 
 
-def test_gradients_of_a_part_of_the_inputs(M):
+# Sizes whose products take other tiles alone than beside others: with values of k split over 1, 2, 4 and 8 waves.
+@pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [(3, 20, 64, 4, 128), (2, 128, 768, 12, 3072), (1, 77, 512, 8, 2048),
+                                                        (4, 130, 256, 4, 1028), (2, 31, 1024, 16, 4096)])
+def test_gradients_of_a_part_of_the_inputs(M, taken, batch, seq, hidden, heads, ffn):
     """Whatever is asked for has the bits it has when everything is."""
-    layer = layer_of(M, 64, 4, 128)
-    x, dy = inputs(3, 20, 64)
+    layer = layer_of(M, hidden, heads, ffn)
+    x, dy = inputs(batch, seq, hidden)
     every = [x, *layer.parameters()]
     full = step(layer, x, dy)[1:]
     for names in ([0], [2], [3, 4], [5], [7, 8], [9], [11, 12], [0, 6], [1, 10]):
@@ -102,6 +105,7 @@ def test_gradients_of_a_part_of_the_inputs(M):
         got = step(layer, x, dy, None, [every[i] for i in names])[1:]
         for i, g in zip(names, got):
             assert torch.equal(g, full[i]), names
+    assert all(taken)
     for t in every:
         t.requires_grad_(True)
 
