@@ -237,16 +237,27 @@ float* beside(const at::Tensor& x, PyObject* o, std::initializer_list<int64_t> s
   return static_cast<float*>(pointer(t));
 }
 constexpr int kEncoderParams = 12;
+// x, or a tensor of its sizes, on the current device: its pointer, and the sizes into e.
+float* input(const at::Tensor& x, tempo_encoder* e) {
+  if (x.scalar_type() != at::kFloat || x.dim() != 3 || x.is_neg()) throw NotPlain{};
+  float* p = static_cast<float*>(pointer(x));
+  if (x.device().index() != c10::hip::current_device()) throw NotPlain{};
+  e->batch = x.size(0);
+  e->seq = x.size(1);
+  e->hidden = x.size(2);
+  return p;
+}
+int64_t integer(PyObject* o) {
+  if (!PyLong_CheckExact(o)) throw NotPlain{};
+  const long long v = PyLong_AsLongLong(o);
+  if (v == -1 && PyErr_Occurred()) throw NotPlain{};
+  return v;
+}
 // The layer of x with heads, eps1, eps2, p, seed, offset and kind at a[0 .. 6], and its parameters at w.
 tempo_encoder encoder(const at::Tensor& x, PyObject* const* a, PyObject* const* w) {
   tempo_encoder e{};
-  if (x.scalar_type() != at::kFloat || x.dim() != 3 || x.is_neg() || x.device().index() != c10::hip::current_device()) throw NotPlain{};
-  e.x = static_cast<float*>(pointer(x));
-  e.batch = x.size(0);
-  e.seq = x.size(1);
-  e.hidden = x.size(2);
-  if (!PyLong_CheckExact(a[0])) throw NotPlain{};
-  e.heads = PyLong_AsLongLong(a[0]);
+  e.x = input(x, &e);
+  e.heads = integer(a[0]);
   e.eps1 = real(a[1]);
   e.eps2 = real(a[2]);
   e.p = real(a[3]);
@@ -331,33 +342,63 @@ TEMPO_METHOD(encoder_fwd) {
   return result(status, all);
 }
 
-// dy, wanted (bits: x, then the parameters), x, heads, eps1, eps2, p, seed, offset, kind, 12 parameters, and of
-// encoder_fwd qkv, probs, keep or None, ctxt, y1, rstd1, h, side, y2, rstd2 -> status and the 13 gradients
+// dy, wanted (bits: x, then the parameters), heads, ffn, p, seed, offset, kind, and of the forward x, wqkv, wproj, w1, w2, gamma1, beta1,
+// gamma2, beta2, qkv, probs, keep (or None: drawn again), ctxt, y1, rstd1, h, side, y2, rstd2, of which only those are looked at
+// that the wanted gradients need -> status and the 13 gradients
 TEMPO_METHOD(encoder_bwd) {
-  if (nargs != 10 + kEncoderParams + 10) Py_RETURN_NONE;
+  if (nargs != 8 + 19) Py_RETURN_NONE;
   at::Tensor dx, dw[kEncoderParams];
   tempo_status status = TEMPO_OK;
   HANDLE_TH_ERRORS  // out of memory, as torch raises it
   try {
-    const at::Tensor& x = tensor(a[2]);
-    tempo_encoder e = encoder(x, a + 3, a + 10);
-    PyObject* const* kept = a + 10 + kEncoderParams;
-    const int64_t B = e.batch, S = e.seq, T = B * S, H = e.hidden, F = e.ffn, n = B * e.heads * S * S;
-    const float* dy = beside(x, a[0], {B, S, H});
+    const at::Tensor& out_grad = tensor(a[0]);
     const uint64_t wanted = bits64(a[1]);
-    e.qkv = beside(x, kept[0], {T, 3 * H});
-    e.probs = beside(x, kept[1], {B, e.heads, S, S});
-    if (kept[2] != Py_None) e.keep = mask_words(kept[2], n);
-    e.ctxt = beside(x, kept[3], {T, H});
-    e.y1 = beside(x, kept[4], {T, H});
-    e.rstd1 = beside(x, kept[5], {T});
-    e.h = beside(x, kept[6], {T, F});
-    e.side = mask_words(kept[7], T * F);
-    e.y2 = beside(x, kept[8], {B, S, H});
-    e.rstd2 = beside(x, kept[9], {T});
+    tempo_encoder e{};
+    const float* dy = input(out_grad, &e);
+    e.heads = integer(a[2]);
+    e.ffn = integer(a[3]);
+    e.p = real(a[4]);
+    e.seed = bits64(a[5]);
+    e.offset = bits64(a[6]);
+    e.kind = gelu_kind(a[7]);
+    if (!tempo_encoder_takes(&e)) throw NotPlain{};
+    const int64_t B = e.batch, S = e.seq, T = B * S, H = e.hidden, F = e.ffn, n = B * e.heads * S * S;
     auto want = [&](int first, int last) { return (wanted >> first & ((uint64_t{2} << (last - first)) - 1)) != 0; };
-    const auto floats = x.options().requires_grad(false);
+    // bits: 0 x, 1 2 qkv, 3 4 proj, 5 6 fc1, 7 8 fc2, 9 10 ln1, 11 12 ln2
+    const bool attention = want(0, 2), first = want(0, 4) || want(9, 10), second = first || want(5, 6);
+    PyObject* const* o = a + 8;
+    auto kept = [&](bool needed, std::initializer_list<int64_t> sizes) {
+      PyObject* t = *o++;
+      return needed ? beside(out_grad, t, sizes) : nullptr;
+    };
+    auto bits = [&](bool needed, int64_t elements) {
+      PyObject* t = *o++;
+      if (!needed) return static_cast<uint32_t*>(nullptr);
+      if (tensor(t).device() != out_grad.device()) throw NotPlain{};
+      return mask_words(t, elements);
+    };
+    e.x = kept(want(1, 1), {B, S, H});
+    e.wqkv = kept(want(0, 0), {3 * H, H});
+    e.wproj = kept(attention, {H, H});
+    e.w1 = kept(first, {F, H});
+    e.w2 = kept(second, {H, F});
+    e.gamma1 = kept(first, {H});
+    e.beta1 = kept(first, {H});
+    e.gamma2 = kept(true, {H});
+    e.beta2 = kept(true, {H});
+    e.qkv = kept(attention, {T, 3 * H});
+    e.probs = kept(attention, {B, e.heads, S, S});
+    e.keep = bits(attention && *o != Py_None, n);
+    e.ctxt = kept(want(3, 3), {T, H});
+    e.y1 = kept(first || want(5, 5), {T, H});
+    e.rstd1 = kept(first, {T});
+    e.h = kept(second || want(7, 7), {T, F});
+    e.side = bits(second, T * F);
+    e.y2 = kept(true, {B, S, H});
+    e.rstd2 = kept(true, {T});
+    const auto floats = out_grad.options().requires_grad(false);
     auto grad = [&](int i, at::IntArrayRef sizes) { return data(dw[i] = at::empty(sizes, floats)); };
+    auto wanted_grad = [&](int i, at::IntArrayRef sizes) { return want(i + 1, i + 1) ? grad(i, sizes) : nullptr; };
     tempo_encoder_grads g{};
     at::Tensor ds = at::empty({T, H}, floats), dh, dy1;
     at::Tensor workspace = at::empty({static_cast<int64_t>(tempo_layernorm_bwd_workspace_bytes(T, H))}, floats.dtype(at::kByte));
@@ -369,20 +410,14 @@ TEMPO_METHOD(encoder_bwd) {
       status = call();
       PyEval_RestoreThread(state);
     };
-    // bits: 0 x, 1 2 qkv, 3 4 proj, 5 6 fc1, 7 8 fc2, 9 10 ln1, 11 12 ln2
-    const bool attention = want(0, 2), first = want(0, 4) || want(9, 10);
     g.dgamma2 = grad(10, {H});
     g.dbeta2 = grad(11, {H});
-    if (want(7, 8)) {
-      g.dw2 = grad(6, {H, F});
-      g.db2 = grad(7, {H});
-    }
-    if (want(5, 6)) {
-      g.dw1 = grad(4, {F, H});
-      g.db1 = grad(5, {F});
-    }
+    g.dw2 = wanted_grad(6, {H, F});
+    g.db2 = wanted_grad(7, {H});
+    g.dw1 = wanted_grad(4, {F, H});
+    g.db1 = wanted_grad(5, {F});
     if (first) dy1 = at::empty({T, H}, floats);
-    if (first || g.dw1) dh = at::empty({T, F}, floats);
+    if (second) dh = at::empty({T, F}, floats);
     run([&] {
       return tempo_encoder_bwd_ffn(&e, &g, dy, data(ds), data(dh), data(dy1), workspace.data_ptr(), workspace_bytes, st);
     });
@@ -397,26 +432,22 @@ TEMPO_METHOD(encoder_bwd) {
     workspace.reset();
     if (want(0, 4)) {
       at::Tensor dctxt, dqkv, dout, out;
-      if (want(3, 4)) {
-        g.dwproj = grad(2, {H, H});
-        g.dbproj = grad(3, {H});
-      }
+      g.dwproj = wanted_grad(2, {H, H});
+      g.dbproj = wanted_grad(3, {H});
       if (attention) {
         dctxt = dy1;  // has been read
         dqkv = at::empty({T, 3 * H}, floats);
         dout = at::empty({B, e.heads, S, S}, floats);
         out = at::empty({B, e.heads, S, S}, floats);
-        if (want(1, 2)) {
-          g.dwqkv = grad(0, {3 * H, H});
-          g.dbqkv = grad(1, {3 * H});
-        }
+        g.dwqkv = wanted_grad(0, {3 * H, H});
+        g.dbqkv = wanted_grad(1, {3 * H});
         if (want(0, 0)) g.dx = data(dx = at::empty({B, S, H}, floats));
       }
       run([&] {
         return tempo_encoder_bwd_attention(&e, &g, data(ds), data(dctxt), data(dqkv), data(dout), data(out), st);
       });
     }
-    for (int i = 0; i < kEncoderParams; ++i)
+    for (int i = 8; i < kEncoderParams; ++i)  // the LayerNorms'
       if (!want(i + 1, i + 1)) dw[i].reset();
   } catch (const NotPlain&) {
     PyErr_Clear();

@@ -18,7 +18,7 @@ typedef struct {
   tempo_gelu_kind kind;
   const float *wqkv, *bqkv, *wproj, *bproj, *w1, *b1, *w2, *b2;  // Linear: [out, in] and [out]
   const float *gamma1, *beta1, *gamma2, *beta2;
-  const float* x;          // [T, hidden]
+  const float* x;          // [T, hidden]; in the backward null, as all else, where the gradients wanted do not need it
   const int32_t* key_len;  // [batch] or null
   // written by the forward, read by the backward
   float *qkv, *probs, *ctxt, *y1, *rstd1, *h, *y2, *rstd2;
@@ -31,7 +31,7 @@ TEMPO_API int tempo_encoder_takes(const tempo_encoder* e);
 // out: scratch as large as probs.
 TEMPO_API tempo_status tempo_encoder_fwd(const tempo_encoder* e, float* out, void* hip_stream);
 
-// The gradients of a layer.  Those of a weight and its bias are written together; both null: not computed.
+// The gradients of a layer; null: not computed.  Those of a LayerNorm are written together.
 typedef struct {
   float *dx, *dwqkv, *dbqkv, *dwproj, *dbproj, *dw1, *db1, *dw2, *db2;
   float *dgamma1, *dbeta1, *dgamma2, *dbeta2;

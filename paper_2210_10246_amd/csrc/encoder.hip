@@ -1,6 +1,7 @@
 // The launches of encoder.h.  Heads are taken from and put into the [T, 3 hidden] and [T, hidden] layouts by the
 // strides of the products, and residuals, biases, 1 / sqrt(d) and the sums for the bias gradients are part of them: no
 // copies, no elementwise passes beside the three layers; GELU is part of the products around it.
+#include <algorithm>
 #include <cmath>
 
 #include "encoder.h"
@@ -21,7 +22,8 @@ MatSide rows_of(const float* p, int64_t ld, int64_t outer = 0, int64_t inner = 0
 MatSide columns_of(const float* p, int64_t ld, int64_t outer = 0, int64_t inner = 0) { return {p, ld, outer, inner, true}; }
 
 Matmul product(MatSide a, MatSide b, float* c, int64_t ldc, int64_t M, int64_t N, int64_t K) {
-  return {a, b, c, ldc, 0, 0, nullptr, nullptr, nullptr, 1.0f, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 1, 1};
+  return {a, b, c, ldc, 0, 0, nullptr, nullptr, nullptr, 1.0f, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 1, 1,
+          static_cast<int>(N)};
 }
 // One product per head.
 Matmul per_head(const Sizes& z, MatSide a, MatSide b, float* c, int64_t ldc, int64_t c_outer, int64_t c_inner, int64_t N,
@@ -46,9 +48,11 @@ Matmul linear_dx(const float* dy, const float* w, const float* add, float* dx, i
   g.add = add;
   return g;
 }
-// dw = dy^T x and db = the column sums of dy
+// dw = dy^T x and db = the column sums of dy, either of which may be null.  Where only db is wanted, x need not be there: the
+// tiles that make the sums take dy for it, and nothing stores what they multiply.
 Matmul linear_dw(const float* dy, const float* x, float* dw, float* db, int64_t T, int64_t out, int64_t in) {
-  Matmul g = product(columns_of(dy, out), columns_of(x, in), dw, in, out, in, T);
+  Matmul g = product(columns_of(dy, out), dw ? columns_of(x, in) : columns_of(dy, out), dw, in, out, dw ? in : std::min(in, out), T);
+  g.n_counted = static_cast<int>(in);
   g.a_sums = db;
   return g;
 }
@@ -72,9 +76,9 @@ struct Run {
   void operator()(const Matmul& g) {
     if (status == TEMPO_OK) status = launch_matmul(g, st);
   }
-  // A layer's dx and dw, either of which may not be wanted: no c.
+  // A layer's dx, and its dw and db, any of which may not be wanted.
   void backward(const Matmul& dx, const Matmul& dw) {
-    if (status == TEMPO_OK && (dx.c || dw.c)) status = launch_matmul_group(dx, dw, nullptr, st);
+    if (status == TEMPO_OK && (dx.c || dw.c || dw.a_sums)) status = launch_matmul_group(dx, dw, nullptr, st);
   }
 };
 
@@ -138,7 +142,7 @@ tempo_status tempo_encoder_bwd_ffn(const tempo_encoder* e, const tempo_encoder_g
   Run run{static_cast<hipStream_t>(hip_stream)};
   run(tempo_layernorm_bwd(dy, e->y2, e->gamma2, e->beta2, e->rstd2, ds2, g->dgamma2, g->dbeta2, workspace, workspace_bytes,
                           z.T, z.H, TEMPO_F32, hip_stream));
-  const bool more = dy1 || g->dw1;
+  const bool more = dy1 || g->dw1 || g->db1;
   Matmul dh2 = linear_dx(ds2, e->w2, nullptr, more ? dh : nullptr, z.T, z.H, z.F);
   if (z.F % 8 == 0) with_gelu(dh2, *e, Matmul::kBackward);
   run.backward(dh2, linear_dw(ds2, e->h, g->dw2, g->db2, z.T, z.H, z.F));

@@ -22,13 +22,14 @@ struct MatSide {
 // c[m][n] = alpha * sum_k a(m, k) b(n, k) + bias[n] + add[m][n]
 struct Matmul {
   MatSide a, b;
-  float* c;
+  float* c;            // null in a group: not computed, but for the sums below
   int64_t ldc, c_outer, c_inner;
   const float* bias;   // [N] or null
   const float* add;    // laid out as c, or null; may be c
   float* a_sums;       // [M]: sum_k a(m, k), or null (k-major a, a single slice)
   float alpha;
   int M, N, K, batch, inner;
+  int n_counted;       // what the choice of a tile takes for N
   // Float32 GELU of c, or its backward from the outputs act_y, laid out as c; side: the bits at or right of the minimum,
   // written or read (N a multiple of 8, a single slice, no addend).
   enum Act { kNone, kForward, kBackward } act = kNone;
@@ -38,7 +39,7 @@ struct Matmul {
 };
 tempo_status launch_matmul(const Matmul& g, hipStream_t st);
 // g (k-major b only) and one or two products of one size with two k-major operands, none of which needs another.  g or h0
-// may have no c: it is not computed, and the other gets the bits that it has beside it.
+// may have no c; everything else gets the bits that it has beside it.
 tempo_status launch_matmul_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st);
 
 }  // namespace tempo

@@ -237,7 +237,7 @@ __device__ __forceinline__ void matmul_tile(const Matmul& g, int block, int tota
   const int m = m0 + wm * kTile + l32;
   auto finish = [&](int q, f32x4 v) {
     const int n = n0 + wn * kTile + 8 * q + 4 * half;
-    const int left = m < g.M ? g.N - n : 0;
+    const int left = m < g.M && (!AKM || g.c) ? g.N - n : 0;
     const int64_t e = outer * g.c_outer + inner * g.c_inner + m * g.ldc + n;
     v *= g.alpha;
     if constexpr (ACT == Matmul::kForward) {
@@ -352,7 +352,9 @@ __global__ __launch_bounds__(C::kThreads) void matmul_group_kernel(Matmul g, Mat
 }
 template <typename C, typename D>
 tempo_status go_group(const Matmul& g, const Matmul& h0, const Matmul* h1, hipStream_t st) {
-  const int64_t g_tiles = g.c ? C::tiles(g) : 0, h_tiles = h0.c ? D::tiles(h0) : 0;
+  // The sums are made by the tiles of the first columns, which come first.
+  const int64_t g_tiles = g.c ? C::tiles(g) : 0;
+  const int64_t h_tiles = h0.c ? D::tiles(h0) : h0.a_sums ? (h0.M + D::BM - 1) / D::BM : 0;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(g_tiles + (h1 ? 2 : 1) * h_tiles), dim3(C::kThreads), 0, st, g, h0, h1 ? *h1 : h0,
                        static_cast<int>(g_tiles), static_cast<int>(h_tiles));
@@ -420,7 +422,9 @@ tempo_status launch_matmul_group(const Matmul& g, const Matmul& h0, const Matmul
   using HL = Large<true, true>;
   using HM = Middle<true, true>;
   using HS = Small<true, true>;
-  const int64_t cus = compute_units(), g_tiles = GL::tiles(g), h_tiles = HL::tiles(h0);
+  Matmul counted = h0;
+  counted.N = h0.n_counted;
+  const int64_t cus = compute_units(), g_tiles = GL::tiles(g), h_tiles = HL::tiles(counted);
   if (g_tiles * 8 >= cus * 5)
     return h_tiles >= cus ? go_group<GL, HL>(g, h0, h1, st) : go_group<GL, HM>(g, h0, h1, st);
   if (g_tiles * 16 >= cus * 5)

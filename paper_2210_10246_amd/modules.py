@@ -187,24 +187,50 @@ class TempoAttentionCore(nn.Module):
 
 
 class _EncoderLayerFn(torch.autograd.Function):
-    """The whole layer, whose forward has been made (_native.tempo_encoder_fwd): keeps what the layers of the general path
-    keep.  The backward is one native call too."""
+    """The whole layer, whose forward has been made (_native.tempo_encoder_fwd): keeps what the layer's parts keep for the
+    inputs that require a gradient.  The backward is one native call too."""
 
     @staticmethod
-    def forward(ctx, made, setting, store_mask, x, *params):
+    def forward(ctx, made, setting, store_mask, place, x, *params):
         qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = made
+        wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, gamma1, beta1, gamma2, beta2 = params
+        # where _grads_of_parts() finds the inputs' graphs: not kept for their values, which may change
+        ctx.places = place, wqkv, bqkv, wproj, bproj, w1, b1, w2, b2
         ctx.setting, ctx.store_mask = setting, store_mask
-        ctx.save_for_backward(x, *params, qkv, probs, keep if store_mask else None, ctxt, y1, rstd1, h, side, y2, rstd2)
+        of = ctx.needs_input_grad[4:]
+        inner = of[0] or of[1] or of[2]                                        # the gradient goes on to qkv,
+        first = inner or of[3] or of[4] or of[9] or of[10]                     # to the first LayerNorm,
+        second = first or of[5] or of[6]                                       # to GELU
+        ctx.save_for_backward(
+            x if of[1] else None, wqkv if of[0] else None, wproj if inner else None, w1 if first else None,
+            w2 if second else None, gamma1 if first else None, beta1 if first else None, gamma2, beta2,
+            qkv if inner else None, probs if inner else None, keep if inner and store_mask else None, ctxt if of[3] else None,
+            y1 if first or of[5] else None, rstd1 if first else None, h if second or of[7] else None,
+            side if second else None, y2, rstd2)
         return y2
 
     @staticmethod
     def backward(ctx, dy):
-        needed = ctx.needs_input_grad[3:]
-        if torch.is_grad_enabled():              # create_graph
-            return (None,) * 3 + _grads_of_parts(ctx, dy, needed)
-        wanted = sum(1 << i for i, n in enumerate(needed) if n)
-        x, *rest = ctx.saved_tensors
-        return (None,) * 3 + B.encoder_bwd(dy.contiguous(), wanted, x, *ctx.setting, *rest)
+        needed = ctx.needs_input_grad[4:]
+        grads = None
+        if not torch.is_grad_enabled():
+            wanted = sum(1 << i for i, n in enumerate(needed) if n)
+            grads = B.encoder_bwd(dy.contiguous(), wanted, *ctx.setting, *ctx.saved_tensors)
+        if grads is None:     # create_graph, or a tensor that is no plain one any more: the gradients of the parts
+            grads = _grads_of_parts(ctx, dy, needed)
+        return (None,) * 4 + grads
+
+
+class _PlaceFn(torch.autograd.Function):
+    """x's place in its graph, without its values."""
+
+    @staticmethod
+    def forward(ctx, x):
+        return x.new_zeros(()).expand(x.shape)
+
+    @staticmethod
+    def backward(ctx, dx):
+        return dx
 
 
 class _MadeLinearFn(torch.autograd.Function):
@@ -241,19 +267,21 @@ class _MadeScoresFn(torch.autograd.Function):
 
 
 def _grads_of_parts(ctx, dy, needed):
-    """The gradients as the layer made of its parts gives them, connected to its inputs.  The graph of the parts is laid over what
-    the forward made: nothing of the forward runs again."""
-    heads, _, _, p, seed, offset, kind = ctx.setting
-    inputs, (qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2) = ctx.saved_tensors[:13], ctx.saved_tensors[13:]
+    """The gradients as the layer made of its parts gives them, connected to its inputs under create_graph.  The graph of the
+    parts is laid over what the forward made: nothing of the forward runs again, and only what was kept is looked at."""
+    heads, ffn, p, seed, offset, kind = ctx.setting
+    x, wqkv, wproj, w1, w2, g1, be1, g2, be2, qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = ctx.saved_tensors
     Bn, S, H = dy.shape
     d = H // heads
 
-    def value(t, *shape):     # t in that shape; zeros without memory where nothing looks at it
+    def value(t, *shape):     # t in that shape; zeros without memory in the place of what nothing looks at
         return dy.new_zeros(()).expand(shape) if t is None else t.reshape(shape)
     with torch.enable_grad():
         # Aliases, which are inputs of this graph alone: x may depend on these parameters, and two of them may be the same
         # tensor, whose gradients the caller's backward adds up.
-        inputs = [t.view_as(t) for t in inputs]
+        kept, places = (x, wqkv, None, wproj, None, w1, None, w2, None), ctx.places
+        inputs = [t.view_as(t) if t is not None else None
+                  for t in (*(p if k is None else k for k, p in zip(kept, places)), g1, be1, g2, be2)]
         x, wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = inputs
 
         def core(q, k, v):
@@ -262,10 +290,11 @@ def _grads_of_parts(ctx, dy, needed):
             return _AttentionCoreFn.apply(scores, v, None, False, p, seed, offset, ctx.store_mask, made)
 
         rows = value(None, Bn, S, H)
+        x, g1, be1 = (value(t, *shape) for t, shape in ((x, (Bn, S, H)), (g1, (H,)), (be1, (H,))))
         a = _attention(_MadeLinearFn.apply(value(qkv, Bn, S, 3 * H), x, wqkv, bqkv), dy.shape, heads, core)
         y1 = _InplaceLayerNormFn.apply(x + _MadeLinearFn.apply(rows, a, wproj, bproj), g1, be1, None,
                                        (value(y1, Bn, S, H), rstd1))
-        h = _InplaceGELUFn.apply(_MadeLinearFn.apply(value(None, Bn, S, len(b1)), y1, w1, b1), kind, (value(h, Bn, S, len(b1)), side))
+        h = _InplaceGELUFn.apply(_MadeLinearFn.apply(value(None, Bn, S, ffn), y1, w1, b1), kind, (value(h, Bn, S, ffn), side))
         out = _InplaceLayerNormFn.apply(y1 + _MadeLinearFn.apply(rows, h, w2, b2), g2, be2, None, (y2, rstd2))
     grads = iter(torch.autograd.grad(out, [t for t, n in zip(inputs, needed) if n], dy, create_graph=torch.is_grad_enabled()))
     return tuple(next(grads) if n else None for n in needed)
@@ -328,15 +357,15 @@ class TempoEncoderLayer(nn.Module):
         qkv, proj, fc1, fc2, ln1, ln2, core = (parts[n] for n in ("qkv", "proj", "fc1", "fc2", "ln1", "ln2", "core"))
         params = (qkv.weight, qkv.bias, proj.weight, proj.bias, fc1.weight, fc1.bias, fc2.weight, fc2.bias,
                   ln1.weight, ln1.bias, ln2.weight, ln2.bias)
-        setting = (self.heads, ln1.eps, ln2.eps, core.p if core.training else 0.0, core.seed, core.offset + 1,
-                   parts["act"].kind)
-        made = B.encoder_fwd(x, key_len, *setting, *params)
+        setting = (core.p if core.training else 0.0, core.seed, core.offset + 1, parts["act"].kind)
+        made = B.encoder_fwd(x, key_len, self.heads, ln1.eps, ln2.eps, *setting, *params)
         if made is None:
             return None
         core.offset += 1
         if not torch.is_grad_enabled():
             return made[8]
-        return _EncoderLayerFn.apply(made, setting, core.store_mask, x, *params)
+        place = _PlaceFn.apply(x) if x.requires_grad and not qkv.weight.requires_grad else None    # else x itself is kept
+        return _EncoderLayerFn.apply(made, (self.heads, fc1.weight.shape[0], *setting), core.store_mask, place, x, *params)
 
 
 def _plain(x):

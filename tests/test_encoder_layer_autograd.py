@@ -91,12 +91,17 @@ class Kernels:
         self.calls[:] = ["fwd"]
         return qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2
 
-    def encoder_bwd(self, dy, wanted, x, heads, eps1, eps2, p, seed, offset, kind, *rest):
+    def encoder_bwd(self, dy, wanted, heads, ffn, p, seed, offset, kind, *rest):
         self.calls.append("bwd")
-        wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = [t.detach() for t in rest[:12]]
-        qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = rest[12:]
+        if self.refuse:
+            return None
         Bn, S, H = dy.shape
-        T, x = Bn * S, x.detach().reshape(Bn * S, H)
+        T, n, d = Bn * S, (Bn, heads, S, S), lambda t, *shape: torch.full(shape, np.nan) if t is None else t.detach()
+        shapes = ((T, H), (3 * H, H), (H, H), (ffn, H), (H, ffn), (H,), (H,), (H,), (H,), (T, 3 * H), n)
+        x, wqkv, wproj, w1, w2, g1, be1, g2, be2, qkv, probs = [d(t, *shape) for t, shape in zip(rest, shapes)]
+        keep, ctxt, y1, rstd1, h, side, y2, rstd2 = rest[11:]
+        ctxt, y1, rstd1, h, x = d(ctxt, T, H), d(y1, T, H), d(rstd1, T), d(h, T, ffn), x.reshape(T, H)
+        side = M._words(h.numel(), "cpu").zero_() if side is None else side
         ds2, dg2, dbe2, ds1, dg1, dbe1 = (torch.empty(s) for s in ((T, H), (H,), (H,)) * 2)
         self.tempo_layernorm_bwd(dy, y2, g2, be2, rstd2, ds2.view(Bn, S, H), dg2, dbe2, None)
         dh = ds2 @ w2
@@ -114,13 +119,15 @@ class Kernels:
         dqkv = dqkv.permute(1, 3, 0, 2, 4).reshape(T, 3 * H)
         grads = [(dqkv @ wqkv + ds1).view(Bn, S, H), dqkv.T @ x, dqkv.sum(0), ds1.T @ ctxt, ds1.sum(0), dh.T @ y1, dh.sum(0),
                  ds2.T @ h, ds2.sum(0), dg1, dbe1, dg2, dbe2]
-        return tuple(g if wanted >> i & 1 else None for i, g in enumerate(grads))
+        grads = tuple(g if wanted >> i & 1 else None for i, g in enumerate(grads))
+        assert all(g is None or not g.isnan().any() for g in grads)      # not of what was not kept
+        return grads
 
 
 @pytest.fixture
 def kernels(monkeypatch):
     k = Kernels()
-    k.calls = []
+    k.calls, k.refuse = [], False
     monkeypatch.setattr(M, "B", k)
     monkeypatch.setattr(M, "_plain", lambda x: True)
     return k
@@ -213,3 +220,105 @@ def test_create_graph_after_key_len_has_changed(kernels, parts, store):
         key_len.fill_(1)
         return torch.autograd.grad(out, [x, *layer.parameters()], dy, create_graph=True)
     same(step(), parts(step))
+
+
+FIRST, ATTENTION = ("qkv.", "proj.", "ln1."), ("qkv.", "proj.")
+
+
+def freeze(layer, x, frozen, x_needs=True):
+    for name, p in layer.named_parameters():
+        p.requires_grad_(not name.startswith(frozen))
+    return x.detach().requires_grad_(x_needs), [p for p in layer.parameters() if p.requires_grad]
+
+
+def kept_bytes(f):
+    seen = {}
+
+    def pack(t):
+        seen[t.untyped_storage().data_ptr()] = t.untyped_storage().nbytes()
+        return t
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+        out = f()
+    return out, sum(seen.values())
+
+
+FROZEN = [(), ("qkv.weight",), ("proj.weight",), ("fc1.weight",), ("fc2.weight",),
+          ("qkv.weight", "proj.weight", "fc1.weight", "fc2.weight", "ln"), ("qkv.",), ("proj.",), ATTENTION, FIRST, FIRST + ("fc1.",), ("fc1.", "fc2."), ("fc2.",), ("ln1.", "ln2."), ("ln2.",),
+          ("qkv.weight", "qkv.bias", "fc2."), FIRST + ("fc1.", "fc2."), FIRST + ("fc1.", "fc2.", "ln2.weight"),
+          ("qkv.bias", "fc1.bias"), FIRST + ("fc1.", "fc2.", "ln2.")]
+
+
+@pytest.mark.parametrize("frozen", FROZEN, ids=lambda f: "+".join(f) or "none")
+@pytest.mark.parametrize("x_needs", [True, False])
+@pytest.mark.parametrize("store", [True, False])
+def test_keeps_what_the_parts_keep(kernels, parts, frozen, x_needs, store):
+    layer, (x, dy) = layer_of(), inputs()
+    layer.core.store_mask = store
+    x, wanted = freeze(layer, x, frozen, x_needs)
+    wanted += [x] * x_needs
+
+    def step(**kw):
+        layer.core.offset = 4
+        out, kept = kept_bytes(lambda: layer(x))
+        grads = torch.autograd.grad(out, wanted, dy, **kw) if wanted else ()
+        if penalty := [g.square().sum() for g in grads if g.requires_grad]:
+            grads += torch.autograd.grad(sum(penalty), wanted, materialize_grads=True)
+        return kept, grads
+    for kw in ({}, {"create_graph": True}):
+        kernels.calls.clear()
+        kept, got = step(**kw)
+        assert "fwd" in kernels.calls
+        parts_kept, want = parts(lambda: step(**kw))
+        assert kept <= parts_kept
+        same(got, want)
+        assert [g.requires_grad for g in got] == [g.requires_grad for g in want]
+
+
+@pytest.mark.parametrize("create_graph", [False, True])
+def test_what_no_backward_reads_may_change(kernels, parts, create_graph):
+    """Biases; and what a frozen layer beside it was made from."""
+    layer, (x, dy) = layer_of(), inputs()
+
+    def step(frozen, change, x_needs=True):
+        leaf, wanted = freeze(layer, x, frozen, x_needs)
+        layer.core.offset = 4
+        into = leaf * 1.0                        # may change in place, being no leaf
+        out = layer(into)
+        changing = change(into)
+        with torch.no_grad():
+            before = [t.clone() for t in changing]
+            for t in changing:
+                t.add_(1)
+        got = torch.autograd.grad(out, wanted + [leaf] * x_needs, dy, create_graph=create_graph)
+        with torch.no_grad():
+            for t, b in zip(changing, before):
+                t.copy_(b)
+        return got
+    for args in (((), lambda x: [getattr(layer, n).bias for n in ("qkv", "proj", "fc1", "fc2")]),
+                 (("qkv.",), lambda x: [x]),
+                 ((), lambda x: [layer.qkv.weight], False),
+                 (FIRST, lambda x: [x, *(p for n, p in layer.named_parameters() if n.startswith(FIRST + ("fc1.weight",)))], False)):
+        same(step(*args), parts(lambda: step(*args)))
+        assert "fwd" in kernels.calls
+
+
+def test_what_a_backward_reads_may_not(kernels):
+    layer, (x, dy) = layer_of(), inputs()
+    for name in ("qkv.weight", "proj.weight", "fc1.weight", "fc2.weight", "ln1.weight", "ln1.bias", "ln2.weight", "ln2.bias"):
+        out = layer(x)
+        with torch.no_grad():
+            layer.get_parameter(name).add_(1)
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            torch.autograd.grad(out, [x], dy)
+
+
+def test_a_backward_that_is_refused_is_that_of_the_parts(kernels, parts):
+    """A kept tensor may come back from a hook as another type or in another layout."""
+    layer, (x, dy) = layer_of(), inputs()
+
+    def step():
+        layer.core.offset = 4
+        return torch.autograd.grad(layer(x), [x, *layer.parameters()], dy)
+    want = step()
+    kernels.refuse = True
+    same(step(), want)

@@ -92,7 +92,8 @@ def test_options_reach_the_kernels(M, monkeypatch, taken, kind, store, training)
 
 # Sizes whose products take other tiles alone than beside others: with values of k split over 1, 2, 4 and 8 waves.
 @pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [(3, 20, 64, 4, 128), (2, 128, 768, 12, 3072), (1, 77, 512, 8, 2048),
-                                                        (4, 130, 256, 4, 1028), (2, 31, 1024, 16, 4096)])
+                                                        (4, 130, 256, 4, 1028), (3, 63, 12, 3, 260),
+                                                        (2, 31, 1024, 16, 4096)])
 def test_gradients_of_a_part_of_the_inputs(M, taken, batch, seq, hidden, heads, ffn):
     """Whatever is asked for has the bits it has when everything is."""
     layer = layer_of(M, hidden, heads, ffn)
@@ -218,3 +219,45 @@ def test_create_graph(M, monkeypatch):
     # two layers and their backwards of products summed in another order (see test_one_call_matches_the_parts), and one more of each
     for i, (a, b) in enumerate(zip(got, want)):
         assert a.requires_grad == b.requires_grad and (a - b).norm() <= 6e-5 * b.norm() + 1e-6 * a.numel() ** 0.5, i
+
+
+@pytest.mark.parametrize("frozen", [("qkv.weight", "proj.weight", "fc1.weight", "fc2.weight"), ("qkv.", "proj."), ("qkv.", "proj.", "ln1."), ("proj.",), ("qkv.", "proj.", "ln1.", "fc1."),
+                                    ("fc1.", "fc2."), ("qkv.", "proj.", "ln1.", "fc1.", "fc2.")])
+@pytest.mark.parametrize("x_needs", [True, False])
+def test_frozen_halves(M, monkeypatch, taken, frozen, x_needs):
+    """The native backward from what a partly frozen layer keeps."""
+    layer = layer_of(M, 128, 4, 260)
+    x, dy = inputs(3, 70, 128)
+    x.requires_grad_(x_needs)
+    for name, p in layer.named_parameters():
+        p.requires_grad_(not name.startswith(frozen))
+    wanted = [x] * x_needs + [p for p in layer.parameters() if p.requires_grad]
+
+    def kept():
+        seen = {}
+
+        def pack(t):
+            seen[t.untyped_storage().data_ptr()] = t.untyped_storage().nbytes()
+            return t
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+            got = step(layer, x, dy, None, wanted)
+        return got, sum(seen.values())
+    got, few = kept()
+    assert taken == [True]
+    with monkeypatch.context() as m:
+        m.setattr(M.TempoEncoderLayer, "_as_one", lambda *a: None)
+        want, most = kept()
+    assert few <= most
+    for a, b in zip(got, want, strict=True):      # the bound of test_one_call_matches_the_parts
+        assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5
+
+
+def test_what_hooks_give_back_in_another_layout(M, taken):
+    layer = layer_of(M, 64, 4, 128)
+    x, dy = inputs(2, 40, 64)
+    want = step(layer, x, dy)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t.t().contiguous().t() if t.shape == (128, 64) else t, lambda t: t):
+        got = step(layer, x, dy)
+    assert taken == [True, True]
+    for a, b in zip(got, want, strict=True):
+        assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5
