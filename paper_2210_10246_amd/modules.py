@@ -17,9 +17,10 @@ from __future__ import annotations
 import math
 
 import torch
+import torch.nn.functional as F
 from torch import nn
 from torch.autograd import forward_ad
-from torch.nn.modules import module
+from torch.nn.modules import linear, module
 
 from . import binding as B
 
@@ -337,22 +338,22 @@ class TempoEncoderLayer(nn.Module):
         return self.ln2(x + self.fc2(self.act(self.fc1(x))))
 
     def _as_one(self, x, key_len):
-        """The layer as one native call each way, or None where anything could see or change its parts: hooks, other
-        modules in their places, autocast, function transforms, tracing, dispatch and function modes, forward-mode AD,
-        tensor subclasses, other types and layouts."""
+        """The layer as one native call each way, or None where something may see or change its parts: hooks, other
+        modules in their places, a forward, a call or a product replaced, autocast, function transforms, tracing, dispatch
+        and function modes, forward-mode AD, tensor subclasses, other types and layouts."""
         if torch.compiler.is_compiling():
             return None
         if not _plain(x):
             return None
         if (torch.is_autocast_enabled() or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
                 or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
-                or torch.jit.is_tracing() or module._has_any_global_hook() or nn.Linear.forward is not _LINEAR):
+                or torch.jit.is_tracing() or module._has_any_global_hook() or _calls() != _CALLS):
             return None
         parts = self._modules
         for name, kind in _PARTS:
             m = parts.get(name)
             if (type(m) is not kind or m._forward_hooks or m._forward_pre_hooks or m._backward_hooks
-                    or m._backward_pre_hooks or "forward" in m.__dict__):
+                    or m._backward_pre_hooks or "forward" in m.__dict__ or m._compiled_call_impl is not None):
                 return None
         qkv, proj, fc1, fc2, ln1, ln2, core = (parts[n] for n in ("qkv", "proj", "fc1", "fc2", "ln1", "ln2", "core"))
         params = (qkv.weight, qkv.bias, proj.weight, proj.bias, fc1.weight, fc1.bias, fc2.weight, fc2.bias,
@@ -375,6 +376,16 @@ def _plain(x):
     return B._native is not None
 
 
-_LINEAR = nn.Linear.forward                      # what the products stand for
 _PARTS = (("qkv", nn.Linear), ("proj", nn.Linear), ("fc1", nn.Linear), ("fc2", nn.Linear), ("ln1", InplaceLayerNorm),
           ("ln2", InplaceLayerNorm), ("act", InplaceGELU), ("core", TempoAttentionCore))
+
+
+def _calls():
+    """What a layer made of its parts goes through."""
+    return (nn.Linear.forward, InplaceLayerNorm.forward, InplaceGELU.forward, TempoAttentionCore.forward, nn.Linear.__call__,
+            InplaceLayerNorm.__call__, InplaceGELU.__call__, TempoAttentionCore.__call__, F.linear, torch.matmul)
+
+
+_CALLS = _calls()                                # what the native call stands for
+if _CALLS[0].__globals__ is not vars(linear) or _CALLS[4] is not nn.Module._wrapped_call_impl or F.linear is not torch._C._nn.linear:
+    _CALLS = None                                # replaced before this module was loaded

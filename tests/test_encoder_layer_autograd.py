@@ -322,3 +322,26 @@ def test_a_backward_that_is_refused_is_that_of_the_parts(kernels, parts):
     want = step()
     kernels.refuse = True
     same(step(), want)
+
+
+def test_a_replaced_part_is_called(kernels, monkeypatch):
+    """A forward, a call or a product that somebody has replaced, on the class or in its module."""
+    layer, (x, _) = layer_of(), inputs()
+    layer(x)
+    assert "fwd" in kernels.calls
+    nn = torch.nn
+    for owner, name in ((nn.Linear, "forward"), (M.InplaceLayerNorm, "forward"), (M.InplaceGELU, "forward"),
+                        (M.TempoAttentionCore, "forward"), (nn.Module, "__call__"), (nn.Linear, "__call__"),
+                        (M.InplaceGELU, "__call__"), (nn.functional, "linear"), (torch, "matmul")):
+        kernels.calls.clear()
+        seen, plain = [], getattr(owner, name)
+        with monkeypatch.context() as m:
+            m.setattr(owner, name, lambda *a, **kw: (seen.append(1), plain(*a, **kw))[1])
+            layer.forward(x)
+        assert seen and "fwd" not in kernels.calls, (owner, name)
+    layer(x)
+    assert "fwd" in kernels.calls
+    kernels.calls.clear()
+    layer.act.compile(backend="eager")
+    layer._as_one(x, None)
+    assert "fwd" not in kernels.calls
