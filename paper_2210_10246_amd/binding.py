@@ -382,8 +382,8 @@ def tempo_mask_bytes_to_bits(bytes_, bits, n, stream=None):
 
 
 def encoder_fwd(*args):
-    """One native call for the forward of modules.TempoEncoderLayer (csrc/binding.cpp names the arguments): what its backward
-    needs, or None if the call was not made."""
+    """One native call for the forward of modules.TempoEncoderLayer (csrc/binding.cpp names the arguments): the offset it
+    drew from and what its backward needs, or None if the call was not made."""
     r = _native.tempo_encoder_fwd(*args)
     if r is None:
         return None

@@ -253,7 +253,7 @@ int64_t integer(PyObject* o) {
   if (v == -1 && PyErr_Occurred()) throw NotPlain{};
   return v;
 }
-// The layer of x with heads, eps1, eps2, p, seed, offset and kind at a[0 .. 6], and its parameters at w.
+// The layer of x with heads, eps1, eps2, p, seed and kind at a[0 .. 5], and its parameters at w.
 tempo_encoder encoder(const at::Tensor& x, PyObject* const* a, PyObject* const* w) {
   tempo_encoder e{};
   e.x = input(x, &e);
@@ -262,8 +262,7 @@ tempo_encoder encoder(const at::Tensor& x, PyObject* const* a, PyObject* const* 
   e.eps2 = real(a[2]);
   e.p = real(a[3]);
   e.seed = bits64(a[4]);
-  e.offset = bits64(a[5]);
-  e.kind = gelu_kind(a[6]);
+  e.kind = gelu_kind(a[5]);
   const at::Tensor& w1 = tensor(w[4]);
   if (w1.dim() != 2) throw NotPlain{};
   e.ffn = w1.size(0);
@@ -284,24 +283,44 @@ tempo_encoder encoder(const at::Tensor& x, PyObject* const* a, PyObject* const* 
   return e;
 }
 float* data(const at::Tensor& t) { return t.defined() ? static_cast<float*>(t.data_ptr()) : nullptr; }
-// (status, tensors), an undefined one as None
-template <size_t N>
-PyObject* result(tempo_status status, const at::Tensor* const (&t)[N]) {
-  PyObject* r = PyTuple_New(N + 1);
-  if (!r) return nullptr;
-  PyTuple_SET_ITEM(r, 0, PyLong_FromLong(status));
-  for (size_t i = 0; i < N; ++i) PyTuple_SET_ITEM(r, i + 1, THPVariable_Wrap(*t[i]));  // None for an undefined one
+// The next offset of the generator, from where a module keeps the last one.  Taken under the interpreter's lock, once nothing
+// can send the call elsewhere any more: threads that share the module draw other bits, and a call made of its parts takes its own.
+PyObject* next_offset(PyObject* module, uint64_t* offset) {
+  PyObject* last = PyDict_CheckExact(module) ? PyDict_GetItemString(module, "offset") : nullptr;
+  if (!last || !PyLong_CheckExact(last)) throw NotPlain{};
+  PyObject* one = PyLong_FromLong(1);
+  PyObject* next = one ? PyNumber_Add(last, one) : nullptr;
+  Py_XDECREF(one);
+  if (!next || PyDict_SetItemString(module, "offset", next) != 0) {
+    Py_XDECREF(next);
+    throw NotPlain{};
+  }
+  *offset = bits64(next);
+  return next;
+}
+// What `front` owns, then the tensors, an undefined one as None.
+template <size_t F, size_t N>
+PyObject* result(PyObject* const (&front)[F], const at::Tensor* const (&t)[N]) {
+  PyObject* r = PyTuple_New(F + N);
+  for (size_t i = 0; i < F; ++i) {
+    if (r) PyTuple_SET_ITEM(r, i, front[i]);
+    else Py_XDECREF(front[i]);
+  }
+  for (size_t i = 0; r && i < N; ++i) PyTuple_SET_ITEM(r, F + i, THPVariable_Wrap(*t[i]));  // None for an undefined one
   return r;
 }
 
-// x, key_len, heads, eps1, eps2, p, seed, offset, kind, 12 parameters -> status and what the backward needs
+// x, key_len, the attention core's __dict__, heads, eps1, eps2, p, seed, kind, 12 parameters -> status, offset and what the
+// backward needs
 TEMPO_METHOD(encoder_fwd) {
   if (nargs != 9 + kEncoderParams) Py_RETURN_NONE;
   at::Tensor qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2;
   tempo_status status;
+  PyObject* offset;
+  HANDLE_TH_ERRORS
   try {
     const at::Tensor& x = tensor(a[0]);
-    tempo_encoder e = encoder(x, a + 2, a + 9);
+    tempo_encoder e = encoder(x, a + 3, a + 9);
     if (a[1] != Py_None) {
       const at::Tensor& k = tensor(a[1]);
       if (k.scalar_type() != at::kInt || k.numel() != e.batch || k.device() != x.device()) throw NotPlain{};
@@ -331,6 +350,7 @@ TEMPO_METHOD(encoder_fwd) {
     e.y2 = data(y2);
     e.rstd2 = data(rstd2);
     void* st = stream();
+    offset = next_offset(a[2], &e.offset);
     PyThreadState* state = PyEval_SaveThread();
     status = tempo_encoder_fwd(&e, data(out), st);
     PyEval_RestoreThread(state);
@@ -339,7 +359,9 @@ TEMPO_METHOD(encoder_fwd) {
     Py_RETURN_NONE;
   }
   const at::Tensor* all[] = {&qkv, &probs, &keep, &ctxt, &y1, &rstd1, &h, &side, &y2, &rstd2};
-  return result(status, all);
+  PyObject* front[] = {PyLong_FromLong(status), offset};
+  return result(front, all);
+  END_HANDLE_TH_ERRORS
 }
 
 // dy, wanted (bits: x, then the parameters), heads, ffn, p, seed, offset, kind, and of the forward x, wqkv, wproj, w1, w2, gamma1, beta1,
@@ -454,7 +476,8 @@ TEMPO_METHOD(encoder_bwd) {
     Py_RETURN_NONE;
   }
   const at::Tensor* all[] = {&dx, dw, dw + 1, dw + 2, dw + 3, dw + 4, dw + 5, dw + 6, dw + 7, dw + 8, dw + 9, dw + 10, dw + 11};
-  return result(status, all);
+  PyObject* front[] = {PyLong_FromLong(status)};
+  return result(front, all);
   END_HANDLE_TH_ERRORS
 }
 

@@ -223,11 +223,11 @@ class _EncoderLayerFn(torch.autograd.Function):
 
 
 class _PlaceFn(torch.autograd.Function):
-    """x's place in its graph, without its values."""
+    """x's place in its graph, without its values; nothing looks at those it has."""
 
     @staticmethod
     def forward(ctx, x):
-        return x.new_zeros(()).expand(x.shape)
+        return x.new_empty(()).expand(x.shape)
 
     @staticmethod
     def backward(ctx, dx):
@@ -358,15 +358,16 @@ class TempoEncoderLayer(nn.Module):
         qkv, proj, fc1, fc2, ln1, ln2, core = (parts[n] for n in ("qkv", "proj", "fc1", "fc2", "ln1", "ln2", "core"))
         params = (qkv.weight, qkv.bias, proj.weight, proj.bias, fc1.weight, fc1.bias, fc2.weight, fc2.bias,
                   ln1.weight, ln1.bias, ln2.weight, ln2.bias)
-        setting = (core.p if core.training else 0.0, core.seed, core.offset + 1, parts["act"].kind)
-        made = B.encoder_fwd(x, key_len, self.heads, ln1.eps, ln2.eps, *setting, *params)
+        p, kind = core.p if core.training else 0.0, parts["act"].kind
+        made = B.encoder_fwd(x, key_len, core.__dict__, self.heads, ln1.eps, ln2.eps, p, core.seed, kind, *params)
         if made is None:
             return None
-        core.offset += 1
+        offset, *made = made
         if not torch.is_grad_enabled():
             return made[8]
+        setting = (self.heads, fc1.weight.shape[0], p, core.seed, offset, kind)
         place = _PlaceFn.apply(x) if x.requires_grad and not qkv.weight.requires_grad else None    # else x itself is kept
-        return _EncoderLayerFn.apply(made, (self.heads, fc1.weight.shape[0], *setting), core.store_mask, place, x, *params)
+        return _EncoderLayerFn.apply(made, setting, core.store_mask, place, x, *params)
 
 
 def _plain(x):

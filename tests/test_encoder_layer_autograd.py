@@ -71,7 +71,8 @@ class Kernels:
         ds, o = O.attn_softmax_dropout_bwd(_np(dout), _np(probs), K, p, "f32")
         _put(dscores, ds), _put(out, o)
 
-    def encoder_fwd(self, x, key_len, heads, eps1, eps2, p, seed, offset, kind, *params):
+    def encoder_fwd(self, x, key_len, core, heads, eps1, eps2, p, seed, kind, *params):
+        core["offset"] = offset = core["offset"] + 1
         wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = [t.detach() for t in params]
         x = x.detach()
         Bn, S, H = x.shape
@@ -89,7 +90,7 @@ class Kernels:
         self.tempo_gelu_fwd(h.clone(), h, side, kind)
         self.tempo_layernorm_fwd((y1 + (h @ w2.T + b2)).view(Bn, S, H), g2, be2, y2, rstd2.view(Bn, S), None, eps2)
         self.calls[:] = ["fwd"]
-        return qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2
+        return offset, qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2
 
     def encoder_bwd(self, dy, wanted, heads, ffn, p, seed, offset, kind, *rest):
         self.calls.append("bwd")

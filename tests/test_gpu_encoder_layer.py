@@ -1,5 +1,7 @@
 """TempoEncoderLayer as one native call each way against the same layer made of its parts: outputs, gradients, and which of
 the two routes a call takes."""
+import threading
+
 import pytest
 import torch
 
@@ -261,3 +263,26 @@ def test_what_hooks_give_back_in_another_layout(M, taken):
     assert taken == [True, True]
     for a, b in zip(got, want, strict=True):
         assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5
+
+
+def test_threads_that_share_a_layer_draw_other_bits(M, monkeypatch):
+    layer, drawn = layer_of(M, 64, 4, 128), []
+    x, _ = inputs(2, 8, 64)
+    fwd = M.B.encoder_fwd
+
+    def spy(*args):
+        r = fwd(*args)
+        drawn.append(r[0])
+        return r
+    monkeypatch.setattr(M.B, "encoder_fwd", spy)
+
+    def calls():
+        with torch.no_grad():
+            for _ in range(200):
+                layer(x)
+    threads = [threading.Thread(target=calls) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert sorted(drawn) == list(range(1, 801)) and layer.core.offset == 800
