@@ -102,11 +102,28 @@ int tempo_encoder_takes(const tempo_encoder* e) {
   for (int64_t n : {tiles(z.T, 3 * z.H), tiles(z.T, z.F), tiles(3 * z.H, z.H), tiles(z.F, z.H), slices * tiles(z.S, z.S),
                     slices * tiles(z.S, z.d)})
     if (n > most / (kTile * kTile)) return 0;
-  // Multiplications of the four layers' weights, forward.  Below, the launches, copies and host time that go count for more than
-  // the library's products gain: parts / this, us forward + backward, 2 x 128 x 768 (2e9) 1094 / 278 (host time), 8 x 128 x 1024
-  // (13e9) 1106 / 775, 8 x 256 x 1024 (26e9) 1589 / 1553, 32 x 256 x 512 (26e9) 1896 / 1860; beyond, 16 x 256 x 768 (29e9)
-  // 1953 / 1924, 12 x 256 x 1024 (39e9) 2269 / 2326, 48 x 256 x 512 (39e9) 2742 / 2776, 16 x 256 x 1024 (52e9) 2890 / 3095.
-  return z.T * (4 * z.H * z.H + 2 * z.H * z.F) <= int64_t{26} * 1000 * 1000 * 1000;
+  // Where the launches, copies and host time that go count for more than the library's products gain.  us of the parts / of this,
+  // forward + backward and, behind a comma, forward alone, of four runs in turn the fastest.
+  // Rows of attention: longer ones leave both to the attention kernels and the library's products win.  1 x 6144 x 256 in 4 heads
+  // 3967 / 3655, 1528 / 1393, 1 x 7168 x 256 5383 / 4904, 2086 / 1832; 1 x 8192 x 256 6440 / 6442, 2569 / 2498, 1 x 8192 x 128 in 2
+  // 3388 / 3452, 1320 / 1309, 1 x 16384 x 64 in 1 6466 / 6712, 2500 / 2493.
+  if (z.S > 7168) return 0;
+  // Multiplications of the four layers' weights, forward: 2 x 128 x 768 (2e9) 814 / 197, 243 / 76, 8 x 128 x 1024 (13e9) 950 / 775,
+  // 310 / 274, 14 x 256 x 768 (25e9) 1863 / 1629, 613 / 534, 8 x 256 x 1024 (26e9) 1570 / 1469, 518 / 497, 32 x 256 x 512 (26e9) 1820
+  // / 1774, 594 / 575.  Beyond, it is 2 to 8 % one way or the other from run to run: 10 x 256 x 1024 (32e9) 1970 / 1904, 655 / 647, 12
+  // x 256 x 1024 (39e9) 2239 / 2164 (another day 2269 / 2326), 24 x 256 x 768 (43e9) 2908 / 2833, 48 x 256 x 512 (39e9) 2714 / 2649
+  // (2742 / 2776), 64 x 256 x 512 (52e9) 3439 / 3549, 16 x 256 x 1024 (52e9) 2890 / 3095.
+  const int64_t weights = 4 * z.H * z.H + 2 * z.H * z.F, products = z.T * weights, billion = 1000 * 1000 * 1000;
+  if (weights <= 30 * 1000 * 1000 && z.d <= 256) return products <= 26 * billion;
+  // Layers wider than 1536 columns: rows count in whole tiles, and the weights themselves count (as 47 more rows; the library streams
+  // them faster).  Heads wider than 256: their own products are as large (counted twice, as there are two each way; the library's are
+  // faster).  256 x 2048 1044 / 798, 313 / 267, 190 x 2304 1160 / 812, 312 / 290, 60 x 3072 1043 / 633, 230 / 210, 8 x 4096 1077 / 771,
+  // 248 / 231; at its worst 100 x 2560 929 / 717, 253 / 274, 24 x 4096 991 / 813, 228 / 237; not taken 257 x 2048 1031 / 952, 311 / 331,
+  // 500 x 2048 1481 / 1442, 456 / 500, 81 x 3072 1012 / 874, 287 / 317, 80 x 4096 1310 / 1345, 402 / 451, 1 x 5120 1127 / 1084, 302 /
+  // 312, 1 x 8192 2029 / 3561, 586 / 606, 8 x 12288 4448 / 6951, 1332 / 1426.  In one head: 1900 x 512 1033 / 694, 230 / 228; not taken
+  // 4096 x 512 1687 / 1732, 545 / 579, 1024 x 1024 993 / 836, 273 / 295, 2048 x 1024 1732 / 1799, 558 / 603.
+  const int64_t rows = (z.T + kTile - 1) / kTile * kTile + 47, attention = z.d > 256 ? 2 * 2 * z.T * z.S * z.H : 0;
+  return rows * weights + attention <= 16 * billion;
 }
 
 tempo_status tempo_encoder_fwd(const tempo_encoder* e, float* out, void* hip_stream) {
