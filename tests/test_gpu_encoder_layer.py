@@ -1,9 +1,14 @@
 """TempoEncoderLayer as one native call each way against the same layer made of its parts: outputs, gradients, and which of
 the two routes a call takes."""
+import math
 import threading
 
+import numpy as np
 import pytest
 import torch
+import torch.nn.functional as F
+
+from oracle import tempo_oracle as O
 
 pytestmark = pytest.mark.gpu
 
@@ -60,12 +65,14 @@ def parts(M, monkeypatch, *args):
 
 
 # Tiles of 32 and 64 rows, columns and steps of k of 16, 32 and 64: one short of them, whole, one more; head sizes and
-# sequences that are no multiple of a piece's 4, and the smallest ones.  The last four come to every tile size, alone and
-# in one launch with another.
+# sequences that are no multiple of a piece's 4, and the smallest ones.  On 256 compute units the last ten come to every tile
+# that launch_matmul() and launch_matmul_group() choose, with and without GELU; with test_options_reach_the_kernels and
+# test_gelu_at_the_end_of_a_product every one of the 37 kernels of matmul.hip runs.
 @pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [
     (1, 1, 32, 2, 64), (2, 31, 64, 4, 100), (3, 33, 96, 3, 36), (2, 33, 64, 2, 72), (1, 65, 128, 2, 512), (2, 130, 40, 5, 44), (5, 7, 192, 12, 768),
     (1, 64, 64, 1, 4), (3, 63, 12, 3, 260), (2, 256, 256, 4, 1024), (4, 97, 512, 8, 2048), (1, 3, 1024, 16, 4096),
-    (1, 128, 512, 8, 3072), (4, 256, 256, 4, 1024)])
+    (1, 128, 512, 8, 3072), (4, 256, 256, 4, 1024), (4, 515, 192, 12, 772), (1, 1, 128, 2, 3080), (1, 515, 64, 1, 64),
+    (1, 130, 512, 8, 2052), (8, 333, 320, 5, 264), (1, 16, 2560, 20, 512)])
 @pytest.mark.parametrize("padded", [False, True])
 def test_one_call_matches_the_parts(M, monkeypatch, taken, batch, seq, hidden, heads, ffn, padded):
     layer = layer_of(M, hidden, heads, ffn, p_attn=0.1)
@@ -80,12 +87,49 @@ def test_one_call_matches_the_parts(M, monkeypatch, taken, batch, seq, hidden, h
         assert (a - b).norm() <= 2e-5 * b.norm() + 1e-6 * a.numel() ** 0.5, i
 
 
-@pytest.mark.parametrize("kind,store,training", [("tanh", True, True), ("erf", False, True), ("erf", True, False)])
-def test_options_reach_the_kernels(M, monkeypatch, taken, kind, store, training):
-    layer = layer_of(M, 128, 2, 256)
+def in_64_bits(layer, x, dy, keep):
+    """Output and gradients of the layer in plain float64."""
+    p = [t.detach().double().requires_grad_() for t in (x, *layer.parameters())]
+    wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, g1, be1, g2, be2 = p[1:]
+    (Bn, S, H), A = x.shape, layer.heads
+    q, k, v = F.linear(p[0], wqkv, bqkv).view(Bn, S, 3, A, H // A).permute(2, 0, 3, 1, 4)
+    probs = torch.softmax(torch.matmul(q, k.transpose(-1, -2)) / math.sqrt(H // A), dim=-1) * keep
+    ctxt = torch.matmul(probs, v).permute(0, 2, 1, 3).reshape(Bn, S, H)
+    y = F.layer_norm(p[0] + F.linear(ctxt, wproj, bproj), (H,), g1, be1, 1e-5)
+    out = F.layer_norm(y + F.linear(F.gelu(F.linear(y, w1, b1)), w2, b2), (H,), g2, be2, 1e-5)
+    return [out.detach(), *torch.autograd.grad(out, p, dy.double())]
+
+
+@pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [(2, 128, 768, 12, 3072), (4, 97, 512, 8, 2048), (1, 515, 64, 1, 64),
+                                                        (8, 256, 256, 4, 1024)])
+def test_as_exact_as_the_parts(M, monkeypatch, taken, batch, seq, hidden, heads, ffn):
+    layer = layer_of(M, hidden, heads, ffn, p_attn=0.1)
+    x, dy = inputs(batch, seq, hidden)
+    K = O.dropout_keep(batch * heads * seq * seq, 0.1, layer.core.seed, 5).reshape(batch, heads, seq, seq)
+    scale = float(np.float32(1.0) / (np.float32(1.0) - np.float32(0.1)))
+    exact = in_64_bits(layer, x, dy, torch.from_numpy(K).cuda().double() * scale)
+    got, want = step(layer, x, dy), parts(M, monkeypatch, layer, x, dy)
+    assert taken == [True]
+    order = [n for n, _ in layer.named_parameters()]
+    for name, a, b, e in zip(["out", "x", *order], got, want, exact, strict=True):
+        if name == "qkv.bias":                    # without the keys', whose gradient is rounding alone
+            a, b, e = (torch.cat([t[:hidden], t[2 * hidden:]]) for t in (a, b, e))
+        one, made = ((t.double() - e).norm() / e.norm() for t in (a, b))
+        print(name, f"{one:.2e} {made:.2e}")
+        # rounding of the same number of sums in another order; inputs or sums of a bit less would double it
+        assert one <= 1.5 * made, name
+
+
+# tanh at sizes that come to every tile of the backward's product with GELU
+@pytest.mark.parametrize("kind,store,training,batch,seq,hidden,heads,ffn", [
+    ("tanh", True, True, 2, 50, 128, 2, 256), ("tanh", True, True, 2, 256, 256, 4, 1024), ("tanh", True, True, 4, 97, 512, 8, 2048),
+    ("tanh", True, True, 1, 3, 1024, 16, 4096), ("tanh", True, True, 4, 256, 256, 4, 1024), ("erf", False, True, 2, 50, 128, 2, 256),
+    ("erf", True, False, 2, 50, 128, 2, 256)])
+def test_options_reach_the_kernels(M, monkeypatch, taken, kind, store, training, batch, seq, hidden, heads, ffn):
+    layer = layer_of(M, hidden, heads, ffn)
     layer.act.kind, layer.core.store_mask = kind, store
     layer.train(training)
-    x, dy = inputs(2, 50, 128)
+    x, dy = inputs(batch, seq, hidden)
     got = step(layer, x, dy)
     assert taken == [True]
     for a, b in zip(got, parts(M, monkeypatch, layer, x, dy)):
@@ -286,3 +330,73 @@ def test_threads_that_share_a_layer_draw_other_bits(M, monkeypatch):
     for t in threads:
         t.join()
     assert sorted(drawn) == list(range(1, 801)) and layer.core.offset == 800
+
+
+def specials(M, kind, n):
+    """n values around GELU's minimum, of every size and sign, infinities and NaN."""
+    star = {"erf": O.GELU_XSTAR_F32["erf"], "tanh": O.GELU_XSTAR_F32["tanh"]}[kind]
+    star = torch.tensor(float(star))
+    at = [star, star.nextafter(torch.tensor(0.0)), star.nextafter(torch.tensor(-9.0))]
+    odd = [0.0, -0.0, 1e-42, -1e-42, 1e-8, -1e-8, 40.0, -40.0, 3e38, -3e38, math.inf, -math.inf, math.nan]
+    v = torch.cat([torch.stack(at), torch.tensor(odd)])
+    fill = torch.linspace(-8, 8, n)
+    fill[torch.arange(0, n, 7)] = v[torch.arange(0, n, 7) // 7 % len(v)]
+    return fill.cuda()
+
+
+def same_values(a, b):
+    """NaN for NaN, all else equal (a product's sum starts at +0, so that -0 does not come out of it)."""
+    return torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(0, math.inf, -math.inf), b.nan_to_num(0, math.inf, -math.inf))
+
+
+# Sizes at which the first feed-forward product takes each of its four tiles.
+@pytest.mark.parametrize("batch,seq,hidden,heads,ffn", [(2, 33, 64, 2, 1024), (8, 64, 64, 4, 1024), (4, 97, 512, 8, 2048),
+                                                        (1, 16, 2560, 20, 512)])
+@pytest.mark.parametrize("kind", ["erf", "tanh"])
+def test_gelu_at_the_end_of_a_product(M, batch, seq, hidden, heads, ffn, kind):
+    """Values and mask bits are those of tempo_gelu_fwd."""
+    layer = layer_of(M, hidden, heads, ffn)
+    layer.act.kind = kind
+    pre = specials(M, kind, ffn)
+    with torch.no_grad():
+        layer.fc1.weight.zero_()                  # so that what GELU gets is the bias
+        layer.fc1.bias.copy_(pre)
+    x, _ = inputs(batch, seq, hidden)
+    h, side = forward(M, layer, x)[6:8]
+    rows = pre.expand(batch * seq, ffn).contiguous()
+    y, mask = torch.empty_like(rows), torch.empty_like(side)
+    M.B.tempo_gelu_fwd(rows, y, mask, kind)
+    assert same_values(h, y), [(v, a, b) for v, a, b in zip(pre.tolist(), h[0].tolist(), y[0].tolist()) if a != b]
+    assert torch.equal(side, mask)
+
+
+def forward(M, layer, x):
+    made = M.B.encoder_fwd(x, None, layer.core.__dict__, layer.heads, 1e-5, 1e-5, 0.1, 7, layer.act.kind, *params_of(layer))
+    assert made is not None
+    return made[1:]
+
+
+def params_of(layer):
+    return [t for m in (layer.qkv, layer.proj, layer.fc1, layer.fc2, layer.ln1, layer.ln2) for t in (m.weight, m.bias)]
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(64, 2, 1024), (128, 2, 3080), (512, 8, 8192)])
+@pytest.mark.parametrize("kind", ["erf", "tanh"])
+def test_gelu_backward_at_the_end_of_a_product(M, hidden, heads, ffn, kind):
+    """The gradient that reaches the first feed-forward layer is that of tempo_gelu_bwd: for one token it is its bias gradient."""
+    layer = layer_of(M, hidden, heads, ffn)
+    layer.act.kind = kind
+    with torch.no_grad():                         # so that each column of h gets one gradient of the layer's output
+        layer.fc2.weight.zero_()
+        layer.fc2.weight[torch.arange(ffn) % hidden, torch.arange(ffn)] = 1.0
+    x, dy = inputs(1, 1, hidden)
+    qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = forward(M, layer, x)
+    pre = specials(M, kind, ffn)
+    M.B.tempo_gelu_fwd(pre, h.view(-1), side, kind)
+    wqkv, _, wproj, _, w1, _, w2, _, g1, be1, g2, be2 = params_of(layer)
+    grads = M.B.encoder_bwd(dy, (1 << 13) - 1, heads, ffn, 0.1, 7, 1, kind, x, wqkv, wproj, w1, w2, g1, be1, g2, be2, qkv, probs,
+                            keep, ctxt, y1, rstd1, h, side, y2, rstd2)
+    db1, db2 = grads[6], grads[8]
+    dh, want = db2[torch.arange(ffn) % hidden], torch.empty(ffn, device="cuda")
+    M.B.tempo_gelu_bwd(dh.contiguous(), h.view(-1), side, want, kind)
+    assert same_values(db1, want)
