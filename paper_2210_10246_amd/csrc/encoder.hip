@@ -58,8 +58,8 @@ Matmul linear_dw(const float* dy, const float* x, float* dw, float* db, int64_t 
 }
 
 // The layer's GELU at the end of a product: the forward's of the first feed-forward layer, the backward's of the second one's
-// dx.  As launches of their own they took 4.5 us each at 2 x 128 x 768 and read and wrote [T, ffn] once more: a step 203.5 / 197.8
-// us, 8 x 256 x 768 1019 / 998.  The mask is bytes to the product: rows of a multiple of 8 columns.
+// dx.  As launches of their own they took 4.5 us each at 2 x 128 x 768 and read and wrote [T, ffn] once more: a replayed step
+// 203.5 / 197.8 us, 8 x 256 x 768 1019 / 998.  The mask is bytes to the product: rows of a multiple of 8 columns.
 void with_gelu(Matmul& g, const tempo_encoder& e, Matmul::Act act) {
   g.act = act;
   g.kind = e.kind;
