@@ -34,7 +34,7 @@ def _words(n: int, device) -> torch.Tensor:
 
 class _InplaceGELUFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, kind, made=None):
+    def forward(ctx, x, kind, made):
         if made is None:
             x = x.contiguous()
             y = torch.empty_like(x)
@@ -69,7 +69,7 @@ class InplaceGELU(nn.Module):
         self.kind = {"none": "erf", "tanh": "tanh"}[approximate]
 
     def forward(self, x):
-        return _InplaceGELUFn.apply(x, self.kind)
+        return _InplaceGELUFn.apply(x, self.kind, None)
 
 
 class InplaceSiLU(nn.Module):
@@ -77,12 +77,12 @@ class InplaceSiLU(nn.Module):
     (Sec. 5.1) on another activation with a single minimum."""
 
     def forward(self, x):
-        return _InplaceGELUFn.apply(x, "silu")
+        return _InplaceGELUFn.apply(x, "silu", None)
 
 
 class _InplaceLayerNormFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, gamma, beta, eps, made=None):
+    def forward(ctx, x, gamma, beta, eps, made):
         if made is None:
             x = x.contiguous()
             M = x.shape[-1]
@@ -134,12 +134,12 @@ class InplaceLayerNorm(nn.Module):
         w, b = self.weight, self.bias
         if w.dtype != torch.float32 or b.dtype != torch.float32:   # parameters replaced by hand
             w, b = w.float(), b.float()
-        return _InplaceLayerNormFn.apply(x, w, b, self.eps)
+        return _InplaceLayerNormFn.apply(x, w, b, self.eps, None)
 
 
 class _AttentionCoreFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, scores, v, key_len, causal, p, seed, offset, store_mask, made=None):
+    def forward(ctx, scores, v, key_len, causal, p, seed, offset, store_mask, made):
         if made is None:
             scores = scores.contiguous()
             probs = torch.empty_like(scores)
@@ -184,7 +184,7 @@ class TempoAttentionCore(nn.Module):
         p = self.p if self.training else 0.0
         self.offset += 1
         return _AttentionCoreFn.apply(scores, v, key_len, causal, p, self.seed, self.offset,
-                                      self.store_mask)
+                                      self.store_mask, None)
 
 
 class _EncoderLayerFn(torch.autograd.Function):
@@ -192,13 +192,13 @@ class _EncoderLayerFn(torch.autograd.Function):
     inputs that require a gradient.  The backward is one native call too."""
 
     @staticmethod
-    def forward(ctx, made, setting, store_mask, place, x, *params):
-        qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2 = made
+    def forward(ctx, made, setting, store_mask, x, *params):
+        qkv, probs, keep, ctxt, y1, rstd1, h, side, y2, rstd2, place = made
         wqkv, bqkv, wproj, bproj, w1, b1, w2, b2, gamma1, beta1, gamma2, beta2 = params
         # where _grads_of_parts() finds the inputs' graphs: not kept for their values, which may change
         ctx.places = place, wqkv, bqkv, wproj, bproj, w1, b1, w2, b2
         ctx.setting, ctx.store_mask = setting, store_mask
-        of = ctx.needs_input_grad[4:]
+        of = ctx.needs_input_grad[3:]
         inner = of[0] or of[1] or of[2]                                        # the gradient goes on to qkv,
         first = inner or of[3] or of[4] or of[9] or of[10]                     # to the first LayerNorm,
         second = first or of[5] or of[6]                                       # to GELU
@@ -212,14 +212,14 @@ class _EncoderLayerFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dy):
-        needed = ctx.needs_input_grad[4:]
+        needed = ctx.needs_input_grad[3:]
         grads = None
         if not torch.is_grad_enabled():
             wanted = sum(1 << i for i, n in enumerate(needed) if n)
             grads = B.encoder_bwd(dy.contiguous(), wanted, *ctx.setting, *ctx.saved_tensors)
         if grads is None:     # create_graph, or a tensor that is no plain one any more: the gradients of the parts
             grads = _grads_of_parts(ctx, dy, needed)
-        return (None,) * 4 + grads
+        return (None,) * 3 + grads
 
 
 class _PlaceFn(torch.autograd.Function):
@@ -366,8 +366,8 @@ class TempoEncoderLayer(nn.Module):
         if not torch.is_grad_enabled():
             return made[8]
         setting = (self.heads, fc1.weight.shape[0], p, core.seed, offset, kind)
-        place = _PlaceFn.apply(x) if x.requires_grad and not qkv.weight.requires_grad else None    # else x itself is kept
-        return _EncoderLayerFn.apply(made, setting, core.store_mask, place, x, *params)
+        made.append(_PlaceFn.apply(x) if x.requires_grad and not qkv.weight.requires_grad else None)    # else x itself is kept
+        return _EncoderLayerFn.apply(made, setting, core.store_mask, x, *params)
 
 
 def _plain(x):

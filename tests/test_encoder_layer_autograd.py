@@ -261,6 +261,8 @@ def test_keeps_what_the_parts_keep(kernels, parts, frozen, x_needs, store):
     def step(**kw):
         layer.core.offset = 4
         out, kept = kept_bytes(lambda: layer(x))
+        edges = [node.name() for node, _ in out.grad_fn.next_functions if node] if out.grad_fn else []
+        assert "_PlaceFnBackward" not in edges   # x is reached as an input and no second time
         grads = torch.autograd.grad(out, wanted, dy, **kw) if wanted else ()
         if penalty := [g.square().sum() for g in grads if g.requires_grad]:
             grads += torch.autograd.grad(sum(penalty), wanted, materialize_grads=True)
